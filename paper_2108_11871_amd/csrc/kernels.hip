@@ -1087,11 +1087,15 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     // are read once and serve every column of the tile; the family-2 values
     // come from the transposed copy [par][t][k1][k0], contiguous in k0 = kx.
     const T *Pt = d == 3 ? static_cast<const T *>(a.sh.P2T) + ((kB & 1) ? 3 * ss2 : 0) : nullptr;
-    for (int k = tid; k <= M; k += NTT) {
-        if (k == 0 || k == M) {
-            for (int sq = 0; sq < nseq; ++sq) lds_cs(buf, rs, k, sq, cx<T>{(T)0, (T)0});
-            continue;
-        }
+    // Fewer than NTT / 2 rows would leave threads over: 2^lgG groups of M - 1
+    // threads then share the sequences of a row (33^3 FP64 solve 226 -> 209 us,
+    // 65^3 261 -> 250 us: this loop is a chain of FP64 operations per column).
+    int lgG = 0;
+    while (lgG < lgs && ((M - 1) << (lgG + 1)) <= NTT) ++lgG;
+    const int kstep = lgG > 0 ? M - 1 : NTT, grp = lgG > 0 ? tid / kstep : 0;
+    const int sq0 = grp << (lgs - lgG), sq1 = sq0 + (nseq >> lgG);
+    for (int z = tid; z < 2 * nseq; z += NTT) lds_cs(buf, rs, (z & 1) ? M : 0, z >> 1, cx<T>{(T)0, (T)0});
+    for (int k = 1 + tid - grp * kstep; k < M && grp < (1 << lgG); k += kstep) {
         T r[SV];
         load12(rv + (k - 1) * SV, r);
         const T lx = r[0], rq = r[1], rs1 = r[2], rs2 = r[3], r10 = r[10], r11 = r[11];
@@ -1099,7 +1103,7 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
         const T Pe0 = r[4], Pe1 = r[5], Pe2 = r[6], Po0 = r[7], Po1 = r[8], Po2 = r[9];
         const int kx = k;
         const bool kodd = (kx & 1) != 0; // family 0 at (ky, kz): parity of kx
-        for (int sq = 0; sq < nseq; ++sq) {
+        for (int sq = sq0; sq < sq1; ++sq) {
             const cx<T> z1 = lds_c(buf, rs, k, sq), z2 = lds_c(buf, rs, N - k, sq);
             T cab[2];
             // the spectrum as loaded (pre), or from the forward transform

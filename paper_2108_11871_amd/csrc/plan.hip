@@ -153,6 +153,29 @@ int tile_width(int N, int maxwork, int ncols)
     return std::min(W, need);
 }
 
+// Blocks that a launch of a small grid is split into: a small grid fills only
+// part of the 256 compute units, and a launch then lasts as long as its widest
+// tile, so tiles are narrowed while a launch has fewer blocks than these. Whole
+// solves in FP64 (order 6), default widths -> narrowed: passes at 256 blocks,
+// 33^3 209 -> 189 us, 65^3 250 -> 203 us, 129^3 283 -> 286 us (512 blocks: 189,
+// 205, 285); contractions at 512, 33^3 209 -> 199 us, 65^3 250 -> 234 us (256:
+// 198, 250), not below 4 columns (2D 513 x 385: 162 us with 2, 156 with 4); the
+// final pass at 256, 65^2 77 -> 72 us, 65^3 250 -> 243 us, and 129^3, which has
+// 1016 blocks, keeps its 283 us (292 when split further).
+constexpr int kFillPass = 256, kFillConv = 512, kFillFinal = 256;
+
+// tile_width, narrowed (down to wmin columns) while nbatch rows of tiles make
+// fewer than `fill` blocks.
+int fill_width(int N, int maxwork, int ncols, int64_t nbatch, int fill, int wmin = 2)
+{
+    int W = tile_width(N, maxwork, ncols);
+    // the tiles with compile-time stages stay whole: even 48 of them beat four
+    // times as many narrower ones with run-time stages (129^3 283 against 286 us)
+    if (N * W == 4096 && (N == 256 || N == 512 || N == 1024)) return W;
+    while (W > wmin && (int64_t)((ncols + W - 1) / W) * nbatch < fill) W /= 2;
+    return W;
+}
+
 // Blocks of a column-contraction launch the chunking aims at (IPS_CC_BLOCKS
 // overrides the default, for measurements).
 int cc_block_target(int N)
@@ -240,6 +263,7 @@ struct ips_plan_s {
     void *B = nullptr; // raw DST of rho along the last d-1 axes, then phi in sine space
     double *part[3] = {nullptr, nullptr, nullptr};
     int nch[3] = {1, 1, 1};
+    int ccW[3] = {2, 2, 2}; // tile widths of the column contractions
     int chunk[3] = {1, 1, 1};
     double *F[3] = {nullptr, nullptr, nullptr};
     double *G[3] = {nullptr, nullptr, nullptr};
@@ -414,7 +438,7 @@ void prep_pass(ips_plan p, PassArgs &a, const FftDesc &fd, const cx<double> *tw)
     a.twf = nullptr;
     for (int ax = 0; ax < p->d; ++ax)
         if (p->tw[ax] == tw) a.twf = p->twf[ax];
-    if (a.W == 0) a.W = tile_width(fd.N, p->work, a.ncols);
+    if (a.W == 0) a.W = fill_width(fd.N, p->work, a.ncols, a.nbatch, kFillPass);
 }
 
 // f32t: FP32 tiles between FP64 input and output
@@ -809,7 +833,7 @@ int plan_build(ips_plan p, hipStream_t st)
         }
         // a tile holds W/2 columns of the first half of the axis and their
         // mirrors: the chunks split the (I + 1)/2 first-half columns
-        const int W = tile_width(N[pen], p->work, I[fam]);
+        const int W = p->ccW[fam] = fill_width(N[pen], p->work, I[fam], nbatch, kFillConv, 4);
         const int hc = (I[fam] + 1) / 2, Wh = W / 2;
         const int ncb = (hc + Wh - 1) / Wh;
         // about 4096 (2M <= 512) or 6144 blocks of 256 threads, a few tiles
@@ -1330,7 +1354,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.Bcs = I[1];
             a.Brs = 1;
             a.Bbs = vxy;
-            a.W = tile_width(N[1], p->work, a.ncols);
+            a.W = p->ccW[0];
             a.fd = p->fd[1];
             a.tw = p->tw[1];
             a.twf = p->twf[1];
@@ -1355,7 +1379,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.Ko = M[0] + 1;
             a.part = p->part[1];
             a.Bout = nullptr;
-            a.W = tile_width(N[0], p->work, a.ncols);
+            a.W = p->ccW[1];
             a.fd = p->fd[0];
             a.tw = p->tw[0];
             a.twf = p->twf[0];
@@ -1402,7 +1426,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.Ko = M[0] + 1;
             a.part = p->part[2];
             a.Bout = nullptr;
-            a.W = tile_width(N[0], p->work, a.ncols);
+            a.W = p->ccW[2];
             a.fd = p->fd[0];
             a.tw = p->tw[0];
             a.twf = p->twf[0];
@@ -1436,7 +1460,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.out_nrows = M[c] + 1;
             a.scale = 1.0 / N[c];
             // few faces: narrow tiles give enough blocks to fill the device
-            a.W = tile_width(N[c], std::min(p->work, 512), a.ncols);
+            a.W = fill_width(N[c], std::min(p->work, 512), a.ncols, 2 * nfam, kFillPass);
             prep_pass(p, a, p->fd[c], p->tw[c]);
             PassArgs &b = fb[fam];
             b = PassArgs{};
@@ -1453,7 +1477,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             b.scale = 1.0 / N[r];
             // the second step reads no partials: the default tile budget
             // (compile-time stages) measured faster than narrow tiles
-            b.W = tile_width(N[r], std::min(p->work, 2048), b.ncols);
+            b.W = fill_width(N[r], std::min(p->work, 2048), b.ncols, 2 * nfam, kFillPass);
             prep_pass(p, b, p->fd[r], p->tw[r]);
         }
         // the families' passes of each step together (one launch each when uniform)
@@ -1505,7 +1529,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
                 a.Brs = 1;
                 a.Bbs = 0;
             }
-            a.W = tile_width(N[pen], p->work, a.ncols);
+            a.W = p->ccW[fam];
             a.fd = p->fd[pen];
             a.tw = p->tw[pen];
             a.twf = p->twf[pen];
@@ -1639,7 +1663,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.bax = -1;
         }
         a.nrows_in = I[0];
-        a.W = tile_width(N[0], N[0] > kLdsMaxN ? p->work : final_work(p->precision), a.ncols);
+        a.W = fill_width(N[0], N[0] > kLdsMaxN ? p->work : final_work(p->precision), a.ncols, a.nbatch, kFillFinal);
         a.order = p->order;
         a.mixed = f32;
         a.geo = p->geo;
