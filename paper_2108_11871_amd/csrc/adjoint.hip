@@ -408,7 +408,7 @@ hipError_t launch_zero_boundary(const AdjArgs &a, double *out, hipStream_t st)
 // followed by the hermitian synthesis along the rows.  Rows 1..M-1 of the
 // result, times `scale`, are stored (3D) or added (2D) to out[(row-1)*ors +
 // col*ocs + batch*obs].
-template <int MAXE, bool P2, int NTT>
+template <int MAXE, int KD, int NTT>
 __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
 {
     constexpr bool BIG = NTT != NTA;
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
     }
     __syncthreads();
     pre_herm<double, MAXE, NTT>(buf, rs, lgs, M, false);
-    fft_tile<double, MAXE, NTT, P2>(buf, rs, lgs, a.fd, tw, true);
+    fft_tile<double, MAXE, NTT, KD>(buf, rs, lgs, a.fd, tw, true);
     double *out = a.out + (int64_t)bt * a.obs + (int64_t)c0 * a.ocs;
     if (a.accum)
         tile_store_acc<double, double, NTT>(buf, rs, 1, out, M - 1, nc, a.ors, a.ocs, a.scale, lgW);
@@ -459,18 +459,18 @@ __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
         tile_store<double, double, NTT>(buf, rs, 1, out, M - 1, nc, a.ors, a.ocs, a.scale, lgW);
 }
 
-static bool pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
-
 template <int MAXE, int NTT = NTA>
 static void launch_expand_m(const ExpandArgs &a, unsigned nblk, size_t lds, hipStream_t st)
 {
-    if (pow2(a.fd.N)) {
-        set_lds((const void *)&k_expand<MAXE, true, NTT>, lds);
-        hipLaunchKernelGGL((k_expand<MAXE, true, NTT>), dim3(nblk), dim3(NTT), lds, st, a);
-    } else {
-        set_lds((const void *)&k_expand<MAXE, false, NTT>, lds);
-        hipLaunchKernelGGL((k_expand<MAXE, false, NTT>), dim3(nblk), dim3(NTT), lds, st, a);
-    }
+    auto go = [&](auto kd) {
+        constexpr int KD = decltype(kd)::value;
+        set_lds((const void *)&k_expand<MAXE, KD, NTT>, lds);
+        hipLaunchKernelGGL((k_expand<MAXE, KD, NTT>), dim3(nblk), dim3(NTT), lds, st, a);
+    };
+    if constexpr (NTT == NTA && MAXE <= 8)
+        by_kind(a.fd.N, go);
+    else
+        by_pow2(a.fd.N, go);
 }
 
 hipError_t launch_expand(const ExpandArgs &a, hipStream_t st)

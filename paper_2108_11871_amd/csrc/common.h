@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "fft_tile.h"
 
 namespace ips {
@@ -12,6 +14,41 @@ namespace ips {
 constexpr int NT = 256;
 
 inline bool is_pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
+
+inline int len_kind(int N)
+{
+    int r = N;
+    for (int p : {2, 3, 5})
+        while (r % p == 0) r /= p;
+    return is_pow2(N) ? kPow2 : r == 1 ? kSmooth : kAnyLen;
+}
+
+// f(kind) with the kind as a compile-time constant.
+template <typename F>
+inline void with_kind(int kind, F f)
+{
+    if (kind == kPow2)
+        f(std::integral_constant<int, kPow2>());
+    else if (kind == kSmooth)
+        f(std::integral_constant<int, kSmooth>());
+    else
+        f(std::integral_constant<int, kAnyLen>());
+}
+template <typename F>
+inline void by_kind(int N, F f)
+{
+    with_kind(len_kind(N), f);
+}
+
+// As by_kind, powers of two and everything else only.
+template <typename F>
+inline void by_pow2(int N, F f)
+{
+    if (is_pow2(N))
+        f(std::integral_constant<int, kPow2>());
+    else
+        f(std::integral_constant<int, kAnyLen>());
+}
 
 // The tile helpers address a tile with 32-bit offsets r * rsd + c * csd built
 // from 24-bit multiplies (toff): strides below 2^23, extent below 2^31.

@@ -21,7 +21,7 @@ namespace ips {
 // an odd count only once), so each kernel-spectrum value loaded serves two
 // columns, and with the C and S rows of the pencil transform four products
 // per face.
-template <typename T, typename TI, int MAXE, bool WB, bool P2, int RPT, int NTT, int WHC, int NC>
+template <typename T, typename TI, int MAXE, bool WB, int KD, int RPT, int NTT, int WHC, int NC>
 __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
 {
     constexpr bool BIG = NTT != NT;
@@ -29,7 +29,7 @@ __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
     // NC > 0: the transform length, known at compile time (only the
     // compile-time Stockham stages of that length are built in)
     // (only the pairs that have compile-time stages: fdc carries no stage list)
-    static_assert(NC == 0 || (P2 && MAXE == 8 && NTT == NT && NC * WHC == 8 * NT), "no compile-time stages");
+    static_assert(NC == 0 || (KD == kPow2 && MAXE == 8 && NTT == NT && NC * WHC == 8 * NT), "no compile-time stages");
     FftDesc fdc{};
     if constexpr (NC > 0) {
         fdc.N = NC;
@@ -111,9 +111,9 @@ __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
         __syncthreads();
         // rows 1..nrows_in <= M-1 hold data, rows from M on are zero
         if (a.nrows_in <= M - 1)
-            fft_tile_zpad<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, tid);
+            fft_tile_zpad<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, tid);
         else
-            fft_tile<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, false, tid);
+            fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, false, tid);
         post_cs<T, MAXE, NTT>(buf, rs, lgs, M, tid);
         if (WB && (a.Mo == 0 || bt > a.Mo)) {
             const int64_t bb = a.Mo == 0 ? 0 : (int64_t)(bt - a.Mo - 1) * a.Bbs;
@@ -199,12 +199,12 @@ __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
     }
 }
 
-template <typename T, typename TI, int MAXE, bool WB, bool P2, int RPT, int NTT = NT, int WHC = 0, int NC = 0>
+template <typename T, typename TI, int MAXE, bool WB, int KD, int RPT, int NTT = NT, int WHC = 0, int NC = 0>
 static void launch_cc_k(const CcArgs &a, int nchunk, hipStream_t st)
 {
     const size_t lds = tile_lds<T>(a.fd.N, a.W);
-    set_lds((const void *)&k_cc<T, TI, MAXE, WB, P2, RPT, NTT, WHC, NC>, lds);
-    hipLaunchKernelGGL((k_cc<T, TI, MAXE, WB, P2, RPT, NTT, WHC, NC>), dim3(nchunk * a.nbatch), dim3(NTT), lds,
+    set_lds((const void *)&k_cc<T, TI, MAXE, WB, KD, RPT, NTT, WHC, NC>, lds);
+    hipLaunchKernelGGL((k_cc<T, TI, MAXE, WB, KD, RPT, NTT, WHC, NC>), dim3(nchunk * a.nbatch), dim3(NTT), lds,
                        st, a, nchunk);
 }
 
@@ -221,40 +221,37 @@ static bool prefetch_fits(const CcArgs &a)
 template <typename T, typename TI, int MAXE, bool WB>
 static void launch_cc_m(const CcArgs &a, int nchunk, hipStream_t st)
 {
-    const bool p2 = is_pow2(a.fd.N);
     if constexpr (MAXE == 8) {
         // the default (length, width) pairs with compile-time Stockham stages
         if (a.fd.N == 512 && prefetch_fits<4, 8>(a))
-            return launch_cc_k<T, TI, 8, WB, true, 2, NT, 4, 512>(a, nchunk, st);
+            return launch_cc_k<T, TI, 8, WB, kPow2, 2, NT, 4, 512>(a, nchunk, st);
         if (a.fd.N == 256 && prefetch_fits<8, 8>(a))
-            return launch_cc_k<T, TI, 8, WB, true, 2, NT, 8, 256>(a, nchunk, st);
+            return launch_cc_k<T, TI, 8, WB, kPow2, 2, NT, 8, 256>(a, nchunk, st);
         if (a.fd.N == 1024 && prefetch_fits<2, 8>(a))
-            return launch_cc_k<T, TI, 8, WB, true, 4, NT, 2, 1024>(a, nchunk, st);
+            return launch_cc_k<T, TI, 8, WB, kPow2, 4, NT, 2, 1024>(a, nchunk, st);
     }
-    if (a.fd.N <= 2 * NT) {
-        if (p2 && prefetch_fits<8, MAXE>(a))
-            launch_cc_k<T, TI, MAXE, WB, true, 2, NT, 8>(a, nchunk, st);
-        else if (p2 && prefetch_fits<4, MAXE>(a))
-            launch_cc_k<T, TI, MAXE, WB, true, 2, NT, 4>(a, nchunk, st);
-        else if (p2)
-            launch_cc_k<T, TI, MAXE, WB, true, 2>(a, nchunk, st);
-        else
-            launch_cc_k<T, TI, MAXE, WB, false, 2>(a, nchunk, st);
-    } else if (a.fd.N <= 4 * NT) {
-        if (p2 && prefetch_fits<2, MAXE>(a))
-            launch_cc_k<T, TI, MAXE, WB, true, 4, NT, 2>(a, nchunk, st);
-        else if (p2)
-            launch_cc_k<T, TI, MAXE, WB, true, 4>(a, nchunk, st);
-        else if (prefetch_fits<2, MAXE>(a))
-            launch_cc_k<T, TI, MAXE, WB, false, 4, NT, 2>(a, nchunk, st);
-        else
-            launch_cc_k<T, TI, MAXE, WB, false, 4>(a, nchunk, st);
-    } else {
-        if (p2)
-            launch_cc_k<T, TI, MAXE, WB, true, 8>(a, nchunk, st);
-        else
-            launch_cc_k<T, TI, MAXE, WB, false, 8>(a, nchunk, st);
-    }
+    auto go = [&](auto kd) {
+        constexpr int KD = decltype(kd)::value;
+        constexpr bool P2 = KD == kPow2;
+        if (a.fd.N <= 2 * NT) {
+            if constexpr (P2) {
+                if (prefetch_fits<8, MAXE>(a)) return launch_cc_k<T, TI, MAXE, WB, KD, 2, NT, 8>(a, nchunk, st);
+                if (prefetch_fits<4, MAXE>(a)) return launch_cc_k<T, TI, MAXE, WB, KD, 2, NT, 4>(a, nchunk, st);
+            }
+            launch_cc_k<T, TI, MAXE, WB, KD, 2>(a, nchunk, st);
+        } else if (a.fd.N <= 4 * NT) {
+            if (prefetch_fits<2, MAXE>(a))
+                launch_cc_k<T, TI, MAXE, WB, KD, 4, NT, 2>(a, nchunk, st);
+            else
+                launch_cc_k<T, TI, MAXE, WB, KD, 4>(a, nchunk, st);
+        } else {
+            launch_cc_k<T, TI, MAXE, WB, KD, 8>(a, nchunk, st);
+        }
+    };
+    if constexpr (MAXE == 8)
+        by_kind(a.fd.N, go);
+    else
+        by_pow2(a.fd.N, go);
 }
 
 template <typename T, typename TI, bool WB>
@@ -263,19 +260,14 @@ static hipError_t launch_cc_t(const CcArgs &a, int nchunk, hipStream_t st)
     const int work = (a.W / 2) * a.fd.N;
     if (big_fft(a.fd.N)) {
         // one complex sequence (a column and its mirror) per tile; rows per thread = N / NTB <= 8
-        const bool p2 = is_pow2(a.fd.N);
         if (a.W != 2 || a.fd.N > 8 * NTB) return hipErrorInvalidValue;
-        if (a.fd.N <= 4 * NTB) {
-            if (p2)
-                launch_cc_k<T, TI, 4, WB, true, 4, NTB>(a, nchunk, st);
+        by_pow2(a.fd.N, [&](auto kd) {
+            constexpr int KD = decltype(kd)::value;
+            if (a.fd.N <= 4 * NTB)
+                launch_cc_k<T, TI, 4, WB, KD, 4, NTB>(a, nchunk, st);
             else
-                launch_cc_k<T, TI, 4, WB, false, 4, NTB>(a, nchunk, st);
-        } else {
-            if (p2)
-                launch_cc_k<T, TI, 8, WB, true, 8, NTB>(a, nchunk, st);
-            else
-                launch_cc_k<T, TI, 8, WB, false, 8, NTB>(a, nchunk, st);
-        }
+                launch_cc_k<T, TI, 8, WB, KD, 8, NTB>(a, nchunk, st);
+        });
         return hipGetLastError();
     }
     if (work <= 8 * NT)

@@ -19,9 +19,9 @@
 //                          with F_k = C_k - i S_k and F_{N-k} = conj(F_k), i.e.
 //                          y_j = C_0 + (-1)^j C_M + 2 sum_{k=1}^{M-1}(C_k cos + S_k sin)
 //
-// The FFT itself is a Stockham autosort transform with radix-2/3/4/5/7/8
-// butterflies held in registers and a direct (output-by-output) stage for
-// any other prime factor.  Twiddles come from a table w[t] = exp(-2 pi i t/N)
+// The FFT itself is a Stockham autosort transform with radix-2/3/4/5/8
+// butterflies held in registers (FP64 also 7, 11 and 13); larger prime factors
+// take a dense product on the matrix cores (FP64) or direct sums (FP32).  Twiddles come from a table w[t] = exp(-2 pi i t/N)
 // computed on the host in extended precision.
 #pragma once
 
@@ -60,10 +60,15 @@ __device__ __forceinline__ cx<T> rot90(cx<T> a)
 
 constexpr int kMaxStages = 16;
 
+// Transform lengths by the radices they need: any, powers of two (2, 4, 8), or
+// no prime factor above 5.
+enum LenKind { kAnyLen = 0, kPow2 = 1, kSmooth = 2 };
+
 struct FftDesc {
     int N;   // transform length (even)
     int M;   // N / 2
     int nst; // number of Stockham stages
+    int direct; // large prime radices as direct sums in every precision (mixed plans)
     int rad[kMaxStages];
     int ns[kMaxStages];          // product of the radices before the stage
     unsigned nsmag[kMaxStages];  // ceil(2^32 / ns) for ns not a power of two, else 0
@@ -137,6 +142,53 @@ __device__ __forceinline__ void dft8_lower(cx<T> *a)
     dft8_combine<T, INV>(a, e, o);
 }
 
+// In-register DFT of odd prime length R from the sums a_r + a_{R-r} and the
+// differences a_r - a_{R-r}: with A_q the cosine sum of the first and B_q the
+// sine sum of the second, X_q and X_{R-q} are A_q + and - rot90(B_q), a quarter
+// of the multiplications of the direct sums. The roots are read from the table
+// (literals would be hoisted out of the loop over the stages and held in
+// registers throughout: 224 instead of 140 VGPRs per thread).
+template <int R, bool INV>
+__device__ __forceinline__ void dft_odd(cx<double> *a, const cx<double> *tw, int N)
+{
+    constexpr int H = (R - 1) / 2;
+    cx<double> w[H];
+#pragma unroll
+    for (int m = 1; m <= H; ++m) w[m - 1] = tw[m * (N / R)]; // (cos, -sin) 2 pi m / R
+    cx<double> x0 = a[0];
+#pragma unroll
+    for (int r = 1; r <= H; ++r) {
+        const cx<double> t = a[r];
+        a[r] = cadd(t, a[R - r]);
+        a[R - r] = csub(t, a[R - r]);
+        x0 = cadd(x0, a[r]);
+    }
+    cx<double> p[H], q[H];
+#pragma unroll
+    for (int k = 1; k <= H; ++k) {
+        cx<double> A = a[0], B = {0.0, 0.0};
+#pragma unroll
+        for (int r = 1; r <= H; ++r) {
+            const int m = (r * k) % R;
+            const double c = w[(m <= H ? m : R - m) - 1].x;
+            const double sn = m <= H ? -w[m - 1].y : w[R - m - 1].y;
+            A.x = fma(c, a[r].x, A.x);
+            A.y = fma(c, a[r].y, A.y);
+            B.x = fma(sn, a[R - r].x, B.x);
+            B.y = fma(sn, a[R - r].y, B.y);
+        }
+        const cx<double> t = rot90<double, INV>(B);
+        p[k - 1] = cadd(A, t);
+        q[k - 1] = csub(A, t);
+    }
+    a[0] = x0;
+#pragma unroll
+    for (int k = 1; k <= H; ++k) {
+        a[k] = p[k - 1];
+        a[R - k] = q[k - 1];
+    }
+}
+
 // In-register DFT of length R (forward: exp(-2 pi i/R); inverse: conjugate).
 template <typename T, int R, bool INV>
 __device__ __forceinline__ void dft_small(cx<T> *a, const cx<T> *tw, int N)
@@ -185,22 +237,12 @@ __device__ __forceinline__ void dft_small(cx<T> *a, const cx<T> *tw, int N)
         a[2] = cadd(t2, u2);
         a[3] = csub(t2, u2);
     } else {
-        // R = 7: direct sum with table roots of unity w_R^m = w_N^(m N/R)
-        cx<T> out[R];
-        const int step = N / R;
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            cx<T> acc = a[0];
-#pragma unroll
-            for (int r = 1; r < R; ++r) acc = cadd(acc, cmul(a[r], twid<T, INV>(tw, ((r * q) % R) * step)));
-            out[q] = acc;
-        }
-#pragma unroll
-        for (int q = 0; q < R; ++q) a[q] = out[q];
+        static_assert(sizeof(T) == 8, "FP32 tiles take direct sums for these radices");
+        dft_odd<R, INV>(a, tw, N);
     }
 }
 
-// One Stockham stage of radix R (R <= 8) over nseq = 2^lgs sequences of
+// One Stockham stage of radix R (R <= 13) over nseq = 2^lgs sequences of
 // length N.  MAXE bounds the complex elements a thread holds
 // (nseq * N <= MAXE * NT).
 template <typename T, int R, int MAXE, int NT, bool INV>
@@ -245,43 +287,224 @@ __device__ __forceinline__ void stage_bfly(T *buf, int rs, int lgs, const FftDes
     __syncthreads();
 }
 
-// Stockham stage of arbitrary radix R computed output by output.
-template <typename T, int MAXE, int NT, bool INV>
+// floor(x / d) = __umulhi(x, recip_u(d)) for 0 <= x < 2^16, 2 <= d < 2^16.
+__device__ __forceinline__ unsigned recip_u(int d) { return 0xffffffffu / (unsigned)d + 1u; }
+
+// Stockham stage of any radix as direct sums. A thread forms ST * QT outputs,
+// QT neighbouring frequencies of ST sequences, so that an input read from LDS
+// serves QT outputs and a twiddle ST (one output at a time was bound by its two
+// LDS reads per input, 16 bytes for four FP32 operations).
+template <typename T, int MAXE, int NT, bool INV, int ST>
 __device__ __forceinline__ void stage_direct(T *buf, int rs, int lgs, const FftDesc &fd, int st,
-                                             const cx<T> *tw, int tid)
+                                                    const cx<T> *tw, int tid)
 {
+    constexpr int QT = (sizeof(T) == 8 ? 4 : 8) / ST; // (FP64: half as many held registers)
+    // items per thread: at most MAXE NT / (R ST) groups times ceil(R / QT), most
+    // groups per frequency at R = 7 (4 of 2, 2 of 4), 13 (4 of 4) and 11 (2 of 8)
+    constexpr int RW = QT == 2 ? 7 : QT == 4 ? 13 : 11, GW = QT == 8 ? 2 : 4;
+    constexpr int IPT = (MAXE * GW + ST * RW - 1) / (ST * RW);
     const int N = fd.N, Ns = fd.ns[st], R = fd.rad[st];
-    const int NR = N / R;
-    const int tot = N << lgs;
-    const int tstep = N / (Ns * R);
-    const int smask = (1 << lgs) - 1;
-    cx<T> out[MAXE];
+    const int NR = N / R, tstep = N / (Ns * R);
+    const int ncg = (NR << lgs) / ST;  // (position, group of ST sequences)
+    const int nqg = (R + QT - 1) / QT;
+    const int items = ncg * nqg, lgsg = lgs - (ST == 2 ? 1 : 0);
+    const unsigned mag = recip_u(ncg);
+    cx<T> acc[IPT][QT][ST];
 #pragma unroll
-    for (int i = 0; i < MAXE; ++i) {
+    for (int i = 0; i < IPT; ++i) {
         const int e = tid + i * NT;
-        if (e < tot) {
-            const int s = e & smask, o = e >> lgs;
-            const int jm = fmod_ns(o, Ns, fd.nsmag[st], fd.nslg[st]);
-            const int t = (o - jm) / Ns, q = t % R, jh = t / R;
-            const int j = jh * Ns + jm;
-            const int E = jm * tstep + q * NR; // exponent per input index r, in units of w_N
-            cx<T> acc = lds_c(buf, rs, j, s);
-            int ex = 0;
-            for (int r = 1; r < R; ++r) {
-                ex += E;
-                if (ex >= N) ex -= N;
-                acc = cadd(acc, cmul(lds_c(buf, rs, j + r * NR, s), twid<T, INV>(tw, ex)));
+        if (e >= items) continue;
+        const int qg = (int)__umulhi((unsigned)e, mag), cg = e - qg * ncg;
+        const int s0 = (cg & ((1 << lgsg) - 1)) * ST, j = cg >> lgsg;
+        const int jm = fmod_ns(j, Ns, fd.nsmag[st], fd.nslg[st]);
+        int E[QT], ex[QT];
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            const int q = min(qg * QT + u, R - 1);
+            E[u] = jm * tstep + q * NR; // exponent per input index r, in units of w_N
+            ex[u] = 0;
+        }
+#pragma unroll
+        for (int v = 0; v < ST; ++v) {
+            const cx<T> x = lds_c(buf, rs, j, s0 + v);
+#pragma unroll
+            for (int u = 0; u < QT; ++u) acc[i][u][v] = x;
+        }
+        for (int r = 1; r < R; ++r) {
+            cx<T> x[ST];
+#pragma unroll
+            for (int v = 0; v < ST; ++v) x[v] = lds_c(buf, rs, j + r * NR, s0 + v);
+#pragma unroll
+            for (int u = 0; u < QT; ++u) {
+                ex[u] += E[u];
+                if (ex[u] >= N) ex[u] -= N;
+                const cx<T> w = twid<T, INV>(tw, ex[u]);
+#pragma unroll
+                for (int v = 0; v < ST; ++v) acc[i][u][v] = cadd(acc[i][u][v], cmul(x[v], w));
             }
-            out[i] = acc;
         }
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < MAXE; ++i) {
+    for (int i = 0; i < IPT; ++i) {
         const int e = tid + i * NT;
-        if (e < tot) lds_cs(buf, rs, e >> lgs, e & smask, out[i]);
+        if (e >= items) continue;
+        const int qg = (int)__umulhi((unsigned)e, mag), cg = e - qg * ncg;
+        const int s0 = (cg & ((1 << lgsg) - 1)) * ST, j = cg >> lgsg;
+        const int jm = fmod_ns(j, Ns, fd.nsmag[st], fd.nslg[st]);
+        const int base = (j - jm) * R + jm;
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            const int q = qg * QT + u;
+            if (q < R) {
+#pragma unroll
+                for (int v = 0; v < ST; ++v) lds_cs(buf, rs, base + q * Ns, s0 + v, acc[i][u][v]);
+            }
+        }
     }
     __syncthreads();
+}
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// The value of the neighbouring lane (lane ^ 1).
+__device__ __forceinline__ double swap_pair(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xF, 0xF, true); // quad_perm [1,0,3,2]
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Most 16 x 16 output blocks of stage_prime per wave.
+constexpr int kPrimeBlocks = 4;
+
+// Blocks of stage_prime: 16 frequencies (of 0..(R-1)/2) by 16 real columns.
+__device__ __forceinline__ int prime_blocks(const FftDesc &fd, int st, int lgs)
+{
+    const int R = fd.rad[st], ncol = (fd.N / R) << (lgs + 1);
+    return ((R + 1) / 2 + 15) / 16 * ((ncol + 15) >> 4);
+}
+
+// FP64 Stockham stage of an odd prime radix R on the matrix cores. The inputs
+// are replaced in LDS by the (twiddled) sums a_r = x_r + x_{R-r} and differences
+// b_r = x_r - x_{R-r}, r = 1..h, h = (R-1)/2; then with the real columns of the
+// tile at all N/R positions as columns,
+//   A_q = x_0 + sum_r cos(2 pi q r/R) a_r,   B_q = sum_r sin(2 pi q r/R) b_r
+// are two (h+1) x h by h x columns products, and X_q, X_{R-q} = A_q -/+ i B_q:
+// half of the multiplications of the direct sums, in 16 x 16 x 4 MFMAs whose
+// operands cost 32 bytes of LDS reads per 32 multiply-adds of a lane (direct sums
+// one output at a time: 32 bytes per 4, which bound them). With the shared direct
+// sums and the register radices: 64 boxes of 33..193 nodes 22.1 -> 12.4 ms,
+// 182x174x167 6.40 -> 1.91 ms, 97x90x113 0.69 -> 0.35 ms. One wave owns a block's cosine and
+// sine sums. A lane's four results are rows 4 v + lane/16, column lane & 15; the
+// real and imaginary parts of a sequence are neighbouring columns, so B_q's other
+// part comes from the neighbouring lane.
+template <int NT, bool INV>
+__device__ __forceinline__ void stage_prime(double *buf, int rs, int lgs, const FftDesc &fd, int st,
+                                            const cx<double> *tw, int tid)
+{
+    const int N = fd.N, Ns = fd.ns[st], R = fd.rad[st];
+    const int NR = N / R, h = (R - 1) / 2, tstep = N / (Ns * R);
+    const int lgW = lgs + 1, smask = (1 << lgs) - 1;
+    {
+        const int ncx = NR << lgs; // (position, sequence) pairs
+        const unsigned mag = recip_u(ncx);
+        for (int e = tid; e < h * ncx; e += NT) {
+            const int r1 = (int)__umulhi((unsigned)e, mag), cj = e - r1 * ncx, r = r1 + 1;
+            const int s = cj & smask, j = cj >> lgs;
+            const int jm = fmod_ns(j, Ns, fd.nsmag[st], fd.nslg[st]);
+            cx<double> u = lds_c(buf, rs, j + r * NR, s), v = lds_c(buf, rs, j + (R - r) * NR, s);
+            if (jm != 0) {
+                u = cmul(u, twid<double, INV>(tw, jm * tstep * r));
+                v = cmul(v, twid<double, INV>(tw, jm * tstep * (R - r)));
+            }
+            lds_cs(buf, rs, j + r * NR, s, cadd(u, v));
+            lds_cs(buf, rs, j + (R - r) * NR, s, csub(u, v));
+        }
+    }
+    __syncthreads();
+    const int lane = tid & 63, lm = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ncol = NR << lgW, ncb = (ncol + 15) >> 4, nblk = ncb * ((h + 16) >> 4);
+    v4d A[kPrimeBlocks], B[kPrimeBlocks];
+#pragma unroll
+    for (int i = 0; i < kPrimeBlocks; ++i) {
+        const int b = wave + i * (NT / 64);
+        if (b >= nblk) continue;
+        const int qb = b / ncb, col = min((b - qb * ncb) * 16 + lm, ncol - 1);
+        const int j = col >> lgW, c = col & ((1 << lgW) - 1);
+        const double *p = buf + j * rs + c;
+        const int pitch = NR * rs;
+        const double x0 = p[0];
+        A[i] = v4d{x0, x0, x0, x0};
+        B[i] = v4d{0.0, 0.0, 0.0, 0.0};
+        // row q of the cosines and sines, r = 1 + lk + 4 step; q r mod R by steps
+        // (rows beyond h are computed and not used)
+        const int q = min(qb * 16 + lm, h);
+        const unsigned magR = recip_u(R);
+        auto modR = [&](int x) { return x - (int)__umulhi((unsigned)x, magR) * R; };
+        int m = modR(q * (1 + lk));
+        const int dm = modR(4 * q);
+        for (int r0 = 1; r0 <= h; r0 += 4) {
+            const int r = min(r0 + lk, h);
+            const bool in = r0 + lk <= h;
+            const cx<double> w = tw[m * NR];
+            const double a = p[r * pitch], d = p[(R - r) * pitch];
+            m += dm;
+            if (m >= R) m -= R;
+            A[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? w.x : 0.0, a, A[i], 0, 0, 0);
+            B[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? -w.y : 0.0, d, B[i], 0, 0, 0);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPrimeBlocks; ++i) {
+        const int b = wave + i * (NT / 64);
+        if (b >= nblk) continue;
+        const int qb = b / ncb, col = (b - qb * ncb) * 16 + lm;
+        const int j = min(col, ncol - 1) >> lgW, c = col & ((1 << lgW) - 1);
+        const int jm = fmod_ns(j, Ns, fd.nsmag[st], fd.nslg[st]);
+        double *p = buf + ((j - jm) * R + jm) * rs + c;
+        const int pitch = Ns * rs;
+        // X_q = A_q - i B_q (forward): real part A.x + B.y, imaginary A.y - B.x
+        const bool plus = ((lm & 1) == 0) != INV;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double o = swap_pair(B[i][v]);
+            const int q = qb * 16 + 4 * v + lk;
+            if (q <= h && col < ncol) {
+                p[q * pitch] = plus ? A[i][v] + o : A[i][v] - o;
+                if (q > 0) p[(R - q) * pitch] = plus ? A[i][v] - o : A[i][v] + o;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Stockham stage of any other radix. FP64 plans: 7, 11 and 13 in registers, larger
+// primes on the matrix cores while a wave holds the blocks (all lengths up to
+// 1024). Otherwise direct sums. In the mixed modes (fd.direct) every transform
+// takes those: the sixth-order symbol multiplies the rounding of the FP64 face
+// spectra by up to (M pi)^4, so that another order of their sums would move the
+// FP32 results by up to their own rounding (182x174x167: 6e-9, and 2e-8).
+template <typename T, int MAXE, int NT, bool INV>
+__device__ __forceinline__ void stage_other(T *buf, int rs, int lgs, const FftDesc &fd, int st, const cx<T> *tw,
+                                            int tid)
+{
+    if constexpr (sizeof(T) == 8) {
+        if (!fd.direct) {
+            const int R = fd.rad[st];
+            if (R == 7) return stage_bfly<T, 7, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid);
+            if (R == 11) return stage_bfly<T, 11, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid);
+            if (R == 13) return stage_bfly<T, 13, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid);
+            if (prime_blocks(fd, st, lgs) <= kPrimeBlocks * (NT / 64))
+                return stage_prime<NT, INV>(buf, rs, lgs, fd, st, tw, tid);
+        }
+    }
+    if (lgs > 0)
+        stage_direct<T, MAXE, NT, INV, 2>(buf, rs, lgs, fd, st, tw, tid);
+    else
+        stage_direct<T, MAXE, NT, INV, 1>(buf, rs, lgs, fd, st, tw, tid);
 }
 
 // Stockham stage with every size known at compile time: transform length
@@ -496,14 +719,15 @@ __device__ __forceinline__ void stage_ct_gout(const T *buf, const cx<T> *tw, TO 
 
 // Full length-N complex FFT of 2^lgs sequences held in LDS (in place), in the
 // direction INV (false: exp(-2 pi i t/N), true: the conjugate).
-// P2: N is a power of two (only radix-2/4/8 stages are compiled in).
+// KD: the radices that are compiled in (LenKind; a kernel for fewer of them holds
+// fewer registers).
 // CT = false keeps the generic stages only.  tid: see fft_ct.
 // Z: the upper half of the inputs is zero; the compile-time transforms skip
 // it in their first stage, the generic ones read the zeros.
-template <typename T, int MAXE, int NT, bool P2, bool CT, bool INV, bool Z = false>
+template <typename T, int MAXE, int NT, int KD, bool CT, bool INV, bool Z = false>
 __device__ __forceinline__ void fft_tile_dir(T *buf, int rs, int lgs, const FftDesc &fd, const cx<T> *tw, int tid)
 {
-    if constexpr (P2 && CT && NT == 256) {
+    if constexpr (KD == kPow2 && CT && NT == 256) {
         // (N, tile width) pairs of the default tile budget: N * W / 2 = MAXE * NT
         if constexpr (MAXE == 8) {
             if (fd.N == 512 && rs == 9) return fft_ct<T, NT, 512, 9, 2, INV, Z>(buf, tw, tid);
@@ -511,7 +735,7 @@ __device__ __forceinline__ void fft_tile_dir(T *buf, int rs, int lgs, const FftD
             if (fd.N == 1024 && rs == 5) return fft_ct<T, NT, 1024, 5, 1, INV, Z>(buf, tw, tid);
         }
     }
-    if constexpr (P2) {
+    if constexpr (KD == kPow2) {
         for (int st = 0; st < fd.nst; ++st) {
             const int R = fd.rad[st];
             if (R == 8)
@@ -524,38 +748,46 @@ __device__ __forceinline__ void fft_tile_dir(T *buf, int rs, int lgs, const FftD
         return;
     }
     for (int st = 0; st < fd.nst; ++st) {
+        // the thread index, opaque to the compiler: per-thread index values of
+        // every stage would otherwise be held in registers across the loop (FP64,
+        // all radices: 248 instead of 144 VGPRs)
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        t &= NT - 1;
         switch (fd.rad[st]) {
-        case 2: stage_bfly<T, 2, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid); break;
-        case 3: stage_bfly<T, 3, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid); break;
-        case 4: stage_bfly<T, 4, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid); break;
-        case 5: stage_bfly<T, 5, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid); break;
-        case 8: stage_bfly<T, 8, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid); break;
-        default: stage_direct<T, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid); break;
+        case 2: stage_bfly<T, 2, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t); break;
+        case 3: stage_bfly<T, 3, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t); break;
+        case 4: stage_bfly<T, 4, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t); break;
+        case 5: stage_bfly<T, 5, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t); break;
+        case 8: stage_bfly<T, 8, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t); break;
+        default:
+            if constexpr (KD == kAnyLen) stage_other<T, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t);
+            break;
         }
     }
 }
 
 // fft_tile_dir with the direction as an argument (a constant argument folds
 // to one instantiation).  tid: see fft_ct (-1: threadIdx.x).
-template <typename T, int MAXE, int NT, bool P2 = false, bool CT = true>
+template <typename T, int MAXE, int NT, int KD = kAnyLen, bool CT = true>
 __device__ __forceinline__ void fft_tile(T *buf, int rs, int lgs, const FftDesc &fd, const cx<T> *tw, bool inv,
                                          int tid = -1)
 {
     if (tid < 0) tid = threadIdx.x;
     if (inv)
-        fft_tile_dir<T, MAXE, NT, P2, CT, true>(buf, rs, lgs, fd, tw, tid);
+        fft_tile_dir<T, MAXE, NT, KD, CT, true>(buf, rs, lgs, fd, tw, tid);
     else
-        fft_tile_dir<T, MAXE, NT, P2, CT, false>(buf, rs, lgs, fd, tw, tid);
+        fft_tile_dir<T, MAXE, NT, KD, CT, false>(buf, rs, lgs, fd, tw, tid);
 }
 
 // Forward transform of zero-padded sequences: rows N/2..N-1 of the tile must
 // hold zeros (the generic stages read them); tid: see fft_ct.
-template <typename T, int MAXE, int NT, bool P2 = false, bool CT = true>
+template <typename T, int MAXE, int NT, int KD = kAnyLen, bool CT = true>
 __device__ __forceinline__ void fft_tile_zpad(T *buf, int rs, int lgs, const FftDesc &fd, const cx<T> *tw,
                                               int tid = -1)
 {
     if (tid < 0) tid = threadIdx.x;
-    fft_tile_dir<T, MAXE, NT, P2, CT, false, true>(buf, rs, lgs, fd, tw, tid);
+    fft_tile_dir<T, MAXE, NT, KD, CT, false, true>(buf, rs, lgs, fd, tw, tid);
 }
 
 // After a forward zero-padded FFT: write C and S in slot layout (in place).

@@ -907,7 +907,7 @@ __device__ __forceinline__ void final_row(const FinalArgs &a, int i, int kB, dou
         for (int t = nt; t < 3; ++t) r[4 + par * 3 + t] = (TR)0;
 }
 
-template <typename T, int MAXE, bool P2, int WC, int NTT, int NC>
+template <typename T, int MAXE, int KD, int WC, int NTT, int NC>
 __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
 {
     constexpr bool BIG = NTT != NT;
@@ -925,7 +925,7 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     // WC > 0: tile width known at compile time (row offsets become shifts)
     // NC > 0: the transform length, known at compile time (only the
     // compile-time Stockham stages of that length are built in)
-    static_assert(NC == 0 || (P2 && MAXE == 8 && !BIG && NC * WC == 16 * NT), "no compile-time stages");
+    static_assert(NC == 0 || (KD == kPow2 && MAXE == 8 && !BIG && NC * WC == 16 * NT), "no compile-time stages");
     FftDesc fdc{};
     if constexpr (NC > 0) {
         fdc.N = NC;
@@ -1067,9 +1067,9 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
         }
     } else if (!a.pre) {
         if (a.nrows_in <= M - 1)
-            fft_tile_zpad<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, tid);
+            fft_tile_zpad<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, tid);
         else
-            fft_tile<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, false, tid);
+            fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, false, tid);
     }
     // One sweep over the row pairs (k, N-k) of every complex sequence s
     // (real columns 2s and 2s+1):
@@ -1151,7 +1151,7 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
             stage_ct_gout<T, T, NTT, NC, WC + 1, LGSC>(buf, tw, g, 1, a.nrows_in, nc, a.irs, a.ics, (T)0.5, tid);
         }
     } else {
-        fft_tile<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, true, tid);
+        fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, true, tid);
         tile_store<T, T, NTT>(buf, rs, 1, g, a.nrows_in, nc, a.irs, a.ics, (T)0.5, lgW, tid);
     }
     if constexpr (!PF) break; // one tile per block: no loop for the compiler to hoist out of
@@ -1159,31 +1159,31 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     }
 }
 
-template <typename T, int MAXE, bool P2, int WC, int NTT = NT, int NC = 0>
+template <typename T, int MAXE, int KD, int WC, int NTT = NT, int NC = 0>
 static void launch_final_n(const FinalArgs &a, int nblk, size_t lds, hipStream_t st)
 {
-    const void *fn = (const void *)&k_final<T, MAXE, P2, WC, NTT, NC>;
+    const void *fn = (const void *)&k_final<T, MAXE, KD, WC, NTT, NC>;
     set_lds(fn, lds);
     int grid = nblk;
     if (WC > 0 && NTT == NT && sizeof(T) == 8 && NC == 0) { // persistent blocks (PF in k_final)
         const int r = resident_blocks(fn, NTT, lds);
         if (r > 0 && r < nblk) grid = r;
     }
-    hipLaunchKernelGGL((k_final<T, MAXE, P2, WC, NTT, NC>), dim3(grid), dim3(NTT), lds, st, a, nblk);
+    hipLaunchKernelGGL((k_final<T, MAXE, KD, WC, NTT, NC>), dim3(grid), dim3(NTT), lds, st, a, nblk);
 }
 
 // Compile-time widths 4, 8, 16 of the default tile budget (N WC / 2 = 8 NT):
 // the transform length at compile time too when it is the plan's.
-template <typename T, int MAXE, bool P2, int WC, int NTT = NT>
+template <typename T, int MAXE, int KD, int WC, int NTT = NT>
 static void launch_final_w(const FinalArgs &a, int nblk, size_t lds, hipStream_t st)
 {
-    constexpr int NCT = (MAXE == 8 && P2 && NTT == NT && (WC == 4 || WC == 8 || WC == 16)) ? 16 * NT / WC : 0;
+    constexpr int NCT = (MAXE == 8 && KD == kPow2 && NTT == NT && (WC == 4 || WC == 8 || WC == 16)) ? 16 * NT / WC : 0;
     if constexpr (NCT > 0)
-        if (a.fd.N == NCT) return launch_final_n<T, MAXE, P2, WC, NTT, NCT>(a, nblk, lds, st);
-    launch_final_n<T, MAXE, P2, WC, NTT>(a, nblk, lds, st);
+        if (a.fd.N == NCT) return launch_final_n<T, MAXE, KD, WC, NTT, NCT>(a, nblk, lds, st);
+    launch_final_n<T, MAXE, KD, WC, NTT>(a, nblk, lds, st);
 }
 
-template <typename T, int MAXE, bool P2>
+template <typename T, int MAXE, int KD>
 static void launch_final_k(const FinalArgs &a, int nblk, hipStream_t st)
 {
     // tile + staged column (W) invariants, 12 values of type T each (the row
@@ -1193,56 +1193,37 @@ static void launch_final_k(const FinalArgs &a, int nblk, hipStream_t st)
     // thread must cover the tile's rows
     const bool rc = a.irs == 1 && a.ics != 1;
     if (a.W == 8 && PairMap<NT, 8, MAXE>::covers(a.nrows_in, rc))
-        launch_final_w<T, MAXE, P2, 8>(a, nblk, lds, st);
+        launch_final_w<T, MAXE, KD, 8>(a, nblk, lds, st);
     else if (a.W == 16 && PairMap<NT, 16, MAXE>::covers(a.nrows_in, rc))
-        launch_final_w<T, MAXE, P2, 16>(a, nblk, lds, st);
+        launch_final_w<T, MAXE, KD, 16>(a, nblk, lds, st);
     else if (a.W == 32 && PairMap<NT, 32, MAXE>::covers(a.nrows_in, rc))
-        launch_final_w<T, MAXE, P2, 32>(a, nblk, lds, st);
+        launch_final_w<T, MAXE, KD, 32>(a, nblk, lds, st);
     else
-        launch_final_w<T, MAXE, P2, 0>(a, nblk, lds, st);
+        launch_final_w<T, MAXE, KD, 0>(a, nblk, lds, st);
 }
 
 template <typename T>
 static void launch_final_t(const FinalArgs &a, int nblk, int work, hipStream_t st)
 {
-    const bool p2 = is_pow2(a.fd.N);
     if (big_fft(a.fd.N)) {
         // tile + staged columns only (the rows come from the global table)
         const size_t lds = tile_lds<T>(a.fd.N, a.W) + 16 + (size_t)a.W * 12 * sizeof(T);
-        if (work <= 4 * NTB) {
-            if (p2)
-                launch_final_w<T, 4, true, 2, NTB>(a, nblk, lds, st);
+        by_pow2(a.fd.N, [&](auto kd) {
+            constexpr int KD = decltype(kd)::value;
+            if (work <= 4 * NTB)
+                launch_final_w<T, 4, KD, 2, NTB>(a, nblk, lds, st);
             else
-                launch_final_w<T, 4, false, 2, NTB>(a, nblk, lds, st);
-        } else {
-            if (p2)
-                launch_final_w<T, 8, true, 2, NTB>(a, nblk, lds, st);
-            else
-                launch_final_w<T, 8, false, 2, NTB>(a, nblk, lds, st);
-        }
+                launch_final_w<T, 8, KD, 2, NTB>(a, nblk, lds, st);
+        });
         return;
     }
-    if (work <= 4 * NT) {
-        if (p2)
-            launch_final_k<T, 4, true>(a, nblk, st);
+    by_kind(a.fd.N, [&](auto kd) {
+        constexpr int KD = decltype(kd)::value;
+        if (work <= 4 * NT)
+            launch_final_k<T, 4, KD>(a, nblk, st);
         else
-            launch_final_k<T, 4, false>(a, nblk, st);
-    } else if (work <= 8 * NT) {
-        if (p2)
-            launch_final_k<T, 8, true>(a, nblk, st);
-        else
-            launch_final_k<T, 8, false>(a, nblk, st);
-    } else if (work <= 16 * NT) {
-        if (p2)
-            launch_final_k<T, 16, true>(a, nblk, st);
-        else
-            launch_final_k<T, 16, false>(a, nblk, st);
-    } else {
-        if (p2)
-            launch_final_k<T, 32, true>(a, nblk, st);
-        else
-            launch_final_k<T, 32, false>(a, nblk, st);
-    }
+            launch_final_k<T, 8, KD>(a, nblk, st);
+    });
 }
 
 // Row table of the final pass in global memory, one per batch index
@@ -1284,7 +1265,7 @@ hipError_t launch_final(const FinalArgs &a, hipStream_t st)
     if (!a.rowtab) return hipErrorInvalidValue; // the row invariants are read from it
     if (big_fft(a.fd.N) && (a.geo.d != 2 || a.W != 2 || work > 8 * NTB))
         return hipErrorInvalidValue;
-    if (!big_fft(a.fd.N) && work > 32 * NT) return hipErrorInvalidValue;
+    if (!big_fft(a.fd.N) && work > 8 * NT) return hipErrorInvalidValue; // (the tile budget of the pass)
     if (!tile_strides_ok(a.nrows_in, a.irs, a.ncols, a.ics)) return hipErrorInvalidValue;
     if (a.mixed)
         launch_final_t<float>(a, nblk, work, st);

@@ -31,13 +31,13 @@ __device__ __forceinline__ void tile_of(const PassArgs &a, int ncb, int lb, int 
 // rows and stored.  WT > 0: the tile width, known at compile time (equal to
 // a.W, which the launcher checks); NC > 0 likewise the transform length (only
 // the compile-time Stockham stages of that length are built in).
-template <typename T, typename TI, typename TO, int MAXE, bool P2, int NTT, int WT = 0, int NC = 0>
+template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT, int WT = 0, int NC = 0>
 __device__ __forceinline__ void pass_tile(const PassArgs &a, int lb)
 {
     constexpr bool BIG = NTT != NT;
     extern __shared__ __align__(16) unsigned char smem[];
     // (only the pairs that have compile-time stages: fdc carries no stage list)
-    static_assert(NC == 0 || (P2 && MAXE == 8 && !BIG && NC * WT == 16 * NT), "no compile-time stages");
+    static_assert(NC == 0 || (KD == kPow2 && MAXE == 8 && !BIG && NC * WT == 16 * NT), "no compile-time stages");
     FftDesc fdc{};
     if constexpr (NC > 0) {
         fdc.N = NC;
@@ -88,9 +88,9 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int lb)
     // zero-padded input (rows 1..nrows_in <= M-1, zeros from row M on):
     // the first stage skips the zero half
     if (a.in_mode == IN_ZPAD && a.nrows_in <= M - 1)
-        fft_tile_zpad<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw);
+        fft_tile_zpad<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw);
     else
-        fft_tile<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, inv);
+        fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, inv);
     if (a.in_mode == IN_ZPAD || a.in_mode == IN_ZPAD0) post_cs<T, MAXE, NTT>(buf, rs, lgs, M);
     if (a.accum)
         tile_store_acc<T, TO, NTT>(buf, rs, a.out_r0, out, a.out_nrows, nc, a.ors, a.ocs, (T)a.scale, lgW);
@@ -107,18 +107,18 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int lb)
 // registers while the current one is transformed.  The thread index is made
 // opaque inside that loop so that the compiler recomputes per-thread index
 // values instead of holding them in registers for the whole loop.
-template <typename T, typename TI, typename TO, int MAXE, bool P2, int NTT, int WC, int EPT, int NC>
+template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT, int WC, int EPT, int NC>
 __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
 {
     constexpr bool PF = WC > 0;
     if constexpr (!PF) {
         // one tile per block (WC < 0: of the compile-time width -WC)
-        pass_tile<T, TI, TO, MAXE, P2, NTT, (WC < 0 ? -WC : 0), NC>(a, xcd_remap(blockIdx.x, ntiles));
+        pass_tile<T, TI, TO, MAXE, KD, NTT, (WC < 0 ? -WC : 0), NC>(a, xcd_remap(blockIdx.x, ntiles));
         return;
     }
     constexpr bool BIG = NTT != NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    static_assert(!PF || NC == 0 || (P2 && MAXE == 8 && !BIG && NC * WC == 16 * NT), "no compile-time stages");
+    static_assert(!PF || NC == 0 || (KD == kPow2 && MAXE == 8 && !BIG && NC * WC == 16 * NT), "no compile-time stages");
     FftDesc fdc{};
     if constexpr (NC > 0) {
         fdc.N = NC;
@@ -197,9 +197,9 @@ __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
             inv = true;
         }
         if (mode == IN_ZPAD && a.nrows_in <= M - 1)
-            fft_tile_zpad<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, tid);
+            fft_tile_zpad<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, tid);
         else
-            fft_tile<T, MAXE, NTT, P2>(buf, rs, lgs, fd, tw, inv, tid);
+            fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, inv, tid);
         if (mode == IN_ZPAD || mode == IN_ZPAD0) post_cs<T, MAXE, NTT>(buf, rs, lgs, M, tid);
         if (a.accum)
             tile_store_acc<T, TO, NTT>(buf, rs, a.out_r0, out0 + oo, a.out_nrows, nc, a.ors, a.ocs, (T)a.scale, lgW,
@@ -211,31 +211,31 @@ __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
     }
 }
 
-template <typename T, typename TI, typename TO, int MAXE, bool P2, int NTT = NT, int WC = 0, int EPT = 0, int NC = 0>
+template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT = NT, int WC = 0, int EPT = 0, int NC = 0>
 static void launch_pass_k(const PassArgs &a, int ntiles, size_t lds, hipStream_t st)
 {
-    const void *fn = (const void *)&k_pass<T, TI, TO, MAXE, P2, NTT, WC, EPT, NC>;
+    const void *fn = (const void *)&k_pass<T, TI, TO, MAXE, KD, NTT, WC, EPT, NC>;
     set_lds(fn, lds);
     int grid = ntiles;
     if (WC > 0) {
         const int r = resident_blocks(fn, NTT, lds);
         if (r > 0 && r < ntiles) grid = r;
     }
-    hipLaunchKernelGGL((k_pass<T, TI, TO, MAXE, P2, NTT, WC, EPT, NC>), dim3((unsigned)grid), dim3(NTT), lds, st,
+    hipLaunchKernelGGL((k_pass<T, TI, TO, MAXE, KD, NTT, WC, EPT, NC>), dim3((unsigned)grid), dim3(NTT), lds, st,
                        a, ntiles);
 }
 
 // A compile-time width |WC|: the transform length of the default tile budget
 // (N |WC| / 2 = 8 NT, lengths 256, 512, 1024) also at compile time when it is
 // the plan's.
-template <typename T, typename TI, typename TO, int MAXE, bool P2, int WC, int EPT>
+template <typename T, typename TI, typename TO, int MAXE, int KD, int WC, int EPT>
 static void launch_pass_w(const PassArgs &a, int ntiles, size_t lds, hipStream_t st)
 {
     constexpr int AW = WC < 0 ? -WC : WC;
-    constexpr int NCT = (MAXE == 8 && P2 && (AW == 4 || AW == 8 || AW == 16)) ? 16 * NT / AW : 0;
+    constexpr int NCT = (MAXE == 8 && KD == kPow2 && (AW == 4 || AW == 8 || AW == 16)) ? 16 * NT / AW : 0;
     if constexpr (NCT > 0)
-        if (a.fd.N == NCT) return launch_pass_k<T, TI, TO, MAXE, P2, NT, WC, EPT, NCT>(a, ntiles, lds, st);
-    launch_pass_k<T, TI, TO, MAXE, P2, NT, WC, EPT>(a, ntiles, lds, st);
+        if (a.fd.N == NCT) return launch_pass_k<T, TI, TO, MAXE, KD, NT, WC, EPT, NCT>(a, ntiles, lds, st);
+    launch_pass_k<T, TI, TO, MAXE, KD, NT, WC, EPT>(a, ntiles, lds, st);
 }
 
 // Compile-time tile widths W = 4, 8, 16 (the default widths of 2M = 1024,
@@ -250,31 +250,31 @@ static bool pass_fits(const PassArgs &a)
     return a.W == WC && PairMap<NT, WC, EPT>::covers(a.nrows_in, a.irs == 1 && a.ics != 1);
 }
 
-template <typename T, typename TI, typename TO, int MAXE, bool P2>
+template <typename T, typename TI, typename TO, int MAXE, int KD>
 static void launch_pass_m(const PassArgs &a, int ntiles, size_t lds, hipStream_t st)
 {
     // other lengths from 2M = 512 up (the small uneven boxes of a batch measured
     // faster with one tile per block)
     if constexpr (MAXE == 8) {
-        if (!(a.in_mode == IN_HERM && a.nsum > 1) && (P2 || a.fd.N >= 512)) {
+        if (!(a.in_mode == IN_HERM && a.nsum > 1) && (KD == kPow2 || a.fd.N >= 512)) {
             constexpr bool wide = sizeof(T) == 8; // FP64 tiles: every mode, EPT up to 2 MAXE
             if (!wide && a.in_mode != IN_ZPAD && a.in_mode != IN_ZPAD0) {
                 // one tile per block, the default widths at compile time
-                if (P2 && a.W == 8) return launch_pass_w<T, TI, TO, MAXE, P2, -8, 0>(a, ntiles, lds, st);
-                if (P2 && a.W == 16) return launch_pass_w<T, TI, TO, MAXE, P2, -16, 0>(a, ntiles, lds, st);
-                return launch_pass_k<T, TI, TO, MAXE, P2>(a, ntiles, lds, st);
+                if (KD == kPow2 && a.W == 8) return launch_pass_w<T, TI, TO, MAXE, KD, -8, 0>(a, ntiles, lds, st);
+                if (KD == kPow2 && a.W == 16) return launch_pass_w<T, TI, TO, MAXE, KD, -16, 0>(a, ntiles, lds, st);
+                return launch_pass_k<T, TI, TO, MAXE, KD>(a, ntiles, lds, st);
             }
-            if (pass_fits<8, 8>(a)) return launch_pass_w<T, TI, TO, 8, P2, 8, 8>(a, ntiles, lds, st);
-            if (pass_fits<16, 8>(a)) return launch_pass_w<T, TI, TO, 8, P2, 16, 8>(a, ntiles, lds, st);
-            if (pass_fits<4, 8>(a)) return launch_pass_w<T, TI, TO, 8, P2, 4, 8>(a, ntiles, lds, st);
+            if (pass_fits<8, 8>(a)) return launch_pass_w<T, TI, TO, 8, KD, 8, 8>(a, ntiles, lds, st);
+            if (pass_fits<16, 8>(a)) return launch_pass_w<T, TI, TO, 8, KD, 16, 8>(a, ntiles, lds, st);
+            if (pass_fits<4, 8>(a)) return launch_pass_w<T, TI, TO, 8, KD, 4, 8>(a, ntiles, lds, st);
             if constexpr (wide) {
-                if (pass_fits<8, 16>(a)) return launch_pass_w<T, TI, TO, 8, P2, 8, 16>(a, ntiles, lds, st);
-                if (pass_fits<16, 16>(a)) return launch_pass_w<T, TI, TO, 8, P2, 16, 16>(a, ntiles, lds, st);
-                if (pass_fits<4, 16>(a)) return launch_pass_w<T, TI, TO, 8, P2, 4, 16>(a, ntiles, lds, st);
+                if (pass_fits<8, 16>(a)) return launch_pass_w<T, TI, TO, 8, KD, 8, 16>(a, ntiles, lds, st);
+                if (pass_fits<16, 16>(a)) return launch_pass_w<T, TI, TO, 8, KD, 16, 16>(a, ntiles, lds, st);
+                if (pass_fits<4, 16>(a)) return launch_pass_w<T, TI, TO, 8, KD, 4, 16>(a, ntiles, lds, st);
             }
         }
     }
-    launch_pass_k<T, TI, TO, MAXE, P2>(a, ntiles, lds, st);
+    launch_pass_k<T, TI, TO, MAXE, KD>(a, ntiles, lds, st);
 }
 
 template <typename T, typename TI, typename TO>
@@ -284,43 +284,31 @@ static hipError_t launch_pass_t(const PassArgs &a, hipStream_t st)
     const int64_t ntl = (int64_t)ncb * a.nbatch;
     const size_t lds = tile_lds<T>(a.fd.N, a.W);
     const int work = (a.W / 2) * a.fd.N;
-    const bool p2 = is_pow2(a.fd.N);
     if (ntl <= 0) return hipSuccess;
     if (ntl > INT32_MAX) return hipErrorInvalidValue;
     const int ntiles = (int)ntl;
     if (big_fft(a.fd.N)) {
         if (a.W != 2 || work > 8 * NTB) return hipErrorInvalidValue;
-        if (work <= 4 * NTB) {
-            if (p2)
-                launch_pass_k<T, TI, TO, 4, true, NTB>(a, ntiles, lds, st);
+        by_pow2(a.fd.N, [&](auto kd) {
+            constexpr int KD = decltype(kd)::value;
+            if (work <= 4 * NTB)
+                launch_pass_k<T, TI, TO, 4, KD, NTB>(a, ntiles, lds, st);
             else
-                launch_pass_k<T, TI, TO, 4, false, NTB>(a, ntiles, lds, st);
-        } else {
-            if (p2)
-                launch_pass_k<T, TI, TO, 8, true, NTB>(a, ntiles, lds, st);
-            else
-                launch_pass_k<T, TI, TO, 8, false, NTB>(a, ntiles, lds, st);
-        }
+                launch_pass_k<T, TI, TO, 8, KD, NTB>(a, ntiles, lds, st);
+        });
         return hipGetLastError();
     }
-    if (work <= 4 * NT) {
-        if (p2)
-            launch_pass_m<T, TI, TO, 4, true>(a, ntiles, lds, st);
-        else
-            launch_pass_m<T, TI, TO, 4, false>(a, ntiles, lds, st);
-    } else if (work <= 8 * NT) {
-        if (p2)
-            launch_pass_m<T, TI, TO, 8, true>(a, ntiles, lds, st);
-        else
-            launch_pass_m<T, TI, TO, 8, false>(a, ntiles, lds, st);
-    } else if (work <= 16 * NT) {
-        if (p2)
-            launch_pass_m<T, TI, TO, 16, true>(a, ntiles, lds, st);
-        else
-            launch_pass_m<T, TI, TO, 16, false>(a, ntiles, lds, st);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    if (work > 16 * NT) return hipErrorInvalidValue;
+    if (work > 8 * NT)
+        by_pow2(a.fd.N, [&](auto kd) { launch_pass_m<T, TI, TO, 16, decltype(kd)::value>(a, ntiles, lds, st); });
+    else
+        by_kind(a.fd.N, [&](auto kd) {
+            constexpr int KD = decltype(kd)::value;
+            if (work <= 4 * NT)
+                launch_pass_m<T, TI, TO, 4, KD>(a, ntiles, lds, st);
+            else
+                launch_pass_m<T, TI, TO, 8, KD>(a, ntiles, lds, st);
+        });
     return hipGetLastError();
 }
 
@@ -335,13 +323,13 @@ static bool pass_strides_ok(const PassArgs &a)
 // share the element types; the tile budget and the LDS are those of the
 // largest tile.  Used where the passes are small (the per-family transforms
 // of uneven boxes), so that they fill the device together.
-template <typename T, typename TI, typename TO, int MAXE, bool P2>
+template <typename T, typename TI, typename TO, int MAXE, int KD>
 __global__ __launch_bounds__(NT) void k_pass_multi(MultiPassArgs m)
 {
     const int b = xcd_remap(blockIdx.x, m.first[m.n]);
     int i = 0;
     while (i + 1 < m.n && b >= m.first[i + 1]) ++i;
-    pass_tile<T, TI, TO, MAXE, P2, NT>(m.p[i], b - m.first[i]);
+    pass_tile<T, TI, TO, MAXE, KD, NT>(m.p[i], b - m.first[i]);
 }
 
 template <typename T, typename TI, typename TO>
@@ -349,7 +337,7 @@ static hipError_t launch_multi_t(MultiPassArgs &m, hipStream_t st)
 {
     size_t lds = 0;
     int work = 0, tot = 0;
-    bool p2 = true;
+    bool p2 = true, smooth = true;
     for (int i = 0; i < m.n; ++i) {
         const PassArgs &a = m.p[i];
         if (big_fft(a.fd.N) || a.W < 2 || !pass_strides_ok(a)) return hipErrorInvalidValue;
@@ -360,24 +348,25 @@ static hipError_t launch_multi_t(MultiPassArgs &m, hipStream_t st)
         lds = std::max(lds, tile_lds<T>(a.fd.N, a.W));
         work = std::max(work, (a.W / 2) * a.fd.N);
         p2 = p2 && is_pow2(a.fd.N);
+        smooth = smooth && len_kind(a.fd.N) != kAnyLen;
     }
     m.first[m.n] = tot;
     if (tot == 0) return hipSuccess;
+    if (work > 16 * NT) return hipErrorInvalidValue;
     auto go = [&](const void *fn, auto kern) {
         set_lds(fn, lds);
         hipLaunchKernelGGL(kern, dim3((unsigned)tot), dim3(NT), lds, st, m);
     };
-#define IPS_MULTI(MX, PP) go((const void *)&k_pass_multi<T, TI, TO, MX, PP>, k_pass_multi<T, TI, TO, MX, PP>)
-    if (work <= 4 * NT) {
-        if (p2) IPS_MULTI(4, true); else IPS_MULTI(4, false);
-    } else if (work <= 8 * NT) {
-        if (p2) IPS_MULTI(8, true); else IPS_MULTI(8, false);
-    } else if (work <= 16 * NT) {
-        if (p2) IPS_MULTI(16, true); else IPS_MULTI(16, false);
-    } else {
-        return hipErrorInvalidValue;
-    }
-#undef IPS_MULTI
+    with_kind(p2 ? kPow2 : smooth && work <= 8 * NT ? kSmooth : kAnyLen, [&](auto kd) {
+        constexpr int KD = decltype(kd)::value;
+        constexpr int KL = KD == kSmooth ? kAnyLen : KD; // the largest budget: no instance of its own
+        if (work <= 4 * NT)
+            go((const void *)&k_pass_multi<T, TI, TO, 4, KD>, k_pass_multi<T, TI, TO, 4, KD>);
+        else if (work <= 8 * NT)
+            go((const void *)&k_pass_multi<T, TI, TO, 8, KD>, k_pass_multi<T, TI, TO, 8, KD>);
+        else
+            go((const void *)&k_pass_multi<T, TI, TO, 16, KL>, k_pass_multi<T, TI, TO, 16, KL>);
+    });
     return hipGetLastError();
 }
 

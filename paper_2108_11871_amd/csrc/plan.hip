@@ -40,8 +40,9 @@ constexpr int kMaxN3 = 2048;   // 3D: longest transform (2M) per axis
 constexpr int kMaxN12 = 8192;  // 1D and 2D: longest transform (one sequence per tile)
 
 // FFT length N = 2M as a list of Stockham radices (8, 4, 2, 3, 5, 7, other primes)
-bool factor_fft(int N, FftDesc &fd)
+bool factor_fft(int N, bool direct, FftDesc &fd)
 {
+    fd.direct = direct;
     fd.N = N;
     fd.M = N / 2;
     fd.nst = 0;
@@ -794,7 +795,7 @@ int plan_build(ips_plan p, hipStream_t st)
     for (int a = 0; a < d; ++a) g.pref *= 2.0 / p->M[a];
 
     for (int a = 0; a < d; ++a) {
-        if (!factor_fft(p->N[a], p->fd[a])) return fail(IPS_E_UNSUPPORTED, "FFT length not factorable");
+        if (!factor_fft(p->N[a], p->precision != IPS_FP64, p->fd[a])) return fail(IPS_E_UNSUPPORTED, "FFT length not factorable");
         std::vector<cx<double>> w = twiddles(p->N[a]);
         int rc = p->mem.alloc((void **)&p->tw[a], w.size() * sizeof(cx<double>));
         if (rc) return rc;
@@ -833,7 +834,10 @@ int plan_build(ips_plan p, hipStream_t st)
         }
         // a tile holds W/2 columns of the first half of the axis and their
         // mirrors: the chunks split the (I + 1)/2 first-half columns
-        const int W = p->ccW[fam] = fill_width(N[pen], p->work, I[fam], nbatch, kFillConv, 4);
+        // (mixed modes keep the widths, and with them the order of the FP64 sums)
+        const int W = p->ccW[fam] = p->precision == IPS_FP64
+                                        ? fill_width(N[pen], p->work, I[fam], nbatch, kFillConv, 4)
+                                        : tile_width(N[pen], p->work, I[fam]);
         const int hc = (I[fam] + 1) / 2, Wh = W / 2;
         const int ncb = (hc + Wh - 1) / Wh;
         // about 4096 (2M <= 512) or 6144 blocks of 256 threads, a few tiles

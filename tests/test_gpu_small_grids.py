@@ -1,6 +1,7 @@
-"""Small and uneven grids at the edges of the launch-shape rules: tile widths
-narrowed to fill the GPU and the row groups of the final pass, against the
-FP64 oracle (1e-12, the bar of every FP64 parity test)."""
+"""Small and uneven grids at the edges of the launch-shape rules (tile widths
+narrowed to fill the GPU, the row groups of the final pass) and of the prime
+radices, against the FP64 oracle (1e-12 in FP64 and 1e-6 in the mixed modes,
+the bars of every parity test)."""
 import pytest
 
 from oracle import poisson as P
@@ -27,3 +28,24 @@ def test_row_groups_and_narrow_tiles(shape, order):
     phi = api.Plan(shape, h, order=order)(to_dev(rho))
     torch.cuda.synchronize()
     assert rel_err(phi.cpu().numpy(), P.solve(rho, h, order)) < TOL
+
+
+# prime factors 7, 11, 13 (registers); 17 .. 509 (matrix cores: one row block,
+# 16 frequencies exactly, one more than 48, the most blocks per wave); 521 (direct
+# sums: too many blocks); squares and products of them, with and without powers
+# of two, in full and narrowed tiles; in 3D both transforms of a face
+@pytest.mark.parametrize("mode,tol", [("fp64", TOL), ("mixed_fp32_slices", 1e-6)])
+@pytest.mark.parametrize("panels", [(7, 11), (13, 49), (17, 31), (37, 97), (121, 56), (143, 66), (169, 23), (289, 29),
+                                    (323, 13), (257, 181), (502, 11), (509, 7), (521, 19), (13, 17, 22),
+                                    (74, 31, 11), (62, 34, 58)])
+def test_prime_radices(panels, mode, tol):
+    import torch
+    from paper_2108_11871_amd import api
+    from gpu_util import banner, rel_err, to_dev
+
+    shape = tuple(m + 1 for m in panels)
+    banner("shape=%s %s" % (shape, mode))
+    rho, h, _ = I.workload_bumps(shape, seed=34, scale=[1.0, 1.2, 0.9][:len(shape)])
+    phi = api.Plan(shape, h, order=6, precision=mode)(to_dev(rho))
+    torch.cuda.synchronize()
+    assert rel_err(phi.cpu().numpy(), P.solve(rho, h, 6, boundary="fft")) < tol
