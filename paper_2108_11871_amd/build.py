@@ -13,7 +13,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["kernels.hip", "pass.hip", "conv.hip", "adjoint.hip", "screen.hip", "plan.hip"]
+SOURCES = ["pass.hip", "pass_f32.hip", "pass_mixed.hip", "conv.hip", "conv_f32.hip", "conv_mixed.hip",
+           "kernels.hip", "adjoint.hip", "screen.hip", "plan.hip"]
 LIB = os.path.join(HERE, "libipoisson.so")
 ARCH = os.environ.get("IPS_OFFLOAD_ARCH", "gfx950")
 

@@ -1,9 +1,9 @@
 // HIP kernels of the infinite-domain Poisson solver (gfx950).
 //
 // Stage map (paper sections):
-//   k_pass    (pass.hip) pencil transforms: DST-I / zero-padded cos+sin / even (DCT-I) /
+//   k_pass    (pass.h) pencil transforms: DST-I / zero-padded cos+sin / even (DCT-I) /
 //             hermitian synthesis along one axis (Sections 3, 4, 5)
-//   k_cc      (conv.hip) boundary values as sums over slices of 2D (3D problems) or 1D
+//   k_cc      (conv.h) boundary values as sums over slices of 2D (3D problems) or 1D
 //             (2D problems) discrete convolutions, accumulated in Fourier
 //             space with the kernel spectra (Section 4, eqs. Trap2D,
 //             Trap2Dconvolution, convolution)
