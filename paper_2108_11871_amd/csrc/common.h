@@ -80,6 +80,21 @@ inline size_t tile_lds(int N, int W)
     return (size_t)N * sizeof(cx<T>) + (size_t)N * (W + 1) * sizeof(T);
 }
 
+// f(N) with N as a compile-time constant where tiles of W columns and N rows are
+// full register tiles; whether they are.
+template <typename F>
+inline bool rt_length(int N, int W, F f)
+{
+#define IPS_RT(n)                                     \
+    if (N == n && W == RegTile<n>::W) {               \
+        f(std::integral_constant<int, n>());          \
+        return true;                                  \
+    }
+    IPS_RT(256) IPS_RT(512) IPS_RT(1024) IPS_RT(2048) IPS_RT(4096) IPS_RT(8192)
+#undef IPS_RT
+    return false;
+}
+
 // Twiddle table of the transform type: LDS copy (short transforms) or the
 // plan's global table (long ones).
 template <typename T, bool BIG>

@@ -15,6 +15,17 @@
 
 namespace ips {
 
+// Batch entry of the logical block group q: for each wavenumber k_b of the other
+// axis its cosine slot and its sine slot are neighbours (q = 0 -> slot 0;
+// q = 2kb-1 -> slot kb; q = 2kb -> slot Mo+kb, kb < Mo; q = 2Mo-1 -> slot Mo).
+__device__ __forceinline__ int cc_batch(int q, int Mo)
+{
+    if (Mo == 0) return q;
+    if (q == 0) return 0;
+    if (q == 2 * Mo - 1) return Mo;
+    return (q & 1) ? (q + 1) / 2 : Mo + q / 2;
+}
+
 // ---------------------------------------------------------------------------
 // Boundary convolution, contraction over the tile columns (3D and 2D)
 // ---------------------------------------------------------------------------
@@ -25,21 +36,12 @@ namespace ips {
 // an odd count only once), so each kernel-spectrum value loaded serves two
 // columns, and with the C and S rows of the pencil transform four products
 // per face.
-template <typename T, typename TI, int MAXE, bool WB, int KD, int RPT, int NTT, int WHC, int NC>
+template <typename T, typename TI, int MAXE, bool WB, int KD, int RPT, int NTT, int WHC>
 __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
 {
     constexpr bool BIG = NTT != NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    // NC > 0: the transform length, known at compile time (only the
-    // compile-time Stockham stages of that length are built in)
-    // (only the pairs that have compile-time stages: fdc carries no stage list)
-    static_assert(NC == 0 || (KD == kPow2 && MAXE == 8 && NTT == NT && NC * WHC == 8 * NT), "no compile-time stages");
-    FftDesc fdc{};
-    if constexpr (NC > 0) {
-        fdc.N = NC;
-        fdc.M = NC / 2;
-    }
-    const FftDesc &fd = NC > 0 ? fdc : a.fd;
+    const FftDesc &fd = a.fd;
     // the prefetching variants run one tile width only (their launcher checks it)
     const int N = fd.N, M = fd.M, W = WHC > 0 ? 2 * WHC : a.W, rs = BIG ? W : W + 1;
     const int lgW = 31 - __clz(W), lgs = lgW - 1, Wh = W >> 1;
@@ -49,17 +51,7 @@ __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
     // and its sin slot are neighbours, so the blocks reading the same kernel
     // spectra K[.][k_b][.] run together on one XCD (shared L2).
     const int lb = xcd_remap(blockIdx.x, nchunk * a.nbatch);
-    const int ch = lb % nchunk, q = lb / nchunk;
-    int bt = q;
-    if (a.Mo > 0) {
-        // q = 0 -> slot 0; q = 2kb-1 -> slot kb; q = 2kb -> slot Mo+kb (kb < Mo); q = 2Mo-1 -> slot Mo
-        if (q == 0)
-            bt = 0;
-        else if (q == 2 * a.Mo - 1)
-            bt = a.Mo;
-        else
-            bt = (q & 1) ? (q + 1) / 2 : a.Mo + q / 2;
-    }
+    const int ch = lb % nchunk, bt = cc_batch(lb / nchunk, a.Mo);
     const int kb = a.Mo > 0 ? (bt <= a.Mo ? bt : bt - a.Mo) : 0;
     const TI *in = static_cast<const TI *>(a.in) + bt * a.ibs;
     T *Bout = static_cast<T *>(a.Bout);
@@ -203,12 +195,175 @@ __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
     }
 }
 
-template <typename T, typename TI, int MAXE, bool WB, int KD, int RPT, int NTT = NT, int WHC = 0, int NC = 0>
+// The contraction in register tiles (see RegTile): inputs straight from global
+// memory (the next tile's during the transform) into the first stage; the cosine
+// and sine parts are formed in registers after the last stage and written to the
+// LDS once, sequence by sequence, for the sums over the columns (same thread per
+// slot row and same order of the sums as k_cc). 257^3: FP64 219/209/214 -> 205/183/185
+// us, FP32 112/124/115 -> 114/118/111 us; 513^3 FP32 1010/1288/1251 -> 709/1237/1258.
+template <typename T, typename TI, int N, bool WB>
+__global__ __launch_bounds__(RegTile<N>::NTH) void k_cc_rt(CcArgs a, int nchunk)
+{
+    using R = RegTile<N>;
+    constexpr int M = N / 2, W = R::W, Wh = W / 2, P = R::P, NTH = R::NTH;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const cx<T> *tw = tw_table<T, !R::LTW>(smem, a.tw, a.twf);
+    cx<T> *buf = reinterpret_cast<cx<T> *>(smem) + (R::LTW ? N : 0);
+    const int lb = xcd_remap(blockIdx.x, nchunk * a.nbatch);
+    const int ch = lb % nchunk, bt = cc_batch(lb / nchunk, a.Mo);
+    const int kb = a.Mo > 0 ? (bt <= a.Mo ? bt : bt - a.Mo) : 0;
+    const TI *in = static_cast<const TI *>(a.in) + bt * a.ibs;
+    constexpr int TPT = M / NTH > 0 ? M / NTH : 1;
+    double a10[TPT], a11[TPT], a20[TPT], a21[TPT]; // [row 1|2][face 0|M]
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) a10[i] = a11[i] = a20[i] = a21[i] = 0.0;
+    if constexpr (R::LTW) load_twiddles<T, NTH>(reinterpret_cast<cx<T> *>(smem), a.tw, N);
+    const int hc = (a.ncols + 1) >> 1; // first-half columns (the chunked range)
+    const int cbeg = a.interleave ? ch * Wh : ch * a.cols_per_chunk;
+    const int cend = a.interleave ? hc : min(hc, cbeg + a.cols_per_chunk);
+    const int cstep = a.interleave ? nchunk * Wh : Wh;
+    auto n_a = [&](int c) { return min(Wh, cend - c); };
+    auto n_b = [&](int c) { return min(n_a(c), max(0, (a.ncols - 2 * c) >> 1)); };
+    // source column of tile column c of the tile at c0 (-1: none)
+    auto src_col = [&](int c, int c0, int nA, int nB) {
+        const int jj = c < Wh ? c : c - Wh;
+        return c < Wh ? (jj < nA ? c0 + jj : -1) : (jj < nB ? a.ncols - 1 - c0 - jj : -1);
+    };
+    auto fetch = [&](TI(&x)[8], int c0, int tid) {
+        int j, s;
+        rt_plain<N>(tid, j, s);
+        const int nA = n_a(c0), nB = n_b(c0);
+        const int q0 = src_col(2 * s, c0, nA, nB), q1 = src_col(2 * s + 1, c0, nA, nB), ics = (int)a.ics;
+        // (full tiles of contiguous columns: ascending, or descending among the mirrors)
+        const int dir = nA == Wh && nB == Wh && ics == 1 && Wh > 1 ? (2 * s < Wh ? 1 : -1) : 0;
+        rt_fetch<TI, N>(x, in, a.irs, q0 < 0 ? -1 : __mul24(q0, ics), q1 < 0 ? -1 : __mul24(q1, ics), dir, j, 1);
+    };
+    TI x[8];
+    if (cbeg < cend) fetch(x, cbeg, threadIdx.x);
+    __syncthreads(); // the twiddles
+    for (int c0 = cbeg; c0 < cend; c0 += cstep) {
+        const int nA = n_a(c0), nB = n_b(c0);
+        const int m0 = a.ncols - 1 - c0; // mirror of c0
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid)); // (as in k_cc)
+        tid &= NTH - 1;
+        int j, s;
+        rt_plain<N>(tid, j, s);
+        cx<T> v[8];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)x[2 * r], (T)x[2 * r + 1]};
+        if (c0 + cstep < cend) fetch(x, c0 + cstep, tid);
+        rt_first_zpad<T, N>(buf, v, j, s);
+        rt_middle<T, N, false>(buf, tw, tid);
+        rt_paired<N>(tid, j, s);
+        rt_last<T, N, false>(buf, tw, v, j, s);
+        cx<T> C[4], S[4];
+        rt_slots<T, N>(v, j, C, S);
+        __syncthreads();
+        // slot rows k and M + k of sequence s (row M of k = 0: the last cosine row)
+        {
+            cx<T> *p = buf + s * R::SP + j;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                rt_put(p + r * P, C[r]);
+                rt_put(p + M + r * P, S[r]);
+            }
+        }
+        __syncthreads();
+        if (WB && (a.Mo == 0 || bt > a.Mo)) {
+            const int64_t bb = a.Mo == 0 ? 0 : (int64_t)(bt - a.Mo - 1) * a.Bbs;
+            const int lane = tid & 63, wave = tid >> 6;
+            for (int c = wave; c < W; c += NTH / 64) {
+                const int col = src_col(c, c0, nA, nB);
+                if (col < 0) continue;
+                const int64_t cb = (int64_t)col * a.Bcs + bb;
+                const T *q = reinterpret_cast<const T *>(buf + (c >> 1) * R::SP + M + 1) + (c & 1);
+                for (int r = lane; r < M - 1; r += 64) {
+                    if (a.Bf32)
+                        static_cast<float *>(a.Bout)[cb + (int64_t)r * a.Brs] = (float)q[2 * r];
+                    else
+                        static_cast<T *>(a.Bout)[cb + (int64_t)r * a.Brs] = q[2 * r];
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) {
+            const int t = tid + i * NTH;
+            if (t < M) {
+                const bool two = t > 0; // row M + t is S_t (else C_M, see below)
+                const T *r1 = reinterpret_cast<const T *>(buf + t), *r2 = r1 + 2 * M;
+                auto at = [&](const T *r, int c) { return (double)r[(c >> 1) * 2 * R::SP + (c & 1)]; };
+                const double *Kr = a.K + (int64_t)kb * a.Ko;
+                const double *KA = Kr + t + (int64_t)c0 * a.Kd; // K at column c0 + jj
+                const double *KB = Kr + t + (int64_t)m0 * a.Kd; // K at column m0 - jj
+                double s10 = a10[i], s11 = a11[i], s20 = a20[i], s21 = a21[i];
+                auto col_pair = [&](int jj) {
+                    const double kA = KA[(int64_t)jj * a.Kd], kB = KB[-(int64_t)jj * a.Kd];
+                    const double ud = at(r1, jj), um = at(r1, Wh + jj);
+                    const double vd = two ? at(r2, jj) : 0.0, vm = two ? at(r2, Wh + jj) : 0.0;
+                    s10 = fma(kA, ud, s10);
+                    s10 = fma(kB, um, s10);
+                    s11 = fma(kB, ud, s11);
+                    s11 = fma(kA, um, s11);
+                    s20 = fma(kA, vd, s20);
+                    s20 = fma(kB, vm, s20);
+                    s21 = fma(kB, vd, s21);
+                    s21 = fma(kA, vm, s21);
+                };
+                if (nA == Wh) {
+#pragma unroll
+                    for (int jj = 0; jj < Wh; ++jj) col_pair(jj);
+                } else {
+                    for (int jj = 0; jj < nA; ++jj) col_pair(jj);
+                }
+                if (!two) {
+                    // C_M (no sine partner) with its own kernel spectrum
+                    const double *MA = Kr + M + (int64_t)c0 * a.Kd, *MB = Kr + M + (int64_t)m0 * a.Kd;
+                    for (int jj = 0; jj < nA; ++jj) {
+                        const double kA = MA[(int64_t)jj * a.Kd], kB = MB[-(int64_t)jj * a.Kd];
+                        const double vd = at(r2, jj), vm = at(r2, Wh + jj);
+                        s20 = fma(kA, vd, s20);
+                        s20 = fma(kB, vm, s20);
+                        s21 = fma(kB, vd, s21);
+                        s21 = fma(kA, vm, s21);
+                    }
+                }
+                a10[i] = s10;
+                a11[i] = s11;
+                a20[i] = s20;
+                a21[i] = s21;
+            }
+        }
+        __syncthreads();
+    }
+    // FP64 partials [face][chunk][batch][slot]: slot rows t and M + t
+    const int64_t o0 = ((int64_t)ch * a.nbatch + bt) * N, o1 = o0 + (int64_t)nchunk * a.nbatch * N;
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) {
+        const int t = threadIdx.x + i * NTH;
+        if (t < M) {
+            a.part[o0 + t] = a10[i];
+            a.part[o1 + t] = a11[i];
+            a.part[o0 + M + t] = a20[i];
+            a.part[o1 + M + t] = a21[i];
+        }
+    }
+}
+
+template <typename T, typename TI, bool WB, int N>
+static void launch_cc_rt(const CcArgs &a, int nchunk, hipStream_t st)
+{
+    const size_t lds = rt_lds<T, N>();
+    set_lds((const void *)&k_cc_rt<T, TI, N, WB>, lds);
+    hipLaunchKernelGGL((k_cc_rt<T, TI, N, WB>), dim3(nchunk * a.nbatch), dim3(RegTile<N>::NTH), lds, st, a, nchunk);
+}
+
+template <typename T, typename TI, int MAXE, bool WB, int KD, int RPT, int NTT = NT, int WHC = 0>
 static void launch_cc_k(const CcArgs &a, int nchunk, hipStream_t st)
 {
     const size_t lds = tile_lds<T>(a.fd.N, a.W);
-    set_lds((const void *)&k_cc<T, TI, MAXE, WB, KD, RPT, NTT, WHC, NC>, lds);
-    hipLaunchKernelGGL((k_cc<T, TI, MAXE, WB, KD, RPT, NTT, WHC, NC>), dim3(nchunk * a.nbatch), dim3(NTT), lds,
+    set_lds((const void *)&k_cc<T, TI, MAXE, WB, KD, RPT, NTT, WHC>, lds);
+    hipLaunchKernelGGL((k_cc<T, TI, MAXE, WB, KD, RPT, NTT, WHC>), dim3(nchunk * a.nbatch), dim3(NTT), lds,
                        st, a, nchunk);
 }
 
@@ -225,15 +380,6 @@ static bool prefetch_fits(const CcArgs &a)
 template <typename T, typename TI, int MAXE, bool WB>
 static void launch_cc_m(const CcArgs &a, int nchunk, hipStream_t st)
 {
-    if constexpr (MAXE == 8) {
-        // the default (length, width) pairs with compile-time Stockham stages
-        if (a.fd.N == 512 && prefetch_fits<4, 8>(a))
-            return launch_cc_k<T, TI, 8, WB, kPow2, 2, NT, 4, 512>(a, nchunk, st);
-        if (a.fd.N == 256 && prefetch_fits<8, 8>(a))
-            return launch_cc_k<T, TI, 8, WB, kPow2, 2, NT, 8, 256>(a, nchunk, st);
-        if (a.fd.N == 1024 && prefetch_fits<2, 8>(a))
-            return launch_cc_k<T, TI, 8, WB, kPow2, 4, NT, 2, 1024>(a, nchunk, st);
-    }
     auto go = [&](auto kd) {
         constexpr int KD = decltype(kd)::value;
         constexpr bool P2 = KD == kPow2;
@@ -262,16 +408,16 @@ template <typename T, typename TI, bool WB>
 hipError_t launch_cc_t(const CcArgs &a, int nchunk, hipStream_t st)
 {
     const int work = (a.W / 2) * a.fd.N;
+    if (a.nrows_in == a.fd.M - 1 &&
+        rt_length(a.fd.N, a.W, [&](auto n) { launch_cc_rt<T, TI, WB, decltype(n)::value>(a, nchunk, st); }))
+        return hipGetLastError();
     if (big_fft(a.fd.N)) {
         // one complex sequence (a column and its mirror) per tile; rows per thread = N / NTB <= 8
         if (a.W != 2 || a.fd.N > 8 * NTB) return hipErrorInvalidValue;
-        by_pow2(a.fd.N, [&](auto kd) {
-            constexpr int KD = decltype(kd)::value;
-            if (a.fd.N <= 4 * NTB)
-                launch_cc_k<T, TI, 4, WB, KD, 4, NTB>(a, nchunk, st);
-            else
-                launch_cc_k<T, TI, 8, WB, KD, 8, NTB>(a, nchunk, st);
-        });
+        if (a.fd.N <= 4 * NTB)
+            launch_cc_k<T, TI, 4, WB, kAnyLen, 4, NTB>(a, nchunk, st);
+        else
+            launch_cc_k<T, TI, 8, WB, kAnyLen, 8, NTB>(a, nchunk, st);
         return hipGetLastError();
     }
     if (work <= 8 * NT)

@@ -31,7 +31,7 @@
 namespace ips {
 
 template <typename T>
-struct cx {
+struct alignas(2 * sizeof(T)) cx {
     T x, y;
 };
 
@@ -591,129 +591,292 @@ __device__ __forceinline__ int toff(int r, int64_t rsd, int c, int64_t csd)
     return __mul24(r, (int)rsd) + __mul24(c, (int)csd);
 }
 
-// The compile-time transforms split for tiles that are read from or written
-// to global memory by the transform itself (default (N, pitch) pairs only,
-// where every stage holds one butterfly per thread):
-//   forward:  stage_ct_gin (first stage, inputs from global) + fft_ct_tail
-//   inverse:  fft_ct_head + stage_ct_gout (last stage, outputs to global)
-// The tile never holds the input rows or the output rows in LDS, which saves
-// one LDS write and one read of the tile, and a barrier, per transform.
+// Radix of the last stage of the compile-time transforms.
 template <int N>
 struct CtLast {
-    static constexpr int R = N == 256 ? 4 : N == 512 ? 8 : 2; // radix of the last stage
+    static constexpr int R = N == 256 || N == 2048 ? 4 : N == 512 || N == 4096 ? 8 : 2;
 };
 
-// Every stage after the first.
-template <typename T, int NT, int N, int RS, int LGS, bool INV>
-__device__ __forceinline__ void fft_ct_tail(T *buf, const cx<T> *tw, int tid)
+// ---------------------------------------------------------------------------
+// Register tiles: N = 256 .. 8192 (a power of two), 2048 / N sequences (one from
+// N = 2048 on), one radix-8 butterfly per thread in every stage.
+//
+// The tile is an array of complex elements, row-major, with one row of padding
+// after every eight: elements are aligned, so each is one 8- or 16-byte LDS
+// access, and the stride-8 row writes of the first stage, the block writes of the
+// later ones and the consecutive rows that every stage reads each fall on all banks
+// evenly (row pitch W + 1 took two accesses per element, with conflicts).
+//
+// The last stage of a transform leaves thread (j, s) with rows j + r N/8, r < 8,
+// of sequence s in registers, and the first stage of the next one starts from
+// the same rows. With j assigned to the threads in pairs (j, N/8 - j) of lanes that
+// mirror each other, row N - k of a row k lies in the mirror lane, so whatever
+// combines rows k and N - k (cosine and sine parts, the spectral combination)
+// works on registers with one cross-lane move per value instead of two or four
+// passes over the tile in LDS.
+// ---------------------------------------------------------------------------
+template <int N>
+struct RegTile {
+    static constexpr int NSEQ = N >= 2048 ? 1 : 2048 / N, W = 2 * NSEQ;
+    static constexpr int LGS = NSEQ == 8 ? 3 : NSEQ == 4 ? 2 : NSEQ == 2 ? 1 : 0;
+    static constexpr int P = N / 8;          // rows between the elements of a thread
+    static constexpr int NTH = P * NSEQ;     // threads of the block
+    static constexpr int ELEMS = (N + N / 8) * NSEQ; // LDS elements
+    static constexpr bool LTW = N <= 2048;   // twiddles in LDS (else the global table)
+    // lane ^ (2 NSEQ - 1): row_mirror, row_half_mirror, quad_perm [3,2,1,0], [1,0,3,2]
+    static constexpr int MIRROR = NSEQ == 8 ? 0x140 : NSEQ == 4 ? 0x141 : NSEQ == 2 ? 0x1B : 0xB1;
+    // a column's rows one after the other (sequence s at s * SP): 16 dwords off a
+    // multiple of the 64 banks per sequence in FP32
+    static constexpr int SP = N + 8;
+};
+
+// LDS bytes of a register tile and its twiddles.
+template <typename T, int N>
+constexpr size_t rt_lds()
 {
-    if constexpr (N == 256) {
-        stage_ct<T, 8, NT, N, 8, RS, LGS, INV>(buf, tw, tid);
-        stage_ct<T, 4, NT, N, 64, RS, LGS, INV>(buf, tw, tid);
-    } else if constexpr (N == 512) {
-        stage_ct<T, 8, NT, N, 8, RS, LGS, INV>(buf, tw, tid);
-        stage_ct<T, 8, NT, N, 64, RS, LGS, INV>(buf, tw, tid);
-    } else if constexpr (N == 1024) {
-        stage_ct<T, 8, NT, N, 8, RS, LGS, INV>(buf, tw, tid);
-        stage_ct<T, 8, NT, N, 64, RS, LGS, INV>(buf, tw, tid);
-        stage_ct<T, 2, NT, N, 512, RS, LGS, INV>(buf, tw, tid);
-    }
+    return ((RegTile<N>::LTW ? N : 0) + RegTile<N>::ELEMS) * sizeof(cx<T>);
 }
 
-// Every stage but the last.
-template <typename T, int NT, int N, int RS, int LGS, bool INV>
-__device__ __forceinline__ void fft_ct_head(T *buf, const cx<T> *tw, int tid)
+template <int N>
+__device__ __forceinline__ constexpr int rt_row(int row)
 {
-    stage_ct<T, 8, NT, N, 1, RS, LGS, INV>(buf, tw, tid);
-    stage_ct<T, 8, NT, N, 8, RS, LGS, INV>(buf, tw, tid);
-    if constexpr (N == 1024) stage_ct<T, 8, NT, N, 64, RS, LGS, INV>(buf, tw, tid);
+    return (row + (row >> 3)) * RegTile<N>::NSEQ;
 }
 
-// The inputs of the first forward stage (radix 8) of thread tid, for
-// zero-padded sequences read from global memory: v[2r] and v[2r+1] are
-// tile row t = j + r N/8 (r < 4) of sequence sq (j = tid >> LGS, sq = its low
-// bits), i.e. source row t - 1 of columns 2 sq and 2 sq + 1; row 0, rows past
-// nrows (nrows < N/2) and columns >= ncols are zero.  Element (r, c) is
-// src[r*rsd + c*csd].  A loop over tiles can hold v while it transforms the
-// previous tile.
-template <typename TI, int NT, int N, int LGS>
-__device__ __forceinline__ void fetch_gin(TI (&v)[8], const TI *src, int nrows, int ncols, int64_t rsd, int64_t csd,
-                                          int tid)
+template <typename T>
+__device__ __forceinline__ cx<T> rt_get(const cx<T> *p)
 {
-    constexpr int NR = N / 8, SMASK = (1 << LGS) - 1;
-    static_assert((NR << LGS) == NT, "one butterfly per thread");
-    const int sq = tid & SMASK, j = tid >> LGS, c = 2 * sq;
+    typedef T V __attribute__((ext_vector_type(2)));
+    const V v = *reinterpret_cast<const V *>(p);
+    return {v.x, v.y};
+}
+
+template <typename T>
+__device__ __forceinline__ void rt_put(cx<T> *p, cx<T> v)
+{
+    typedef T V __attribute__((ext_vector_type(2)));
+    *reinterpret_cast<V *>(p) = V{v.x, v.y};
+}
+
+// Thread -> (j, s), and the paired form.
+template <int N>
+__device__ __forceinline__ void rt_plain(int tid, int &j, int &s)
+{
+    j = tid >> RegTile<N>::LGS;
+    s = tid & (RegTile<N>::NSEQ - 1);
+}
+
+template <int N>
+__device__ __forceinline__ void rt_paired(int tid, int &j, int &s)
+{
+    using R = RegTile<N>;
+    const int u = tid >> R::LGS, m = u >> 1, odd = u & 1, l = tid & (R::NSEQ - 1);
+    j = odd ? (m ? R::P - m : R::P / 2) : m;
+    s = odd ? R::NSEQ - 1 - l : l;
+}
+
+template <int N>
+__device__ __forceinline__ float rt_mirror(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), RegTile<N>::MIRROR, 0xF, 0xF, true));
+}
+
+template <int N>
+__device__ __forceinline__ double rt_mirror(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), RegTile<N>::MIRROR, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), RegTile<N>::MIRROR, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Rows N - k of the rows k = j + r N/8, r < 4, of a paired thread, from the rows
+// a[0..7] of its own and its mirror thread (k = 0: itself).
+template <typename T, int N>
+__device__ __forceinline__ void rt_reflect(const cx<T> (&a)[8], int j, cx<T> (&b)[4])
+{
+    // (selects on values: a branch would make the compiler address the arrays)
+    const bool z = j == 0, h = j == RegTile<N>::P / 2;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int t = j + r * NR;
-        const bool ok = t >= 1 && t <= nrows;
-        const TI *p = src + toff(ok ? t - 1 : 0, rsd, c, csd);
-        v[2 * r] = ok && c < ncols ? p[0] : (TI)0;
-        v[2 * r + 1] = ok && c + 1 < ncols ? p[csd] : (TI)0;
+        const cx<T> t0 = a[(8 - r) & 7], t1 = a[7 - r];
+        const cx<T> m = {rt_mirror<N>(t1.x), rt_mirror<N>(t1.y)};
+        b[r].x = z ? t0.x : h ? t1.x : m.x;
+        b[r].y = z ? t0.y : h ? t1.y : m.y;
     }
 }
 
-// First forward stage (radix 8, upper half of the inputs zero) from the
-// registers fetch_gin filled; writes every row of the tile.  Ends with a
-// barrier.
-template <typename T, typename TI, int NT, int N, int RS, int LGS>
-__device__ __forceinline__ void stage_ct_rin(T *buf, const TI (&v)[8], int tid)
+// The inverse: rows j + r N/8, r = 4..7, of an odd sequence (row N - k the negative
+// of row k, rows 0 and N/2 zero) from its rows k = j + r N/8, r < 4, in a[0..3] of
+// the thread and its mirror.
+template <typename T, int N>
+__device__ __forceinline__ void rt_unfold_odd(cx<T> (&a)[8], int j)
 {
-    constexpr int SMASK = (1 << LGS) - 1;
-    const int sq = tid & SMASK, j = tid >> LGS;
-    cx<T> a[8];
+    const bool z = j == 0, h = j == RegTile<N>::P / 2;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[r] = cx<T>{(T)v[2 * r], (T)v[2 * r + 1]};
-    dft8_lower<T, false>(a);
+    for (int r = 0; r < 4; ++r) {
+        const cx<T> t1 = a[r];
+        const cx<T> m = {rt_mirror<N>(t1.x), rt_mirror<N>(t1.y)};
+        // row j + (7 - r) N/8; of j = 0: row (4 + (3 - r)) N/8, the mirror of row (r + 1) N/8
+        const cx<T> t8 = r < 3 ? a[r + 1] : cx<T>{(T)0, (T)0};
+        a[7 - r].x = -(z ? t8.x : h ? t1.x : m.x);
+        a[7 - r].y = -(z ? t8.y : h ? t1.y : m.y);
+    }
+}
+
+// First stage (radix 8): rows j + r N/8 in a, written to the tile.
+template <typename T, int N, bool INV>
+__device__ __forceinline__ void rt_first(cx<T> *buf, cx<T> (&a)[8], int j, int s)
+{
+    rt_pin(a);
+    dft_small<T, 8, INV>(a, nullptr, N);
+    cx<T> *p = buf + 9 * j * RegTile<N>::NSEQ + s;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) lds_cs(buf, RS, 8 * j + r, sq, a[r]);
+    for (int r = 0; r < 8; ++r) rt_put(p + r * RegTile<N>::NSEQ, a[r]);
     __syncthreads();
 }
 
-// The first forward stage straight from global memory (fetch_gin, then
-// stage_ct_rin).
-template <typename T, typename TI, int NT, int N, int RS, int LGS>
-__device__ __forceinline__ void stage_ct_gin(T *buf, const TI *src, int nrows, int ncols, int64_t rsd,
-                                             int64_t csd, int tid)
+// As rt_first for rows N/2.. that are zero (a[0..3] given).
+template <typename T, int N>
+__device__ __forceinline__ void rt_first_zpad(cx<T> *buf, cx<T> (&a)[8], int j, int s)
 {
-    TI v[8];
-    fetch_gin<TI, NT, N, LGS>(v, src, nrows, ncols, rsd, csd, tid);
-    stage_ct_rin<T, TI, NT, N, RS, LGS>(buf, v, tid);
+    dft8_lower<T, false>(a);
+    cx<T> *p = buf + 9 * j * RegTile<N>::NSEQ + s;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) rt_put(p + r * RegTile<N>::NSEQ, a[r]);
+    __syncthreads();
 }
 
-// Last stage (radix CtLast<N>::R) of the inverse transform, written straight
-// to global memory: only output rows t < N/2 are formed (the sine synthesis
-// of an odd-symmetric spectrum needs no more; the caller checks that the rows
-// it keeps lie below N/2), and rows t = row0..row0+nrows-1 of sequence sq go,
-// scaled, to row t - row0 of columns 2 sq and 2 sq + 1 of dst (columns >=
-// ncols are skipped).  Element (r, c) is dst[r*rsd + c*csd].
-template <typename T, typename TO, int NT, int N, int RS, int LGS>
-__device__ __forceinline__ void stage_ct_gout(const T *buf, const cx<T> *tw, TO *dst, int row0, int nrows,
-                                              int ncols, int64_t rsd, int64_t csd, T scale, int tid)
+template <typename T, int N>
+__device__ __forceinline__ void rt_rows(const cx<T> *buf, cx<T> (&a)[8], int j, int s)
 {
-    constexpr int R = CtLast<N>::R, NR = N / R, NBF = NR << LGS, SMASK = (1 << LGS) - 1;
-    static_assert(NBF % NT == 0, "whole butterflies per thread");
+    const cx<T> *p = buf + rt_row<N>(j) + s;
 #pragma unroll
-    for (int i = 0; i < NBF / NT; ++i) {
-        const int b = tid + i * NT;
-        const int sq = b & SMASK, j = b >> LGS, c = 2 * sq;
+    for (int r = 0; r < 8; ++r) a[r] = rt_get(p + r * rt_row<N>(RegTile<N>::P));
+}
+
+// One radix-8 stage in LDS after product NS of earlier radices.
+template <typename T, int N, int NS, bool INV>
+__device__ __forceinline__ void rt_stage(cx<T> *buf, const cx<T> *tw, int tid)
+{
+    int j, s;
+    rt_plain<N>(tid, j, s);
+    cx<T> a[8];
+    rt_rows<T, N>(buf, a, j, s);
+    const int jm = j & (NS - 1);
+    if (jm != 0) {
+        const int e = jm * (N / (NS * 8));
+#pragma unroll
+        for (int r = 1; r < 8; ++r) a[r] = cmul(a[r], twid<T, INV>(tw, e * r));
+    }
+    dft_small<T, 8, INV>(a, tw, N);
+    __syncthreads();
+    cx<T> *p = buf + rt_row<N>((j - jm) * 8 + jm) + s;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) rt_put(p + r * rt_row<N>(NS), a[r]);
+    __syncthreads();
+}
+
+// The stages between the first and the last.
+template <typename T, int N, bool INV>
+__device__ __forceinline__ void rt_middle(cx<T> *buf, const cx<T> *tw, int tid)
+{
+    rt_stage<T, N, 8, INV>(buf, tw, tid);
+    if constexpr (N >= 1024) rt_stage<T, N, 64, INV>(buf, tw, tid);
+    if constexpr (N >= 8192) rt_stage<T, N, 512, INV>(buf, tw, tid);
+}
+
+// Values as they come back from memory: keeps the compiler from contracting an
+// operation on them with the one that made them (so that results do not depend
+// on where a value is kept).
+template <typename T, int K>
+__device__ __forceinline__ void rt_pin(cx<T> (&a)[K])
+{
+#pragma unroll
+    for (int r = 0; r < K; ++r) asm volatile("" : "+v"(a[r].x), "+v"(a[r].y));
+}
+
+// The last stage (radix 4, 8 or 2 for N = 256, 512, 1024, and so on): rows j + r N/8 of the
+// result in a. No barrier.
+template <typename T, int N, bool INV>
+__device__ __forceinline__ void rt_last(const cx<T> *buf, const cx<T> *tw, cx<T> (&a)[8], int j, int s)
+{
+    constexpr int R = CtLast<N>::R, NB = 8 / R; // NB butterflies of radix R
+    rt_rows<T, N>(buf, a, j, s);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int e = j + i * RegTile<N>::P;
         cx<T> v[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = lds_c(buf, RS, j + r * NR, sq);
-        if (j != 0) {
+        for (int r = 0; r < R; ++r) v[r] = a[i + NB * r];
+        if (e != 0) {
 #pragma unroll
-            for (int r = 1; r < R; ++r) v[r] = cmul(v[r], twid<T, true>(tw, j * r));
+            for (int r = 1; r < R; ++r) v[r] = cmul(v[r], twid<T, INV>(tw, e * r));
         }
-        dft_small<T, R, true>(v, tw, N);
+        dft_small<T, R, INV>(v, tw, N);
 #pragma unroll
-        for (int r = 0; r < R / 2; ++r) {
-            const int t = j + r * NR - row0;
-            if (t >= 0 && t < nrows) {
-                TO *p = dst + toff(t, rsd, c, csd);
-                if (c < ncols) p[0] = (TO)(scale * v[r].x);
-                if (c + 1 < ncols) p[csd] = (TO)(scale * v[r].y);
-            }
+        for (int r = 0; r < R; ++r) a[i + NB * r] = v[r];
+    }
+    rt_pin(a);
+}
+
+// Cosine and sine parts of a zero-padded forward transform (rows a of a paired
+// thread): C and S of rows k = j + r N/8, r < 4, of both columns; S of k = 0 is
+// C_{N/2}, as in the slot layout.
+template <typename T, int N>
+__device__ __forceinline__ void rt_slots(const cx<T> (&a)[8], int j, cx<T> (&C)[4], cx<T> (&S)[4])
+{
+    cx<T> b[4];
+    rt_reflect<T, N>(a, j, b);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        C[r] = cx<T>{(T)0.5 * (a[r].x + b[r].x), (T)0.5 * (a[r].y + b[r].y)};
+        S[r] = cx<T>{(T)0.5 * (b[r].y - a[r].y), (T)0.5 * (a[r].x - b[r].x)};
+    }
+    S[0].x = j == 0 ? a[4].x : S[0].x;
+    S[0].y = j == 0 ? a[4].y : S[0].y;
+}
+
+// Two neighbouring elements as one access (element-aligned only, which global
+// memory instructions take).
+template <typename T>
+struct __attribute__((packed, aligned(sizeof(T)))) pair_t {
+    T a, b;
+};
+
+// Rows t = j + r N/8, r < 4, of columns 2s and 2s + 1 from global memory: source
+// row t - row0 (row0 = 1: row t = 0 is zero). Element (row, column) is
+// src[row*rsd + col], with col0, col1 the offsets of the two columns (negative:
+// zero). dir = 1 or -1: col1 = col0 + dir for every thread of the block, read
+// together (two single loads cost two passes over the same cache lines).
+template <typename TI, int N>
+__device__ __forceinline__ void rt_fetch(TI (&x)[8], const TI *src, int64_t rsd, int col0, int col1, int dir, int j,
+                                         int row0)
+{
+    const int step = __mul24(RegTile<N>::P, (int)rsd);
+    int o = __mul24(j - row0, (int)rsd);
+    const bool first = j >= row0;
+    if (dir != 0) {
+        const int c = min(col0, col1);
+        const bool rev = dir < 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool ok = r > 0 || first;
+            const pair_t<TI> v = *reinterpret_cast<const pair_t<TI> *>(src + (ok ? o : 0) + c);
+            x[2 * r] = ok ? (rev ? v.b : v.a) : (TI)0;
+            x[2 * r + 1] = ok ? (rev ? v.a : v.b) : (TI)0;
+            o += step;
         }
+        return;
+    }
+    const int c0 = max(col0, 0), c1 = max(col1, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const bool ok = r > 0 || first;
+        const int q = ok ? o : 0;
+        const TI v0 = src[q + c0], v1 = src[q + c1];
+        x[2 * r] = ok && col0 >= 0 ? v0 : (TI)0;
+        x[2 * r + 1] = ok && col1 >= 0 ? v1 : (TI)0;
+        o += step;
     }
 }
 

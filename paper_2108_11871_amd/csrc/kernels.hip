@@ -907,31 +907,120 @@ __device__ __forceinline__ void final_row(const FinalArgs &a, int i, int kB, dou
         for (int t = nt; t < 3; ++t) r[4 + par * 3 + t] = (TR)0;
 }
 
-template <typename T, int MAXE, int KD, int WC, int NTT, int NC>
+// Tile lb of the final pass -> (column block, batch entry), in the logical order:
+// groups of a.group neighbouring column blocks (together 256 bytes of every row),
+// then the batch, then the group index -- the blocks that share a line run side
+// by side on one XCD, and each XCD sweeps all batches over a narrow band of columns,
+// so the per-element shell data of that band stays in its L2.
+__device__ __forceinline__ void final_tile(const FinalArgs &a, int ncb, int lb, int &cb, int &bt)
+{
+    const int G = a.group;
+    const int full = ncb / G;
+    if (lb < G * full * a.nbatch) {
+        const int pr = lb / (G * a.nbatch), rem = lb % (G * a.nbatch);
+        bt = rem / G;
+        cb = G * pr + rem % G;
+    } else {
+        const int left = ncb - G * full; // the last, partial group
+        const int rem = lb - G * full * a.nbatch;
+        bt = rem / left;
+        cb = G * full + rem % left;
+    }
+}
+
+// Staged column j = k1 - 1 of the final pass at batch index kB = k2: 12 values
+// (layout below, in k_final).
+template <typename T>
+__device__ __forceinline__ void final_col(const FinalArgs &a, int j, int kB, T *r)
+{
+    const Geo &geo = a.geo;
+    const int d = geo.d, I1 = geo.M[1] - 1, I2 = d == 3 ? geo.M[2] - 1 : 1;
+    const int nt = a.order == 6 ? 3 : 1;
+    const double lamB = d == 3 ? a.tab[2].lam[kB - 1] : 0.0;
+    const double c2yz = d == 3 ? geo.c2[1][2] : 0.0;
+    const double c4yz = d == 3 ? geo.c4[1][2] : 0.0, c4zy = d == 3 ? geo.c4[2][1] : 0.0;
+    const double ly = a.tab[1].lam[j];
+    r[0] = (T)ly;
+    r[1] = (T)a.tab[1].q[j];
+    r[2] = (T)a.tab[1].s[j];
+    r[3] = (T)a.tab[1].s[I1 + j];
+    r[10] = (T)(ly + c2yz * ly * lamB);
+    r[11] = (T)(ly * lamB * (c4yz * ly + c4zy * lamB));
+    // family 0: other index (k1, k2) in 3D, (k1) in 2D
+    const int64_t ss0 = shell_size(geo, 0), o = d == 3 ? (int64_t)j * I2 + (kB - 1) : j;
+    for (int par = 0; par < 2; ++par)
+        for (int t = 0; t < nt; ++t) r[4 + par * 3 + t] = (T)a.sh.P[0][(par * 3 + t) * ss0 + o];
+}
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// One coefficient of the combination: row record r and column record q (layout in
+// k_final), kxodd / kyodd the parities of the wavenumbers, Pe the family-2 values of
+// the element (stride ss2), beta the raw sine coefficient of rho. The fused
+// operations are written out, so that every kernel rounds alike.
+template <typename T>
+struct FinalConst {
+    T c2xy, c4xy, c4yx, pref, lamB, s1B, s2B;
+    int64_t ss2;
+    bool six, d3;
+};
+
+template <typename T>
+__device__ __forceinline__ T final_value(const FinalConst<T> &f, const T *r, const T *q, bool kxodd, bool kyodd,
+                                         const T *Pe, T beta)
+{
+    const T *Pr = r + (kyodd ? 7 : 4), *Pc = q + (kxodd ? 7 : 4);
+    const T lxy = r[0] * q[0];
+    const T L = fma_t(f.c2xy, lxy, r[10] + q[10] + f.lamB);
+    T h = fma_t(q[2], Pr[0], r[2] * Pc[0]);
+    T dh = (T)0;
+    if (f.six) dh = fma_t(q[3], Pr[2], fma_t(q[2], Pr[1], fma_t(r[2], Pc[1], r[3] * Pc[2])));
+    if (f.d3) {
+        h = fma_t(f.s1B, Pe[0], h);
+        if (f.six) dh += fma_t(f.s1B, Pe[f.ss2], f.s2B * Pe[2 * f.ss2]);
+    }
+    const T iL = recip(L);
+    if (f.six) {
+        const T R = fma_t(lxy, fma_t(f.c4yx, q[0], f.c4xy * r[0]), r[11] + q[11]);
+        h = fma_t(h, fma_t(R, iL, (T)1), dh);
+    }
+    return f.pref * fma_t(h, iL, -(beta * recip(r[1] + q[1])));
+}
+
+template <typename T>
+__device__ __forceinline__ FinalConst<T> final_const(const FinalArgs &a, int kB)
+{
+    const Geo &g = a.geo;
+    FinalConst<T> f;
+    f.c2xy = (T)g.c2[0][1];
+    f.c4xy = (T)g.c4[0][1];
+    f.c4yx = (T)g.c4[1][0];
+    f.pref = (T)g.pref;
+    f.six = a.order == 6;
+    f.d3 = g.d == 3;
+    f.lamB = f.s1B = f.s2B = (T)0;
+    f.ss2 = 0;
+    if (f.d3) {
+        f.lamB = (T)a.tab[2].lam[kB - 1];
+        f.s1B = (T)a.tab[2].s[kB - 1];
+        f.s2B = (T)a.tab[2].s[g.M[2] - 1 + kB - 1];
+        f.ss2 = shell_size(g, 2);
+    }
+    return f;
+}
+
+template <typename T, int MAXE, int KD, int WC, int NTT>
 __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
 {
     constexpr bool BIG = NTT != NT;
-    // FP64 tiles of a compile-time width (short transforms) without
-    // compile-time stages: persistent blocks that fetch the next tile into
-    // registers while the current one is processed (for FP32 tiles, and for
-    // the compile-time stages with their direct global I/O, one tile per
-    // block measured faster)
-    constexpr bool PF = WC > 0 && !BIG && sizeof(T) == 8 && NC == 0;
-    // one-tile blocks with compile-time stages: direct global I/O in the
-    // first forward and the last inverse stage (LGSC: log2 of the sequences)
-    constexpr bool DIO = NC > 0 && !PF;
-    constexpr int LGSC = WC == 4 ? 1 : WC == 8 ? 2 : 3;
+    // FP64 tiles of a compile-time width (short transforms): persistent blocks
+    // that fetch the next tile into registers while the current one is processed
+    // (for FP32 tiles one tile per block measured faster)
+    constexpr bool PF = WC > 0 && !BIG && sizeof(T) == 8;
     extern __shared__ __align__(16) unsigned char smem[];
     // WC > 0: tile width known at compile time (row offsets become shifts)
-    // NC > 0: the transform length, known at compile time (only the
-    // compile-time Stockham stages of that length are built in)
-    static_assert(NC == 0 || (KD == kPow2 && MAXE == 8 && !BIG && NC * WC == 16 * NT), "no compile-time stages");
-    FftDesc fdc{};
-    if constexpr (NC > 0) {
-        fdc.N = NC;
-        fdc.M = NC / 2;
-    }
-    const FftDesc &fd = NC > 0 ? fdc : a.fd;
+    const FftDesc &fd = a.fd;
     const int N = fd.N, M = fd.M, W = WC > 0 ? WC : a.W, rs = BIG ? W : W + 1;
     const int lgW = WC > 0 ? __builtin_ctz(WC > 0 ? WC : 1) : 31 - __clz(W), lgs = lgW - 1;
     const cx<T> *tw = tw_table<T, BIG>(smem, a.tw, a.twf);
@@ -939,25 +1028,6 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     T *buf = reinterpret_cast<T *>(smem + twb);
     const int ncb = (a.ncols + W - 1) / W;
     const int grid = gridDim.x;
-    // logical order: groups of a.group neighbouring column blocks (together one
-    // 128-byte line of every row), then the batch, then the group index -- the
-    // blocks that share a line run side by side on one XCD, and each XCD sweeps
-    // all batches over a narrow band of columns, so the per-element shell data
-    // of that band stays in its L2
-    auto decode = [&](int lb, int &cb, int &bt) {
-        const int G = a.group;
-        const int full = ncb / G;
-        if (lb < G * full * a.nbatch) {
-            const int pr = lb / (G * a.nbatch), rem = lb % (G * a.nbatch);
-            bt = rem / G;
-            cb = G * pr + rem % G;
-        } else {
-            const int left = ncb - G * full; // the last, partial group
-            const int rem = lb - G * full * a.nbatch;
-            bt = rem / left;
-            cb = G * full + rem % left;
-        }
-    };
     const int lb0 = xcd_remap(blockIdx.x, grid);
     const bool rcont = a.irs == 1 && a.ics != 1;
     if (!BIG) load_twiddles<T, NTT>(reinterpret_cast<cx<T> *>(smem), a.tw, N);
@@ -965,7 +1035,7 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     if constexpr (PF) {
         if (lb0 < ntiles) {
             int cb, bt;
-            decode(lb0, cb, bt);
+            final_tile(a, ncb, lb0, cb, bt);
             const int c0 = cb * W;
             fetch_pair<T, NTT, (PF ? WC : 2), MAXE, false>(pf, static_cast<const T *>(a.buf) + bt * a.ibs + c0 * a.ics,
                                                           a.nrows_in, a.irs, a.ics, 0, min(W, a.ncols - c0), 0, 0,
@@ -979,30 +1049,24 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
         tid &= NTT - 1;
     }
     int cb, bt;
-    decode(it, cb, bt);
+    final_tile(a, ncb, it, cb, bt);
     const int c0 = cb * W;
     const int nc = min(W, a.ncols - c0);
     T *g = static_cast<T *>(a.buf) + bt * a.ibs + c0 * a.ics;
-    // Compile-time transforms of one-tile blocks read their input rows in the
-    // first stage of the forward transform and write their output rows in the
-    // last stage of the inverse, straight from and to B (no tile load or store).
-    const bool direct = DIO && !a.pre && a.nrows_in <= M - 1;
-    if (!direct) {
-        zero_rows<T, NTT>(buf, rs, lgW, 0, 1, tid);
-        zero_rows<T, NTT>(buf, rs, lgW, 1 + a.nrows_in, N, tid);
-    }
+    zero_rows<T, NTT>(buf, rs, lgW, 0, 1, tid);
+    zero_rows<T, NTT>(buf, rs, lgW, 1 + a.nrows_in, N, tid);
     if constexpr (PF) {
         put_pair<T, T, NTT, (PF ? WC : 2), MAXE>(buf, rs, 1, pf, a.nrows_in, rcont, tid);
         const int nx = it + grid;
         if (nx < ntiles) {
             int cb1, bt1;
-            decode(nx, cb1, bt1);
+            final_tile(a, ncb, nx, cb1, bt1);
             const int c1 = cb1 * W;
             fetch_pair<T, NTT, (PF ? WC : 2), MAXE, false>(pf, static_cast<const T *>(a.buf) + bt1 * a.ibs + c1 * a.ics,
                                                           a.nrows_in, a.irs, a.ics, 0, min(W, a.ncols - c1), 0, 0,
                                                           tid);
         }
-    } else if (!direct) {
+    } else {
         tile_load<T, T, NTT>(buf, rs, 1, g, a.nrows_in, nc, a.irs, a.ics, lgW, tid);
     }
     const Geo &geo = a.geo;
@@ -1027,45 +1091,12 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     const size_t soff = (twb + (size_t)N * rs * sizeof(T) + 15) & ~(size_t)15;
     const T *__restrict__ rv = static_cast<const T *>(a.rowtab) + (int64_t)bt * (M - 1) * SV;
     T *cv = reinterpret_cast<T *>(smem + soff);
-    const int I0 = geo.M[0] - 1, I1 = geo.M[1] - 1, I2 = d == 3 ? geo.M[2] - 1 : 1;
+    const int I0 = geo.M[0] - 1;
     const int kB = bt + 1;
-    const int64_t ss0 = shell_size(geo, 0), ss1 = shell_size(geo, 1);
-    // batch (axis 2) constants and the per-element family 2
-    double lamB = 0.0, qB = 0.0, s1B = 0.0, s2B = 0.0;
-    int64_t ss2 = 0;
-    if (d == 3) {
-        lamB = a.tab[2].lam[kB - 1];
-        qB = a.tab[2].q[kB - 1];
-        s1B = a.tab[2].s[kB - 1];
-        s2B = a.tab[2].s[I2 + kB - 1];
-        ss2 = shell_size(geo, 2);
-    }
-    const double c2xz = d == 3 ? geo.c2[0][2] : 0.0, c2yz = d == 3 ? geo.c2[1][2] : 0.0;
-    const double c4xz = d == 3 ? geo.c4[0][2] : 0.0, c4zx = d == 3 ? geo.c4[2][0] : 0.0;
-    const double c4yz = d == 3 ? geo.c4[1][2] : 0.0, c4zy = d == 3 ? geo.c4[2][1] : 0.0;
-    for (int i = tid; i < nc; i += NTT) {
-        T *r = cv + i * SV;
-        const int j = c0 + i; // k1 - 1
-        const double ly = a.tab[1].lam[j];
-        r[0] = (T)ly;
-        r[1] = (T)a.tab[1].q[j];
-        r[2] = (T)a.tab[1].s[j];
-        r[3] = (T)a.tab[1].s[I1 + j];
-        r[10] = (T)(ly + c2yz * ly * lamB);
-        r[11] = (T)(ly * lamB * (c4yz * ly + c4zy * lamB));
-        // family 0: other index (k1, k2) in 3D, (k1) in 2D
-        const int64_t o = d == 3 ? (int64_t)j * I2 + (kB - 1) : j;
-        for (int par = 0; par < 2; ++par)
-            for (int t = 0; t < nt; ++t) r[4 + par * 3 + t] = (T)a.sh.P[0][(par * 3 + t) * ss0 + o];
-    }
+    for (int i = tid; i < nc; i += NTT) final_col(a, c0 + i, kB, cv + i * SV);
     __syncthreads();
     // forward transform of the zero-padded rows 1..M0-1 (unless B already holds the spectrum)
-    if (direct) {
-        if constexpr (DIO) {
-            stage_ct_gin<T, T, NTT, NC, WC + 1, LGSC>(buf, g, a.nrows_in, nc, a.irs, a.ics, tid);
-            fft_ct_tail<T, NTT, NC, WC + 1, LGSC, false>(buf, tw, tid);
-        }
-    } else if (!a.pre) {
+    if (!a.pre) {
         if (a.nrows_in <= M - 1)
             fft_tile_zpad<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, tid);
         else
@@ -1080,13 +1111,12 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     //   z(k) = (c_b, -c_a), z(N-k) = (-c_b, c_a), rows 0 and M zero.
     // Each thread owns both rows of its pair, so no barrier is needed between
     // the reads and the writes.
-    const T c2xy = (T)geo.c2[0][1], c4xy = (T)geo.c4[0][1], c4yx = (T)geo.c4[1][0];
-    const T lamBt = (T)lamB, s1Bt = (T)s1B, s2Bt = (T)s2B, preft = (T)geo.pref;
+    const FinalConst<T> f = final_const<T>(a, kB);
     const int nseq = 1 << lgs;
     // Row k per thread (consecutive k across the lanes): the row invariants
     // are read once and serve every column of the tile; the family-2 values
     // come from the transposed copy [par][t][k1][k0], contiguous in k0 = kx.
-    const T *Pt = d == 3 ? static_cast<const T *>(a.sh.P2T) + ((kB & 1) ? 3 * ss2 : 0) : nullptr;
+    const T *Pt = f.d3 ? static_cast<const T *>(a.sh.P2T) + ((kB & 1) ? 3 * f.ss2 : 0) : nullptr;
     // Fewer than NTT / 2 rows would leave threads over: 2^lgG groups of M - 1
     // threads then share the sequences of a row (33^3 FP64 solve 226 -> 209 us,
     // 65^3 261 -> 250 us: this loop is a chain of FP64 operations per column).
@@ -1098,9 +1128,6 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     for (int k = 1 + tid - grp * kstep; k < M && grp < (1 << lgG); k += kstep) {
         T r[SV];
         load12(rv + (k - 1) * SV, r);
-        const T lx = r[0], rq = r[1], rs1 = r[2], rs2 = r[3], r10 = r[10], r11 = r[11];
-        // family 1 at (kx, kz) for even / odd ky
-        const T Pe0 = r[4], Pe1 = r[5], Pe2 = r[6], Po0 = r[7], Po1 = r[8], Po2 = r[9];
         const int kx = k;
         const bool kodd = (kx & 1) != 0; // family 0 at (ky, kz): parity of kx
         for (int sq = sq0; sq < sq1; ++sq) {
@@ -1116,27 +1143,8 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
                     const int ky = 1 + c0 + c; // c0 is even: ky is odd for h2 = 0
                     T q1[SV];
                     load12(cv + c * SV, q1);
-                    const T P0 = h2 ? Pe0 : Po0, P1v = h2 ? Pe1 : Po1, P2v = h2 ? Pe2 : Po2;
-                    const T Pc[3] = {kodd ? q1[7] : q1[4], kodd ? q1[8] : q1[5], kodd ? q1[9] : q1[6]};
-                    const T ly = q1[0], lxy = lx * ly;
-                    const T Lm = r10 + q1[10] + lamBt + c2xy * lxy;
-                    T gt = rs1 * Pc[0] + q1[2] * P0;
-                    T dh = (T)0;
-                    if (six) dh = rs1 * Pc[1] + rs2 * Pc[2] + q1[2] * P1v + q1[3] * P2v;
-                    if (d == 3) {
-                        const T *Pe = Pt + (int64_t)(ky - 1) * I0 + (kx - 1);
-                        gt += s1Bt * Pe[0];
-                        if (six) dh += s1Bt * Pe[ss2] + s2Bt * Pe[2 * ss2];
-                    }
-                    const T iL = recip(Lm);
-                    T harm;
-                    if (six) {
-                        const T Rm = r11 + q1[11] + lxy * (c4xy * lx + c4yx * ly);
-                        harm = (gt * ((T)1 + Rm * iL) + dh) * iL;
-                    } else {
-                        harm = gt * iL;
-                    }
-                    cval = preft * (harm - beta2[h2] * recip(rq + q1[1]));
+                    const T *Pe = f.d3 ? Pt + (int64_t)(ky - 1) * I0 + (kx - 1) : nullptr;
+                    cval = final_value(f, r, q1, kodd, h2 == 0, Pe, beta2[h2]);
                 }
                 cab[h2] = cval;
             }
@@ -1145,42 +1153,172 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
         }
     }
     __syncthreads();
-    if (direct) {
-        if constexpr (DIO) {
-            fft_ct_head<T, NTT, NC, WC + 1, LGSC, true>(buf, tw, tid);
-            stage_ct_gout<T, T, NTT, NC, WC + 1, LGSC>(buf, tw, g, 1, a.nrows_in, nc, a.irs, a.ics, (T)0.5, tid);
-        }
-    } else {
-        fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, true, tid);
-        tile_store<T, T, NTT>(buf, rs, 1, g, a.nrows_in, nc, a.irs, a.ics, (T)0.5, lgW, tid);
-    }
+    fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, true, tid);
+    tile_store<T, T, NTT>(buf, rs, 1, g, a.nrows_in, nc, a.irs, a.ics, (T)0.5, lgW, tid);
     if constexpr (!PF) break; // one tile per block: no loop for the compiler to hoist out of
     __syncthreads();          // the next tile reuses the LDS
     }
 }
 
-template <typename T, int MAXE, int KD, int WC, int NTT = NT, int NC = 0>
-static void launch_final_n(const FinalArgs &a, int nblk, size_t lds, hipStream_t st)
+// The value of lane i of the NL lanes (1, 2 or 4) a lane belongs to.
+template <int NL, int I>
+__device__ __forceinline__ float quad_get(float v)
 {
-    const void *fn = (const void *)&k_final<T, MAXE, KD, WC, NTT, NC>;
-    set_lds(fn, lds);
-    int grid = nblk;
-    if (WC > 0 && NTT == NT && sizeof(T) == 8 && NC == 0) { // persistent blocks (PF in k_final)
-        const int r = resident_blocks(fn, NTT, lds);
-        if (r > 0 && r < nblk) grid = r;
-    }
-    hipLaunchKernelGGL((k_final<T, MAXE, KD, WC, NTT, NC>), dim3(grid), dim3(NTT), lds, st, a, nblk);
+    constexpr int ctrl = NL == 4 ? I * 0x55 : I ? 0xF5 : 0xA0;
+    if constexpr (NL == 1) return v;
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xF, 0xF, true));
 }
 
-// Compile-time widths 4, 8, 16 of the default tile budget (N WC / 2 = 8 NT):
-// the transform length at compile time too when it is the plan's.
+template <int NL, int I>
+__device__ __forceinline__ double quad_get(double v)
+{
+    constexpr int ctrl = NL == 4 ? I * 0x55 : I ? 0xF5 : 0xA0;
+    if constexpr (NL == 1) return v;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// The final pass in register tiles (full tiles of the power-of-two lengths): 8
+// instead of 12 passes over the tile in LDS, six barriers less. Its row records are
+// read a part per lane (whole records per lane: 117 us) and its columns in pairs.
+// Now bound by VALU issue and the latency of B and the shell spectra. 257^3: FP32
+// 102 us as before, FP64 191 -> 182 us; 513^3 FP32 1243 -> 854 us.
+// the first forward and the last inverse stage read and write B directly, and
+// the spectral combination works on the registers between the last forward and
+// the first inverse stage (see RegTile): thread (j, s) combines rows k = j + r N/8,
+// r < 4, of its two columns; its inverse inputs are these and its mirror's.
+template <typename T, int N>
+__global__ __launch_bounds__(RegTile<N>::NTH) void k_final_rt(FinalArgs a, int ntiles)
+{
+    using R = RegTile<N>;
+    constexpr int M = N / 2, W = R::W, SV = 12, P = R::P, NL = R::NSEQ < 4 ? R::NSEQ : 4;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const cx<T> *tw = tw_table<T, !R::LTW>(smem, a.tw, a.twf);
+    cx<T> *buf = reinterpret_cast<cx<T> *>(smem) + (R::LTW ? N : 0);
+    T *cv = reinterpret_cast<T *>(buf + R::ELEMS);
+    const int tid = threadIdx.x;
+    const int ncb = (a.ncols + W - 1) / W;
+    int cb, bt;
+    final_tile(a, ncb, xcd_remap(blockIdx.x, ntiles), cb, bt);
+    const int c0 = cb * W, nc = min(W, a.ncols - c0);
+    T *g = static_cast<T *>(a.buf) + bt * a.ibs + c0 * a.ics;
+    if constexpr (R::LTW) load_twiddles<T, R::NTH>(reinterpret_cast<cx<T> *>(smem), a.tw, N);
+    const int kB = bt + 1;
+    for (int i = tid; i < nc; i += R::NTH) final_col(a, c0 + i, kB, cv + i * SV);
+    __syncthreads();
+    cx<T> v[8];
+    int j, s;
+    const int c = 2 * (tid & (R::NSEQ - 1));
+    T x[8];
+    auto load = [&]() {
+        const int cc = 2 * s;
+        rt_fetch<T, N>(x, g, a.irs, cc < nc ? cc * (int)a.ics : -1, cc + 1 < nc ? (cc + 1) * (int)a.ics : -1,
+                       nc == W && a.ics == 1, j, 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = cx<T>{x[2 * r], x[2 * r + 1]};
+    };
+    if (!a.pre) {
+        rt_plain<N>(tid, j, s);
+        load();
+        rt_first_zpad<T, N>(buf, v, j, s);
+        rt_middle<T, N, false>(buf, tw, tid);
+        rt_paired<N>(tid, j, s);
+        rt_last<T, N, false>(buf, tw, v, j, s);
+    } else {
+        // B holds the spectrum
+        rt_paired<N>(tid, j, s);
+        load();
+    }
+    {
+        cx<T> z2[4];
+        if (!a.pre) {
+            rt_reflect<T, N>(v, j, z2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)0.5 * (z2[r].y - v[r].y), (T)0.5 * (v[r].x - z2[r].x)};
+        }
+    }
+    // v[r]: the raw sine coefficients of columns 2s and 2s + 1 at kx = k
+    const FinalConst<T> f = final_const<T>(a, kB);
+    const int I0 = M - 1;
+    const T *Pt = f.d3 ? static_cast<const T *>(a.sh.P2T) + ((kB & 1) ? 3 * f.ss2 : 0) : nullptr;
+    const T *__restrict__ rv = static_cast<const T *>(a.rowtab) + (int64_t)bt * (M - 1) * SV;
+    const bool kodd = (j & 1) != 0; // parity of every k of the thread
+    auto combine = [&](int k, cx<T> beta) -> cx<T> {
+        if (k == 0) return cx<T>{(T)0, (T)0};
+        // the NL neighbouring lanes that hold this row read a part of its record
+        // each and pass it on (whole records per lane: NL times the L1 traffic)
+        T rr[SV], part[SV / NL];
+#pragma unroll
+        for (int i = 0; i < SV / NL; ++i) part[i] = rv[(k - 1) * SV + (tid & (NL - 1)) * (SV / NL) + i];
+#pragma unroll
+        for (int i = 0; i < SV / NL; ++i) {
+            rr[i] = quad_get<NL, 0>(part[i]);
+            if constexpr (NL >= 2) rr[SV / NL + i] = quad_get<NL, 1>(part[i]);
+            if constexpr (NL == 4) {
+                rr[2 * (SV / NL) + i] = quad_get<NL, 2>(part[i]);
+                rr[3 * (SV / NL) + i] = quad_get<NL, 3>(part[i]);
+            }
+        }
+        T out[2];
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+            const int c = 2 * s + h2; // ky = 1 + c0 + c; c0 is even: odd for h2 = 0
+            out[h2] = (T)0;
+            if (c < nc) {
+                T q1[SV];
+                load12(cv + c * SV, q1);
+                const T *Pe = f.d3 ? Pt + (int64_t)(c0 + c) * I0 + (k - 1) : nullptr;
+                out[h2] = final_value(f, rr, q1, kodd, h2 == 0, Pe, h2 ? beta.y : beta.x);
+            }
+        }
+        return cx<T>{out[0], out[1]};
+    };
+    const cx<T> cab[4] = {combine(j, v[0]), combine(j + P, v[1]), combine(j + 2 * P, v[2]), combine(j + 3 * P, v[3])};
+    // hermitian input: z(k) = (c_b, -c_a), z(N - k) = (-c_b, c_a), rows 0 and M zero
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = cx<T>{cab[r].y, -cab[r].x};
+    rt_unfold_odd<T, N>(v, j);
+    __syncthreads(); // every wave has read the forward transform
+    rt_first<T, N, true>(buf, v, j, s);
+    rt_middle<T, N, true>(buf, tw, tid);
+    rt_plain<N>(tid, j, s);
+    rt_last<T, N, true>(buf, tw, v, j, s);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int t = j + r * P;
+        if (t < 1 || t > a.nrows_in) continue;
+        T *p = g + toff(t - 1, a.irs, c, a.ics);
+        const T y0 = (T)0.5 * v[r].x, y1 = (T)0.5 * v[r].y;
+        if (nc == W && a.ics == 1) {
+            *reinterpret_cast<pair_t<T> *>(p) = pair_t<T>{y0, y1};
+        } else {
+            if (c < nc) p[0] = y0;
+            if (c + 1 < nc) p[a.ics] = y1;
+        }
+    }
+}
+
 template <typename T, int MAXE, int KD, int WC, int NTT = NT>
 static void launch_final_w(const FinalArgs &a, int nblk, size_t lds, hipStream_t st)
 {
-    constexpr int NCT = (MAXE == 8 && KD == kPow2 && NTT == NT && (WC == 4 || WC == 8 || WC == 16)) ? 16 * NT / WC : 0;
-    if constexpr (NCT > 0)
-        if (a.fd.N == NCT) return launch_final_n<T, MAXE, KD, WC, NTT, NCT>(a, nblk, lds, st);
-    launch_final_n<T, MAXE, KD, WC, NTT>(a, nblk, lds, st);
+    const void *fn = (const void *)&k_final<T, MAXE, KD, WC, NTT>;
+    set_lds(fn, lds);
+    int grid = nblk;
+    if (WC > 0 && NTT == NT && sizeof(T) == 8) { // persistent blocks (PF in k_final)
+        const int r = resident_blocks(fn, NTT, lds);
+        if (r > 0 && r < nblk) grid = r;
+    }
+    hipLaunchKernelGGL((k_final<T, MAXE, KD, WC, NTT>), dim3(grid), dim3(NTT), lds, st, a, nblk);
+}
+
+template <typename T, int N>
+static void launch_final_rt(const FinalArgs &a, int nblk, hipStream_t st)
+{
+    using R = RegTile<N>;
+    const size_t lds = rt_lds<T, N>() + (size_t)R::W * 12 * sizeof(T);
+    set_lds((const void *)&k_final_rt<T, N>, lds);
+    hipLaunchKernelGGL((k_final_rt<T, N>), dim3(nblk), dim3(R::NTH), lds, st, a, nblk);
 }
 
 template <typename T, int MAXE, int KD>
@@ -1205,16 +1343,16 @@ static void launch_final_k(const FinalArgs &a, int nblk, hipStream_t st)
 template <typename T>
 static void launch_final_t(const FinalArgs &a, int nblk, int work, hipStream_t st)
 {
+    // full tiles of the power-of-two lengths (narrowed tiles of small grids keep the
+    // generic stages)
+    if (rt_length(a.fd.N, a.W, [&](auto n) { launch_final_rt<T, decltype(n)::value>(a, nblk, st); })) return;
     if (big_fft(a.fd.N)) {
         // tile + staged columns only (the rows come from the global table)
         const size_t lds = tile_lds<T>(a.fd.N, a.W) + 16 + (size_t)a.W * 12 * sizeof(T);
-        by_pow2(a.fd.N, [&](auto kd) {
-            constexpr int KD = decltype(kd)::value;
-            if (work <= 4 * NTB)
-                launch_final_w<T, 4, KD, 2, NTB>(a, nblk, lds, st);
-            else
-                launch_final_w<T, 8, KD, 2, NTB>(a, nblk, lds, st);
-        });
+        if (work <= 4 * NTB)
+            launch_final_w<T, 4, kAnyLen, 2, NTB>(a, nblk, lds, st);
+        else
+            launch_final_w<T, 8, kAnyLen, 2, NTB>(a, nblk, lds, st);
         return;
     }
     by_kind(a.fd.N, [&](auto kd) {

@@ -32,23 +32,14 @@ __device__ __forceinline__ void tile_of(const PassArgs &a, int ncb, int lb, int 
 
 // One tile of a pass: tile lb (column block lb % ncb of batch entry lb / ncb),
 // loaded into LDS (rows placed as the input mode needs), transformed along its
-// rows and stored.  WT > 0: the tile width, known at compile time (equal to
-// a.W, which the launcher checks); NC > 0 likewise the transform length (only
-// the compile-time Stockham stages of that length are built in).
-template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT, int WT = 0, int NC = 0>
+// rows and stored.
+template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT>
 __device__ __forceinline__ void pass_tile(const PassArgs &a, int lb)
 {
     constexpr bool BIG = NTT != NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    // (only the pairs that have compile-time stages: fdc carries no stage list)
-    static_assert(NC == 0 || (KD == kPow2 && MAXE == 8 && !BIG && NC * WT == 16 * NT), "no compile-time stages");
-    FftDesc fdc{};
-    if constexpr (NC > 0) {
-        fdc.N = NC;
-        fdc.M = NC / 2;
-    }
-    const FftDesc &fd = NC > 0 ? fdc : a.fd;
-    const int N = fd.N, M = fd.M, W = WT > 0 ? WT : a.W, rs = BIG ? W : W + 1;
+    const FftDesc &fd = a.fd;
+    const int N = fd.N, M = fd.M, W = a.W, rs = BIG ? W : W + 1;
     const int lgW = 31 - __clz(W), lgs = lgW - 1;
     const cx<T> *tw = tw_table<T, BIG>(smem, a.tw, a.twf);
     T *buf = reinterpret_cast<T *>(smem + (BIG ? 0 : (size_t)N * sizeof(cx<T>)));
@@ -111,24 +102,18 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int lb)
 // registers while the current one is transformed.  The thread index is made
 // opaque inside that loop so that the compiler recomputes per-thread index
 // values instead of holding them in registers for the whole loop.
-template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT, int WC, int EPT, int NC>
+template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT, int WC, int EPT>
 __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
 {
     constexpr bool PF = WC > 0;
     if constexpr (!PF) {
-        // one tile per block (WC < 0: of the compile-time width -WC)
-        pass_tile<T, TI, TO, MAXE, KD, NTT, (WC < 0 ? -WC : 0), NC>(a, xcd_remap(blockIdx.x, ntiles));
+        // one tile per block
+        pass_tile<T, TI, TO, MAXE, KD, NTT>(a, xcd_remap(blockIdx.x, ntiles));
         return;
     }
     constexpr bool BIG = NTT != NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    static_assert(!PF || NC == 0 || (KD == kPow2 && MAXE == 8 && !BIG && NC * WC == 16 * NT), "no compile-time stages");
-    FftDesc fdc{};
-    if constexpr (NC > 0) {
-        fdc.N = NC;
-        fdc.M = NC / 2;
-    }
-    const FftDesc &fd = NC > 0 ? fdc : a.fd;
+    const FftDesc &fd = a.fd;
     const int N = fd.N, M = fd.M, W = PF ? WC : a.W, rs = BIG ? W : W + 1;
     const int lgW = 31 - __clz(W), lgs = lgW - 1;
     const cx<T> *tw = tw_table<T, BIG>(smem, a.tw, a.twf);
@@ -215,39 +200,177 @@ __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
     }
 }
 
-template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT = NT, int WC = 0, int EPT = 0, int NC = 0>
+// A pass in register tiles (see RegTile): inputs straight from global memory into
+// the first stage, results straight from the last one. MODE: IN_ZPAD (forward
+// cosine/sine, or the sine rows alone), IN_SPECS (sine synthesis: the first stage's
+// upper rows are the mirror lane's, negated) or IN_HERM. One tile per block: resident
+// blocks that walk the tiles and fetch the next one's inputs ahead measured slower
+// (257^3 FP64 1392 -> 1443 us), the blocks of a CU overlap by themselves. Bound by
+// the latency and the partial cache lines of its strided rows: 257^3 rho_y FP64
+// 123 -> 93 us, inv_y 97 -> 66 us, inv_z 98 -> 60 us (4.4 TB/s), FP32 rho_z 103 ->
+// 102, rho_y 94 -> 83, inv_y 50 -> 35, inv_z 53 -> 46 us.
+template <typename T, typename TI, typename TO, int N, int MODE>
+__global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int ntiles)
+{
+    using R = RegTile<N>;
+    constexpr int M = N / 2, W = R::W, P = R::P, NV = MODE == IN_HERM ? 16 : 8;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const cx<T> *tw = tw_table<T, !R::LTW>(smem, a.tw, a.twf);
+    cx<T> *buf = reinterpret_cast<cx<T> *>(smem) + (R::LTW ? N : 0);
+    const int ncb = (a.ncols + W - 1) / W;
+    const int tid = threadIdx.x;
+    int cb, bt, j, s;
+    tile_of(a, ncb, xcd_remap(blockIdx.x, ntiles), cb, bt);
+    const int c0 = cb * W, nc = min(W, a.ncols - c0);
+    const TI *in = static_cast<const TI *>(a.in) + bt * a.ibs + c0 * a.ics;
+    TO *out = static_cast<TO *>(a.out) + bt * a.obs + c0 * a.ocs;
+    if constexpr (MODE == IN_ZPAD)
+        rt_plain<N>(tid, j, s);
+    else
+        rt_paired<N>(tid, j, s);
+    TI x[NV];
+    {
+        const int c = 2 * s, ics = (int)a.ics;
+        const int o0 = c < nc ? c * ics : -1, o1 = c + 1 < nc ? (c + 1) * ics : -1, dir = nc == W && ics == 1;
+        if constexpr (MODE == IN_HERM) {
+            // cosine rows k and sine rows M + k (row M of k = 0: the last cosine row)
+            TI y[8], z[8];
+            rt_fetch<TI, N>(y, in, a.irs, o0, o1, dir, j, 0);
+            rt_fetch<TI, N>(z, in + M * a.irs, a.irs, o0, o1, dir, j, 0);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                x[r] = y[r];
+                x[8 + r] = z[r];
+            }
+        } else {
+            rt_fetch<TI, N>(x, in, a.irs, o0, o1, dir, j, 1);
+        }
+    }
+    if constexpr (R::LTW) load_twiddles<T, R::NTH>(reinterpret_cast<cx<T> *>(smem), a.tw, N);
+    cx<T> v[8];
+    if constexpr (MODE == IN_ZPAD) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)x[2 * r], (T)x[2 * r + 1]};
+    } else if constexpr (MODE == IN_SPECS) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)x[2 * r + 1], -(T)x[2 * r]};
+        rt_unfold_odd<T, N>(v, j);
+    } else {
+        const bool z0 = j == 0, h = j == P / 2;
+        cx<T> up[4], cm;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const T ca = (T)x[2 * r], cb2 = (T)x[2 * r + 1];
+            T sa = (T)x[8 + 2 * r], sb = (T)x[9 + 2 * r];
+            if (r == 0) {
+                cm = cx<T>{sa, sb};
+                sa = z0 ? (T)0 : sa;
+                sb = z0 ? (T)0 : sb;
+            }
+            v[r] = cx<T>{ca + sb, cb2 - sa};
+            up[r] = cx<T>{ca - sb, cb2 + sa}; // row N - k
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            // rows j + (7 - r) N/8: the mirror's N - k; of j = 0 the thread's own
+            const cx<T> own = r < 3 ? up[r + 1] : cm;
+            const cx<T> m = {rt_mirror<N>(up[r].x), rt_mirror<N>(up[r].y)};
+            v[7 - r].x = z0 ? own.x : h ? up[r].x : m.x;
+            v[7 - r].y = z0 ? own.y : h ? up[r].y : m.y;
+        }
+    }
+    if constexpr (MODE == IN_ZPAD)
+        rt_first_zpad<T, N>(buf, v, j, s);
+    else
+        rt_first<T, N, true>(buf, v, j, s);
+    rt_middle<T, N, MODE != IN_ZPAD>(buf, tw, tid);
+    if constexpr (MODE == IN_ZPAD)
+        rt_paired<N>(tid, j, s);
+    else
+        rt_plain<N>(tid, j, s);
+    rt_last<T, N, MODE != IN_ZPAD>(buf, tw, v, j, s);
+    const T scale = (T)a.scale;
+    const int c = 2 * s, ocs = (int)a.ocs, ors = (int)a.ors;
+    auto put = [&](int row, cx<T> w) {
+        const int t = row - a.out_r0;
+        if (t < 0 || t >= a.out_nrows) return;
+        TO *p = out + toff(t, ors, c, ocs);
+        if (nc == W && ocs == 1 && !a.accum) {
+            *reinterpret_cast<pair_t<TO> *>(p) = pair_t<TO>{(TO)(scale * w.x), (TO)(scale * w.y)};
+        } else if (a.accum) {
+            if (c < nc) p[0] += (TO)(scale * w.x);
+            if (c + 1 < nc) p[ocs] += (TO)(scale * w.y);
+        } else {
+            if (c < nc) p[0] = (TO)(scale * w.x);
+            if (c + 1 < nc) p[ocs] = (TO)(scale * w.y);
+        }
+    };
+    if constexpr (MODE == IN_ZPAD) {
+        cx<T> C[4], S[4];
+        rt_slots<T, N>(v, j, C, S);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            put(j + r * P, C[r]);
+            put(M + j + r * P, S[r]);
+        }
+    } else {
+        // rows beyond M are not kept (row M itself: j = 0 of r = 4)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) put(j + r * P, v[r]);
+        if (j == 0) put(M, v[4]);
+    }
+}
+
+template <typename T, typename TI, typename TO, int N, int MODE>
+static void launch_pass_rt_m(const PassArgs &a, int ntiles, hipStream_t st)
+{
+    using R = RegTile<N>;
+    const void *fn = (const void *)&k_pass_rt<T, TI, TO, N, MODE>;
+    const size_t lds = rt_lds<T, N>();
+    set_lds(fn, lds);
+    hipLaunchKernelGGL((k_pass_rt<T, TI, TO, N, MODE>), dim3((unsigned)ntiles), dim3(R::NTH), lds, st, a, ntiles);
+}
+
+// Full register tiles of the modes k_pass_rt takes; whether the pass is one.
+template <typename T, typename TI, typename TO>
+static bool launch_pass_rt(const PassArgs &a, int ntiles, hipStream_t st)
+{
+    const int M = a.fd.M;
+    const int mode = a.in_mode;
+    if (mode == IN_HERM ? a.nsum > 1 || a.nrows_in != 2 * M : mode == IN_ZPAD || mode == IN_SPECS ? a.nrows_in != M - 1 : true)
+        return false;
+    // synthesis keeps rows 0..M
+    if (mode != IN_ZPAD && a.out_r0 + a.out_nrows > M + 1) return false;
+    return rt_length(a.fd.N, a.W, [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        if (mode == IN_ZPAD)
+            launch_pass_rt_m<T, TI, TO, N, IN_ZPAD>(a, ntiles, st);
+        else if (mode == IN_SPECS)
+            launch_pass_rt_m<T, TI, TO, N, IN_SPECS>(a, ntiles, st);
+        else
+            launch_pass_rt_m<T, TI, TO, N, IN_HERM>(a, ntiles, st);
+    });
+}
+
+template <typename T, typename TI, typename TO, int MAXE, int KD, int NTT = NT, int WC = 0, int EPT = 0>
 static void launch_pass_k(const PassArgs &a, int ntiles, size_t lds, hipStream_t st)
 {
-    const void *fn = (const void *)&k_pass<T, TI, TO, MAXE, KD, NTT, WC, EPT, NC>;
+    const void *fn = (const void *)&k_pass<T, TI, TO, MAXE, KD, NTT, WC, EPT>;
     set_lds(fn, lds);
     int grid = ntiles;
     if (WC > 0) {
         const int r = resident_blocks(fn, NTT, lds);
         if (r > 0 && r < ntiles) grid = r;
     }
-    hipLaunchKernelGGL((k_pass<T, TI, TO, MAXE, KD, NTT, WC, EPT, NC>), dim3((unsigned)grid), dim3(NTT), lds, st,
+    hipLaunchKernelGGL((k_pass<T, TI, TO, MAXE, KD, NTT, WC, EPT>), dim3((unsigned)grid), dim3(NTT), lds, st,
                        a, ntiles);
 }
 
-// A compile-time width |WC|: the transform length of the default tile budget
-// (N |WC| / 2 = 8 NT, lengths 256, 512, 1024) also at compile time when it is
-// the plan's.
-template <typename T, typename TI, typename TO, int MAXE, int KD, int WC, int EPT>
-static void launch_pass_w(const PassArgs &a, int ntiles, size_t lds, hipStream_t st)
-{
-    constexpr int AW = WC < 0 ? -WC : WC;
-    constexpr int NCT = (MAXE == 8 && KD == kPow2 && (AW == 4 || AW == 8 || AW == 16)) ? 16 * NT / AW : 0;
-    if constexpr (NCT > 0)
-        if (a.fd.N == NCT) return launch_pass_k<T, TI, TO, MAXE, KD, NT, WC, EPT, NCT>(a, ntiles, lds, st);
-    launch_pass_k<T, TI, TO, MAXE, KD, NT, WC, EPT>(a, ntiles, lds, st);
-}
-
-// Compile-time tile widths W = 4, 8, 16 (the default widths of 2M = 1024,
-// 512, 256 and of the lengths near them) with plain loads get the register
-// prefetch when EPT
-// registers per thread cover the loaded rows.  FP32 tiles: only the forward
-// zero-padded transforms (EPT = MAXE); for the inverse passes the
-// prefetching loop measured slower than one tile per block.
+// Compile-time tile widths W = 4, 8, 16 (lengths near 2M = 1024, 512, 256) with
+// plain loads get the register prefetch when EPT registers per thread cover the
+// loaded rows. FP32 tiles: only the forward zero-padded transforms (EPT = MAXE);
+// for the inverse passes the prefetching loop measured slower than one tile per
+// block.
 template <int WC, int EPT>
 static bool pass_fits(const PassArgs &a)
 {
@@ -260,21 +383,19 @@ static void launch_pass_m(const PassArgs &a, int ntiles, size_t lds, hipStream_t
     // other lengths from 2M = 512 up (the small uneven boxes of a batch measured
     // faster with one tile per block)
     if constexpr (MAXE == 8) {
-        if (!(a.in_mode == IN_HERM && a.nsum > 1) && (KD == kPow2 || a.fd.N >= 512)) {
-            constexpr bool wide = sizeof(T) == 8; // FP64 tiles: every mode, EPT up to 2 MAXE
-            if (!wide && a.in_mode != IN_ZPAD && a.in_mode != IN_ZPAD0) {
-                // one tile per block, the default widths at compile time
-                if (KD == kPow2 && a.W == 8) return launch_pass_w<T, TI, TO, MAXE, KD, -8, 0>(a, ntiles, lds, st);
-                if (KD == kPow2 && a.W == 16) return launch_pass_w<T, TI, TO, MAXE, KD, -16, 0>(a, ntiles, lds, st);
-                return launch_pass_k<T, TI, TO, MAXE, KD>(a, ntiles, lds, st);
-            }
-            if (pass_fits<8, 8>(a)) return launch_pass_w<T, TI, TO, 8, KD, 8, 8>(a, ntiles, lds, st);
-            if (pass_fits<16, 8>(a)) return launch_pass_w<T, TI, TO, 8, KD, 16, 8>(a, ntiles, lds, st);
-            if (pass_fits<4, 8>(a)) return launch_pass_w<T, TI, TO, 8, KD, 4, 8>(a, ntiles, lds, st);
-            if constexpr (wide) {
-                if (pass_fits<8, 16>(a)) return launch_pass_w<T, TI, TO, 8, KD, 8, 16>(a, ntiles, lds, st);
-                if (pass_fits<16, 16>(a)) return launch_pass_w<T, TI, TO, 8, KD, 16, 16>(a, ntiles, lds, st);
-                if (pass_fits<4, 16>(a)) return launch_pass_w<T, TI, TO, 8, KD, 4, 16>(a, ntiles, lds, st);
+        constexpr bool wide = sizeof(T) == 8; // FP64 tiles: every mode, EPT up to 2 MAXE
+        // (FP32 passes of the powers of two are register tiles or narrow)
+        if constexpr (wide || KD != kPow2) {
+            if (!(a.in_mode == IN_HERM && a.nsum > 1) && (KD == kPow2 || a.fd.N >= 512) &&
+                (wide || a.in_mode == IN_ZPAD || a.in_mode == IN_ZPAD0)) {
+                if (pass_fits<8, 8>(a)) return launch_pass_k<T, TI, TO, 8, KD, NT, 8, 8>(a, ntiles, lds, st);
+                if (pass_fits<16, 8>(a)) return launch_pass_k<T, TI, TO, 8, KD, NT, 16, 8>(a, ntiles, lds, st);
+                if (pass_fits<4, 8>(a)) return launch_pass_k<T, TI, TO, 8, KD, NT, 4, 8>(a, ntiles, lds, st);
+                if constexpr (wide) {
+                    if (pass_fits<8, 16>(a)) return launch_pass_k<T, TI, TO, 8, KD, NT, 8, 16>(a, ntiles, lds, st);
+                    if (pass_fits<16, 16>(a)) return launch_pass_k<T, TI, TO, 8, KD, NT, 16, 16>(a, ntiles, lds, st);
+                    if (pass_fits<4, 16>(a)) return launch_pass_k<T, TI, TO, 8, KD, NT, 4, 16>(a, ntiles, lds, st);
+                }
             }
         }
     }
@@ -291,6 +412,7 @@ hipError_t launch_pass_t(const PassArgs &a, hipStream_t st)
     if (ntl <= 0) return hipSuccess;
     if (ntl > INT32_MAX) return hipErrorInvalidValue;
     const int ntiles = (int)ntl;
+    if (launch_pass_rt<T, TI, TO>(a, ntiles, st)) return hipGetLastError();
     if (big_fft(a.fd.N)) {
         if (a.W != 2 || work > 8 * NTB) return hipErrorInvalidValue;
         by_pow2(a.fd.N, [&](auto kd) {

@@ -1,6 +1,6 @@
 """Small and uneven grids at the edges of the launch-shape rules (tile widths
-narrowed to fill the GPU, the row groups of the final pass) and of the prime
-radices, against the FP64 oracle (1e-12 in FP64 and 1e-6 in the mixed modes,
+narrowed to fill the GPU, the row groups of the final pass), of the prime radices
+and of the register tiles, against the FP64 oracle (1e-12 in FP64 and 1e-6 in the mixed modes,
 the bars of every parity test)."""
 import pytest
 
@@ -46,6 +46,23 @@ def test_prime_radices(panels, mode, tol):
     shape = tuple(m + 1 for m in panels)
     banner("shape=%s %s" % (shape, mode))
     rho, h, _ = I.workload_bumps(shape, seed=34, scale=[1.0, 1.2, 0.9][:len(shape)])
+    phi = api.Plan(shape, h, order=6, precision=mode)(to_dev(rho))
+    torch.cuda.synchronize()
+    assert rel_err(phi.cpu().numpy(), P.solve(rho, h, 6, boundary="fft")) < tol
+
+
+# register tiles: every length 2M = 256 .. 4096 (8192: test_gpu_long.py), the columns
+# one ragged tile, one more than whole tiles, and many
+@pytest.mark.parametrize("mode,tol", [("fp64", TOL), ("mixed_fp32", 1e-6), ("mixed_fp32_slices", 1e-6)])
+@pytest.mark.parametrize("shape", [(129, 257), (257, 19), (513, 129), (1025, 257), (2049, 12), (130, 2049),
+                                   (129, 9, 257), (257, 129, 20)])
+def test_register_tiles(shape, mode, tol):
+    import torch
+    from paper_2108_11871_amd import api
+    from gpu_util import banner, rel_err, to_dev
+
+    banner("shape=%s %s" % (shape, mode))
+    rho, h, _ = I.workload_bumps(shape, seed=35, scale=[1.0, 1.2, 0.9][:len(shape)])
     phi = api.Plan(shape, h, order=6, precision=mode)(to_dev(rho))
     torch.cuda.synchronize()
     assert rel_err(phi.cpu().numpy(), P.solve(rho, h, 6, boundary="fft")) < tol
