@@ -106,7 +106,8 @@ struct PackArgs {
     double *P1T; // 3D only
     void *P2T;   // 3D only: FP32 if p2t_f32, else FP64
     int p2t_f32;
-    int withD;   // also pack the deferred-correction layers
+    int withD;   // pack the deferred-correction layers (else the g~ layers)
+    int nblk[3]; // filled by the launcher
 };
 
 struct FinalArgs {
@@ -206,6 +207,15 @@ struct R6Args {
 // splits * 10 * (sum of the shell sizes) doubles
 int r6t_splits(const Geo &g);
 
+// Face values after the inverse transforms: node (side f, in-face indices j_lo,
+// j_hi of the lower and the higher other axis) of family a holds
+// g / scale[a] at F[a][f*fs[a][0] + j_lo*fs[a][1] + j_hi*fs[a][2]].
+struct FaceVals {
+    const double *F[3]; // F[0] == nullptr: no face arrays, boundary values in phi only
+    int64_t fs[3][3];
+    double scale[3];
+};
+
 struct DcorrArgs {
     Geo geo;
     int64_t n[3];
@@ -220,15 +230,15 @@ struct GtArgs {
     Geo geo;
     int64_t n[3];
     const double *phi;
+    FaceVals face;
+    double wf[3], we[3][3]; // weights of face and edge neighbours, filled by the launcher
     double *G[3]; // [2][..][..]
 };
 
 struct BwriteArgs {
     Geo geo;
     int64_t n[3];
-    const double *F[3];   // face values after the inverse transforms
-    int64_t fs[3][3];     // strides (face, row, col) of F[a]
-    double scale[3];
+    FaceVals face;
     double *phi;
 };
 
@@ -290,8 +300,8 @@ hipError_t launch_cc(const CcArgs &a, int nchunk, bool f32, bool in_f32, hipStre
 // out[s][i] = sum over the chunks c of part[s][c][i]  (nset sets of nchunk rows of len)
 hipError_t launch_reduce(const double *part, double *out, int64_t len, int nchunk, int nset, hipStream_t st);
 hipError_t launch_bwrite(const BwriteArgs &a, hipStream_t st);
-hipError_t launch_gtilde(const GtArgs &a, hipStream_t st);
-hipError_t launch_pack(const PackArgs &a, hipStream_t st);
+hipError_t launch_gtilde(GtArgs a, hipStream_t st);
+hipError_t launch_pack(PackArgs a, hipStream_t st);
 hipError_t launch_r6t(R6Args a, hipStream_t st);
 hipError_t launch_dcorr(const DcorrArgs &a, hipStream_t st);
 // Caller's block n at offset off inside the extended grid ne: embed (extract =

@@ -197,6 +197,15 @@ __device__ __forceinline__ bool on_boundary(const Geo &g, const int *i)
     return false;
 }
 
+// Boundary value at a face node, rounded as it is stored in phi (never the product
+// of a fused multiply-add).
+__device__ __forceinline__ double face_val(const FaceVals &v, int fam, int f, int jlo, int jhi)
+{
+    double g = v.scale[fam] * v.F[fam][f * v.fs[fam][0] + jlo * v.fs[fam][1] + jhi * v.fs[fam][2]];
+    asm volatile("" : "+v"(g));
+    return g;
+}
+
 // ---------------------------------------------------------------------------
 // Boundary values -> phi (faces, then edges and corners by lowest axis)
 // ---------------------------------------------------------------------------
@@ -225,9 +234,7 @@ __global__ void k_bwrite(BwriteArgs a)
             int idx[3];
             idx[fam] = f ? g.M[fam] : 0;
             for (int q = 0; q < na; ++q) idx[ax[q]] = j[q];
-            const double v =
-                a.F[fam][f * a.fs[fam][0] + j[0] * a.fs[fam][1] + (na == 2 ? j[1] * a.fs[fam][2] : 0)];
-            a.phi[node_off(a.n, d, idx)] = a.scale[fam] * v;
+            a.phi[node_off(a.n, d, idx)] = face_val(a.face, fam, f, j[0], na == 2 ? j[1] : 0);
             return;
         }
         e -= cnt;
@@ -262,60 +269,80 @@ __host__ __device__ __forceinline__ int64_t shell_size(const Geo &g, int a)
 // ---------------------------------------------------------------------------
 // Parity packing of the shell spectra (see ShellSpec::P)
 // ---------------------------------------------------------------------------
-__global__ void k_pack(PackArgs a)
+// A block takes one 16 x 16 tile of a family's (k_lo, k_hi) plane, an element per
+// thread; the transposed copies go through LDS, so that every write is a run of 16.
+// The g~ part (t = 0) is packed by the call without D layers, the D parts by the
+// one with them. 257^3: 8 + 13 -> 6 + 7 us, 513^3 13 + 41 -> 11 + 18 us (one element
+// per thread with strided copies before); bound by launch latency below.
+constexpr int kPackTile = 16;
+
+__global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
 {
+    __shared__ double tile[4][kPackTile][kPackTile + 1];
     const Geo &g = a.geo;
-    int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    for (int fam = 0; fam < g.d; ++fam) {
-        const int64_t ss = shell_size(g, fam);
-        if (e < ss) {
-            const double *G = a.G[fam];
-            double *P = a.P[fam];
-            const double g0 = G[e], g1 = G[ss + e];
-            double v[6];
-            v[0] = g0 - g1; // par 0 (even k), t 0
-            v[3] = g0 + g1; // par 1 (odd k), t 0
-            if (a.withD) {
-                const double *D = a.D[fam];
-                const double d1 = D[e], d2 = D[ss + e], d3 = D[2 * ss + e], d4 = D[3 * ss + e];
-                v[1] = d1 - d4;
-                v[2] = d2 - d3;
-                v[4] = d1 + d4;
-                v[5] = d2 + d3;
-            }
-            const int nt = a.withD ? 6 : 1;
-            for (int t = 0; t < 6; ++t)
-                if (t % 3 < nt) P[t * ss + e] = v[t];
-            if (fam == 2 && g.d == 3 && a.P2T) {
-                // e = (k0-1) * I1 + (k1-1)  ->  (k1-1) * I0 + (k0-1)
-                const int I0 = g.M[0] - 1, I1 = g.M[1] - 1;
-                const int64_t et = (e % I1) * I0 + e / I1;
-                for (int t = 0; t < 6; ++t)
-                    if (t % 3 < nt) {
-                        if (a.p2t_f32)
-                            static_cast<float *>(a.P2T)[t * ss + et] = (float)v[t];
-                        else
-                            static_cast<double *>(a.P2T)[t * ss + et] = v[t];
-                    }
-            }
-            if (fam == 1 && g.d == 3 && a.P1T) {
-                // e = (k0-1) * I2 + (k2-1)  ->  (k2-1) * I0 + (k0-1)
-                const int I0 = g.M[0] - 1, I2 = g.M[2] - 1;
-                const int64_t et = (e % I2) * I0 + e / I2;
-                for (int t = 0; t < 6; ++t)
-                    if (t % 3 < nt) a.P1T[t * ss + et] = v[t];
-            }
-            return;
+    int fam = 0, blk = blockIdx.x;
+    while (fam < g.d - 1 && blk >= a.nblk[fam]) blk -= a.nblk[fam++];
+    const int lo = fam == 0 ? 1 : 0, hi = fam == 2 ? 1 : 2;
+    const int Il = g.d == 3 ? g.M[lo] - 1 : 1, Ih = (g.d == 3 ? g.M[hi] : g.M[1 - fam]) - 1;
+    const int nbh = (Ih + kPackTile - 1) / kPackTile;
+    const int r0 = blk / nbh * kPackTile, c0 = blk % nbh * kPackTile;
+    const int64_t ss = (int64_t)Il * Ih;
+    const int tx = threadIdx.x & (kPackTile - 1), ty = threadIdx.x / kPackTile;
+    const bool tr = g.d == 3 && fam > 0;
+    const int nk = a.withD ? 4 : 2; // values per element, of kind (parity, t)
+    auto kind = [&](int q) { return a.withD ? (q >> 1) * 3 + 1 + (q & 1) : 3 * q; };
+    if (r0 + ty < Il && c0 + tx < Ih) {
+        const int64_t e = (int64_t)(r0 + ty) * Ih + c0 + tx;
+        double v[4];
+        if (a.withD) {
+            const double *D = a.D[fam];
+            const double d1 = D[e], d2 = D[ss + e], d3 = D[2 * ss + e], d4 = D[3 * ss + e];
+            v[0] = d1 - d4; // even k, t = 1
+            v[1] = d2 - d3; // even k, t = 2
+            v[2] = d1 + d4; // odd k, t = 1
+            v[3] = d2 + d3; // odd k, t = 2
+        } else {
+            const double g0 = a.G[fam][e], g1 = a.G[fam][ss + e];
+            v[0] = g0 - g1; // even k, t = 0
+            v[1] = g0 + g1; // odd k, t = 0
+            v[2] = v[3] = 0.0;
         }
-        e -= ss;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q >= nk) break;
+            a.P[fam][kind(q) * ss + e] = v[q];
+            if (tr) tile[q][ty][tx] = v[q];
+        }
+    }
+    if (!tr) return;
+    __syncthreads();
+    // (k_lo, k_hi) -> [k_hi][k_lo]: lo is axis 0 of families 1 and 2
+    if (c0 + ty >= Ih || r0 + tx >= Il) return;
+    const int64_t et = (int64_t)(c0 + ty) * Il + r0 + tx;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (q >= nk) break;
+        const double v = tile[q][tx][ty];
+        if (fam == 1)
+            a.P1T[kind(q) * ss + et] = v;
+        else if (a.p2t_f32)
+            static_cast<float *>(a.P2T)[kind(q) * ss + et] = (float)v;
+        else
+            static_cast<double *>(a.P2T)[kind(q) * ss + et] = v;
     }
 }
 
-hipError_t launch_pack(const PackArgs &a, hipStream_t st)
+hipError_t launch_pack(PackArgs a, hipStream_t st)
 {
-    int64_t tot = 0;
-    for (int fam = 0; fam < a.geo.d; ++fam) tot += shell_size(a.geo, fam);
-    hipLaunchKernelGGL(k_pack, dim3((unsigned)((tot + NT - 1) / NT)), dim3(NT), 0, st, a);
+    const Geo &g = a.geo;
+    int tot = 0;
+    for (int fam = 0; fam < g.d; ++fam) {
+        const int lo = fam == 0 ? 1 : 0, hi = fam == 2 ? 1 : 2;
+        const int Il = g.d == 3 ? g.M[lo] - 1 : 1, Ih = (g.d == 3 ? g.M[hi] : g.M[1 - fam]) - 1;
+        a.nblk[fam] = (Il + kPackTile - 1) / kPackTile * ((Ih + kPackTile - 1) / kPackTile);
+        tot += a.nblk[fam];
+    }
+    hipLaunchKernelGGL(k_pack, dim3((unsigned)tot), dim3(kPackTile * kPackTile), 0, st, a);
     return hipGetLastError();
 }
 
@@ -769,9 +796,10 @@ hipError_t launch_dcorr(const DcorrArgs &a, hipStream_t st)
 // ---------------------------------------------------------------------------
 // g~ = -(L_h B) on the interior nodes next to the boundary, split into one
 // layer pair per axis (a node belongs to the lowest axis whose index is 1 or
-// M-1 there; other layers hold 0 at that node).  Every neighbour of such a
-// node is a grid node, so all are loaded at once and those off the boundary
-// are dropped.
+// M-1 there; other layers hold 0 at that node). Nodes away from the edges read their
+// five neighbours from the face array; the others all 18 at once (bound by the latency
+// of these loads: one after the other 12 us on the smallest grid; 513^3 113 -> 41 us,
+// whose z faces are a row apart per node in phi).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(NT) void k_gtilde(GtArgs a)
@@ -797,45 +825,110 @@ __global__ __launch_bounds__(NT) void k_gtilde(GtArgs a)
     for (int b = 0; b < fam; ++b)
         if (i[b] == 1 || i[b] == g.M[b] - 1) owned = false;
     double s = 0.0;
-    if (owned) {
+    bool bulk = a.face.F[0] != nullptr && g.M[fam] > 2;
+#pragma unroll
+    for (int q = 0; q < D - 1; ++q) bulk = bulk && i[ob[q]] >= 2 && i[ob[q]] <= g.M[ob[q]] - 2;
+    auto add = [&](double w, double v) { // (no fused multiply-add)
+        double t = w * v;
+        asm volatile("" : "+v"(t));
+        s += t;
+    };
+    if (bulk) {
+        // only the node's own face is near: its neighbours there, from the face array
+        // (contiguous across the lanes), in the order of the general sum below
+        const int jl = i[ob[0]], jh = D == 3 ? i[ob[1]] : 0;
+        double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        const double *F = a.face.F[fam] + f * a.face.fs[fam][0] + jl * a.face.fs[fam][1] + jh * a.face.fs[fam][2];
+        v[0] = F[0];
+#pragma unroll
+        for (int q = 0; q < D - 1; ++q) {
+            v[1 + 2 * q] = F[-a.face.fs[fam][1 + q]];
+            v[2 + 2 * q] = F[a.face.fs[fam][1 + q]];
+        }
+        asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]));
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            v[q] = a.face.scale[fam] * v[q];
+            asm volatile("" : "+v"(v[q])); // as stored in phi
+        }
+        add(a.wf[fam], v[0]);
+#pragma unroll
+        for (int q = 0; q < D - 1; ++q) {
+            add(a.we[fam][ob[q]], v[1 + 2 * q]);
+            add(a.we[fam][ob[q]], v[2 + 2 * q]);
+        }
+        s = -s;
+    } else if (owned) {
+        // every neighbour is a grid node: all are loaded at once, those off the
+        // boundary dropped
+        double v[2 * D + 2 * D * (D - 1)];
+        bool on[2 * D + 2 * D * (D - 1)];
+        int m = 0;
+        auto get = [&](int p, int sp, int q, int sq) {
+            int j[3] = {i[0], i[1], i[2]};
+            j[p] += sp;
+            j[q] += sq;
+            v[m] = a.phi[node_off(a.n, D, j)];
+            on[m++] = on_boundary(g, j);
+        };
 #pragma unroll
         for (int p = 0; p < D; ++p) {
-            double w = 1.0 / (g.h[p] * g.h[p]);
-#pragma unroll
-            for (int q = 0; q < D; ++q)
-                if (q != p) w -= 2.0 * g.c2[p][q] / (g.h[p] * g.h[p] * g.h[q] * g.h[q]);
-#pragma unroll
-            for (int sg = -1; sg <= 1; sg += 2) {
-                int j[3] = {i[0], i[1], i[2]};
-                j[p] += sg;
-                const double v = a.phi[node_off(a.n, D, j)];
-                s += on_boundary(g, j) ? w * v : 0.0;
-            }
+            get(p, -1, p, 0);
+            get(p, 1, p, 0);
         }
 #pragma unroll
         for (int p = 0; p < D; ++p)
 #pragma unroll
             for (int q = p + 1; q < D; ++q) {
-                const double w = g.c2[p][q] / (g.h[p] * g.h[p] * g.h[q] * g.h[q]);
-#pragma unroll
-                for (int sp = -1; sp <= 1; sp += 2)
-#pragma unroll
-                    for (int sq = -1; sq <= 1; sq += 2) {
-                        int j[3] = {i[0], i[1], i[2]};
-                        j[p] += sp;
-                        j[q] += sq;
-                        const double v = a.phi[node_off(a.n, D, j)];
-                        s += on_boundary(g, j) ? w * v : 0.0;
-                    }
+                get(p, -1, q, -1);
+                get(p, -1, q, 1);
+                get(p, 1, q, -1);
+                get(p, 1, q, 1);
             }
+        // (one use of all of them: the loads are in flight together)
+        if constexpr (D == 3) {
+            asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+                         "+v"(v[7]), "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]),
+                         "+v"(v[14]), "+v"(v[15]), "+v"(v[16]), "+v"(v[17]));
+        } else {
+            asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+                         "+v"(v[7]));
+        }
+        m = 0;
+        auto use = [&](double w) {
+            add(w, on[m] ? v[m] : 0.0);
+            ++m;
+        };
+#pragma unroll
+        for (int p = 0; p < D; ++p) {
+            use(a.wf[p]);
+            use(a.wf[p]);
+        }
+#pragma unroll
+        for (int p = 0; p < D; ++p)
+#pragma unroll
+            for (int q = p + 1; q < D; ++q)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) use(a.we[p][q]);
         s = -s;
     }
     a.G[fam][(int64_t)f * ss + e] = s;
 }
 
-hipError_t launch_gtilde(const GtArgs &a, hipStream_t st)
+hipError_t launch_gtilde(GtArgs a, hipStream_t st)
 {
     const int d = a.geo.d;
+    const Geo &g = a.geo;
+    // weights of L_h's face and edge neighbours
+    for (int p = 0; p < d; ++p) {
+        a.wf[p] = 1.0 / (g.h[p] * g.h[p]);
+        for (int q = 0; q < d; ++q) {
+            if (q == p) continue;
+            a.wf[p] -= 2.0 * g.c2[p][q] / (g.h[p] * g.h[p] * g.h[q] * g.h[q]);
+            const int lo = std::min(p, q), hi = std::max(p, q);
+            a.we[p][q] = g.c2[lo][hi] / (g.h[lo] * g.h[lo] * g.h[hi] * g.h[hi]);
+        }
+    }
     int64_t mx = 1;
     for (int fam = 0; fam < d; ++fam) mx = std::max(mx, shell_size(a.geo, fam));
     const unsigned nb = (unsigned)((mx + NT - 1) / NT);

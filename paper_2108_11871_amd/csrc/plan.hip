@@ -1307,6 +1307,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         IPS_HIP(launch_1d(rho, phi, M[0], p->h[0], p->fd[0], p->tw[0], p->tab[0], p->screen ? 1 : 0, st));
         return IPS_OK;
     }
+    FaceVals face{}; // stays empty for screening plans (boundary values in phi only)
     if (p->screen) {
         if ((rc = screen_boundary(p, rho, phi, st))) return rc;
     } else if (d == 3) {
@@ -1493,16 +1494,17 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         a.geo = p->geo;
         for (int q = 0; q < 3; ++q) a.n[q] = n[q];
         for (int fam = 0; fam < 3; ++fam) {
-            a.F[fam] = p->F[fam];
-            a.scale[fam] = p->h[0] * p->h[1] * p->h[2];
+            a.face.F[fam] = p->F[fam];
+            a.face.scale[fam] = p->h[0] * p->h[1] * p->h[2];
             const int r = fr[fam], c = fc[fam];
-            a.fs[fam][0] = (int64_t)N[r] * N[c];
+            a.face.fs[fam][0] = (int64_t)N[r] * N[c];
             // lower in-face axis first
             const int lo = std::min(r, c);
-            a.fs[fam][1] = lo == c ? 1 : N[c];
-            a.fs[fam][2] = lo == c ? N[c] : 1;
+            a.face.fs[fam][1] = lo == c ? 1 : N[c];
+            a.face.fs[fam][2] = lo == c ? N[c] : 1;
         }
         a.phi = phi;
+        face = a.face;
         IPS_HIP(launch_bwrite(a, st));
     } else {
         // d == 2: faces are lines
@@ -1568,13 +1570,14 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         a.geo = p->geo;
         for (int q = 0; q < 3; ++q) a.n[q] = q < 2 ? n[q] : 1;
         for (int fam = 0; fam < 2; ++fam) {
-            a.F[fam] = p->F[fam];
-            a.fs[fam][0] = N[1 - fam];
-            a.fs[fam][1] = 1;
-            a.fs[fam][2] = 0;
-            a.scale[fam] = p->h[0] * p->h[1];
+            a.face.F[fam] = p->F[fam];
+            a.face.fs[fam][0] = N[1 - fam];
+            a.face.fs[fam][1] = 1;
+            a.face.fs[fam][2] = 0;
+            a.face.scale[fam] = p->h[0] * p->h[1];
         }
         a.phi = phi;
+        face = a.face;
         IPS_HIP(launch_bwrite(a, st));
     }
 
@@ -1585,6 +1588,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         a.geo = p->geo;
         for (int q = 0; q < 3; ++q) a.n[q] = q < d ? n[q] : 1;
         a.phi = phi;
+        a.face = face;
         for (int fam = 0; fam < d; ++fam) a.G[fam] = p->G[fam];
         IPS_HIP(launch_gtilde(a, st));
         if ((rc = shell_dst_all(p, p->G, 2, false, st))) return rc;
