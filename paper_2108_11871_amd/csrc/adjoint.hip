@@ -15,12 +15,17 @@
 //   b      = L0^-1 U_I                (order 6)
 //   lambda = w_boundary + T^T (a + b) + U_boundary
 //   rho_bar_I = phi_star(w_I) + B^T lambda,  rho_bar_boundary = 0
+// FP64 plans evaluate this on the shell, as the forward solve does (launch_adj_*
+// below: volume transforms of w alone); the mixed modes by whole-volume transforms
+// and stencils (their FP32 tiles' rounding is kept).
 // B^T spreads boundary values back over the interior with the same Green's
 // function sums, evaluated by FFT convolutions with the plan's kernel
 // spectra: for every slice s normal to a face family,
 //   slice(s) = IFFT2[ K_hat(s - 1) . FFT2(lambda_face0)
 //                     + K_hat(M - 1 - s) . FFT2(lambda_faceM) ].
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "common.h"
 #include "kernels.h"
@@ -368,6 +373,509 @@ hipError_t launch_adj_lambda(const AdjArgs &a, const double *w, const double *y1
         hipLaunchKernelGGL(k_adj_lambda<3>, dim3(nb), dim3(NTA), 0, st, a, w, y1, y2, U);
     else
         hipLaunchKernelGGL(k_adj_lambda<2>, dim3(nb), dim3(NTA), 0, st, a, w, y1, y2, U);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// The shell form of the adjoint (FP64). With W the raw sine spectrum of w_I and
+// gt_hat, D_hat, V as in the forward solve, c(k) = pref [(gt_hat (1 + m_R/Lambda) +
+// D_hat)/Lambda - beta/q] transposes to
+//   D layers:    D_hat_l(k_o)  = sum over k_a of sin(pi k_a l/M_a) X(k),  X = pref W/Lambda
+//   their values by sine sums, the extrapolation and the sixth-order stencils
+//   transposed on the layers (R_spec layers, boundary terms Z), back to spectra T,
+//   g~ layers:   the same sums over k_a of X (1 + m_R/Lambda) + pref m_R/Lambda V,
+//                V(k) = sum over the layers of all families of sin(pi k_f l/M_f) T_l(k_o)
+// and lambda collects g~ and Z. Three volume transforms instead of twelve and no
+// volume stencils: 257^3 forward and backward 5.03 -> 3.93 ms, 4097^2 5.52 -> 4.29 ms.
+// The sums over k_a read X once per family (24..47 us at 257^3, near the copy rate);
+// k_adj_x (158 us) is bound by its ten cached loads per element.
+// ---------------------------------------------------------------------------
+struct ContractArgs {
+    const double *X, *s; // s[(j-1)*Ia + k-1] = sin(pi k j/M)
+    int Ia;
+    int64_t np, st;             // positions, stride of k_a
+    int64_t inner, outer;       // position p starts at (p / inner) * outer + p % inner
+    double *out;                // [splits][nl][np]
+};
+
+// Layer sums from the odd and the even wavenumbers' sums of weights 1 (and 2).
+template <int NW>
+__device__ __forceinline__ void layer_out(double *out, int64_t np, int64_t p, const double (&o)[NW], const double (&e)[NW])
+{
+    out[p] = o[0] + e[0];
+    out[(2 * NW - 1) * np + p] = o[0] - e[0];
+    if constexpr (NW == 2) {
+        out[np + p] = o[1] + e[1];
+        out[2 * np + p] = o[1] - e[1];
+    }
+}
+
+// Strided axis: one position per thread, neighbouring positions side by side.
+template <int NW>
+__global__ __launch_bounds__(NTA) void k_adj_contract(ContractArgs a)
+{
+    const int64_t p = blockIdx.x * (int64_t)NTA + threadIdx.x;
+    if (p >= a.np) return;
+    const int sp = blockIdx.y, ns = gridDim.y;
+    // whole pairs of wavenumbers (odd, even) per split
+    const int pairs = (a.Ia + 1) / 2;
+    const int i0 = 2 * (int)((int64_t)pairs * sp / ns), i1 = min(a.Ia, 2 * (int)((int64_t)pairs * (sp + 1) / ns));
+    const double *X = a.X + p / a.inner * a.outer + p % a.inner;
+    double o[NW], e[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) o[w] = e[w] = 0.0;
+    int i = i0;
+    for (; i + 8 <= i1; i += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = X[(i + u) * a.st];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                double &t = u & 1 ? e[w] : o[w];
+                t = fma(a.s[w * a.Ia + i + u], v[u], t);
+            }
+    }
+    for (; i < i1; ++i) {
+        const double v = X[i * a.st];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const double t = a.s[w * a.Ia + i] * v;
+            o[w] += i & 1 ? 0.0 : t;
+            e[w] += i & 1 ? t : 0.0;
+        }
+    }
+    layer_out<NW>(a.out + sp * (2 * NW) * a.np, a.np, p, o, e);
+}
+
+// Contiguous axis: one position (row) per wave; lane parity is wavenumber parity.
+template <int NW>
+__global__ __launch_bounds__(NTA) void k_adj_contract_row(ContractArgs a)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t p = blockIdx.x * (int64_t)(NTA / 64) + (threadIdx.x >> 6);
+    if (p >= a.np) return;
+    const double *X = a.X + p * a.outer;
+    double t[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t[w] = 0.0;
+    for (int i = lane; i < a.Ia; i += 64) {
+        const double v = X[i];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t[w] = fma(a.s[w * a.Ia + i], v, t[w]);
+    }
+    double o[NW], e[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+#pragma unroll
+        for (int m = 2; m < 64; m <<= 1) t[w] += __shfl_xor(t[w], m);
+        o[w] = t[w];
+        e[w] = __shfl_xor(t[w], 1);
+    }
+    if (lane == 0) layer_out<NW>(a.out, a.np, p, o, e);
+}
+
+int adj_splits(const Geo &g, int a, int nl)
+{
+    if (a == g.d - 1) return 1; // rows
+    int64_t np = 1;
+    for (int b = 0; b < g.d; ++b)
+        if (b != a) np *= g.M[b] - 1;
+    const int Ia = g.M[a] - 1;
+    const int64_t want = ((int64_t)512 * 1024 + np - 1) / np; // threads of a full device
+    return (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min(Ia / nl, Ia / 16)));
+}
+
+hipError_t launch_adj_contract(const AdjArgs &a, int ax, int nl, const double *X, double *part, double *out,
+                               hipStream_t st)
+{
+    const Geo &g = a.geo;
+    if (nl != 2 && nl != 4) return hipErrorInvalidValue;
+    ContractArgs c{};
+    c.X = X;
+    c.s = a.tab[ax].s;
+    c.Ia = g.M[ax] - 1;
+    c.np = 1;
+    c.st = 1;
+    for (int b = 0; b < g.d; ++b) {
+        if (b != ax) c.np *= g.M[b] - 1;
+        if (b > ax) c.st *= g.M[b] - 1;
+    }
+    c.inner = c.st;
+    c.outer = c.st * c.Ia;
+    const int ks = adj_splits(g, ax, nl);
+    c.out = ks > 1 ? part : out;
+    if (ax == g.d - 1) {
+        const unsigned nb = (unsigned)((c.np + NTA / 64 - 1) / (NTA / 64));
+        if (nl == 2)
+            hipLaunchKernelGGL(k_adj_contract_row<1>, dim3(nb), dim3(NTA), 0, st, c);
+        else
+            hipLaunchKernelGGL(k_adj_contract_row<2>, dim3(nb), dim3(NTA), 0, st, c);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)((c.np + NTA - 1) / NTA), (unsigned)ks);
+    if (nl == 2)
+        hipLaunchKernelGGL(k_adj_contract<1>, grid, dim3(NTA), 0, st, c);
+    else
+        hipLaunchKernelGGL(k_adj_contract<2>, grid, dim3(NTA), 0, st, c);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && ks > 1) e = launch_reduce(part, out, nl * c.np, ks, 1, st);
+    return e;
+}
+
+// ---- transposed extrapolation and stencils on the shell ---------------------------
+__device__ __forceinline__ int64_t adj_shell_size(const Geo &g, int a)
+{
+    int64_t s = 1;
+    for (int b = 0; b < g.d; ++b)
+        if (b != a) s *= g.M[b] - 1;
+    return s;
+}
+
+// Position e of family fam -> the indices of the other axes.
+template <int D>
+__device__ __forceinline__ void shell_pos(const Geo &g, int fam, int e, int *ob, int *i)
+{
+    int q = 0;
+    ob[1] = 0;
+#pragma unroll
+    for (int b = 0; b < D; ++b)
+        if (b != fam) ob[q++] = b;
+    if (D == 3) {
+        const int Ic = g.M[ob[1]] - 1;
+        i[ob[0]] = 1 + e / Ic;
+        i[ob[1]] = 1 + e % Ic;
+    } else {
+        i[ob[0]] = 1 + e;
+    }
+}
+
+// Index along the family axis of core layer l (2..5, M-5..M-2) and R_spec slot of
+// index i (1..5, then M-1..M-5).
+__device__ __forceinline__ int core_index(int l, int M) { return l < 4 ? 2 + l : M - 9 + l; }
+__device__ __forceinline__ int rs_slot(int i, int M) { return i <= 5 ? i - 1 : 5 + (M - 1 - i); }
+
+// Whether family fam owns the D values at index i of a lower axis.
+__device__ __forceinline__ bool d_owned(int i, int M) { return i > 2 && i < M - 2; }
+
+// Cb[fam][l] = transposed cubic extrapolation of the owned D layers: core node p of
+// an axis feeds the shell nodes p, 1 (p <= 5) and M-1 (p >= M-5).
+template <int D>
+__global__ __launch_bounds__(NTA) void k_adj_core(AdjArgs a, AdjShell s)
+{
+    const Geo &g = a.geo;
+    const int fam = blockIdx.y >> 3, l = blockIdx.y & 7;
+    const int64_t ss = adj_shell_size(g, fam);
+    const int e = blockIdx.x * NTA + threadIdx.x;
+    if (e >= ss) return;
+    int ob[2], i[3] = {0, 0, 0};
+    shell_pos<D>(g, fam, e, ob, i);
+    const int Mf = g.M[fam];
+    i[fam] = core_index(l, Mf);
+    bool core = true;
+    for (int b = 0; b < D; ++b) core = core && i[b] >= 2 && i[b] <= g.M[b] - 2;
+    double v = 0.0;
+    if (core) {
+        const double wt[4] = {4.0, -6.0, 4.0, -1.0};
+        const double *Db = s.Db[fam];
+        const double wf = wt[l < 4 ? l : 7 - l];
+        const int jx = l < 4 ? 0 : 3, j1 = l == 0 ? 1 : l == 7 ? 2 : -1;
+        const int Ic = D == 3 ? g.M[ob[1]] - 1 : 1;
+        // sources along each other axis: itself, node 1, node M-1 (weight 0: none)
+        int src[2][3];
+        double w[2][3];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            src[q][0] = src[q][1] = src[q][2] = 1;
+            w[q][0] = q < D - 1 ? 0.0 : 1.0;
+            w[q][1] = w[q][2] = 0.0;
+            if (q >= D - 1) continue;
+            const int b = ob[q], M = g.M[b], p = i[b];
+            src[q][0] = p;
+            src[q][2] = M - 1;
+            w[q][0] = b > fam || d_owned(p, M) ? 1.0 : 0.0;
+            if (b > fam) { // a lower axis owns its own shell nodes
+                w[q][1] = p <= 5 ? wt[p - 2] : 0.0;
+                w[q][2] = p >= M - 5 ? wt[M - 2 - p] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int t = 0; t < (D == 3 ? 3 : 1); ++t) {
+                const double ww = w[0][u] * w[1][t];
+                if (ww == 0.0) continue;
+                const int64_t o = D == 3 ? (int64_t)(src[0][u] - 1) * Ic + (src[1][t] - 1) : src[0][u] - 1;
+                double d = wf * Db[jx * ss + o];
+                if (j1 >= 0) d += Db[j1 * ss + o];
+                v += ww * d;
+            }
+    }
+    s.Cb[fam][(int64_t)l * ss + e] = v;
+}
+
+// Rb[fam][r] = core layers' part minus the owned D layers (D = R - R_spec).
+template <int D>
+__global__ __launch_bounds__(NTA) void k_adj_rs(AdjArgs a, AdjShell s)
+{
+    const Geo &g = a.geo;
+    const int fam = blockIdx.y / 10, r = blockIdx.y % 10;
+    const int64_t ss = adj_shell_size(g, fam);
+    const int e = blockIdx.x * NTA + threadIdx.x;
+    if (e >= ss) return;
+    int ob[2], i[3] = {0, 0, 0};
+    shell_pos<D>(g, fam, e, ob, i);
+    const int Mf = g.M[fam];
+    bool owned = true;
+    for (int b = 0; b < fam; ++b) owned = owned && d_owned(i[b], g.M[b]);
+    const int L4[4] = {1, 2, Mf - 2, Mf - 1};
+    double v = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (owned && rs_slot(L4[j], Mf) == r) v -= s.Db[fam][j * ss + e];
+#pragma unroll
+    for (int l = 0; l < 8; ++l)
+        if (rs_slot(core_index(l, Mf), Mf) == r) v += s.Cb[fam][l * ss + e];
+    s.Rb[fam][(int64_t)r * ss + e] = v;
+}
+
+// Z[x][side]: the transposed core values at the nodes with index 2 (M-2) along x,
+// of every family whose core layers hold the node, over h_x^4.
+template <int D>
+__global__ __launch_bounds__(NTA) void k_adj_z(AdjArgs a, AdjShell s)
+{
+    const Geo &g = a.geo;
+    const int x = blockIdx.y >> 1, f = blockIdx.y & 1;
+    const int64_t ss = adj_shell_size(g, x);
+    const int e = blockIdx.x * NTA + threadIdx.x;
+    if (e >= ss) return;
+    int ob[2], i[3] = {0, 0, 0};
+    shell_pos<D>(g, x, e, ob, i);
+    i[x] = f ? g.M[x] - 2 : 2;
+    bool core = true;
+    for (int b = 0; b < D; ++b) core = core && i[b] >= 2 && i[b] <= g.M[b] - 2;
+    double v = 0.0;
+    if (core) {
+#pragma unroll
+        for (int fam = 0; fam < D; ++fam) {
+            if (i[fam] > 5 && i[fam] < g.M[fam] - 5) continue;
+            int64_t o = 0;
+#pragma unroll
+            for (int b = 0; b < D; ++b)
+                if (b != fam) o = o * (g.M[b] - 1) + (i[b] - 1);
+            const int64_t sf = adj_shell_size(g, fam);
+            for (int l = 0; l < 8; ++l)
+                if (core_index(l, g.M[fam]) == i[fam]) v += s.Cb[fam][l * sf + o];
+        }
+        const double h2 = g.h[x] * g.h[x];
+        v /= h2 * h2;
+    }
+    s.Z[x][(int64_t)f * ss + e] = v;
+}
+
+hipError_t launch_adj_shell(const AdjArgs &a, const AdjShell &s, hipStream_t st)
+{
+    const Geo &g = a.geo;
+    int64_t mx = 1;
+    for (int f = 0; f < g.d; ++f) {
+        int64_t ss = 1;
+        for (int b = 0; b < g.d; ++b)
+            if (b != f) ss *= g.M[b] - 1;
+        mx = std::max(mx, ss);
+    }
+    const unsigned nb = (unsigned)((mx + NTA - 1) / NTA), d = (unsigned)g.d;
+    if (d == 3) {
+        hipLaunchKernelGGL(k_adj_core<3>, dim3(nb, 8 * d), dim3(NTA), 0, st, a, s);
+        hipLaunchKernelGGL(k_adj_rs<3>, dim3(nb, 10 * d), dim3(NTA), 0, st, a, s);
+        hipLaunchKernelGGL(k_adj_z<3>, dim3(nb, 2 * d), dim3(NTA), 0, st, a, s);
+    } else {
+        hipLaunchKernelGGL(k_adj_core<2>, dim3(nb, 8 * d), dim3(NTA), 0, st, a, s);
+        hipLaunchKernelGGL(k_adj_rs<2>, dim3(nb, 10 * d), dim3(NTA), 0, st, a, s);
+        hipLaunchKernelGGL(k_adj_z<2>, dim3(nb, 2 * d), dim3(NTA), 0, st, a, s);
+    }
+    return hipGetLastError();
+}
+
+// Tp[fam][par][j] = T_{j+1} + sg T_{M-1-j}, sg = +1 for odd wavenumbers (par = 1).
+__global__ __launch_bounds__(NTA) void k_adj_tpack(AdjArgs a, AdjShell s)
+{
+    const int fam = blockIdx.y;
+    const int64_t len = 5 * adj_shell_size(a.geo, fam);
+    for (int64_t e = blockIdx.x * (int64_t)NTA + threadIdx.x; e < len; e += (int64_t)gridDim.x * NTA) {
+        const double lo = s.Rb[fam][e], hi = s.Rb[fam][len + e];
+        s.Tp[fam][e] = lo - hi;
+        s.Tp[fam][len + e] = lo + hi;
+    }
+}
+
+// One position of the axes after the first per thread (neighbours side by side), a
+// range of k0 per block row: the family-0 values of the position stay in registers.
+template <int D>
+__global__ __launch_bounds__(NTA) void k_adj_x(AdjArgs a, AdjShell s, double *X)
+{
+    const Geo &g = a.geo;
+    const int I0 = g.M[0] - 1, I1 = g.M[1] - 1, I2 = D == 3 ? g.M[2] - 1 : 1;
+    const int64_t np = (int64_t)I1 * I2, p = blockIdx.x * (int64_t)NTA + threadIdx.x;
+    if (p >= np) return;
+    const int i1 = D == 3 ? (int)(p / I2) : (int)p, i2 = D == 3 ? (int)(p % I2) : 0;
+    const int k0 = (int)((int64_t)I0 * blockIdx.y / gridDim.y), k1 = (int)((int64_t)I0 * (blockIdx.y + 1) / gridDim.y);
+    const double l1 = a.tab[1].lam[i1], l2 = D == 3 ? a.tab[2].lam[i2] : 0.0;
+    double T0[2][5], s1[5], s2[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+        T0[0][j] = s.Tp[0][j * np + p];
+        T0[1][j] = s.Tp[0][(5 + j) * np + p];
+        s1[j] = a.tab[1].s[j * I1 + i1];
+        s2[j] = D == 3 ? a.tab[2].s[j * I2 + i2] : 0.0;
+    }
+    const int64_t n1 = (int64_t)I0 * I2, n2 = (int64_t)I0 * I1;
+    const double *T1 = s.Tp[1] + ((i1 + 1) & 1) * 5 * n1 + i2, *T2 = D == 3 ? s.Tp[2] + ((i2 + 1) & 1) * 5 * n2 + i1 : nullptr;
+    // Lambda and m_R as polynomials of lambda_0
+    double A0 = l1, A1 = 1.0 + g.c2[0][1] * l1, B0 = 0.0, B1 = g.c4[1][0] * l1 * l1, B2 = g.c4[0][1] * l1;
+    if (D == 3) {
+        A0 += l2 + g.c2[1][2] * l1 * l2;
+        A1 += g.c2[0][2] * l2;
+        B0 = g.c4[1][2] * l1 * l1 * l2 + g.c4[2][1] * l1 * l2 * l2;
+        B1 += g.c4[2][0] * l2 * l2;
+        B2 += g.c4[0][2] * l2;
+    }
+    for (int i0 = k0; i0 < k1; ++i0) {
+        const bool odd = (i0 & 1) == 0;
+        double V = 0.0;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            V = fma(a.tab[0].s[j * I0 + i0], odd ? T0[1][j] : T0[0][j], V);
+            V = fma(s1[j], T1[j * n1 + (int64_t)i0 * I2], V);
+            if (D == 3) V = fma(s2[j], T2[j * n2 + (int64_t)i0 * I1], V);
+        }
+        const double l0 = a.tab[0].lam[i0];
+        const double L = fma(A1, l0, A0), R = fma(fma(B2, l0, B1), l0, B0);
+        const double q = R / L;
+        const int64_t e = i0 * np + p;
+        X[e] = fma(X[e], q, X[e]) + g.pref * q * V;
+    }
+}
+
+hipError_t launch_adj_x(const AdjArgs &a, const AdjShell &s, double *X, hipStream_t st)
+{
+    const Geo &g = a.geo;
+    const int I0 = g.M[0] - 1;
+    int64_t np = 1;
+    for (int b = 1; b < g.d; ++b) np *= g.M[b] - 1;
+    hipLaunchKernelGGL(k_adj_tpack, dim3(512, (unsigned)g.d), dim3(NTA), 0, st, a, s);
+    const int64_t want = ((int64_t)512 * 1024 + np - 1) / np;
+    const unsigned ks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (I0 + 7) / 8));
+    const dim3 grid((unsigned)((np + NTA - 1) / NTA), ks);
+    if (g.d == 3)
+        hipLaunchKernelGGL(k_adj_x<3>, grid, dim3(NTA), 0, st, a, s, X);
+    else
+        hipLaunchKernelGGL(k_adj_x<2>, grid, dim3(NTA), 0, st, a, s, X);
+    return hipGetLastError();
+}
+
+// As k_adj_lambda, with the transfer's transpose taken on the g~ layers (an interior
+// neighbour belongs to the lowest axis with index 1 or M-1 there) and the boundary
+// terms of the sixth-order stencils from Z (zero off the core).
+template <int D>
+__global__ __launch_bounds__(NTA) void k_adj_lambda_shell(AdjArgs a, AdjShell sh, const double *w, int six)
+{
+    const Geo &g = a.geo;
+    int fam = 0;
+    int64_t e = blockIdx.x * (int64_t)NTA + threadIdx.x;
+    while (fam < D && e >= a.lf_size[fam]) {
+        e -= a.lf_size[fam];
+        ++fam;
+    }
+    if (fam >= D) return;
+    const int b = a.fb[fam], c = a.fc[fam];
+    const int nb = g.M[b] + 1, ncn = D == 3 ? g.M[c] + 1 : 1;
+    const int per = nb * ncn;
+    const int f = (int)(e / per);
+    const int rem = (int)(e % per);
+    int i[3] = {0, 0, 0};
+    i[fam] = f ? g.M[fam] : 0;
+    i[b] = rem / ncn;
+    if (D == 3) i[c] = rem % ncn;
+    bool owned = true;
+    for (int x = 0; x < fam; ++x)
+        if (i[x] == 0 || i[x] == g.M[x]) owned = false;
+    double lam = 0.0;
+    if (owned) {
+        lam = w[grid_off(a.n, D, i)];
+        // g~ layer value of an interior node next to the boundary
+        auto gt = [&](const int *j) -> double {
+            int x = 0;
+            while (x < D - 1 && j[x] != 1 && j[x] != g.M[x] - 1) ++x;
+            int64_t o = 0;
+#pragma unroll
+            for (int z = 0; z < D; ++z)
+                if (z != x) o = o * (g.M[z] - 1) + (j[z] - 1);
+            return sh.Gb[x][(j[x] == 1 ? 0 : adj_shell_size(g, x)) + o];
+        };
+        auto inside = [&](const int *j) {
+            bool in = true;
+#pragma unroll
+            for (int z = 0; z < D; ++z) in = in && j[z] >= 1 && j[z] <= g.M[z] - 1;
+            return in;
+        };
+        double s = 0.0;
+#pragma unroll
+        for (int p = 0; p < D; ++p) {
+            double wf = 1.0 / (g.h[p] * g.h[p]);
+#pragma unroll
+            for (int q = 0; q < D; ++q)
+                if (q != p) wf -= 2.0 * g.c2[p][q] / (g.h[p] * g.h[p] * g.h[q] * g.h[q]);
+#pragma unroll
+            for (int sg = -1; sg <= 1; sg += 2) {
+                int j[3] = {i[0], i[1], i[2]};
+                j[p] += sg;
+                if (inside(j)) s += wf * gt(j);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < D; ++p)
+#pragma unroll
+            for (int q = p + 1; q < D; ++q) {
+                const double we = g.c2[p][q] / (g.h[p] * g.h[p] * g.h[q] * g.h[q]);
+#pragma unroll
+                for (int sp = -1; sp <= 1; sp += 2)
+#pragma unroll
+                    for (int sq = -1; sq <= 1; sq += 2) {
+                        int j[3] = {i[0], i[1], i[2]};
+                        j[p] += sp;
+                        j[q] += sq;
+                        if (inside(j)) s += we * gt(j);
+                    }
+            }
+        lam -= s;
+        if (six) {
+            // in-face axes in storage order of Z (increasing)
+            const int o0 = fam == 0 ? 1 : 0, o1 = D == 3 ? (fam == 2 ? 1 : 2) : o0;
+            const double *Z = sh.Z[fam] + (f ? adj_shell_size(g, fam) : 0);
+            auto z = [&](int j0, int j1) {
+                if (j0 < 2 || j0 > g.M[o0] - 2) return 0.0;
+                if (D == 3 && (j1 < 2 || j1 > g.M[o1] - 2)) return 0.0;
+                return Z[D == 3 ? (int64_t)(j0 - 1) * (g.M[o1] - 1) + (j1 - 1) : j0 - 1];
+            };
+            const int j0 = i[o0], j1 = D == 3 ? i[o1] : 0;
+            const double z0 = z(j0, j1);
+            lam += g.c4[fam][o0] / (g.h[o0] * g.h[o0]) * (z(j0 - 1, j1) - 2.0 * z0 + z(j0 + 1, j1));
+            if (D == 3) lam += g.c4[fam][o1] / (g.h[o1] * g.h[o1]) * (z(j0, j1 - 1) - 2.0 * z0 + z(j0, j1 + 1));
+        }
+    }
+    a.LF[fam][e] = lam;
+}
+
+hipError_t launch_adj_lambda_shell(const AdjArgs &a, const AdjShell &s, const double *w, bool six, hipStream_t st)
+{
+    int64_t tot = 0;
+    for (int fam = 0; fam < a.geo.d; ++fam) tot += a.lf_size[fam];
+    const unsigned nb = (unsigned)((tot + NTA - 1) / NTA);
+    if (a.geo.d == 3)
+        hipLaunchKernelGGL(k_adj_lambda_shell<3>, dim3(nb), dim3(NTA), 0, st, a, s, w, six ? 1 : 0);
+    else
+        hipLaunchKernelGGL(k_adj_lambda_shell<2>, dim3(nb), dim3(NTA), 0, st, a, s, w, six ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -252,6 +252,14 @@ struct AdjArgs {
     int fb[3], fc[3];    // in-face axes (b, c) of each family, c contiguous (3D)
 };
 
+// Shell arrays of the FP64 adjoint, per family over the two other axes (3D) or the
+// other one, as the forward solve's: transposed D layers [4], R_spec layers [10],
+// core layers [8], their boundary terms on the faces [2], g~ layers [2], and the
+// R_spec spectra packed by parity [2][5].
+struct AdjShell {
+    double *Db[3], *Rb[3], *Cb[3], *Z[3], *Gb[3], *Tp[3];
+};
+
 // Face-to-slice expansion (first transform), see k_expand.
 struct ExpandArgs {
     int d;
@@ -269,6 +277,19 @@ struct ExpandArgs {
     const cx<double> *tw;
 };
 
+// splits of the contraction over axis a with nl output layers (1: none); the
+// partials of more take splits * nl * (other axes) doubles, at most the volume
+int adj_splits(const Geo &g, int a, int nl);
+// layers (1, M - 1; nl = 4: 1, 2, M - 2, M - 1) of the sine series X along axis ax,
+// as spectra over the other axes
+hipError_t launch_adj_contract(const AdjArgs &a, int ax, int nl, const double *X, double *part, double *out,
+                               hipStream_t st);
+// transposed extrapolation and sixth-order stencils on the shell (Db -> Cb, Rb, Z)
+hipError_t launch_adj_shell(const AdjArgs &a, const AdjShell &s, hipStream_t st);
+// X <- X (1 + m_R/Lambda) + pref m_R/Lambda (sine series of the layers Rb, packed into Tp)
+hipError_t launch_adj_x(const AdjArgs &a, const AdjShell &s, double *X, hipStream_t st);
+// lambda from the g~ layers Gb and the boundary terms Z (null: none)
+hipError_t launch_adj_lambda_shell(const AdjArgs &a, const AdjShell &s, const double *w, bool six, hipStream_t st);
 hipError_t launch_adj_spec(const AdjArgs &a, double *X, double *Y, hipStream_t st);
 // T: 3D scratch of one grid-shaped array (unused in 2D)
 hipError_t launch_adj_r6(const AdjArgs &a, const double *A, double *F, double *U, double *T, hipStream_t st);

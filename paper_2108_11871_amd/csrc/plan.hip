@@ -309,6 +309,7 @@ struct ips_plan_s {
     double *AX = nullptr, *AY = nullptr, *AX2 = nullptr; // interior volumes
     double *AF = nullptr, *AU = nullptr;                 // grid-shaped (order 6)
     double *AZ = nullptr;                                // 3D expansion scratch
+    AdjShell ash{};                                      // FP64: shell arrays instead of AX2, AF, AU
     double *LF[3] = {nullptr, nullptr, nullptr};         // face weights
     double *LH[3] = {nullptr, nullptr, nullptr};         // their slot spectra
     // stage timing
@@ -721,8 +722,9 @@ void layout_ws(ips_plan p, Carver &c)
     if (p->ws_adj) layout_adj(p, c);
 }
 
-// The adjoint's buffers: three interior volumes, two grids (order 6), face
-// weights and their spectra, and one slice stack (3D).
+// The adjoint's buffers: two interior volumes, the shell arrays (FP64) or another
+// volume and two grids (mixed modes, order 6), face weights and their spectra, and
+// one slice stack (3D).
 void layout_adj(ips_plan p, Carver &c)
 {
     const int d = p->d;
@@ -734,7 +736,29 @@ void layout_adj(ips_plan p, Carver &c)
     }
     c.take(&p->AX, vol * sizeof(double));
     c.take(&p->AY, vol * sizeof(double));
-    if (p->order == 6) {
+    const bool shell = p->precision == IPS_FP64;
+    if (shell) {
+        // families back to back, as the forward solve's shell layers
+        size_t ss[3] = {0, 0, 0}, ts = 0;
+        for (int fam = 0; fam < d; ++fam) ts += ss[fam] = vol / I[fam];
+        auto take = [&](double **arr, int nl) {
+            double *blk;
+            c.take(&blk, nl * ts * sizeof(double));
+            size_t os = 0;
+            for (int fam = 0; fam < d; ++fam) {
+                arr[fam] = blk ? blk + nl * os : nullptr;
+                os += ss[fam];
+            }
+        };
+        take(p->ash.Gb, 2);
+        if (p->order == 6) {
+            take(p->ash.Db, 4);
+            take(p->ash.Rb, 10);
+            take(p->ash.Cb, 8);
+            take(p->ash.Tp, 10);
+            take(p->ash.Z, 2);
+        }
+    } else if (p->order == 6) {
         c.take(&p->AX2, vol * sizeof(double));
         c.take(&p->AF, grid * sizeof(double));
         c.take(&p->AU, grid * sizeof(double));
@@ -750,7 +774,7 @@ void layout_adj(ips_plan p, Carver &c)
         if (d == 3) zmax = std::max(zmax, (size_t)I[fam] * N[b] * I[cc]);
     }
     // order 6 also uses it as one grid-shaped scratch array (adjoint stencil)
-    if (d == 3 && p->order == 6) zmax = std::max(zmax, grid);
+    if (d == 3 && p->order == 6 && !shell) zmax = std::max(zmax, grid);
     if (d == 3) c.take(&p->AZ, zmax * sizeof(double));
 }
 
@@ -1948,16 +1972,33 @@ int execute_adjoint(ips_plan p, const double *w, double *out, hipStream_t st)
     if ((rc = vol_fwd(p, w + off, gst, p->AX, st, f32t))) return rc;
     IPS_HIP(launch_adj_spec(aa, p->AX, p->AY, st));
     if ((rc = vol_inv(p, p->AY, out + off, gst, st, f32t))) return rc;
-    if ((rc = vol_inv(p, p->AX, p->AX, pst, st, f32t))) return rc;
-    if (six) {
-        // AZ (the slice stack of the boundary expansion, used later) is scratch here
-        IPS_HIP(launch_adj_r6(aa, p->AX, p->AF, p->AU, p->AZ, st));
-        if ((rc = vol_fwd(p, p->AU + off, gst, p->AX2, st, f32t))) return rc;
-        IPS_HIP(launch_adj_spec(aa, p->AX2, nullptr, st));
-        if ((rc = vol_inv(p, p->AX2, p->AX2, pst, st, f32t))) return rc;
-    }
     IPS_HIP(launch_zero_boundary(aa, out, st));
-    IPS_HIP(launch_adj_lambda(aa, w, p->AX, six ? p->AX2 : nullptr, six ? p->AU : nullptr, st));
+    if (p->precision == IPS_FP64) {
+        // the harmonic part on the shell (AY, consumed above, holds split partials)
+        const AdjShell &sh = p->ash;
+        if (six) {
+            for (int fam = 0; fam < d; ++fam)
+                IPS_HIP(launch_adj_contract(aa, fam, 4, p->AX, p->AY, sh.Db[fam], st));
+            if ((rc = shell_dst_all(p, sh.Db, 4, true, st))) return rc;
+            IPS_HIP(launch_adj_shell(aa, sh, st));
+            if ((rc = shell_dst_all(p, sh.Rb, 10, false, st))) return rc;
+            IPS_HIP(launch_adj_x(aa, sh, p->AX, st));
+        }
+        for (int fam = 0; fam < d; ++fam)
+            IPS_HIP(launch_adj_contract(aa, fam, 2, p->AX, p->AY, sh.Gb[fam], st));
+        if ((rc = shell_dst_all(p, sh.Gb, 2, true, st))) return rc;
+        IPS_HIP(launch_adj_lambda_shell(aa, sh, w, six, st));
+    } else {
+        if ((rc = vol_inv(p, p->AX, p->AX, pst, st, f32t))) return rc;
+        if (six) {
+            // AZ (the slice stack of the boundary expansion, used later) is scratch here
+            IPS_HIP(launch_adj_r6(aa, p->AX, p->AF, p->AU, p->AZ, st));
+            if ((rc = vol_fwd(p, p->AU + off, gst, p->AX2, st, f32t))) return rc;
+            IPS_HIP(launch_adj_spec(aa, p->AX2, nullptr, st));
+            if ((rc = vol_inv(p, p->AX2, p->AX2, pst, st, f32t))) return rc;
+        }
+        IPS_HIP(launch_adj_lambda(aa, w, p->AX, six ? p->AX2 : nullptr, six ? p->AU : nullptr, st));
+    }
     double vh = 1.0;
     for (int a = 0; a < d; ++a) vh *= p->h[a];
     for (int fam = 0; fam < d; ++fam) {

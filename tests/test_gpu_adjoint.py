@@ -209,3 +209,22 @@ def test_autograd_257_cube_sixteen_directions(precision):
         print("  direction %2d: <grad,v> %.12e  FD %.12e  rel %.2e" % (t, an, fd, rel), flush=True)
     plan.close()
     assert worst < (1e-10 if precision == "fp64" else 1e-4)
+
+
+# shell form of the FP64 adjoint: the smallest grids (core layers of both sides share
+# nodes up to M = 9), layers of one node, one and several splits of the sums, rows
+# shorter and longer than a wave
+@pytest.mark.parametrize("shape,order", [((8, 8, 8), 6), ((8, 9, 13), 6), ((11, 10, 66), 6), ((70, 8, 9), 6),
+                                         ((9, 131, 10), 6), ((3, 4, 5), 4), ((40, 3, 6), 4), ((8, 8), 6), ((9, 12), 6),
+                                         ((257, 9), 6), ((10, 300), 6), ((3, 7), 4)])
+def test_shell_adjoint_small(shape, order):
+    import torch
+    from paper_2108_11871_amd import api
+    from gpu_util import banner, rel_err, to_dev
+
+    banner("adjoint shape=%s order=%d" % (shape, order))
+    h = I.grid_spacing(shape, -1.0, 1.3)
+    w = np.random.default_rng(5).standard_normal(shape)
+    got = api.Plan(shape, h, order=order, adjoint=True).adjoint(to_dev(w))
+    torch.cuda.synchronize()
+    assert rel_err(got.cpu().numpy(), P.adjoint(w, h, order)) < 1e-12
