@@ -80,17 +80,20 @@ inline size_t tile_lds(int N, int W)
     return (size_t)N * sizeof(cx<T>) + (size_t)N * (W + 1) * sizeof(T);
 }
 
-// f(N) with N as a compile-time constant where tiles of W columns and N rows are
-// full register tiles; whether they are.
-template <typename F>
-inline bool rt_length(int N, int W, F f)
+// f(RegTile) of the register tile that has N rows and W columns; whether there is
+// one: the default width of every power of two from 256 on, and twice that at the
+// lengths in DOUBLE (512 | 1024), where a kernel measured faster so.
+template <int DOUBLE, typename F>
+inline bool rt_tile(int N, int W, F f)
 {
-#define IPS_RT(n)                                     \
-    if (N == n && W == RegTile<n>::W) {               \
-        f(std::integral_constant<int, n>());          \
-        return true;                                  \
+#define IPS_RT(...)                                                     \
+    if (RegTile<__VA_ARGS__>::N == N && RegTile<__VA_ARGS__>::W == W) { \
+        f(RegTile<__VA_ARGS__>());                                      \
+        return true;                                                    \
     }
     IPS_RT(256) IPS_RT(512) IPS_RT(1024) IPS_RT(2048) IPS_RT(4096) IPS_RT(8192)
+    if constexpr (DOUBLE & 512) IPS_RT(512, 8)
+    if constexpr (DOUBLE & 1024) IPS_RT(1024, 4)
 #undef IPS_RT
     return false;
 }

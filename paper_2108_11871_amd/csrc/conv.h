@@ -199,30 +199,36 @@ __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
 // memory (the next tile's during the transform) into the first stage; the cosine
 // and sine parts are formed in registers after the last stage and written to the
 // LDS once, sequence by sequence, for the sums over the columns (same thread per
-// slot row and same order of the sums as k_cc). 257^3: FP64 219/209/214 -> 205/183/185
+// slot row and same order of the sums as k_cc; PAIRS: tiles of twice the width whose
+// halves belong to neighbouring chunks, each with its own sums). 257^3: FP64 219/209/214 -> 205/183/185
 // us, FP32 112/124/115 -> 114/118/111 us; 513^3 FP32 1010/1288/1251 -> 709/1237/1258.
-template <typename T, typename TI, int N, bool WB>
-__global__ __launch_bounds__(RegTile<N>::NTH) void k_cc_rt(CcArgs a, int nchunk)
+template <typename T, typename TI, typename R, bool WB, bool PAIRS>
+__global__ __launch_bounds__(R::NTH) void k_cc_rt(CcArgs a, int nchunk)
 {
-    using R = RegTile<N>;
-    constexpr int M = N / 2, W = R::W, Wh = W / 2, P = R::P, NTH = R::NTH;
+    constexpr int N = R::N, M = N / 2, W = R::W, Wh = W / 2, P = R::P, NTH = R::NTH;
     extern __shared__ __align__(16) unsigned char smem[];
     const cx<T> *tw = tw_table<T, !R::LTW>(smem, a.tw, a.twf);
     cx<T> *buf = reinterpret_cast<cx<T> *>(smem) + (R::LTW ? N : 0);
-    const int lb = xcd_remap(blockIdx.x, nchunk * a.nbatch);
-    const int ch = lb % nchunk, bt = cc_batch(lb / nchunk, a.Mo);
+    // PAIRS: chunks NG ch .. of Wg first-half columns each per tile
+    constexpr int NG = PAIRS ? 2 : 1, Wg = Wh / NG;
+    const int nblk = (nchunk + NG - 1) / NG;
+    const int lb = xcd_remap(blockIdx.x, nblk * a.nbatch);
+    const int ch = lb % nblk * NG, bt = cc_batch(lb / nblk, a.Mo);
     const int kb = a.Mo > 0 ? (bt <= a.Mo ? bt : bt - a.Mo) : 0;
     const TI *in = static_cast<const TI *>(a.in) + bt * a.ibs;
     constexpr int TPT = M / NTH > 0 ? M / NTH : 1;
-    double a10[TPT], a11[TPT], a20[TPT], a21[TPT]; // [row 1|2][face 0|M]
+    double a10[TPT][NG], a11[TPT][NG], a20[TPT][NG], a21[TPT][NG]; // [row 1|2][face 0|M]
 #pragma unroll
-    for (int i = 0; i < TPT; ++i) a10[i] = a11[i] = a20[i] = a21[i] = 0.0;
+    for (int i = 0; i < TPT; ++i)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) a10[i][g] = a11[i][g] = a20[i][g] = a21[i][g] = 0.0;
     if constexpr (R::LTW) load_twiddles<T, NTH>(reinterpret_cast<cx<T> *>(smem), a.tw, N);
     const int hc = (a.ncols + 1) >> 1; // first-half columns (the chunked range)
-    const int cbeg = a.interleave ? ch * Wh : ch * a.cols_per_chunk;
+    const int cbeg = a.interleave ? ch * Wg : ch * a.cols_per_chunk;
     const int cend = a.interleave ? hc : min(hc, cbeg + a.cols_per_chunk);
-    const int cstep = a.interleave ? nchunk * Wh : Wh;
-    auto n_a = [&](int c) { return min(Wh, cend - c); };
+    const int cstep = a.interleave ? nchunk * Wg : Wh;
+    const int wmax = PAIRS && ch + NG > nchunk ? Wg : Wh; // the last of an odd number of chunks
+    auto n_a = [&](int c) { return min(wmax, cend - c); };
     auto n_b = [&](int c) { return min(n_a(c), max(0, (a.ncols - 2 * c) >> 1)); };
     // source column of tile column c of the tile at c0 (-1: none)
     auto src_col = [&](int c, int c0, int nA, int nB) {
@@ -231,12 +237,12 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_cc_rt(CcArgs a, int nchunk)
     };
     auto fetch = [&](TI(&x)[8], int c0, int tid) {
         int j, s;
-        rt_plain<N>(tid, j, s);
+        rt_plain<R>(tid, j, s);
         const int nA = n_a(c0), nB = n_b(c0);
         const int q0 = src_col(2 * s, c0, nA, nB), q1 = src_col(2 * s + 1, c0, nA, nB), ics = (int)a.ics;
         // (full tiles of contiguous columns: ascending, or descending among the mirrors)
         const int dir = nA == Wh && nB == Wh && ics == 1 && Wh > 1 ? (2 * s < Wh ? 1 : -1) : 0;
-        rt_fetch<TI, N>(x, in, a.irs, q0 < 0 ? -1 : __mul24(q0, ics), q1 < 0 ? -1 : __mul24(q1, ics), dir, j, 1);
+        rt_fetch<TI, R>(x, in, a.irs, q0 < 0 ? -1 : __mul24(q0, ics), q1 < 0 ? -1 : __mul24(q1, ics), dir, j, 1);
     };
     TI x[8];
     if (cbeg < cend) fetch(x, cbeg, threadIdx.x);
@@ -248,17 +254,17 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_cc_rt(CcArgs a, int nchunk)
         asm volatile("" : "+v"(tid)); // (as in k_cc)
         tid &= NTH - 1;
         int j, s;
-        rt_plain<N>(tid, j, s);
+        rt_plain<R>(tid, j, s);
         cx<T> v[8];
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)x[2 * r], (T)x[2 * r + 1]};
         if (c0 + cstep < cend) fetch(x, c0 + cstep, tid);
-        rt_first_zpad<T, N>(buf, v, j, s);
-        rt_middle<T, N, false>(buf, tw, tid);
-        rt_paired<N>(tid, j, s);
-        rt_last<T, N, false>(buf, tw, v, j, s);
+        rt_first_zpad<T, R>(buf, v, j, s);
+        rt_middle<T, R, false>(buf, tw, tid);
+        rt_paired<R>(tid, j, s);
+        rt_last<T, R, false>(buf, tw, v, j, s);
         cx<T> C[4], S[4];
-        rt_slots<T, N>(v, j, C, S);
+        rt_slots<T, R>(v, j, C, S);
         __syncthreads();
         // slot rows k and M + k of sequence s (row M of k = 0: the last cosine row)
         {
@@ -287,16 +293,18 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_cc_rt(CcArgs a, int nchunk)
             }
         }
 #pragma unroll
-        for (int i = 0; i < TPT; ++i) {
-            const int t = tid + i * NTH;
-            if (t < M) {
+        for (int i = 0; i < TPT; ++i)
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int t = tid + i * NTH;
+                if (NTH > M && t >= M) continue;
                 const bool two = t > 0; // row M + t is S_t (else C_M, see below)
                 const T *r1 = reinterpret_cast<const T *>(buf + t), *r2 = r1 + 2 * M;
                 auto at = [&](const T *r, int c) { return (double)r[(c >> 1) * 2 * R::SP + (c & 1)]; };
                 const double *Kr = a.K + (int64_t)kb * a.Ko;
                 const double *KA = Kr + t + (int64_t)c0 * a.Kd; // K at column c0 + jj
                 const double *KB = Kr + t + (int64_t)m0 * a.Kd; // K at column m0 - jj
-                double s10 = a10[i], s11 = a11[i], s20 = a20[i], s21 = a21[i];
+                double s10 = a10[i][g], s11 = a11[i][g], s20 = a20[i][g], s21 = a21[i][g];
                 auto col_pair = [&](int jj) {
                     const double kA = KA[(int64_t)jj * a.Kd], kB = KB[-(int64_t)jj * a.Kd];
                     const double ud = at(r1, jj), um = at(r1, Wh + jj);
@@ -310,16 +318,17 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_cc_rt(CcArgs a, int nchunk)
                     s21 = fma(kB, vd, s21);
                     s21 = fma(kA, vm, s21);
                 };
-                if (nA == Wh) {
+                const int j0 = g * Wg, j1 = min(j0 + Wg, nA);
+                if (j1 == j0 + Wg) {
 #pragma unroll
-                    for (int jj = 0; jj < Wh; ++jj) col_pair(jj);
+                    for (int jj = 0; jj < Wg; ++jj) col_pair(j0 + jj);
                 } else {
-                    for (int jj = 0; jj < nA; ++jj) col_pair(jj);
+                    for (int jj = j0; jj < j1; ++jj) col_pair(jj);
                 }
                 if (!two) {
                     // C_M (no sine partner) with its own kernel spectrum
                     const double *MA = Kr + M + (int64_t)c0 * a.Kd, *MB = Kr + M + (int64_t)m0 * a.Kd;
-                    for (int jj = 0; jj < nA; ++jj) {
+                    for (int jj = j0; jj < j1; ++jj) {
                         const double kA = MA[(int64_t)jj * a.Kd], kB = MB[-(int64_t)jj * a.Kd];
                         const double vd = at(r2, jj), vm = at(r2, Wh + jj);
                         s20 = fma(kA, vd, s20);
@@ -328,34 +337,35 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_cc_rt(CcArgs a, int nchunk)
                         s21 = fma(kA, vm, s21);
                     }
                 }
-                a10[i] = s10;
-                a11[i] = s11;
-                a20[i] = s20;
-                a21[i] = s21;
+                a10[i][g] = s10;
+                a11[i][g] = s11;
+                a20[i][g] = s20;
+                a21[i][g] = s21;
             }
-        }
         __syncthreads();
     }
     // FP64 partials [face][chunk][batch][slot]: slot rows t and M + t
-    const int64_t o0 = ((int64_t)ch * a.nbatch + bt) * N, o1 = o0 + (int64_t)nchunk * a.nbatch * N;
 #pragma unroll
-    for (int i = 0; i < TPT; ++i) {
-        const int t = threadIdx.x + i * NTH;
-        if (t < M) {
-            a.part[o0 + t] = a10[i];
-            a.part[o1 + t] = a11[i];
-            a.part[o0 + M + t] = a20[i];
-            a.part[o1 + M + t] = a21[i];
+    for (int i = 0; i < TPT; ++i)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int t = threadIdx.x + i * NTH;
+            if ((NTH > M && t >= M) || ch + g >= nchunk) continue;
+            const int64_t o0 = ((int64_t)(ch + g) * a.nbatch + bt) * N, o1 = o0 + (int64_t)nchunk * a.nbatch * N;
+            a.part[o0 + t] = a10[i][g];
+            a.part[o1 + t] = a11[i][g];
+            a.part[o0 + M + t] = a20[i][g];
+            a.part[o1 + M + t] = a21[i][g];
         }
-    }
 }
 
-template <typename T, typename TI, bool WB, int N>
+template <typename T, typename TI, bool WB, typename R, bool PAIRS>
 static void launch_cc_rt(const CcArgs &a, int nchunk, hipStream_t st)
 {
-    const size_t lds = rt_lds<T, N>();
-    set_lds((const void *)&k_cc_rt<T, TI, N, WB>, lds);
-    hipLaunchKernelGGL((k_cc_rt<T, TI, N, WB>), dim3(nchunk * a.nbatch), dim3(RegTile<N>::NTH), lds, st, a, nchunk);
+    const size_t lds = rt_lds<T, R>();
+    const int nblk = PAIRS ? (nchunk + 1) / 2 : nchunk;
+    set_lds((const void *)&k_cc_rt<T, TI, R, WB, PAIRS>, lds);
+    hipLaunchKernelGGL((k_cc_rt<T, TI, R, WB, PAIRS>), dim3(nblk * a.nbatch), dim3(R::NTH), lds, st, a, nchunk);
 }
 
 template <typename T, typename TI, int MAXE, bool WB, int KD, int RPT, int NTT = NT, int WHC = 0>
@@ -408,8 +418,13 @@ template <typename T, typename TI, bool WB>
 hipError_t launch_cc_t(const CcArgs &a, int nchunk, hipStream_t st)
 {
     const int work = (a.W / 2) * a.fd.N;
-    if (a.nrows_in == a.fd.M - 1 &&
-        rt_length(a.fd.N, a.W, [&](auto n) { launch_cc_rt<T, TI, WB, decltype(n)::value>(a, nchunk, st); }))
+    const bool rt = a.nrows_in == a.fd.M - 1;
+    if (a.pairs) {
+        if (!rt || a.fd.N != 1024 || a.W != RegTile<1024, 4>::W || !a.interleave) return hipErrorInvalidValue;
+        launch_cc_rt<T, TI, WB, RegTile<1024, 4>, true>(a, nchunk, st);
+        return hipGetLastError();
+    }
+    if (rt && rt_tile<0>(a.fd.N, a.W, [&](auto tile) { launch_cc_rt<T, TI, WB, decltype(tile), false>(a, nchunk, st); }))
         return hipGetLastError();
     if (big_fft(a.fd.N)) {
         // one complex sequence (a column and its mirror) per tile; rows per thread = N / NTB <= 8

@@ -615,9 +615,9 @@ struct CtLast {
 // works on registers with one cross-lane move per value instead of two or four
 // passes over the tile in LDS.
 // ---------------------------------------------------------------------------
-template <int N>
+template <int LEN, int SEQS = (LEN >= 2048 ? 1 : 2048 / LEN)>
 struct RegTile {
-    static constexpr int NSEQ = N >= 2048 ? 1 : 2048 / N, W = 2 * NSEQ;
+    static constexpr int N = LEN, NSEQ = SEQS, W = 2 * NSEQ;
     static constexpr int LGS = NSEQ == 8 ? 3 : NSEQ == 4 ? 2 : NSEQ == 2 ? 1 : 0;
     static constexpr int P = N / 8;          // rows between the elements of a thread
     static constexpr int NTH = P * NSEQ;     // threads of the block
@@ -631,16 +631,16 @@ struct RegTile {
 };
 
 // LDS bytes of a register tile and its twiddles.
-template <typename T, int N>
+template <typename T, typename R>
 constexpr size_t rt_lds()
 {
-    return ((RegTile<N>::LTW ? N : 0) + RegTile<N>::ELEMS) * sizeof(cx<T>);
+    return ((R::LTW ? R::N : 0) + R::ELEMS) * sizeof(cx<T>);
 }
 
-template <int N>
+template <typename R>
 __device__ __forceinline__ constexpr int rt_row(int row)
 {
-    return (row + (row >> 3)) * RegTile<N>::NSEQ;
+    return (row + (row >> 3)) * R::NSEQ;
 }
 
 template <typename T>
@@ -659,47 +659,46 @@ __device__ __forceinline__ void rt_put(cx<T> *p, cx<T> v)
 }
 
 // Thread -> (j, s), and the paired form.
-template <int N>
+template <typename R>
 __device__ __forceinline__ void rt_plain(int tid, int &j, int &s)
 {
-    j = tid >> RegTile<N>::LGS;
-    s = tid & (RegTile<N>::NSEQ - 1);
+    j = tid >> R::LGS;
+    s = tid & (R::NSEQ - 1);
 }
 
-template <int N>
+template <typename R>
 __device__ __forceinline__ void rt_paired(int tid, int &j, int &s)
 {
-    using R = RegTile<N>;
     const int u = tid >> R::LGS, m = u >> 1, odd = u & 1, l = tid & (R::NSEQ - 1);
     j = odd ? (m ? R::P - m : R::P / 2) : m;
     s = odd ? R::NSEQ - 1 - l : l;
 }
 
-template <int N>
+template <typename R>
 __device__ __forceinline__ float rt_mirror(float v)
 {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), RegTile<N>::MIRROR, 0xF, 0xF, true));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), R::MIRROR, 0xF, 0xF, true));
 }
 
-template <int N>
+template <typename R>
 __device__ __forceinline__ double rt_mirror(double v)
 {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), RegTile<N>::MIRROR, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), RegTile<N>::MIRROR, 0xF, 0xF, true);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), R::MIRROR, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), R::MIRROR, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
 
 // Rows N - k of the rows k = j + r N/8, r < 4, of a paired thread, from the rows
 // a[0..7] of its own and its mirror thread (k = 0: itself).
-template <typename T, int N>
+template <typename T, typename R>
 __device__ __forceinline__ void rt_reflect(const cx<T> (&a)[8], int j, cx<T> (&b)[4])
 {
     // (selects on values: a branch would make the compiler address the arrays)
-    const bool z = j == 0, h = j == RegTile<N>::P / 2;
+    const bool z = j == 0, h = j == R::P / 2;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const cx<T> t0 = a[(8 - r) & 7], t1 = a[7 - r];
-        const cx<T> m = {rt_mirror<N>(t1.x), rt_mirror<N>(t1.y)};
+        const cx<T> m = {rt_mirror<R>(t1.x), rt_mirror<R>(t1.y)};
         b[r].x = z ? t0.x : h ? t1.x : m.x;
         b[r].y = z ? t0.y : h ? t1.y : m.y;
     }
@@ -708,14 +707,14 @@ __device__ __forceinline__ void rt_reflect(const cx<T> (&a)[8], int j, cx<T> (&b
 // The inverse: rows j + r N/8, r = 4..7, of an odd sequence (row N - k the negative
 // of row k, rows 0 and N/2 zero) from its rows k = j + r N/8, r < 4, in a[0..3] of
 // the thread and its mirror.
-template <typename T, int N>
+template <typename T, typename R>
 __device__ __forceinline__ void rt_unfold_odd(cx<T> (&a)[8], int j)
 {
-    const bool z = j == 0, h = j == RegTile<N>::P / 2;
+    const bool z = j == 0, h = j == R::P / 2;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const cx<T> t1 = a[r];
-        const cx<T> m = {rt_mirror<N>(t1.x), rt_mirror<N>(t1.y)};
+        const cx<T> m = {rt_mirror<R>(t1.x), rt_mirror<R>(t1.y)};
         // row j + (7 - r) N/8; of j = 0: row (4 + (3 - r)) N/8, the mirror of row (r + 1) N/8
         const cx<T> t8 = r < 3 ? a[r + 1] : cx<T>{(T)0, (T)0};
         a[7 - r].x = -(z ? t8.x : h ? t1.x : m.x);
@@ -724,65 +723,65 @@ __device__ __forceinline__ void rt_unfold_odd(cx<T> (&a)[8], int j)
 }
 
 // First stage (radix 8): rows j + r N/8 in a, written to the tile.
-template <typename T, int N, bool INV>
+template <typename T, typename R, bool INV>
 __device__ __forceinline__ void rt_first(cx<T> *buf, cx<T> (&a)[8], int j, int s)
 {
     rt_pin(a);
-    dft_small<T, 8, INV>(a, nullptr, N);
-    cx<T> *p = buf + 9 * j * RegTile<N>::NSEQ + s;
+    dft_small<T, 8, INV>(a, nullptr, R::N);
+    cx<T> *p = buf + 9 * j * R::NSEQ + s;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) rt_put(p + r * RegTile<N>::NSEQ, a[r]);
+    for (int r = 0; r < 8; ++r) rt_put(p + r * R::NSEQ, a[r]);
     __syncthreads();
 }
 
 // As rt_first for rows N/2.. that are zero (a[0..3] given).
-template <typename T, int N>
+template <typename T, typename R>
 __device__ __forceinline__ void rt_first_zpad(cx<T> *buf, cx<T> (&a)[8], int j, int s)
 {
     dft8_lower<T, false>(a);
-    cx<T> *p = buf + 9 * j * RegTile<N>::NSEQ + s;
+    cx<T> *p = buf + 9 * j * R::NSEQ + s;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) rt_put(p + r * RegTile<N>::NSEQ, a[r]);
+    for (int r = 0; r < 8; ++r) rt_put(p + r * R::NSEQ, a[r]);
     __syncthreads();
 }
 
-template <typename T, int N>
+template <typename T, typename R>
 __device__ __forceinline__ void rt_rows(const cx<T> *buf, cx<T> (&a)[8], int j, int s)
 {
-    const cx<T> *p = buf + rt_row<N>(j) + s;
+    const cx<T> *p = buf + rt_row<R>(j) + s;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) a[r] = rt_get(p + r * rt_row<N>(RegTile<N>::P));
+    for (int r = 0; r < 8; ++r) a[r] = rt_get(p + r * rt_row<R>(R::P));
 }
 
 // One radix-8 stage in LDS after product NS of earlier radices.
-template <typename T, int N, int NS, bool INV>
+template <typename T, typename R, int NS, bool INV>
 __device__ __forceinline__ void rt_stage(cx<T> *buf, const cx<T> *tw, int tid)
 {
     int j, s;
-    rt_plain<N>(tid, j, s);
+    rt_plain<R>(tid, j, s);
     cx<T> a[8];
-    rt_rows<T, N>(buf, a, j, s);
+    rt_rows<T, R>(buf, a, j, s);
     const int jm = j & (NS - 1);
     if (jm != 0) {
-        const int e = jm * (N / (NS * 8));
+        const int e = jm * (R::N / (NS * 8));
 #pragma unroll
         for (int r = 1; r < 8; ++r) a[r] = cmul(a[r], twid<T, INV>(tw, e * r));
     }
-    dft_small<T, 8, INV>(a, tw, N);
+    dft_small<T, 8, INV>(a, tw, R::N);
     __syncthreads();
-    cx<T> *p = buf + rt_row<N>((j - jm) * 8 + jm) + s;
+    cx<T> *p = buf + rt_row<R>((j - jm) * 8 + jm) + s;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) rt_put(p + r * rt_row<N>(NS), a[r]);
+    for (int r = 0; r < 8; ++r) rt_put(p + r * rt_row<R>(NS), a[r]);
     __syncthreads();
 }
 
 // The stages between the first and the last.
-template <typename T, int N, bool INV>
+template <typename T, typename R, bool INV>
 __device__ __forceinline__ void rt_middle(cx<T> *buf, const cx<T> *tw, int tid)
 {
-    rt_stage<T, N, 8, INV>(buf, tw, tid);
-    if constexpr (N >= 1024) rt_stage<T, N, 64, INV>(buf, tw, tid);
-    if constexpr (N >= 8192) rt_stage<T, N, 512, INV>(buf, tw, tid);
+    rt_stage<T, R, 8, INV>(buf, tw, tid);
+    if constexpr (R::N >= 1024) rt_stage<T, R, 64, INV>(buf, tw, tid);
+    if constexpr (R::N >= 8192) rt_stage<T, R, 512, INV>(buf, tw, tid);
 }
 
 // Values as they come back from memory: keeps the compiler from contracting an
@@ -797,24 +796,24 @@ __device__ __forceinline__ void rt_pin(cx<T> (&a)[K])
 
 // The last stage (radix 4, 8 or 2 for N = 256, 512, 1024, and so on): rows j + r N/8 of the
 // result in a. No barrier.
-template <typename T, int N, bool INV>
+template <typename T, typename R, bool INV>
 __device__ __forceinline__ void rt_last(const cx<T> *buf, const cx<T> *tw, cx<T> (&a)[8], int j, int s)
 {
-    constexpr int R = CtLast<N>::R, NB = 8 / R; // NB butterflies of radix R
-    rt_rows<T, N>(buf, a, j, s);
+    constexpr int RX = CtLast<R::N>::R, NB = 8 / RX; // NB butterflies of radix RX
+    rt_rows<T, R>(buf, a, j, s);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        const int e = j + i * RegTile<N>::P;
-        cx<T> v[R];
+        const int e = j + i * R::P;
+        cx<T> v[RX];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = a[i + NB * r];
+        for (int r = 0; r < RX; ++r) v[r] = a[i + NB * r];
         if (e != 0) {
 #pragma unroll
-            for (int r = 1; r < R; ++r) v[r] = cmul(v[r], twid<T, INV>(tw, e * r));
+            for (int r = 1; r < RX; ++r) v[r] = cmul(v[r], twid<T, INV>(tw, e * r));
         }
-        dft_small<T, R, INV>(v, tw, N);
+        dft_small<T, RX, INV>(v, tw, R::N);
 #pragma unroll
-        for (int r = 0; r < R; ++r) a[i + NB * r] = v[r];
+        for (int r = 0; r < RX; ++r) a[i + NB * r] = v[r];
     }
     rt_pin(a);
 }
@@ -822,11 +821,11 @@ __device__ __forceinline__ void rt_last(const cx<T> *buf, const cx<T> *tw, cx<T>
 // Cosine and sine parts of a zero-padded forward transform (rows a of a paired
 // thread): C and S of rows k = j + r N/8, r < 4, of both columns; S of k = 0 is
 // C_{N/2}, as in the slot layout.
-template <typename T, int N>
+template <typename T, typename R>
 __device__ __forceinline__ void rt_slots(const cx<T> (&a)[8], int j, cx<T> (&C)[4], cx<T> (&S)[4])
 {
     cx<T> b[4];
-    rt_reflect<T, N>(a, j, b);
+    rt_reflect<T, R>(a, j, b);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         C[r] = cx<T>{(T)0.5 * (a[r].x + b[r].x), (T)0.5 * (a[r].y + b[r].y)};
@@ -848,11 +847,11 @@ struct __attribute__((packed, aligned(sizeof(T)))) pair_t {
 // src[row*rsd + col], with col0, col1 the offsets of the two columns (negative:
 // zero). dir = 1 or -1: col1 = col0 + dir for every thread of the block, read
 // together (two single loads cost two passes over the same cache lines).
-template <typename TI, int N>
+template <typename TI, typename R>
 __device__ __forceinline__ void rt_fetch(TI (&x)[8], const TI *src, int64_t rsd, int col0, int col1, int dir, int j,
                                          int row0)
 {
-    const int step = __mul24(RegTile<N>::P, (int)rsd);
+    const int step = __mul24(R::P, (int)rsd);
     int o = __mul24(j - row0, (int)rsd);
     const bool first = j >= row0;
     if (dir != 0) {

@@ -48,6 +48,7 @@ struct CcArgs {
     int Mo;            // M of that axis (slot -> wavenumber), 0 if none
     int cols_per_chunk; // first-half columns per chunk (a tile pairs column c with ncols-1-c)
     int interleave;     // chunk ch takes tiles ch, ch + nchunk, ... instead of a contiguous run
+    int pairs;          // (interleave) W spans the tiles of two neighbouring chunks
     const double *K;   // K[d][k_o][k_p], k_p contiguous (FP64 in every mode)
     int64_t Kd, Ko;
     double *part;      // FP64 chunk partials [2][nchunk][nbatch][2 M_p]

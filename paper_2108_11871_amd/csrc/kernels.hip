@@ -1281,11 +1281,10 @@ __device__ __forceinline__ double quad_get(double v)
 // the spectral combination works on the registers between the last forward and
 // the first inverse stage (see RegTile): thread (j, s) combines rows k = j + r N/8,
 // r < 4, of its two columns; its inverse inputs are these and its mirror's.
-template <typename T, int N>
-__global__ __launch_bounds__(RegTile<N>::NTH) void k_final_rt(FinalArgs a, int ntiles)
+template <typename T, typename R>
+__global__ __launch_bounds__(R::NTH) void k_final_rt(FinalArgs a, int ntiles)
 {
-    using R = RegTile<N>;
-    constexpr int M = N / 2, W = R::W, SV = 12, P = R::P, NL = R::NSEQ < 4 ? R::NSEQ : 4;
+    constexpr int N = R::N, M = N / 2, W = R::W, SV = 12, P = R::P, NL = R::NSEQ < 4 ? R::NSEQ : 4;
     extern __shared__ __align__(16) unsigned char smem[];
     const cx<T> *tw = tw_table<T, !R::LTW>(smem, a.tw, a.twf);
     cx<T> *buf = reinterpret_cast<cx<T> *>(smem) + (R::LTW ? N : 0);
@@ -1306,27 +1305,27 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_final_rt(FinalArgs a, int n
     T x[8];
     auto load = [&]() {
         const int cc = 2 * s;
-        rt_fetch<T, N>(x, g, a.irs, cc < nc ? cc * (int)a.ics : -1, cc + 1 < nc ? (cc + 1) * (int)a.ics : -1,
+        rt_fetch<T, R>(x, g, a.irs, cc < nc ? cc * (int)a.ics : -1, cc + 1 < nc ? (cc + 1) * (int)a.ics : -1,
                        nc == W && a.ics == 1, j, 1);
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = cx<T>{x[2 * r], x[2 * r + 1]};
     };
     if (!a.pre) {
-        rt_plain<N>(tid, j, s);
+        rt_plain<R>(tid, j, s);
         load();
-        rt_first_zpad<T, N>(buf, v, j, s);
-        rt_middle<T, N, false>(buf, tw, tid);
-        rt_paired<N>(tid, j, s);
-        rt_last<T, N, false>(buf, tw, v, j, s);
+        rt_first_zpad<T, R>(buf, v, j, s);
+        rt_middle<T, R, false>(buf, tw, tid);
+        rt_paired<R>(tid, j, s);
+        rt_last<T, R, false>(buf, tw, v, j, s);
     } else {
         // B holds the spectrum
-        rt_paired<N>(tid, j, s);
+        rt_paired<R>(tid, j, s);
         load();
     }
     {
         cx<T> z2[4];
         if (!a.pre) {
-            rt_reflect<T, N>(v, j, z2);
+            rt_reflect<T, R>(v, j, z2);
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)0.5 * (z2[r].y - v[r].y), (T)0.5 * (v[r].x - z2[r].x)};
         }
@@ -1371,12 +1370,12 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_final_rt(FinalArgs a, int n
     // hermitian input: z(k) = (c_b, -c_a), z(N - k) = (-c_b, c_a), rows 0 and M zero
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] = cx<T>{cab[r].y, -cab[r].x};
-    rt_unfold_odd<T, N>(v, j);
+    rt_unfold_odd<T, R>(v, j);
     __syncthreads(); // every wave has read the forward transform
-    rt_first<T, N, true>(buf, v, j, s);
-    rt_middle<T, N, true>(buf, tw, tid);
-    rt_plain<N>(tid, j, s);
-    rt_last<T, N, true>(buf, tw, v, j, s);
+    rt_first<T, R, true>(buf, v, j, s);
+    rt_middle<T, R, true>(buf, tw, tid);
+    rt_plain<R>(tid, j, s);
+    rt_last<T, R, true>(buf, tw, v, j, s);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int t = j + r * P;
@@ -1405,13 +1404,12 @@ static void launch_final_w(const FinalArgs &a, int nblk, size_t lds, hipStream_t
     hipLaunchKernelGGL((k_final<T, MAXE, KD, WC, NTT>), dim3(grid), dim3(NTT), lds, st, a, nblk);
 }
 
-template <typename T, int N>
+template <typename T, typename R>
 static void launch_final_rt(const FinalArgs &a, int nblk, hipStream_t st)
 {
-    using R = RegTile<N>;
-    const size_t lds = rt_lds<T, N>() + (size_t)R::W * 12 * sizeof(T);
-    set_lds((const void *)&k_final_rt<T, N>, lds);
-    hipLaunchKernelGGL((k_final_rt<T, N>), dim3(nblk), dim3(R::NTH), lds, st, a, nblk);
+    const size_t lds = rt_lds<T, R>() + (size_t)R::W * 12 * sizeof(T);
+    set_lds((const void *)&k_final_rt<T, R>, lds);
+    hipLaunchKernelGGL((k_final_rt<T, R>), dim3(nblk), dim3(R::NTH), lds, st, a, nblk);
 }
 
 template <typename T, int MAXE, int KD>
@@ -1438,7 +1436,7 @@ static void launch_final_t(const FinalArgs &a, int nblk, int work, hipStream_t s
 {
     // full tiles of the power-of-two lengths (narrowed tiles of small grids keep the
     // generic stages)
-    if (rt_length(a.fd.N, a.W, [&](auto n) { launch_final_rt<T, decltype(n)::value>(a, nblk, st); })) return;
+    if (rt_tile<0>(a.fd.N, a.W, [&](auto tile) { launch_final_rt<T, decltype(tile)>(a, nblk, st); })) return;
     if (big_fft(a.fd.N)) {
         // tile + staged columns only (the rows come from the global table)
         const size_t lds = tile_lds<T>(a.fd.N, a.W) + 16 + (size_t)a.W * 12 * sizeof(T);
@@ -1496,7 +1494,7 @@ hipError_t launch_final(const FinalArgs &a, hipStream_t st)
     if (!a.rowtab) return hipErrorInvalidValue; // the row invariants are read from it
     if (big_fft(a.fd.N) && (a.geo.d != 2 || a.W != 2 || work > 8 * NTB))
         return hipErrorInvalidValue;
-    if (!big_fft(a.fd.N) && work > 8 * NT) return hipErrorInvalidValue; // (the tile budget of the pass)
+    if (!big_fft(a.fd.N) && work > 8 * NT) return hipErrorInvalidValue;
     if (!tile_strides_ok(a.nrows_in, a.irs, a.ncols, a.ics)) return hipErrorInvalidValue;
     if (a.mixed)
         launch_final_t<float>(a, nblk, work, st);

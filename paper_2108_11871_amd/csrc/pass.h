@@ -209,11 +209,10 @@ __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
 // the latency and the partial cache lines of its strided rows: 257^3 rho_y FP64
 // 123 -> 93 us, inv_y 97 -> 66 us, inv_z 98 -> 60 us (4.4 TB/s), FP32 rho_z 103 ->
 // 102, rho_y 94 -> 83, inv_y 50 -> 35, inv_z 53 -> 46 us.
-template <typename T, typename TI, typename TO, int N, int MODE>
-__global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int ntiles)
+template <typename T, typename TI, typename TO, typename R, int MODE>
+__global__ __launch_bounds__(R::NTH) void k_pass_rt(PassArgs a, int ntiles)
 {
-    using R = RegTile<N>;
-    constexpr int M = N / 2, W = R::W, P = R::P, NV = MODE == IN_HERM ? 16 : 8;
+    constexpr int N = R::N, M = N / 2, W = R::W, P = R::P, NV = MODE == IN_HERM ? 16 : 8;
     extern __shared__ __align__(16) unsigned char smem[];
     const cx<T> *tw = tw_table<T, !R::LTW>(smem, a.tw, a.twf);
     cx<T> *buf = reinterpret_cast<cx<T> *>(smem) + (R::LTW ? N : 0);
@@ -225,9 +224,9 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int nti
     const TI *in = static_cast<const TI *>(a.in) + bt * a.ibs + c0 * a.ics;
     TO *out = static_cast<TO *>(a.out) + bt * a.obs + c0 * a.ocs;
     if constexpr (MODE == IN_ZPAD)
-        rt_plain<N>(tid, j, s);
+        rt_plain<R>(tid, j, s);
     else
-        rt_paired<N>(tid, j, s);
+        rt_paired<R>(tid, j, s);
     TI x[NV];
     {
         const int c = 2 * s, ics = (int)a.ics;
@@ -235,15 +234,15 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int nti
         if constexpr (MODE == IN_HERM) {
             // cosine rows k and sine rows M + k (row M of k = 0: the last cosine row)
             TI y[8], z[8];
-            rt_fetch<TI, N>(y, in, a.irs, o0, o1, dir, j, 0);
-            rt_fetch<TI, N>(z, in + M * a.irs, a.irs, o0, o1, dir, j, 0);
+            rt_fetch<TI, R>(y, in, a.irs, o0, o1, dir, j, 0);
+            rt_fetch<TI, R>(z, in + M * a.irs, a.irs, o0, o1, dir, j, 0);
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 x[r] = y[r];
                 x[8 + r] = z[r];
             }
         } else {
-            rt_fetch<TI, N>(x, in, a.irs, o0, o1, dir, j, 1);
+            rt_fetch<TI, R>(x, in, a.irs, o0, o1, dir, j, 1);
         }
     }
     if constexpr (R::LTW) load_twiddles<T, R::NTH>(reinterpret_cast<cx<T> *>(smem), a.tw, N);
@@ -254,7 +253,7 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int nti
     } else if constexpr (MODE == IN_SPECS) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)x[2 * r + 1], -(T)x[2 * r]};
-        rt_unfold_odd<T, N>(v, j);
+        rt_unfold_odd<T, R>(v, j);
     } else {
         const bool z0 = j == 0, h = j == P / 2;
         cx<T> up[4], cm;
@@ -274,21 +273,21 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int nti
         for (int r = 0; r < 4; ++r) {
             // rows j + (7 - r) N/8: the mirror's N - k; of j = 0 the thread's own
             const cx<T> own = r < 3 ? up[r + 1] : cm;
-            const cx<T> m = {rt_mirror<N>(up[r].x), rt_mirror<N>(up[r].y)};
+            const cx<T> m = {rt_mirror<R>(up[r].x), rt_mirror<R>(up[r].y)};
             v[7 - r].x = z0 ? own.x : h ? up[r].x : m.x;
             v[7 - r].y = z0 ? own.y : h ? up[r].y : m.y;
         }
     }
     if constexpr (MODE == IN_ZPAD)
-        rt_first_zpad<T, N>(buf, v, j, s);
+        rt_first_zpad<T, R>(buf, v, j, s);
     else
-        rt_first<T, N, true>(buf, v, j, s);
-    rt_middle<T, N, MODE != IN_ZPAD>(buf, tw, tid);
+        rt_first<T, R, true>(buf, v, j, s);
+    rt_middle<T, R, MODE != IN_ZPAD>(buf, tw, tid);
     if constexpr (MODE == IN_ZPAD)
-        rt_paired<N>(tid, j, s);
+        rt_paired<R>(tid, j, s);
     else
-        rt_plain<N>(tid, j, s);
-    rt_last<T, N, MODE != IN_ZPAD>(buf, tw, v, j, s);
+        rt_plain<R>(tid, j, s);
+    rt_last<T, R, MODE != IN_ZPAD>(buf, tw, v, j, s);
     const T scale = (T)a.scale;
     const int c = 2 * s, ocs = (int)a.ocs, ors = (int)a.ors;
     auto put = [&](int row, cx<T> w) {
@@ -307,7 +306,7 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int nti
     };
     if constexpr (MODE == IN_ZPAD) {
         cx<T> C[4], S[4];
-        rt_slots<T, N>(v, j, C, S);
+        rt_slots<T, R>(v, j, C, S);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             put(j + r * P, C[r]);
@@ -321,14 +320,13 @@ __global__ __launch_bounds__(RegTile<N>::NTH) void k_pass_rt(PassArgs a, int nti
     }
 }
 
-template <typename T, typename TI, typename TO, int N, int MODE>
+template <typename T, typename TI, typename TO, typename R, int MODE>
 static void launch_pass_rt_m(const PassArgs &a, int ntiles, hipStream_t st)
 {
-    using R = RegTile<N>;
-    const void *fn = (const void *)&k_pass_rt<T, TI, TO, N, MODE>;
-    const size_t lds = rt_lds<T, N>();
+    const void *fn = (const void *)&k_pass_rt<T, TI, TO, R, MODE>;
+    const size_t lds = rt_lds<T, R>();
     set_lds(fn, lds);
-    hipLaunchKernelGGL((k_pass_rt<T, TI, TO, N, MODE>), dim3((unsigned)ntiles), dim3(R::NTH), lds, st, a, ntiles);
+    hipLaunchKernelGGL((k_pass_rt<T, TI, TO, R, MODE>), dim3((unsigned)ntiles), dim3(R::NTH), lds, st, a, ntiles);
 }
 
 // Full register tiles of the modes k_pass_rt takes; whether the pass is one.
@@ -341,14 +339,14 @@ static bool launch_pass_rt(const PassArgs &a, int ntiles, hipStream_t st)
         return false;
     // synthesis keeps rows 0..M
     if (mode != IN_ZPAD && a.out_r0 + a.out_nrows > M + 1) return false;
-    return rt_length(a.fd.N, a.W, [&](auto n) {
-        constexpr int N = decltype(n)::value;
+    return rt_tile<512 | 1024>(a.fd.N, a.W, [&](auto tile) {
+        using R = decltype(tile);
         if (mode == IN_ZPAD)
-            launch_pass_rt_m<T, TI, TO, N, IN_ZPAD>(a, ntiles, st);
+            launch_pass_rt_m<T, TI, TO, R, IN_ZPAD>(a, ntiles, st);
         else if (mode == IN_SPECS)
-            launch_pass_rt_m<T, TI, TO, N, IN_SPECS>(a, ntiles, st);
+            launch_pass_rt_m<T, TI, TO, R, IN_SPECS>(a, ntiles, st);
         else
-            launch_pass_rt_m<T, TI, TO, N, IN_HERM>(a, ntiles, st);
+            launch_pass_rt_m<T, TI, TO, R, IN_HERM>(a, ntiles, st);
     });
 }
 

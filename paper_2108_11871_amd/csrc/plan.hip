@@ -455,14 +455,35 @@ int run_pass(ips_plan p, PassArgs a, const FftDesc &fd, const cx<double> *tw, bo
     return IPS_OK;
 }
 
-// Tile width of the forward slot passes of rho: with FP32 tiles and
-// transforms of 1024 points (513^3), twice the plan's budget, whose 8-column
-// tiles read 64-byte runs of the strided rho rows (rho_y 1.43 -> 1.13 ms at
-// 513^3; at 2M = 512 the default measured faster).  0 keeps the plan's default.
-int rho_pass_width(ips_plan p, int N, int ncols, bool f32)
+// Tile width of the passes between a contiguous and a strided side (rho along z and
+// y, the adjoint's last one), 0 for the plan's default: double-width register tiles
+// at 2M = 512 and 1024, whose rows of 16 and 8 columns reach more of the strided
+// lines at once, where enough blocks are left. rho_z and rho_y together, default ->
+// double: 257^3 FP64 1305 -> 1270 us of the solve, mixed FP32 902 -> 884; 513^3 mixed
+// FP32 7559 -> 7247, FP64 10766 -> 10670; the adjoint's pass at 2M = 512 3888 -> 3842
+// (at 1024 0.5 ms slower, so not there). inv_y, inv_z and the final pass gain nothing.
+// FP32 tiles of the lengths from 1024 on without register tiles take twice the plan's
+// budget.
+int wide_width(ips_plan p, int N, int ncols, int nbatch, bool f32)
 {
-    if (!f32 || N < 1024 || N > kLdsMaxN || 2 * p->work > 4096) return 0;
+    if (N == 512 || N == 1024) {
+        const int W = tile_width(N, 4096, ncols);
+        if (p->work == 2048 && W * N == 8192 && (int64_t)nbatch * (ncols / W) >= 4 * kFillPass) return W;
+        return 0;
+    }
+    if (!f32 || N < 1024 || N > kLdsMaxN || 2 * p->work > 4096 || (N & (N - 1)) == 0) return 0;
     return tile_width(N, 2 * p->work, ncols);
+}
+
+// Width of an interleaved contraction: FP32 tiles at 2M = 1024 take two neighbouring
+// chunks at once, for rows of 2 x 4 columns of the strided input (513^3 mixed: 7250
+// -> 6640 us of the solve; FP64 10660 -> 12260, so not there, and at 2M = 512, whose
+// rows are as long with single chunks, 3% slower).
+void pair_chunks(ips_plan p, CcArgs &a, int fam, bool f32)
+{
+    a.W = p->ccW[fam];
+    a.pairs = f32 && a.fd.N == 1024 && a.W == RegTile<1024>::W && (int64_t)p->nch[fam] * a.nbatch >= 2 * kFillConv;
+    if (a.pairs) a.W *= 2;
 }
 
 // Independent passes (prepared) in one launch when their transforms fit the
@@ -1357,7 +1378,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.out_r0 = 0;
             a.out_nrows = N[2];
             a.scale = 1.0;
-            a.W = rho_pass_width(p, N[2], a.ncols, f32s);
+            a.W = wide_width(p, N[2], a.ncols, a.nbatch, f32s);
             if ((rc = run_pass(p, a, p->fd[2], p->tw[2], false, f32s, st))) return rc;
         }
         {
@@ -1408,10 +1429,10 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.Ko = M[0] + 1;
             a.part = p->part[1];
             a.Bout = nullptr;
-            a.W = p->ccW[1];
             a.fd = p->fd[0];
             a.tw = p->tw[0];
             a.twf = p->twf[0];
+            pair_chunks(p, a, 1, f32s);
             IPS_HIP(launch_cc(a, p->nch[1], f32s, f32s, st));
         }
         {
@@ -1433,7 +1454,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.out_r0 = 0;
             a.out_nrows = N[1];
             a.scale = 1.0;
-            a.W = rho_pass_width(p, N[1], a.ncols, f32s);
+            a.W = wide_width(p, N[1], a.ncols, a.nbatch, f32s);
             if ((rc = run_pass(p, a, p->fd[1], p->tw[1], false, f32s, st))) return rc;
         }
         {
@@ -1455,10 +1476,10 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.Ko = M[0] + 1;
             a.part = p->part[2];
             a.Bout = nullptr;
-            a.W = p->ccW[2];
             a.fd = p->fd[0];
             a.tw = p->tw[0];
             a.twf = p->twf[0];
+            pair_chunks(p, a, 2, f32s);
             IPS_HIP(launch_cc(a, p->nch[2], f32s, f32s, st));
         }
         STAGE(IPS_STAGE_FACES);
@@ -2070,6 +2091,7 @@ int execute_adjoint(ips_plan p, const double *w, double *out, hipStream_t st)
             z.ncols = I[c];
             z.nbatch = I[fam];
             z.in_mode = IN_HERM;
+            z.W = N[b] == 512 ? wide_width(p, N[b], z.ncols, z.nbatch, false) : 0;
             z.out_r0 = 1;
             z.out_nrows = I[b];
             z.scale = vh / N[b];
