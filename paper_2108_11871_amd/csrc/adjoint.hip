@@ -62,36 +62,48 @@ __device__ __forceinline__ void mode_symbols(const AdjArgs &a, const int *k, dou
 
 // X holds raw sine coefficients over the interior modes ([k0][k1][k2], last
 // fastest).  Y (if given) <- -pref X / q  (the phi_star map);  X <- pref X / Lambda.
+// A wave per 256 elements of a row of the last axis: contiguous, no index divisions
+// per element, four loads in flight (257^3, 267 MB: 89 -> 73 us; a position of the last
+// axes per thread, walking along the first: 92).
 template <int D>
 __global__ __launch_bounds__(NTA) void k_adj_spec(AdjArgs a, double *X, double *Y)
 {
+    constexpr int U = 4;
     const Geo &g = a.geo;
-    int64_t tot = 1;
-    for (int x = 0; x < D; ++x) tot *= g.M[x] - 1;
-    for (int64_t e = blockIdx.x * (int64_t)NTA + threadIdx.x; e < tot; e += (int64_t)gridDim.x * NTA) {
-        int k[3];
-        int64_t r = e;
+    const int I1 = g.M[D - 2] - 1, n = g.M[D - 1] - 1, lane = threadIdx.x & 63;
+    const uint32_t row = __builtin_amdgcn_readfirstlane(blockIdx.x * (NTA / 64) + (threadIdx.x >> 6));
+    int k[3] = {1 + (int)row, 0, 0};
+    if (D == 3) {
+        k[0] = 1 + (int)(row / (uint32_t)I1);
+        k[1] = 1 + (int)(row % (uint32_t)I1);
+    }
+    if (k[0] >= g.M[0]) return;
+    double *Xr = X + (int64_t)row * n, *Yr = Y ? Y + (int64_t)row * n : nullptr;
+    const int i = blockIdx.y * 64 * U + lane;
+    double v[U];
 #pragma unroll
-        for (int x = D - 1; x >= 0; --x) {
-            const int I = g.M[x] - 1;
-            k[x] = 1 + (int)(r % I);
-            r /= I;
-        }
+    for (int u = 0; u < U; ++u) v[u] = Xr[min(i + 64 * u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int c = i + 64 * u;
+        if (c >= n) break;
         double L, q;
+        k[D - 1] = 1 + c;
         mode_symbols<D>(a, k, L, q);
-        const double v = X[e];
-        if (Y) Y[e] = -g.pref * v / q;
-        X[e] = g.pref * v / L;
+        if (Yr) Yr[c] = -g.pref * v[u] / q;
+        Xr[c] = g.pref * v[u] / L;
     }
 }
 
 hipError_t launch_adj_spec(const AdjArgs &a, double *X, double *Y, hipStream_t st)
 {
-    const int nb = 4096;
+    int64_t rows = 1;
+    for (int x = 0; x + 1 < a.geo.d; ++x) rows *= a.geo.M[x] - 1;
+    const dim3 grid((unsigned)((rows + NTA / 64 - 1) / (NTA / 64)), (unsigned)((a.geo.M[a.geo.d - 1] + 254) / 256));
     if (a.geo.d == 3)
-        hipLaunchKernelGGL(k_adj_spec<3>, dim3(nb), dim3(NTA), 0, st, a, X, Y);
+        hipLaunchKernelGGL(k_adj_spec<3>, grid, dim3(NTA), 0, st, a, X, Y);
     else
-        hipLaunchKernelGGL(k_adj_spec<2>, dim3(nb), dim3(NTA), 0, st, a, X, Y);
+        hipLaunchKernelGGL(k_adj_spec<2>, grid, dim3(NTA), 0, st, a, X, Y);
     return hipGetLastError();
 }
 
@@ -711,9 +723,12 @@ __global__ __launch_bounds__(NTA) void k_adj_tpack(AdjArgs a, AdjShell s)
 
 // One position of the axes after the first per thread (neighbours side by side), a
 // range of k0 per block row: the family-0 values of the position stay in registers.
+// Bound by the ten loads of the other families' values per element, two elements' at
+// once in flight (257^3: 159 -> 148 us).
 template <int D>
 __global__ __launch_bounds__(NTA) void k_adj_x(AdjArgs a, AdjShell s, double *X)
 {
+    constexpr int U = 2;
     const Geo &g = a.geo;
     const int I0 = g.M[0] - 1, I1 = g.M[1] - 1, I2 = D == 3 ? g.M[2] - 1 : 1;
     const int64_t np = (int64_t)I1 * I2, p = blockIdx.x * (int64_t)NTA + threadIdx.x;
@@ -740,20 +755,35 @@ __global__ __launch_bounds__(NTA) void k_adj_x(AdjArgs a, AdjShell s, double *X)
         B1 += g.c4[2][0] * l2 * l2;
         B2 += g.c4[0][2] * l2;
     }
-    for (int i0 = k0; i0 < k1; ++i0) {
-        const bool odd = (i0 & 1) == 0;
-        double V = 0.0;
+    for (int i0 = k0; i0 < k1; i0 += U) {
+        double x[U], t1[U][5], t2[U][5];
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            V = fma(a.tab[0].s[j * I0 + i0], odd ? T0[1][j] : T0[0][j], V);
-            V = fma(s1[j], T1[j * n1 + (int64_t)i0 * I2], V);
-            if (D == 3) V = fma(s2[j], T2[j * n2 + (int64_t)i0 * I1], V);
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = min(i0 + u, k1 - 1);
+            x[u] = X[i * np + p];
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                t1[u][j] = T1[j * n1 + i * I2];
+                t2[u][j] = D == 3 ? T2[j * n2 + i * I1] : 0.0;
+            }
         }
-        const double l0 = a.tab[0].lam[i0];
-        const double L = fma(A1, l0, A0), R = fma(fma(B2, l0, B1), l0, B0);
-        const double q = R / L;
-        const int64_t e = i0 * np + p;
-        X[e] = fma(X[e], q, X[e]) + g.pref * q * V;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u;
+            if (i >= k1) break;
+            const bool odd = (i & 1) == 0;
+            double V = 0.0;
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                V = fma(a.tab[0].s[j * I0 + i], odd ? T0[1][j] : T0[0][j], V);
+                V = fma(s1[j], t1[u][j], V);
+                if (D == 3) V = fma(s2[j], t2[u][j], V);
+            }
+            const double l0 = a.tab[0].lam[i];
+            const double L = fma(A1, l0, A0), R = fma(fma(B2, l0, B1), l0, B0);
+            const double q = R / L;
+            X[i * np + p] = fma(x[u], q, x[u]) + g.pref * q * V;
+        }
     }
 }
 
@@ -879,42 +909,50 @@ hipError_t launch_adj_lambda_shell(const AdjArgs &a, const AdjShell &s, const do
     return hipGetLastError();
 }
 
-// Zero the boundary nodes of a grid-shaped array.
+// Zero the boundary nodes of a grid-shaped array, a wave per row of the last axis:
+// whole rows on the faces of the others, else the two ends (257^3: 33 us for a walk
+// over all nodes -> 10).
 template <int D>
-__global__ __launch_bounds__(NTA) void k_zero_boundary(AdjArgs a, double *out)
+__global__ __launch_bounds__(NTA) void k_zero_boundary(AdjArgs a, double *out, int64_t rows)
 {
-    int64_t tot = 1;
-    for (int x = 0; x < D; ++x) tot *= a.n[x];
-    for (int64_t e = blockIdx.x * (int64_t)NTA + threadIdx.x; e < tot; e += (int64_t)gridDim.x * NTA) {
-        int64_t r = e;
-        bool bnd = false;
+    const int lane = threadIdx.x & 63, n = (int)a.n[D - 1];
+    const int64_t row = blockIdx.x * (int64_t)(NTA / 64) + (threadIdx.x >> 6);
+    if (row >= rows) return;
+    int64_t r = row;
+    bool face = false;
 #pragma unroll
-        for (int x = D - 1; x >= 0; --x) {
-            const int ix = (int)(r % a.n[x]);
-            r /= a.n[x];
-            bnd = bnd || ix == 0 || ix == a.geo.M[x];
-        }
-        if (bnd) out[e] = 0.0;
+    for (int x = D - 2; x >= 0; --x) {
+        const int ix = (int)(r % a.n[x]);
+        r /= a.n[x];
+        face = face || ix == 0 || ix == a.geo.M[x];
+    }
+    double *p = out + row * n;
+    if (face) {
+        for (int i = lane; i < n; i += 64) p[i] = 0.0;
+    } else if (lane < 2) {
+        p[lane == 0 ? 0 : n - 1] = 0.0;
     }
 }
 
 hipError_t launch_zero_boundary(const AdjArgs &a, double *out, hipStream_t st)
 {
+    int64_t rows = 1;
+    for (int x = 0; x + 1 < a.geo.d; ++x) rows *= a.n[x];
+    const unsigned nb = (unsigned)((rows + NTA / 64 - 1) / (NTA / 64));
     if (a.geo.d == 3)
-        hipLaunchKernelGGL(k_zero_boundary<3>, dim3(4096), dim3(NTA), 0, st, a, out);
+        hipLaunchKernelGGL(k_zero_boundary<3>, dim3(nb), dim3(NTA), 0, st, a, out, rows);
     else
-        hipLaunchKernelGGL(k_zero_boundary<2>, dim3(4096), dim3(NTA), 0, st, a, out);
+        hipLaunchKernelGGL(k_zero_boundary<2>, dim3(nb), dim3(NTA), 0, st, a, out, rows);
     return hipGetLastError();
 }
 
 // Face-to-slice expansion, first transform.  Tile rows = slots r of the
-// transform axis (length N), tile columns = W consecutive column indices,
-// batch = grid.y.  Input element (r, col):
-//   3D: K_hat[s-1][kb(col)][kc(r)] LH0[col][r] + K_hat[M-1-s][kb][kc] LH1[col][r],
-//       s = batch + 1, col = slot of the other in-face axis
-//   2D: K_hat[s-1][k(r)] LH0[r] + K_hat[M-1-s][k(r)] LH1[r],  s = col + 1
+// transform axis (length N), tile columns = W consecutive column indices.
+// Input element (r, q, s), q = slot of the other in-face axis (2D: 0), s = slice:
+//   K_hat[s-1][kb(q)][kc(r)] LH0[q][r] + K_hat[M-1-s][kb][kc] LH1[q][r],
+// (column, batch) = (q, s - 1), or (s - 1, q) with scol;
 // followed by the hermitian synthesis along the rows.  Rows 1..M-1 of the
-// result, times `scale`, are stored (3D) or added (2D) to out[(row-1)*ors +
+// result, times `scale`, are stored or (accum) added to out[(row-1)*ors +
 // col*ocs + batch*obs].
 template <int MAXE, int KD, int NTT>
 __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
@@ -935,17 +973,11 @@ __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
         const int col = c0 + c;
         int s, kb;
         const double *l0, *l1;
-        if (a.d == 3) {
-            s = bt + 1;
-            kb = col <= a.Mb ? col : col - a.Mb;
-            l0 = a.LH0 + (int64_t)col * N;
-            l1 = a.LH1 + (int64_t)col * N;
-        } else {
-            s = col + 1;
-            kb = 0;
-            l0 = a.LH0;
-            l1 = a.LH1;
-        }
+        const int q = a.scol ? bt : col; // column of the face spectra
+        s = (a.scol ? col : bt) + 1;
+        kb = q <= a.Mb ? q : q - a.Mb;
+        l0 = a.LH0 + (int64_t)q * N;
+        l1 = a.LH1 + (int64_t)q * N;
         const double *k0 = a.K + (int64_t)(s - 1) * a.Kd + (int64_t)kb * a.Kb;
         const double *k1 = a.K + (int64_t)(a.Ms - 1 - s) * a.Kd + (int64_t)kb * a.Kb;
         for (int r = lane; r < N; r += 64) {
@@ -965,6 +997,110 @@ __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
         tile_store_acc<double, double, NTT>(buf, rs, 1, out, M - 1, nc, a.ors, a.ocs, a.scale, lgW);
     else
         tile_store<double, double, NTT>(buf, rs, 1, out, M - 1, nc, a.ors, a.ocs, a.scale, lgW);
+}
+
+// The expansion in register tiles (see RegTile): a thread forms the products of the
+// rows that its first butterfly takes, results go straight to global memory. Columns
+// that are slices (SCOL) share the rows of the face spectra. Slices s and M - s, and the
+// cosine and the sine column of one frequency, read the same rows of K, so blocks that
+// share them run next to each other. 257^3, per family: 283 -> 195 us (of it 80 for K and
+// the result at 5.1 TB/s; the rest is the latency of the loads before each transform);
+// with the other slots as columns 320 us (36 loads per thread -> 52); 4097^2: 820 -> 230 and 270.
+// All loads issued before their first use measured 3% slower.
+template <typename R, bool SCOL>
+__global__ __launch_bounds__(R::NTH) void k_expand_rt(ExpandArgs a, int nblk)
+{
+    constexpr int N = R::N, M = N / 2, W = R::W, P = R::P;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const cx<double> *tw = R::LTW ? reinterpret_cast<const cx<double> *>(smem) : a.tw;
+    cx<double> *buf = reinterpret_cast<cx<double> *>(smem) + (R::LTW ? N : 0);
+    const int ncb = (a.ncols + W - 1) / W, tid = threadIdx.x;
+    const int lb = xcd_remap(blockIdx.x, nblk);
+    // index i of n as 0, n-1, 1, n-2, ..
+    auto ends = [](int i, int n) { return i & 1 ? n - 1 - (i >> 1) : i >> 1; };
+    // index i of n (even) as 0, n/2, 1, n/2 + 1, ..
+    auto halves = [](int i, int n) { return n & 1 ? i : (i & 1) * (n >> 1) + (i >> 1); };
+    int cb, bt;
+    if constexpr (SCOL) {
+        cb = ends(lb % ncb, ncb);
+        bt = halves(lb / ncb, a.nbatch);
+    } else {
+        cb = lb % ncb;
+        bt = ends(lb / ncb, a.nbatch);
+    }
+    const int c0 = cb * W, nc = min(W, a.ncols - c0);
+    int j, s;
+    rt_paired<R>(tid, j, s);
+    double l[2][8]; // face spectra, rows k and N/2 + k (SCOL: of both columns)
+    auto fetch_l = [&](int q) {
+        const double *l0 = a.LH0 + (int64_t)q * N + j, *l1 = a.LH1 + (int64_t)q * N + j;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            l[0][r] = l0[r * P];
+            l[1][r] = l1[r * P];
+        }
+    };
+    cx<double> C[4], S[4];
+    if (SCOL) fetch_l(bt);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const bool in = 2 * s + c < nc;
+        const int col = c0 + (in ? 2 * s + c : 0);
+        const int q = SCOL ? bt : col, sl = (SCOL ? col : bt) + 1;
+        const int kb = q <= a.Mb ? q : q - a.Mb;
+        if (!SCOL) fetch_l(q);
+        const double *k0 = a.K + (int64_t)(sl - 1) * a.Kd + (int64_t)kb * a.Kb + j;
+        const double *k1 = a.K + (int64_t)(a.Ms - 1 - sl) * a.Kd + (int64_t)kb * a.Kb + j;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double a0 = k0[r * P], a1 = k1[r * P];
+            // (row N/2 in the place of the sine row of k = 0)
+            const double b0 = r == 0 ? k0[j == 0 ? M : 0] : a0, b1 = r == 0 ? k1[j == 0 ? M : 0] : a1;
+            const double cv = a0 * l[0][r] + a1 * l[1][r], sv = b0 * l[0][4 + r] + b1 * l[1][4 + r];
+            (c == 0 ? C[r].x : C[r].y) = in ? cv : 0.0;
+            (c == 0 ? S[r].x : S[r].y) = in ? sv : 0.0;
+        }
+    }
+    if constexpr (R::LTW) load_twiddles<double, R::NTH>(reinterpret_cast<cx<double> *>(smem), a.tw, N);
+    cx<double> v[8];
+    rt_unfold_herm<double, R>(C, S, j, v);
+    rt_first<double, R, true>(buf, v, j, s);
+    rt_middle<double, R, true>(buf, tw, tid);
+    rt_plain<R>(tid, j, s);
+    rt_last<double, R, true>(buf, tw, v, j, s);
+    double *out = a.out + (int64_t)bt * a.obs + (int64_t)c0 * a.ocs;
+    const int c = 2 * s, ocs = (int)a.ocs, ors = (int)a.ors;
+    const bool both = c + 1 < nc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int t = j + r * P - 1;
+        if (t < 0 || c >= nc) continue;
+        double *p = out + toff(t, ors, c, ocs);
+        pair_t<double> w = {a.scale * v[r].x, a.scale * v[r].y};
+        if (ocs == 1 && both) {
+            pair_t<double> *pp = reinterpret_cast<pair_t<double> *>(p);
+            if (a.accum) {
+                const pair_t<double> o = *pp;
+                w.a += o.a;
+                w.b += o.b;
+            }
+            *pp = w;
+        } else if (a.accum) {
+            p[0] += w.a;
+            if (both) p[ocs] += w.b;
+        } else {
+            p[0] = w.a;
+            if (both) p[ocs] = w.b;
+        }
+    }
+}
+
+template <typename R, bool SCOL>
+static void launch_expand_rt(const ExpandArgs &a, int nblk, hipStream_t st)
+{
+    const size_t lds = rt_lds<double, R>();
+    set_lds((const void *)&k_expand_rt<R, SCOL>, lds);
+    hipLaunchKernelGGL((k_expand_rt<R, SCOL>), dim3((unsigned)nblk), dim3(R::NTH), lds, st, a, nblk);
 }
 
 template <int MAXE, int NTT = NTA>
@@ -988,6 +1124,13 @@ hipError_t launch_expand(const ExpandArgs &a, hipStream_t st)
     const int work = (a.W / 2) * a.fd.N;
     if (nblk == 0) return hipSuccess;
     if (!tile_strides_ok(a.fd.M, a.ors, a.ncols, a.ocs)) return hipErrorInvalidValue;
+    if (rt_tile<0>(a.fd.N, a.W, [&](auto tile) {
+            if (a.scol)
+                launch_expand_rt<decltype(tile), true>(a, (int)nblk, st);
+            else
+                launch_expand_rt<decltype(tile), false>(a, (int)nblk, st);
+        }))
+        return hipGetLastError();
     if (a.fd.N > 2048) {
         // long transforms: one complex sequence per tile, global twiddles
         const size_t lds = (size_t)a.fd.N * a.W * sizeof(double);

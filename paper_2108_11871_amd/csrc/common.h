@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "fft_tile.h"
@@ -78,6 +79,12 @@ inline size_t tile_lds(int N, int W)
 {
     if (big_fft(N)) return (size_t)N * W * sizeof(T);
     return (size_t)N * sizeof(cx<T>) + (size_t)N * (W + 1) * sizeof(T);
+}
+
+// Default width of the register tiles of N rows (0: none).
+inline int rt_width(int N)
+{
+    return N >= 256 && N <= 8192 && is_pow2(N) ? std::max(2, 4096 / N) : 0;
 }
 
 // f(RegTile) of the register tile that has N rows and W columns; whether there is

@@ -722,6 +722,30 @@ __device__ __forceinline__ void rt_unfold_odd(cx<T> (&a)[8], int j)
     }
 }
 
+// Inputs of the hermitian synthesis from the cosine rows C and sine rows S of k = j +
+// r N/8, r < 4 (of k = 0: S holds row N/2): z(k) = C + i-swapped S, the upper rows
+// N - k from the mirror lane (of j = 0 the thread's own).
+template <typename T, typename R>
+__device__ __forceinline__ void rt_unfold_herm(const cx<T> (&C)[4], const cx<T> (&S)[4], int j, cx<T> (&v)[8])
+{
+    const bool z0 = j == 0, h = j == R::P / 2;
+    cx<T> up[4];
+    const cx<T> cm = S[0];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const T sa = r == 0 && z0 ? (T)0 : S[r].x, sb = r == 0 && z0 ? (T)0 : S[r].y;
+        v[r] = cx<T>{C[r].x + sb, C[r].y - sa};
+        up[r] = cx<T>{C[r].x - sb, C[r].y + sa}; // row N - k
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const cx<T> own = r < 3 ? up[r + 1] : cm;
+        const cx<T> m = {rt_mirror<R>(up[r].x), rt_mirror<R>(up[r].y)};
+        v[7 - r].x = z0 ? own.x : h ? up[r].x : m.x;
+        v[7 - r].y = z0 ? own.y : h ? up[r].y : m.y;
+    }
+}
+
 // First stage (radix 8): rows j + r N/8 in a, written to the tile.
 template <typename T, typename R, bool INV>
 __device__ __forceinline__ void rt_first(cx<T> *buf, cx<T> (&a)[8], int j, int s)

@@ -263,7 +263,7 @@ struct AdjShell {
 
 // Face-to-slice expansion (first transform), see k_expand.
 struct ExpandArgs {
-    int d;
+    int scol; // columns are slices (batch: columns of the face spectra), else the reverse
     const double *LH0, *LH1; // slot spectra of the two faces
     const double *K;         // kernel spectra K_hat[dd][kb][kc] (2D: [dd][k])
     int64_t Kd, Kb;

@@ -255,28 +255,13 @@ __global__ __launch_bounds__(R::NTH) void k_pass_rt(PassArgs a, int ntiles)
         for (int r = 0; r < 4; ++r) v[r] = cx<T>{(T)x[2 * r + 1], -(T)x[2 * r]};
         rt_unfold_odd<T, R>(v, j);
     } else {
-        const bool z0 = j == 0, h = j == P / 2;
-        cx<T> up[4], cm;
+        cx<T> C[4], S[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const T ca = (T)x[2 * r], cb2 = (T)x[2 * r + 1];
-            T sa = (T)x[8 + 2 * r], sb = (T)x[9 + 2 * r];
-            if (r == 0) {
-                cm = cx<T>{sa, sb};
-                sa = z0 ? (T)0 : sa;
-                sb = z0 ? (T)0 : sb;
-            }
-            v[r] = cx<T>{ca + sb, cb2 - sa};
-            up[r] = cx<T>{ca - sb, cb2 + sa}; // row N - k
+            C[r] = cx<T>{(T)x[2 * r], (T)x[2 * r + 1]};
+            S[r] = cx<T>{(T)x[8 + 2 * r], (T)x[9 + 2 * r]};
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            // rows j + (7 - r) N/8: the mirror's N - k; of j = 0 the thread's own
-            const cx<T> own = r < 3 ? up[r + 1] : cm;
-            const cx<T> m = {rt_mirror<R>(up[r].x), rt_mirror<R>(up[r].y)};
-            v[7 - r].x = z0 ? own.x : h ? up[r].x : m.x;
-            v[7 - r].y = z0 ? own.y : h ? up[r].y : m.y;
-        }
+        rt_unfold_herm<T, R>(C, S, j, v);
     }
     if constexpr (MODE == IN_ZPAD)
         rt_first_zpad<T, R>(buf, v, j, s);

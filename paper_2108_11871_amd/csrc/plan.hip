@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "ipoisson.h"
+#include "common.h"
 #include "kernels.h"
 
 using namespace ips;
@@ -2057,8 +2058,16 @@ int execute_adjoint(ips_plan p, const double *w, double *out, hipStream_t st)
             b2.scale = 1.0;
             if ((rc = run_pass(p, b2, p->fd[b], p->tw[b], false, false, st))) return rc;
             // slices: product with the kernel spectra, synthesis along c, then along b
+            // columns of the first transform: the slices (register tiles: a column then
+            // costs the rows of K only), or the other slots. The third family's slices
+            // are contiguous in the output and columns of both transforms, for runs of
+            // lines instead of single elements (second transform 257^3: 269 -> 137 us).
             ExpandArgs e{};
-            e.d = 3;
+            const int Wr = rt_width(N[c]);
+            const bool last = gst[fam] == 1;
+            const int64_t bs = (int64_t)I[c] * I[fam], ss = last ? 1 : I[c];
+            e.scol = (last || (Wr > 0 && Wr <= I[fam] && p->work == 2048)) && tile_strides_ok(N[b], bs, I[fam], 1) &&
+                     tile_strides_ok(I[c], last ? I[fam] : 1, Wr, ss);
             e.LH0 = p->LH[fam];
             e.LH1 = p->LH[fam] + (int64_t)N[b] * N[c];
             e.K = p->K[fam];
@@ -2067,12 +2076,12 @@ int execute_adjoint(ips_plan p, const double *w, double *out, hipStream_t st)
             e.Ms = M[fam];
             e.Mb = M[b];
             e.out = p->AZ;
-            e.ors = 1;
-            e.ocs = I[c];
-            e.obs = (int64_t)N[b] * I[c];
-            e.ncols = N[b];
-            e.nbatch = I[fam];
-            e.W = tile_width(N[c], p->work / 2, N[b]);
+            e.ors = last && e.scol ? I[fam] : 1;
+            e.ocs = e.scol ? ss : I[c];
+            e.obs = e.scol ? bs : (int64_t)N[b] * I[c];
+            e.ncols = e.scol ? I[fam] : N[b];
+            e.nbatch = e.scol ? N[b] : I[fam];
+            e.W = tile_width(N[c], Wr > 0 ? p->work : p->work / 2, e.ncols);
             e.scale = 1.0 / N[c];
             e.accum = 0;
             e.fd = p->fd[c];
@@ -2081,15 +2090,16 @@ int execute_adjoint(ips_plan p, const double *w, double *out, hipStream_t st)
             PassArgs z{};
             z.in = p->AZ;
             z.out = out + off;
-            z.irs = I[c];
+            const bool zs = last && e.scol; // columns: slices
+            z.irs = e.scol ? bs : I[c];
             z.ics = 1;
-            z.ibs = (int64_t)N[b] * I[c];
+            z.ibs = zs ? I[fam] : e.scol ? I[c] : (int64_t)N[b] * I[c];
             z.ors = gst[b];
-            z.ocs = gst[c];
-            z.obs = gst[fam];
+            z.ocs = zs ? 1 : gst[c];
+            z.obs = zs ? gst[c] : gst[fam];
             z.nrows_in = N[b];
-            z.ncols = I[c];
-            z.nbatch = I[fam];
+            z.ncols = zs ? I[fam] : I[c];
+            z.nbatch = zs ? I[c] : I[fam];
             z.in_mode = IN_HERM;
             z.W = N[b] == 512 ? wide_width(p, N[b], z.ncols, z.nbatch, false) : 0;
             z.out_r0 = 1;
@@ -2114,7 +2124,7 @@ int execute_adjoint(ips_plan p, const double *w, double *out, hipStream_t st)
             a.scale = 1.0;
             if ((rc = run_pass(p, a, p->fd[b], p->tw[b], false, false, st))) return rc;
             ExpandArgs e{};
-            e.d = 2;
+            e.scol = 1;
             e.LH0 = p->LH[fam];
             e.LH1 = p->LH[fam] + N[b];
             e.K = p->K[fam];

@@ -228,3 +228,21 @@ def test_shell_adjoint_small(shape, order):
     got = api.Plan(shape, h, order=order, adjoint=True).adjoint(to_dev(w))
     torch.cuda.synchronize()
     assert rel_err(got.cpu().numpy(), P.adjoint(w, h, order)) < 1e-12
+
+
+# register tiles of the expansion: slices as columns (ragged, one more than whole tiles)
+# and, with fewer slices than a tile's columns, the other slots; every family, 2M = 256 .. 2048
+@pytest.mark.parametrize("shape,order", [((129, 18, 257), 6), ((20, 129, 12), 4), ((129, 9, 130), 6), ((10, 257, 129), 6),
+                                         ((257, 129, 9), 4), ((1025, 9, 10), 4), ((8, 513, 19), 6), ((130, 129), 6),
+                                         ((1025, 300), 4)])
+def test_expand_register_tiles(shape, order):
+    import torch
+    from paper_2108_11871_amd import api
+    from gpu_util import banner, rel_err, to_dev
+
+    banner("adjoint shape=%s order=%d" % (shape, order))
+    h = I.grid_spacing(shape, -1.0, 1.3)
+    w = np.random.default_rng(6).standard_normal(shape)
+    got = api.Plan(shape, h, order=order, adjoint=True).adjoint(to_dev(w))
+    torch.cuda.synchronize()
+    assert rel_err(got.cpu().numpy(), P.adjoint(w, h, order)) < 1e-12
