@@ -532,7 +532,7 @@ hipError_t launch_adj_contract(const AdjArgs &a, int ax, int nl, const double *X
     else
         hipLaunchKernelGGL(k_adj_contract<2>, grid, dim3(NTA), 0, st, c);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && ks > 1) e = launch_reduce(part, out, nl * c.np, ks, 1, st);
+    if (e == hipSuccess && ks > 1) e = launch_reduce(ReduceArgs{{{part, out, nl * c.np, ks}}, 1, 1}, st);
     return e;
 }
 

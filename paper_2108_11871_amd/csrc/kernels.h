@@ -108,6 +108,9 @@ struct PackArgs {
     void *P2T;   // 3D only: FP32 if p2t_f32, else FP64
     int p2t_f32;
     int withD;   // pack the deferred-correction layers (else the g~ layers)
+    void *rowtab; // the final pass's row table (FP32 if mixed, else FP64), set in the last call only
+    int mixed;
+    AxisTabs tab[3];
     int nblk[3]; // filled by the launcher
 };
 
@@ -129,7 +132,7 @@ struct FinalArgs {
     int group;      // neighbouring column blocks taken together (their rows share 128-byte lines)
     int pre;        // buf already holds the raw sine spectrum along axis 0 (no forward transform)
     void *rowtab;   // row table [nbatch][M0 - 1][12] (transform type) in global memory, written by
-                    // launch_final_rows before the pass; both launchers reject a null table
+                    // the last launch_pack before the pass; launch_final rejects a null table
 };
 
 // Boundary values from the screening charge (screen.hip).
@@ -217,6 +220,18 @@ struct FaceVals {
     double scale[3];
 };
 
+// Sums of chunk partials: out[s][i] = sum over c of part[s][c][i], s < nset, per job.
+struct ReduceJob {
+    const double *part;
+    double *out;
+    int64_t len;
+    int nchunk;
+};
+struct ReduceArgs {
+    ReduceJob job[2];
+    int njobs, nset;
+};
+
 struct DcorrArgs {
     Geo geo;
     int64_t n[3];
@@ -230,17 +245,10 @@ struct DcorrArgs {
 struct GtArgs {
     Geo geo;
     int64_t n[3];
-    const double *phi;
-    FaceVals face;
+    double *phi;
+    FaceVals face; // given: boundary values, written to phi too
     double wf[3], we[3][3]; // weights of face and edge neighbours, filled by the launcher
     double *G[3]; // [2][..][..]
-};
-
-struct BwriteArgs {
-    Geo geo;
-    int64_t n[3];
-    FaceVals face;
-    double *phi;
 };
 
 // Adjoint (rho_bar = A^T phi_bar), FP64.
@@ -320,8 +328,7 @@ hipError_t launch_pass_multi(const PassArgs *p, int n, bool in_f32, bool out_f32
 // in_f32: input data in FP32 (else FP64); f32: transform type
 hipError_t launch_cc(const CcArgs &a, int nchunk, bool f32, bool in_f32, hipStream_t st);
 // out[s][i] = sum over the chunks c of part[s][c][i]  (nset sets of nchunk rows of len)
-hipError_t launch_reduce(const double *part, double *out, int64_t len, int nchunk, int nset, hipStream_t st);
-hipError_t launch_bwrite(const BwriteArgs &a, hipStream_t st);
+hipError_t launch_reduce(const ReduceArgs &a, hipStream_t st);
 hipError_t launch_gtilde(GtArgs a, hipStream_t st);
 hipError_t launch_pack(PackArgs a, hipStream_t st);
 hipError_t launch_r6t(R6Args a, hipStream_t st);
@@ -331,7 +338,6 @@ hipError_t launch_dcorr(const DcorrArgs &a, hipStream_t st);
 hipError_t launch_embed(const double *src, double *dst, int d, const int64_t *n, const int64_t *ne,
                         const int64_t *off, bool extract, hipStream_t st);
 // Row table of the final pass: once per solve, before launch_final.
-hipError_t launch_final_rows(const FinalArgs &a, hipStream_t st);
 hipError_t launch_final(const FinalArgs &a, hipStream_t st);
 // K[dd][ib][ic] (3D) or K[dd][ib] (2D) for faces normal to axis a; (b, c) are
 // the in-face axes in storage order (c contiguous).

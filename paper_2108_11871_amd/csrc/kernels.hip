@@ -117,13 +117,15 @@ hipError_t launch_embed(const double *src, double *dst, int d, const int64_t *n,
 // eight loads in flight, combined in LDS in a fixed order.
 constexpr int kRedWaves = 16;
 
-__global__ __launch_bounds__(64 * kRedWaves) void k_reduce(const double *part, double *out, int64_t len,
-                                                           int nchunk)
+__global__ __launch_bounds__(64 * kRedWaves) void k_reduce(ReduceArgs a)
 {
+    const ReduceJob &jb = a.job[blockIdx.z];
+    const int64_t len = jb.len;
+    const int nchunk = jb.nchunk;
     __shared__ double red[kRedWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i = blockIdx.x * (int64_t)64 + lane;
-    const double *src = part + (int64_t)blockIdx.y * nchunk * len + i;
+    const double *src = jb.part + (int64_t)blockIdx.y * nchunk * len + i;
     double s = 0.0;
     if (i < len) {
         for (int c0 = wave; c0 < nchunk; c0 += 8 * kRedWaves) {
@@ -141,16 +143,17 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce(const double *part, d
     __syncthreads();
     if (wave == 0 && i < len) {
         for (int w = 1; w < kRedWaves; ++w) s += red[w][lane];
-        out[(int64_t)blockIdx.y * len + i] = s;
+        jb.out[(int64_t)blockIdx.y * len + i] = s;
     }
 }
 
-hipError_t launch_reduce(const double *part, double *out, int64_t len, int nchunk, int nset, hipStream_t st)
+hipError_t launch_reduce(const ReduceArgs &a, hipStream_t st)
 {
-    const int64_t nb = (len + 63) / 64;
-    if (nb > INT32_MAX || nset < 1 || nset > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_reduce, dim3((unsigned)nb, (unsigned)nset), dim3(64 * kRedWaves), 0, st, part, out, len,
-                       nchunk);
+    int64_t nb = 0;
+    for (int j = 0; j < a.njobs; ++j) nb = std::max(nb, (a.job[j].len + 63) / 64);
+    if (nb > INT32_MAX || a.nset < 1 || a.nset > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_reduce, dim3((unsigned)nb, (unsigned)a.nset, (unsigned)a.njobs), dim3(64 * kRedWaves), 0, st,
+                       a);
     return hipGetLastError();
 }
 
@@ -209,11 +212,10 @@ __device__ __forceinline__ double face_val(const FaceVals &v, int fam, int f, in
 // ---------------------------------------------------------------------------
 // Boundary values -> phi (faces, then edges and corners by lowest axis)
 // ---------------------------------------------------------------------------
-__global__ void k_bwrite(BwriteArgs a)
+__device__ __forceinline__ void write_boundary(const GtArgs &a, int64_t e)
 {
     const Geo &g = a.geo;
     const int d = g.d;
-    int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     for (int fam = 0; fam < d; ++fam) {
         // ranges of the in-face axes: lower axes exclude their end nodes
         int lo[2] = {0, 0}, len[2] = {1, 1}, ax[2] = {0, 0}, na = 0;
@@ -241,18 +243,16 @@ __global__ void k_bwrite(BwriteArgs a)
     }
 }
 
-hipError_t launch_bwrite(const BwriteArgs &a, hipStream_t st)
+static int64_t boundary_nodes(const Geo &g)
 {
     int64_t tot = 0;
-    const Geo &g = a.geo;
     for (int fam = 0; fam < g.d; ++fam) {
         int64_t c = 2;
         for (int b = 0; b < g.d; ++b)
             if (b != fam) c *= b < fam ? g.M[b] - 1 : g.M[b] + 1;
         tot += c;
     }
-    hipLaunchKernelGGL(k_bwrite, dim3((unsigned)((tot + NT - 1) / NT)), dim3(NT), 0, st, a);
-    return hipGetLastError();
+    return tot;
 }
 
 // ---------------------------------------------------------------------------
@@ -273,12 +273,48 @@ __host__ __device__ __forceinline__ int64_t shell_size(const Geo &g, int a)
 // thread; the transposed copies go through LDS, so that every write is a run of 16.
 // The g~ part (t = 0) is packed by the call without D layers, the D parts by the
 // one with them. 257^3: 8 + 13 -> 6 + 7 us, 513^3 13 + 41 -> 11 + 18 us (one element
-// per thread with strided copies before); bound by launch latency below.
+// per thread with strided copies before); bound by launch latency below. The last call
+// also writes the final pass's row table from the values in hand (257^3 7 + 7 us for
+// two launches -> 11).
 constexpr int kPackTile = 16;
+
+// Row i of batch index kB - 1 of the final pass's row table [batch][M0 - 1][12] (see
+// k_final for the layout), from family 1's packed spectra v = (even t = 1, 2, odd
+// t = 1, 2, even t = 0, odd t = 0).
+template <typename TR>
+__device__ __forceinline__ void final_row_t(const PackArgs &a, int i, int b, const double *v, int64_t e)
+{
+    const Geo &geo = a.geo;
+    const int d = geo.d, I0 = geo.M[0] - 1;
+    const double lamB = d == 3 ? a.tab[2].lam[b] : 0.0, qB = d == 3 ? a.tab[2].q[b] : 0.0;
+    const double c2xz = d == 3 ? geo.c2[0][2] : 0.0;
+    const double c4xz = d == 3 ? geo.c4[0][2] : 0.0, c4zx = d == 3 ? geo.c4[2][0] : 0.0;
+    const double lx = a.tab[0].lam[i];
+    TR *r = static_cast<TR *>(a.rowtab) + e * 12;
+    r[0] = (TR)lx;
+    r[1] = (TR)(a.tab[0].q[i] + qB);
+    r[2] = (TR)a.tab[0].s[i];
+    r[3] = (TR)a.tab[0].s[I0 + i];
+    r[4] = (TR)v[4];
+    r[5] = (TR)v[0];
+    r[6] = (TR)v[1];
+    r[7] = (TR)v[5];
+    r[8] = (TR)v[2];
+    r[9] = (TR)v[3];
+    r[10] = (TR)(lx + c2xz * lx * lamB);
+    r[11] = (TR)(lx * lamB * (c4xz * lx + c4zx * lamB));
+}
+__device__ __forceinline__ void final_row(const PackArgs &a, int i, int b, const double *v, int64_t e)
+{
+    if (a.mixed)
+        final_row_t<float>(a, i, b, v, e);
+    else
+        final_row_t<double>(a, i, b, v, e);
+}
 
 __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
 {
-    __shared__ double tile[4][kPackTile][kPackTile + 1];
+    __shared__ double tile[6][kPackTile][kPackTile + 1];
     const Geo &g = a.geo;
     int fam = 0, blk = blockIdx.x;
     while (fam < g.d - 1 && blk >= a.nblk[fam]) blk -= a.nblk[fam++];
@@ -289,11 +325,17 @@ __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
     const int64_t ss = (int64_t)Il * Ih;
     const int tx = threadIdx.x & (kPackTile - 1), ty = threadIdx.x / kPackTile;
     const bool tr = g.d == 3 && fam > 0;
+    const bool rows = fam == 1 && a.rowtab; // (the last call: all parts are known)
     const int nk = a.withD ? 4 : 2; // values per element, of kind (parity, t)
     auto kind = [&](int q) { return a.withD ? (q >> 1) * 3 + 1 + (q & 1) : 3 * q; };
     if (r0 + ty < Il && c0 + tx < Ih) {
         const int64_t e = (int64_t)(r0 + ty) * Ih + c0 + tx;
-        double v[4];
+        double v[6];
+        if (!a.withD || rows) {
+            const double g0 = a.G[fam][e], g1 = a.G[fam][ss + e];
+            v[0] = v[4] = g0 - g1; // even k, t = 0
+            v[1] = v[5] = g0 + g1; // odd k, t = 0
+        }
         if (a.withD) {
             const double *D = a.D[fam];
             const double d1 = D[e], d2 = D[ss + e], d3 = D[2 * ss + e], d4 = D[3 * ss + e];
@@ -302,9 +344,6 @@ __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
             v[2] = d1 + d4; // odd k, t = 1
             v[3] = d2 + d3; // odd k, t = 2
         } else {
-            const double g0 = a.G[fam][e], g1 = a.G[fam][ss + e];
-            v[0] = g0 - g1; // even k, t = 0
-            v[1] = g0 + g1; // odd k, t = 0
             v[2] = v[3] = 0.0;
         }
 #pragma unroll
@@ -312,6 +351,14 @@ __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
             if (q >= nk) break;
             a.P[fam][kind(q) * ss + e] = v[q];
             if (tr) tile[q][ty][tx] = v[q];
+        }
+        if (tr && rows) {
+            tile[4][ty][tx] = v[4];
+            tile[5][ty][tx] = v[5];
+        }
+        if (!tr && rows) {
+            if (!a.withD) v[0] = v[1] = 0.0;
+            final_row(a, c0 + tx, 0, v, e);
         }
     }
     if (!tr) return;
@@ -329,6 +376,12 @@ __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
             static_cast<float *>(a.P2T)[kind(q) * ss + et] = (float)v;
         else
             static_cast<double *>(a.P2T)[kind(q) * ss + et] = v;
+    }
+    if (rows) {
+        double v[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) v[q] = q < 4 && !a.withD ? 0.0 : tile[q][tx][ty];
+        final_row(a, r0 + tx, c0 + ty, v, et);
     }
 }
 
@@ -559,8 +612,9 @@ __global__ __launch_bounds__(NT) void k_r6t(R6Args a)
 }
 
 // T[ax][l][p] = sum over the splits of part[ax][s][l][p] (10 layers of npos)
-__global__ void k_r6t_sum(R6Args a, int ax, int ks)
+__global__ void k_r6t_sum(R6Args a, int ks)
 {
+    const int ax = blockIdx.y;
     const int64_t len = 10 * shell_size(a.geo, ax);
     const double *src = a.part + a.part_off[ax];
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len; i += (int64_t)gridDim.x * blockDim.x) {
@@ -590,10 +644,11 @@ static hipError_t launch_r6t_p(R6Args a, hipStream_t st)
     else
         hipLaunchKernelGGL((k_r6t<2, PPT, KU>), dim3(tot, ks), dim3(NT), 0, st, a);
     hipError_t e = hipGetLastError();
-    for (int ax = 0; ax < d && ks > 1 && e == hipSuccess; ++ax) {
-        const int64_t len = 10 * shell_size(a.geo, ax);
+    if (ks > 1 && e == hipSuccess) {
+        int64_t len = 0;
+        for (int ax = 0; ax < d; ++ax) len = std::max(len, 10 * shell_size(a.geo, ax));
         const unsigned nb = (unsigned)std::min<int64_t>((len + NT - 1) / NT, 4096);
-        hipLaunchKernelGGL(k_r6t_sum, dim3(nb), dim3(NT), 0, st, a, ax, ks);
+        hipLaunchKernelGGL(k_r6t_sum, dim3(nb, (unsigned)d), dim3(NT), 0, st, a, ks);
         e = hipGetLastError();
     }
     return e;
@@ -799,11 +854,17 @@ hipError_t launch_dcorr(const DcorrArgs &a, hipStream_t st)
 // M-1 there; other layers hold 0 at that node). Nodes away from the edges read their
 // five neighbours from the face array; the others all 18 at once (bound by the latency
 // of these loads: one after the other 12 us on the smallest grid; 513^3 113 -> 41 us,
-// whose z faces are a row apart per node in phi).
+// whose z faces are a row apart per node in phi). FACES: boundary values come from the
+// face arrays, and the block rows from 2 D on write them to phi, in one launch (257^3
+// 11 + 15 -> 14 us, 33^3 4 + 11 -> 5 us and a launch less); else they are in phi.
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, bool FACES>
 __global__ __launch_bounds__(NT) void k_gtilde(GtArgs a)
 {
+    if (FACES && blockIdx.y >= 2 * D) {
+        write_boundary(a, ((int64_t)(blockIdx.y - 2 * D) * gridDim.x + blockIdx.x) * NT + threadIdx.x);
+        return;
+    }
     const Geo &g = a.geo;
     const int fam = blockIdx.y >> 1, f = blockIdx.y & 1;
     const int64_t ss = shell_size(g, fam);
@@ -825,7 +886,7 @@ __global__ __launch_bounds__(NT) void k_gtilde(GtArgs a)
     for (int b = 0; b < fam; ++b)
         if (i[b] == 1 || i[b] == g.M[b] - 1) owned = false;
     double s = 0.0;
-    bool bulk = a.face.F[0] != nullptr && g.M[fam] > 2;
+    bool bulk = FACES && g.M[fam] > 2;
 #pragma unroll
     for (int q = 0; q < D - 1; ++q) bulk = bulk && i[ob[q]] >= 2 && i[ob[q]] <= g.M[ob[q]] - 2;
     auto add = [&](double w, double v) { // (no fused multiply-add)
@@ -862,14 +923,38 @@ __global__ __launch_bounds__(NT) void k_gtilde(GtArgs a)
         // every neighbour is a grid node: all are loaded at once, those off the
         // boundary dropped
         double v[2 * D + 2 * D * (D - 1)];
+        double scl[FACES ? 2 * D + 2 * D * (D - 1) : 1];
         bool on[2 * D + 2 * D * (D - 1)];
         int m = 0;
         auto get = [&](int p, int sp, int q, int sq) {
             int j[3] = {i[0], i[1], i[2]};
             j[p] += sp;
             j[q] += sq;
-            v[m] = a.phi[node_off(a.n, D, j)];
-            on[m++] = on_boundary(g, j);
+            bool any = false;
+            if constexpr (FACES) {
+                // the face of the lowest axis at its end, as in phi
+                const double *F = nullptr;
+                double sc = 0.0;
+                int o = 0;
+#pragma unroll
+                for (int b = D - 1; b >= 0; --b) {
+                    const bool at = j[b] == 0 || j[b] == g.M[b];
+                    const int lo = b == 0 ? 1 : 0, hi = b == 2 ? 1 : 2;
+                    const int ob = (j[b] ? (int)a.face.fs[b][0] : 0) + j[lo] * (int)a.face.fs[b][1] +
+                                   (D == 3 ? j[hi] * (int)a.face.fs[b][2] : 0);
+                    const bool take = at || b == D - 1; // (of no face: any address)
+                    F = take ? a.face.F[b] : F;
+                    sc = take ? a.face.scale[b] : sc;
+                    o = take ? ob : o;
+                    any = any || at;
+                }
+                v[m] = F[any ? o : 0];
+                scl[m] = sc;
+            } else {
+                v[m] = a.phi[node_off(a.n, D, j)];
+                any = on_boundary(g, j);
+            }
+            on[m++] = any;
         };
 #pragma unroll
         for (int p = 0; p < D; ++p) {
@@ -896,7 +981,12 @@ __global__ __launch_bounds__(NT) void k_gtilde(GtArgs a)
         }
         m = 0;
         auto use = [&](double w) {
-            add(w, on[m] ? v[m] : 0.0);
+            double t = v[m];
+            if constexpr (FACES) {
+                t = scl[m] * t;
+                asm volatile("" : "+v"(t)); // as stored in phi
+            }
+            add(w, on[m] ? t : 0.0);
             ++m;
         };
 #pragma unroll
@@ -932,10 +1022,17 @@ hipError_t launch_gtilde(GtArgs a, hipStream_t st)
     int64_t mx = 1;
     for (int fam = 0; fam < d; ++fam) mx = std::max(mx, shell_size(a.geo, fam));
     const unsigned nb = (unsigned)((mx + NT - 1) / NT);
-    if (d == 3)
-        hipLaunchKernelGGL(k_gtilde<3>, dim3(nb, 2 * d), dim3(NT), 0, st, a);
+    const bool faces = a.face.F[0] != nullptr;
+    const unsigned nw = faces ? (unsigned)((boundary_nodes(g) + (int64_t)nb * NT - 1) / ((int64_t)nb * NT)) : 0;
+    const dim3 grid(nb, 2 * d + nw);
+    if (d == 3 && faces)
+        hipLaunchKernelGGL((k_gtilde<3, true>), grid, dim3(NT), 0, st, a);
+    else if (d == 3)
+        hipLaunchKernelGGL((k_gtilde<3, false>), grid, dim3(NT), 0, st, a);
+    else if (faces)
+        hipLaunchKernelGGL((k_gtilde<2, true>), grid, dim3(NT), 0, st, a);
     else
-        hipLaunchKernelGGL(k_gtilde<2>, dim3(nb, 2 * d), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((k_gtilde<2, false>), grid, dim3(NT), 0, st, a);
     return hipGetLastError();
 }
 
@@ -970,34 +1067,6 @@ __device__ __forceinline__ void load12(const double *p, double *r)
         r[2 * i] = t.x;
         r[2 * i + 1] = t.y;
     }
-}
-
-// Staged row kx-1 = i of the final pass (see k_final for the layout).
-template <typename TR>
-__device__ __forceinline__ void final_row(const FinalArgs &a, int i, int kB, double lamB, double qB,
-                                          TR *r)
-{
-    const Geo &geo = a.geo;
-    const int d = geo.d;
-    const int I0 = geo.M[0] - 1;
-    const int nt = a.order == 6 ? 3 : 1;
-    const double c2xz = d == 3 ? geo.c2[0][2] : 0.0;
-    const double c4xz = d == 3 ? geo.c4[0][2] : 0.0, c4zx = d == 3 ? geo.c4[2][0] : 0.0;
-    const double lx = a.tab[0].lam[i];
-    r[0] = (TR)lx;
-    r[1] = (TR)(a.tab[0].q[i] + qB);
-    r[2] = (TR)a.tab[0].s[i];
-    r[3] = (TR)a.tab[0].s[I0 + i];
-    r[10] = (TR)(lx + c2xz * lx * lamB);
-    r[11] = (TR)(lx * lamB * (c4xz * lx + c4zx * lamB));
-    // family 1: other index (k0, k2) in 3D (transposed copy: k0 contiguous), (k0) in 2D
-    const int64_t ss1 = shell_size(geo, 1);
-    const double *P1 = d == 3 ? a.sh.P1T : a.sh.P[1];
-    const int64_t o = d == 3 ? (int64_t)(kB - 1) * I0 + i : i;
-    for (int par = 0; par < 2; ++par)
-        for (int t = 0; t < nt; ++t) r[4 + par * 3 + t] = (TR)P1[(par * 3 + t) * ss1 + o];
-    for (int par = 0; par < 2; ++par)
-        for (int t = nt; t < 3; ++t) r[4 + par * 3 + t] = (TR)0;
 }
 
 // Tile lb of the final pass -> (column block, batch entry), in the logical order:
@@ -1176,7 +1245,7 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     // m_R = r11 + c11 + lx ly (c4[0][1] lx + c4[1][0] ly).
     constexpr int SV = 12;
     // The row invariants come from the per-solve table in global memory
-    // (written by k_final_rows); the column invariants are staged in LDS after
+    // (written by k_pack); the column invariants are staged in LDS after
     // the tile, 16-byte aligned and addressed from smem, so that every access
     // to them is an LDS instruction (a pointer that may point to either space
     // would make every access a flat one). Staged values and the per-element
@@ -1453,37 +1522,6 @@ static void launch_final_t(const FinalArgs &a, int nblk, int work, hipStream_t s
         else
             launch_final_k<T, 8, KD>(a, nblk, st);
     });
-}
-
-// Row table of the final pass in global memory, one per batch index
-// (rowtab[kB - 1][kx - 1][12]); 2D has a single batch index.
-__global__ void k_final_rows(FinalArgs a)
-{
-    const int I0 = a.geo.M[0] - 1;
-    const int64_t tot = (int64_t)I0 * a.nbatch;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < tot;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(e % I0), b = (int)(e / I0);
-        const int kB = b + 1;
-        double lamB = 0.0, qB = 0.0;
-        if (a.geo.d == 3) {
-            lamB = a.tab[2].lam[kB - 1];
-            qB = a.tab[2].q[kB - 1];
-        }
-        if (a.mixed)
-            final_row<float>(a, i, kB, lamB, qB, static_cast<float *>(a.rowtab) + e * 12);
-        else
-            final_row<double>(a, i, kB, lamB, qB, static_cast<double *>(a.rowtab) + e * 12);
-    }
-}
-
-hipError_t launch_final_rows(const FinalArgs &a, hipStream_t st)
-{
-    if (!a.rowtab) return hipErrorInvalidValue;
-    const int64_t tot = (int64_t)(a.geo.M[0] - 1) * a.nbatch;
-    const unsigned nb = (unsigned)std::min<int64_t>((tot + NT - 1) / NT, 4096);
-    hipLaunchKernelGGL(k_final_rows, dim3(nb), dim3(NT), 0, st, a);
-    return hipGetLastError();
 }
 
 hipError_t launch_final(const FinalArgs &a, hipStream_t st)

@@ -1534,24 +1534,18 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         // the families' passes of each step together (one launch each when uniform)
         if ((rc = run_passes(fa, nf, false, false, st))) return rc;
         if ((rc = run_passes(fb, nf, false, false, st))) return rc;
-        // (8) boundary values into phi; F[fam][face][j_r][j_c] -> strides of the in-face
-        //     axes in increasing order
-        BwriteArgs a{};
-        a.geo = p->geo;
-        for (int q = 0; q < 3; ++q) a.n[q] = n[q];
+        // (8) boundary values: F[fam][face][j_r][j_c] -> strides of the in-face axes in
+        //     increasing order
         for (int fam = 0; fam < 3; ++fam) {
-            a.face.F[fam] = p->F[fam];
-            a.face.scale[fam] = p->h[0] * p->h[1] * p->h[2];
+            face.F[fam] = p->F[fam];
+            face.scale[fam] = p->h[0] * p->h[1] * p->h[2];
             const int r = fr[fam], c = fc[fam];
-            a.face.fs[fam][0] = (int64_t)N[r] * N[c];
+            face.fs[fam][0] = (int64_t)N[r] * N[c];
             // lower in-face axis first
             const int lo = std::min(r, c);
-            a.face.fs[fam][1] = lo == c ? 1 : N[c];
-            a.face.fs[fam][2] = lo == c ? N[c] : 1;
+            face.fs[fam][1] = lo == c ? 1 : N[c];
+            face.fs[fam][2] = lo == c ? N[c] : 1;
         }
-        a.phi = phi;
-        face = a.face;
-        IPS_HIP(launch_bwrite(a, st));
     } else {
         // d == 2: faces are lines
         const int64_t s0 = n[1];
@@ -1588,15 +1582,18 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             IPS_HIP(launch_cc(a, p->nch[fam], f32s, false, st));
         }
         STAGE(IPS_STAGE_FACES);
-        for (int fam = 0; fam < 2; ++fam) {
-            if (p->cube && fam > 0) break;
-            const int nfam = p->cube ? 2 : 1;
+        // the chunk partials of every face summed in parallel (a face line has
+        // few columns, so a summing load inside the pass would leave most of
+        // the GPU idle), then the inverse transforms in place; the families together
+        ReduceArgs ra{};
+        ra.njobs = p->cube ? 1 : 2;
+        ra.nset = p->cube ? 4 : 2;
+        PassArgs fa[2];
+        for (int fam = 0; fam < ra.njobs; ++fam) {
             const int pen = 1 - fam;
-            // the chunk partials of every face summed in parallel (a face line has
-            // few columns, so a summing load inside the pass would leave most of
-            // the GPU idle), then the inverse transform in place
-            IPS_HIP(launch_reduce(p->part[fam], p->F[fam], N[pen], p->nch[fam], 2 * nfam, st));
-            PassArgs a{};
+            ra.job[fam] = {p->part[fam], p->F[fam], N[pen], p->nch[fam]};
+            PassArgs &a = fa[fam];
+            a = PassArgs{};
             a.in = p->F[fam];
             a.out = p->F[fam];
             a.irs = a.ors = 1;
@@ -1604,27 +1601,22 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.ocs = N[pen];
             a.ibs = a.obs = 0;
             a.nrows_in = N[pen];
-            a.ncols = 2 * nfam;
+            a.ncols = ra.nset;
             a.nbatch = 1;
             a.in_mode = IN_HERM;
             a.out_r0 = 0;
             a.out_nrows = M[pen] + 1;
             a.scale = 1.0 / N[pen];
-            if ((rc = run_pass(p, a, p->fd[pen], p->tw[pen], false, false, st))) return rc;
+            prep_pass(p, a, p->fd[pen], p->tw[pen]);
         }
-        BwriteArgs a{};
-        a.geo = p->geo;
-        for (int q = 0; q < 3; ++q) a.n[q] = q < 2 ? n[q] : 1;
+        IPS_HIP(launch_reduce(ra, st));
+        if ((rc = run_passes(fa, ra.njobs, false, false, st))) return rc;
         for (int fam = 0; fam < 2; ++fam) {
-            a.face.F[fam] = p->F[fam];
-            a.face.fs[fam][0] = N[1 - fam];
-            a.face.fs[fam][1] = 1;
-            a.face.fs[fam][2] = 0;
-            a.face.scale[fam] = p->h[0] * p->h[1];
+            face.F[fam] = p->F[fam];
+            face.fs[fam][0] = N[1 - fam];
+            face.fs[fam][1] = 1;
+            face.scale[fam] = p->h[0] * p->h[1];
         }
-        a.phi = phi;
-        face = a.face;
-        IPS_HIP(launch_bwrite(a, st));
     }
 
     // ---- harmonic part: shell spectra ------------------------------------------------
@@ -1656,6 +1648,9 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
     pk.P2T = p->P2T;
     pk.p2t_f32 = f32;
     pk.withD = 0;
+    pk.mixed = f32;
+    for (int q = 0; q < d; ++q) pk.tab[q] = p->tab[q];
+    pk.rowtab = p->order == 6 ? nullptr : p->rowtab;
     IPS_HIP(launch_pack(pk, st));
     if (p->order == 6) {
         STAGE(IPS_STAGE_SHELL_R6);
@@ -1692,6 +1687,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         IPS_HIP(launch_dcorr(a, st));
         if ((rc = shell_dst_all(p, p->D, 4, false, st))) return rc;
         pk.withD = 1;
+        pk.rowtab = p->rowtab;
         IPS_HIP(launch_pack(pk, st));
     }
     // ---- combination and inverse transforms ------------------------------------------
@@ -1729,7 +1725,6 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         a.rowtab = p->rowtab;
         a.group = final_group(a.W, f32 ? 4 : 8);
         a.pre = p->screen ? 1 : 0; // B already holds the spectrum along axis 0
-        IPS_HIP(launch_final_rows(a, st));
         STAGE(IPS_STAGE_FINAL);
         IPS_HIP(launch_final(a, st));
     }
