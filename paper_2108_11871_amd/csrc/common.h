@@ -88,9 +88,12 @@ inline int rt_width(int N)
 }
 
 // f(RegTile) of the register tile that has N rows and W columns; whether there is
-// one: the default width of every power of two from 256 on, and twice that at the
-// lengths in DOUBLE (512 | 1024), where a kernel measured faster so.
-template <int DOUBLE, typename F>
+// one: the default width of every power of two from 256 on, and those of WIDER (a sum
+// of kWide512, kWide1024: twice the default; kQuad1024: four times), where a kernel
+// measured faster so.
+enum { kWide512 = 1, kWide1024 = 2, kQuad1024 = 4 };
+
+template <int WIDER, typename F>
 inline bool rt_tile(int N, int W, F f)
 {
 #define IPS_RT(...)                                                     \
@@ -99,8 +102,9 @@ inline bool rt_tile(int N, int W, F f)
         return true;                                                    \
     }
     IPS_RT(256) IPS_RT(512) IPS_RT(1024) IPS_RT(2048) IPS_RT(4096) IPS_RT(8192)
-    if constexpr (DOUBLE & 512) IPS_RT(512, 8)
-    if constexpr (DOUBLE & 1024) IPS_RT(1024, 4)
+    if constexpr ((WIDER & kWide512) != 0) IPS_RT(512, 8)
+    if constexpr ((WIDER & kWide1024) != 0) IPS_RT(1024, 4)
+    if constexpr ((WIDER & kQuad1024) != 0) IPS_RT(1024, 8)
 #undef IPS_RT
     return false;
 }

@@ -200,8 +200,10 @@ __global__ __launch_bounds__(NTT) void k_cc(CcArgs a, int nchunk)
 // and sine parts are formed in registers after the last stage and written to the
 // LDS once, sequence by sequence, for the sums over the columns (same thread per
 // slot row and same order of the sums as k_cc; PAIRS: tiles of twice the width whose
-// halves belong to neighbouring chunks, each with its own sums). 257^3: FP64 219/209/214 -> 205/183/185
-// us, FP32 112/124/115 -> 114/118/111 us; 513^3 FP32 1010/1288/1251 -> 709/1237/1258.
+// halves belong to neighbouring chunks, each with its own sums). Bound by LDS (45% of
+// its cycles, half of it conflicts) and the latency of B and K. 257^3: FP64 219/209/214
+// -> 200/180/183 us, FP32 112/124/115 -> 112/115/111 us; 513^3 FP32 1010/1288/1251 ->
+// 726/968/950 (single chunks 709/1237/1258).
 template <typename T, typename TI, typename R, bool WB, bool PAIRS>
 __global__ __launch_bounds__(R::NTH) void k_cc_rt(CcArgs a, int nchunk)
 {

@@ -206,9 +206,10 @@ __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
 // upper rows are the mirror lane's, negated) or IN_HERM. One tile per block: resident
 // blocks that walk the tiles and fetch the next one's inputs ahead measured slower
 // (257^3 FP64 1392 -> 1443 us), the blocks of a CU overlap by themselves. Bound by
-// the latency and the partial cache lines of its strided rows: 257^3 rho_y FP64
-// 123 -> 93 us, inv_y 97 -> 66 us, inv_z 98 -> 60 us (4.4 TB/s), FP32 rho_z 103 ->
-// 102, rho_y 94 -> 83, inv_y 50 -> 35, inv_z 53 -> 46 us.
+// the latency and the partial cache lines of its strided rows: 257^3 FP64 rho_z 140 ->
+// 90 us, rho_y 123 -> 85, inv_y 97 -> 62, inv_z 98 -> 60 us (4.4 TB/s), FP32 rho_z 103 ->
+// 90, rho_y 94 -> 66, inv_y 50 -> 35, inv_z 53 -> 44 us; 513^3 FP32 rho_z 1127 -> 591,
+// rho_y 1124 -> 504, inv_z 522 us (3.1 TB/s).
 template <typename T, typename TI, typename TO, typename R, int MODE>
 __global__ __launch_bounds__(R::NTH) void k_pass_rt(PassArgs a, int ntiles)
 {
@@ -324,7 +325,7 @@ static bool launch_pass_rt(const PassArgs &a, int ntiles, hipStream_t st)
         return false;
     // synthesis keeps rows 0..M
     if (mode != IN_ZPAD && a.out_r0 + a.out_nrows > M + 1) return false;
-    return rt_tile<512 | 1024>(a.fd.N, a.W, [&](auto tile) {
+    return rt_tile<kWide512 + (sizeof(T) == 4 ? kWide1024 + kQuad1024 : kWide1024)>(a.fd.N, a.W, [&](auto tile) {
         using R = decltype(tile);
         if (mode == IN_ZPAD)
             launch_pass_rt_m<T, TI, TO, R, IN_ZPAD>(a, ntiles, st);

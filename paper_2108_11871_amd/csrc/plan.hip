@@ -457,19 +457,23 @@ int run_pass(ips_plan p, PassArgs a, const FftDesc &fd, const cx<double> *tw, bo
 }
 
 // Tile width of the passes between a contiguous and a strided side (rho along z and
-// y, the adjoint's last one), 0 for the plan's default: double-width register tiles
-// at 2M = 512 and 1024, whose rows of 16 and 8 columns reach more of the strided
-// lines at once, where enough blocks are left. rho_z and rho_y together, default ->
-// double: 257^3 FP64 1305 -> 1270 us of the solve, mixed FP32 902 -> 884; 513^3 mixed
-// FP32 7559 -> 7247, FP64 10766 -> 10670; the adjoint's pass at 2M = 512 3888 -> 3842
-// (at 1024 0.5 ms slower, so not there). inv_y, inv_z and the final pass gain nothing.
-// FP32 tiles of the lengths from 1024 on without register tiles take twice the plan's
-// budget.
+// y, the adjoint's last one), 0 for the plan's default: wider register tiles at 2M =
+// 512 and 1024, whose rows of 16 and 8 columns (FP32 at 1024: 16) reach more of the
+// strided lines at once, where enough blocks are left. rho_z and rho_y together,
+// default -> double: 257^3 FP64 1305 -> 1270 us of the solve, mixed FP32 902 -> 884;
+// 513^3 mixed FP32 7559 -> 7247, FP64 10766 -> 10670; FP32 at 1024 double -> four times
+// 6600 -> 6320 (513^3 rho_z 791 -> 591, rho_y 586 -> 504). The adjoint's pass at 2M =
+// 512 3888 -> 3842 (at 1024 0.5 ms slower, so not there). inv_y, inv_z and the final
+// pass gain nothing. FP32 tiles of the lengths from 1024 on without register tiles
+// take twice the plan's budget.
 int wide_width(ips_plan p, int N, int ncols, int nbatch, bool f32)
 {
     if (N == 512 || N == 1024) {
-        const int W = tile_width(N, 4096, ncols);
-        if (p->work == 2048 && W * N == 8192 && (int64_t)nbatch * (ncols / W) >= 4 * kFillPass) return W;
+        if (p->work != 2048) return 0;
+        for (int wide = N == 1024 && f32 ? 4 : 2; wide > 1; wide /= 2) {
+            const int W = tile_width(N, 2048 * wide, ncols);
+            if (W * N == 4096 * wide && (int64_t)nbatch * (ncols / W) >= 4 * kFillPass) return W;
+        }
         return 0;
     }
     if (!f32 || N < 1024 || N > kLdsMaxN || 2 * p->work > 4096 || (N & (N - 1)) == 0) return 0;
@@ -478,8 +482,8 @@ int wide_width(ips_plan p, int N, int ncols, int nbatch, bool f32)
 
 // Width of an interleaved contraction: FP32 tiles at 2M = 1024 take two neighbouring
 // chunks at once, for rows of 2 x 4 columns of the strided input (513^3 mixed: 7250
-// -> 6640 us of the solve; FP64 10660 -> 12260, so not there, and at 2M = 512, whose
-// rows are as long with single chunks, 3% slower).
+// -> 6640 us of the solve; four chunks 6930; FP64 10660 -> 12260, so not there, and at
+// 2M = 512, whose rows are as long with single chunks, 3% slower).
 void pair_chunks(ips_plan p, CcArgs &a, int fam, bool f32)
 {
     a.W = p->ccW[fam];

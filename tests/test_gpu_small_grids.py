@@ -68,11 +68,13 @@ def test_register_tiles(shape, mode, tol):
     assert rel_err(phi.cpu().numpy(), P.solve(rho, h, 6, boundary="fft")) < tol
 
 
-# double-width register tiles: rho along z and along y at 2M = 512 and 1024 (enough
-# blocks for them, ragged columns), contractions of two chunks per tile at 2M = 1024
+# wider register tiles: rho along z and along y at 2M = 512 and 1024 (enough blocks for
+# twice and, in FP32, four times the default, ragged columns), contractions of two
+# chunks per tile at 2M = 1024
 # with an odd number of chunks and an even one
 @pytest.mark.parametrize("mode,tol", [("fp64", TOL), ("mixed_fp32", 1e-6), ("mixed_fp32_slices", 1e-6)])
-@pytest.mark.parametrize("shape", [(131, 131, 257), (131, 257, 132), (129, 75, 513), (513, 37, 65), (513, 34, 66)])
+@pytest.mark.parametrize("shape", [(131, 131, 257), (131, 257, 132), (129, 75, 513), (129, 150, 513),
+                                   (513, 37, 65), (513, 34, 66)])
 def test_double_width_tiles(shape, mode, tol):
     import torch
     from paper_2108_11871_amd import api
