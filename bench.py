@@ -283,13 +283,13 @@ print(json.dumps(out))
 
 # stage -> (kernel-name substring, occurrence within one solve) in dispatch order
 STAGE_DISPATCH = {
-    "final": ("k_final<", 0),
+    "final": ("k_final", 0),
     "conv_x": ("k_cc", 0),
     "conv_y": ("k_cc", 1),
     "conv_z": ("k_cc", 2),
     # the two forward slot passes of rho (FP64 in, FP32 slots: the mixed-slices mode)
-    "rho_z": ("k_pass<float, double, float", 0),
-    "rho_y": ("k_pass<float, double, float", 1),
+    "rho_z": ("<float, double, float", 0),
+    "rho_y": ("<float, double, float", 1),
 }
 
 
@@ -326,7 +326,7 @@ def ingest_traffic(fetch_csv, write_csv, n, mode, mib, cmd):
                 per.setdefault(stage, {})[cname] = hits[occ]["v"] * 1024.0 * factor
         # the whole last solve: from the forward pass of rho before its first
         # contraction to the two inverse passes after its final pass
-        last = max(i for i, e in enumerate(d) if "k_final<" in e["name"])
+        last = max(i for i, e in enumerate(d) if "k_final" in e["name"])
         first = last
         while first > 0 and "k_cc" not in d[first]["name"]:
             first -= 1
@@ -374,7 +374,7 @@ def ingest_counters(csv_a, csv_b, title, cmd, out_name, cu=256, xcd=8):
 
     a, b = load(csv_a), load(csv_b)
     # the last solve: from the last rho_z-style forward pass of k_pass before the final k_final
-    last_final = max(i for i, e in enumerate(a) if "k_final<" in e["name"])
+    last_final = max(i for i, e in enumerate(a) if "k_final" in e["name"])
     first = last_final
     while first > 0 and "k_cc" not in a[first]["name"]:
         first -= 1

@@ -250,7 +250,9 @@ int ips_execute_static(ips_plan p, const double *rho, double *phi, void *stream)
  * Used for gradients: if J depends on phi, dJ/drho = A^T dJ/dphi.
  * Buffers: a plan created with IPS_FLAG_ADJOINT keeps them in its workspace;
  * otherwise the first adjoint call allocates them (later calls allocate
- * nothing).  About four interior volumes plus two grids (order 6) in FP64.
+ * nothing).  FP64: about three interior volumes (one of them the slice stack of
+ * the boundary expansion, 2 M per axis); mixed modes (order 6): two volumes and
+ * two grids more.
  */
 #define IPS_FLAG_ADJOINT 2u
 
