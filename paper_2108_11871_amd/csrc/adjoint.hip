@@ -991,7 +991,7 @@ __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
     }
     __syncthreads();
     pre_herm<double, MAXE, NTT>(buf, rs, lgs, M, false);
-    fft_tile<double, MAXE, NTT, KD>(buf, rs, lgs, a.fd, tw, true);
+    fft_tile<double, MAXE, NTT, KD, false>(buf, rs, lgs, a.fd, tw, true);
     double *out = a.out + (int64_t)bt * a.obs + (int64_t)c0 * a.ocs;
     if (a.accum)
         tile_store_acc<double, double, NTT>(buf, rs, 1, out, M - 1, nc, a.ors, a.ocs, a.scale, lgW);

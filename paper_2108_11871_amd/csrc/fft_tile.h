@@ -511,12 +511,9 @@ __device__ __forceinline__ void stage_other(T *buf, int rs, int lgs, const FftDe
 // N, radix R, product of the earlier radices NS (a power of two), row pitch
 // RS and 2^LGS sequences.  Same data movement as stage_bfly; the index and
 // twiddle arithmetic folds to shifts and constants.
-// Z: the inputs of rows N/2..N-1 are zero (first stage, radix 8, of a
-// zero-padded sequence): they are not loaded, and the butterfly skips them.
-template <typename T, int R, int NT, int N, int NS, int RS, int LGS, bool INV, bool Z = false>
+template <typename T, int R, int NT, int N, int NS, int RS, int LGS, bool INV>
 __device__ __forceinline__ void stage_ct(T *buf, const cx<T> *tw, int tid)
 {
-    static_assert(!Z || (R == 8 && NS == 1), "the zero upper half applies to a first radix-8 stage");
     constexpr int NR = N / R, NBF = NR << LGS, TSTEP = N / (NS * R), SMASK = (1 << LGS) - 1;
     constexpr int BPT = (NBF + NT - 1) / NT;
     cx<T> v[BPT][R];
@@ -528,20 +525,14 @@ __device__ __forceinline__ void stage_ct(T *buf, const cx<T> *tw, int tid)
             const int sq = b & SMASK, j = b >> LGS;
             const int jm = j & (NS - 1);
             base[i] = (j - jm) * R + jm;
-            if constexpr (Z) {
 #pragma unroll
-                for (int r = 0; r < R / 2; ++r) v[i][r] = lds_c(buf, RS, j + r * NR, sq);
-                dft8_lower<T, INV>(v[i]);
-            } else {
+            for (int r = 0; r < R; ++r) v[i][r] = lds_c(buf, RS, j + r * NR, sq);
+            if (NS > 1 && jm != 0) {
+                const int e = jm * TSTEP;
 #pragma unroll
-                for (int r = 0; r < R; ++r) v[i][r] = lds_c(buf, RS, j + r * NR, sq);
-                if (NS > 1 && jm != 0) {
-                    const int e = jm * TSTEP;
-#pragma unroll
-                    for (int r = 1; r < R; ++r) v[i][r] = cmul(v[i][r], twid<T, INV>(tw, e * r));
-                }
-                dft_small<T, R, INV>(v[i], tw, N);
+                for (int r = 1; r < R; ++r) v[i][r] = cmul(v[i][r], twid<T, INV>(tw, e * r));
             }
+            dft_small<T, R, INV>(v[i], tw, N);
         }
     }
     __syncthreads();
@@ -563,20 +554,19 @@ __device__ __forceinline__ void stage_ct(T *buf, const cx<T> *tw, int tid)
 // may pass one the compiler cannot see through, so that the per-thread index
 // and twiddle values are recomputed for each transform instead of being held
 // in registers across the loop).
-// Z: the upper half of the inputs is zero (see stage_ct).
-template <typename T, int NT, int N, int RS, int LGS, bool INV, bool Z = false>
+template <typename T, int NT, int N, int RS, int LGS, bool INV>
 __device__ __forceinline__ void fft_ct(T *buf, const cx<T> *tw, int tid)
 {
     if constexpr (N == 256) {
-        stage_ct<T, 8, NT, N, 1, RS, LGS, INV, Z>(buf, tw, tid);
+        stage_ct<T, 8, NT, N, 1, RS, LGS, INV>(buf, tw, tid);
         stage_ct<T, 8, NT, N, 8, RS, LGS, INV>(buf, tw, tid);
         stage_ct<T, 4, NT, N, 64, RS, LGS, INV>(buf, tw, tid);
     } else if constexpr (N == 512) {
-        stage_ct<T, 8, NT, N, 1, RS, LGS, INV, Z>(buf, tw, tid);
+        stage_ct<T, 8, NT, N, 1, RS, LGS, INV>(buf, tw, tid);
         stage_ct<T, 8, NT, N, 8, RS, LGS, INV>(buf, tw, tid);
         stage_ct<T, 8, NT, N, 64, RS, LGS, INV>(buf, tw, tid);
     } else if constexpr (N == 1024) {
-        stage_ct<T, 8, NT, N, 1, RS, LGS, INV, Z>(buf, tw, tid);
+        stage_ct<T, 8, NT, N, 1, RS, LGS, INV>(buf, tw, tid);
         stage_ct<T, 8, NT, N, 8, RS, LGS, INV>(buf, tw, tid);
         stage_ct<T, 8, NT, N, 64, RS, LGS, INV>(buf, tw, tid);
         stage_ct<T, 2, NT, N, 512, RS, LGS, INV>(buf, tw, tid);
@@ -907,18 +897,17 @@ __device__ __forceinline__ void rt_fetch(TI (&x)[8], const TI *src, int64_t rsd,
 // direction INV (false: exp(-2 pi i t/N), true: the conjugate).
 // KD: the radices that are compiled in (LenKind; a kernel for fewer of them holds
 // fewer registers).
-// CT = false keeps the generic stages only.  tid: see fft_ct.
-// Z: the upper half of the inputs is zero; the compile-time transforms skip
-// it in their first stage, the generic ones read the zeros.
-template <typename T, int MAXE, int NT, int KD, bool CT, bool INV, bool Z = false>
+// CT = false keeps the generic stages only (kernels whose full tiles of the powers of
+// two are register tiles).  tid: see fft_ct.
+template <typename T, int MAXE, int NT, int KD, bool CT, bool INV>
 __device__ __forceinline__ void fft_tile_dir(T *buf, int rs, int lgs, const FftDesc &fd, const cx<T> *tw, int tid)
 {
     if constexpr (KD == kPow2 && CT && NT == 256) {
         // (N, tile width) pairs of the default tile budget: N * W / 2 = MAXE * NT
         if constexpr (MAXE == 8) {
-            if (fd.N == 512 && rs == 9) return fft_ct<T, NT, 512, 9, 2, INV, Z>(buf, tw, tid);
-            if (fd.N == 256 && rs == 17) return fft_ct<T, NT, 256, 17, 3, INV, Z>(buf, tw, tid);
-            if (fd.N == 1024 && rs == 5) return fft_ct<T, NT, 1024, 5, 1, INV, Z>(buf, tw, tid);
+            if (fd.N == 512 && rs == 9) return fft_ct<T, NT, 512, 9, 2, INV>(buf, tw, tid);
+            if (fd.N == 256 && rs == 17) return fft_ct<T, NT, 256, 17, 3, INV>(buf, tw, tid);
+            if (fd.N == 1024 && rs == 5) return fft_ct<T, NT, 1024, 5, 1, INV>(buf, tw, tid);
         }
     }
     if constexpr (KD == kPow2) {
@@ -964,16 +953,6 @@ __device__ __forceinline__ void fft_tile(T *buf, int rs, int lgs, const FftDesc 
         fft_tile_dir<T, MAXE, NT, KD, CT, true>(buf, rs, lgs, fd, tw, tid);
     else
         fft_tile_dir<T, MAXE, NT, KD, CT, false>(buf, rs, lgs, fd, tw, tid);
-}
-
-// Forward transform of zero-padded sequences: rows N/2..N-1 of the tile must
-// hold zeros (the generic stages read them); tid: see fft_ct.
-template <typename T, int MAXE, int NT, int KD = kAnyLen, bool CT = true>
-__device__ __forceinline__ void fft_tile_zpad(T *buf, int rs, int lgs, const FftDesc &fd, const cx<T> *tw,
-                                              int tid = -1)
-{
-    if (tid < 0) tid = threadIdx.x;
-    fft_tile_dir<T, MAXE, NT, KD, CT, false, true>(buf, rs, lgs, fd, tw, tid);
 }
 
 // After a forward zero-padded FFT: write C and S in slot layout (in place).

@@ -1258,12 +1258,7 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
     for (int i = tid; i < nc; i += NTT) final_col(a, c0 + i, kB, cv + i * SV);
     __syncthreads();
     // forward transform of the zero-padded rows 1..M0-1 (unless B already holds the spectrum)
-    if (!a.pre) {
-        if (a.nrows_in <= M - 1)
-            fft_tile_zpad<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, tid);
-        else
-            fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, false, tid);
-    }
+    if (!a.pre) fft_tile<T, MAXE, NTT, KD, false>(buf, rs, lgs, fd, tw, false, tid);
     // One sweep over the row pairs (k, N-k) of every complex sequence s
     // (real columns 2s and 2s+1):
     //   sine coefficients  S_a = (z(N-k).y - z(k).y)/2,  S_b = (z(k).x - z(N-k).x)/2
@@ -1315,7 +1310,7 @@ __global__ __launch_bounds__(NTT) void k_final(FinalArgs a, int ntiles)
         }
     }
     __syncthreads();
-    fft_tile<T, MAXE, NTT, KD>(buf, rs, lgs, fd, tw, true, tid);
+    fft_tile<T, MAXE, NTT, KD, false>(buf, rs, lgs, fd, tw, true, tid);
     tile_store<T, T, NTT>(buf, rs, 1, g, a.nrows_in, nc, a.irs, a.ics, (T)0.5, lgW, tid);
     if constexpr (!PF) break; // one tile per block: no loop for the compiler to hoist out of
     __syncthreads();          // the next tile reuses the LDS
