@@ -204,7 +204,7 @@ int ips_plan_create_extended(ips_plan *out, int d, const int64_t *n, const doubl
  * stream).  Returns once the work is enqueued; it allocates nothing and
  * performs no host synchronisation, so it may be captured in a hipGraph.
  * rho and phi as in ips_solve; they must stay valid until the stream has
- * executed the work.
+ * executed the work.  Until then phi may hold intermediate values.
  */
 int ips_execute(ips_plan p, const double *rho, double *phi, void *stream);
 
@@ -250,9 +250,12 @@ int ips_execute_static(ips_plan p, const double *rho, double *phi, void *stream)
  * Used for gradients: if J depends on phi, dJ/drho = A^T dJ/dphi.
  * Buffers: a plan created with IPS_FLAG_ADJOINT keeps them in its workspace;
  * otherwise the first adjoint call allocates them (later calls allocate
- * nothing).  FP64: about three interior volumes (one of them the slice stack of
- * the boundary expansion, 2 M per axis); mixed modes (order 6): two volumes and
- * two grids more.
+ * nothing).  FP64: two interior volumes and for every pair of faces their weights
+ * and slot spectra (2 (M + 1)^2 + 8 M^2 doubles at equal panel counts M); 3D also the
+ * slice stack of the boundary expansion, about two volumes.  The shell layers of order
+ * 6 lie in those of the forward solve, or, where the first call allocates, in the
+ * slice stack (24 layers per axis, which can exceed it on thin boxes).  Mixed modes,
+ * order 6: one volume and two grids more.
  */
 #define IPS_FLAG_ADJOINT 2u
 

@@ -264,6 +264,7 @@ struct ips_plan_s {
     void *A = nullptr; // slot transforms of rho along one axis (3D)
     void *B = nullptr; // raw DST of rho along the last d-1 axes, then phi in sine space
     double *part[3] = {nullptr, nullptr, nullptr};
+    bool part_phi[3] = {false, false, false}; // chunk partials in phi (see plan_chunks)
     int nch[3] = {1, 1, 1};
     int ccW[3] = {2, 2, 2}; // tile widths of the column contractions
     int chunk[3] = {1, 1, 1};
@@ -297,8 +298,9 @@ struct ips_plan_s {
     double *PA[3] = {nullptr, nullptr, nullptr}, *PB[3] = {nullptr, nullptr, nullptr};
     double *QA[3] = {nullptr, nullptr, nullptr}, *QB[3] = {nullptr, nullptr, nullptr};
     DevBuf mem;   // tables: twiddles, axis tables, kernel spectra (and an extended plan's arrays)
-    // execution workspace: one block carved into the buffers above (B, A, part, F,
-    // G, P, T, D, C, P1T, P2T, rowtab) and, for IPS_FLAG_ADJOINT plans, the adjoint's
+    // execution workspace: one block carved into the buffers above (B, A, F, and on
+    // common ground part and the shell's rowtab, G, P, T, D, C, P1T, P2T) and, for
+    // IPS_FLAG_ADJOINT plans, the adjoint's
     size_t ws_bytes = 0;  // bytes the carving needs
     void *ws = nullptr;   // bound block (plan-owned or the caller's), nullptr: none
     bool ws_adj = false;  // the adjoint buffers are part of the workspace
@@ -620,24 +622,86 @@ struct Carver {
 
 void layout_adj(ips_plan p, Carver &c);
 
+// In-face sizes of family fam: slots of its two faces, interior nodes of one.
+void family_sizes(ips_plan p, int fam, size_t &slots, size_t &nodes)
+{
+    slots = 2;
+    nodes = 1;
+    for (int b = 0; b < p->d; ++b)
+        if (b != fam) {
+            slots *= (size_t)p->N[b];
+            nodes *= (size_t)p->I[b];
+        }
+}
+
+// Chunk partials of family fam (doubles).
+size_t part_size(ips_plan p, int fam)
+{
+    size_t slots, nodes;
+    family_sizes(p, fam, slots, nodes);
+    return slots * p->nch[fam];
+}
+
+// The buffers of the harmonic part and the final pass's row table: written after the
+// chunk partials have been read.
+void layout_shell(ips_plan p, Carver &c)
+{
+    const int d = p->d;
+    size_t ssz[3] = {0, 0, 0}, ts = 0;
+    for (int fam = 0; fam < d; ++fam) {
+        size_t slots;
+        family_sizes(p, fam, slots, ssz[fam]);
+        ts += ssz[fam];
+    }
+    c.take(&p->rowtab, (d == 3 ? (size_t)p->I[2] : 1) * p->I[0] * 12 * sizeof(double));
+    // one contiguous buffer per kind (families back to back)
+    double *bg, *bpk, *bt = nullptr, *bd = nullptr, *bc = nullptr;
+    c.take(&bg, 2 * ts * sizeof(double));
+    c.take(&bpk, 6 * ts * sizeof(double));
+    p->r6part = nullptr;
+    if (p->order == 6) {
+        c.take(&bt, 10 * ts * sizeof(double));
+        c.take(&bd, 4 * ts * sizeof(double));
+        c.take(&bc, 8 * ts * sizeof(double));
+        const int ks = r6t_splits(p->geo);
+        if (ks > 1) c.take(&p->r6part, (size_t)ks * 10 * ts * sizeof(double));
+    }
+    for (int fam = 0; fam < 3; ++fam) {
+        p->G[fam] = p->P[fam] = p->T[fam] = p->D[fam] = p->C[fam] = nullptr;
+        p->Tf[fam] = nullptr;
+    }
+    size_t os = 0;
+    for (int fam = 0; fam < d && c.base; ++fam) {
+        p->G[fam] = bg + 2 * os;
+        p->P[fam] = bpk + 6 * os;
+        if (bt) {
+            p->T[fam] = bt + 10 * os;
+            p->Tf[fam] = reinterpret_cast<float *>(bt) + 10 * os;
+        }
+        if (bd) p->D[fam] = bd + 4 * os;
+        if (bc) p->C[fam] = bc + 8 * os;
+        os += ssz[fam];
+    }
+    if (d == 3) {
+        c.take(&p->P1T, 6 * ssz[1] * sizeof(double));
+        c.take(&p->P2T, 6 * ssz[2] * sizeof(double));
+    }
+}
+
 // The execution workspace of a plan (everything one solve writes besides phi):
-// the sine-space volume B, the slot array A, the chunk partials, face values,
-// shell layers, the final pass's row table and, for plans with ws_adj, the
-// adjoint's buffers.  Assigns the plan's pointers from c.base.
+// the sine-space volume B, the slot array A, the face values, the chunk partials and,
+// in the same place, the shell layers and the final pass's row table and, for plans
+// with ws_adj, the adjoint's buffers.  Assigns the plan's pointers from c.base.
 void layout_ws(ips_plan p, Carver &c)
 {
     const int d = p->d;
     if (d == 1) return;
     const int *I = p->I, *M = p->M, *N = p->N;
-    size_t vol = 1, grid = 1;
-    for (int a = 0; a < d; ++a) {
-        vol *= (size_t)I[a];
-        grid *= (size_t)p->n[a];
-    }
+    size_t vol = 1;
+    for (int a = 0; a < d; ++a) vol *= (size_t)I[a];
     const size_t wsz = p->precision != IPS_FP64 ? sizeof(float) : sizeof(double);
     const size_t asz = p->precision == IPS_MIXED_FP32_SLICES ? sizeof(float) : sizeof(double);
     c.take(&p->B, vol * wsz);
-    c.take(&p->rowtab, (d == 3 ? (size_t)I[2] : 1) * I[0] * 12 * sizeof(double));
     if (p->screen) {
         // no slice transforms or chunk partials: the face coefficients of the
         // screening charge and the surface node list instead
@@ -690,67 +754,43 @@ void layout_ws(ips_plan p, Carver &c)
     } else {
         p->A = nullptr;
     }
-    // per-family sizes, one contiguous buffer per kind (families back to back)
-    size_t fsz[3] = {0, 0, 0}, ssz[3] = {0, 0, 0};
-    size_t tp = 0, tf = 0, ts = 0;
+    // (families back to back)
+    double *bp = nullptr, *bf = nullptr;
+    size_t tp = 0, tf = 0;
     for (int fam = 0; fam < d; ++fam) {
-        fsz[fam] = 2;
-        ssz[fam] = 1;
-        for (int b = 0; b < d; ++b)
-            if (b != fam) {
-                fsz[fam] *= (size_t)N[b];
-                ssz[fam] *= (size_t)I[b];
-            }
-        tp += fsz[fam] * p->nch[fam];
-        tf += fsz[fam];
-        ts += ssz[fam];
+        size_t slots, nodes;
+        family_sizes(p, fam, slots, nodes);
+        tp += p->part_phi[fam] ? 0 : part_size(p, fam);
+        tf += slots;
     }
-    double *bp = nullptr, *bf = nullptr, *bg, *bpk, *bt = nullptr, *bd = nullptr, *bc = nullptr;
-    if (!p->screen) {
-        c.take(&bp, tp * sizeof(double));
-        c.take(&bf, tf * sizeof(double));
-    }
-    c.take(&bg, 2 * ts * sizeof(double));
-    c.take(&bpk, 6 * ts * sizeof(double));
-    p->r6part = nullptr;
-    if (p->order == 6) {
-        c.take(&bt, 10 * ts * sizeof(double));
-        c.take(&bd, 4 * ts * sizeof(double));
-        c.take(&bc, 8 * ts * sizeof(double));
-        const int ks = r6t_splits(p->geo);
-        if (ks > 1) c.take(&p->r6part, (size_t)ks * 10 * ts * sizeof(double));
-    }
-    size_t op = 0, of = 0, os = 0;
+    if (!p->screen) c.take(&bf, tf * sizeof(double));
+    Carver sh = c;
+    if (!p->screen) c.take(&bp, tp * sizeof(double));
+    layout_shell(p, sh);
+    c.off = std::max(c.off, sh.off);
+    size_t op = 0, of = 0;
     for (int fam = 0; fam < 3; ++fam) {
-        p->part[fam] = p->F[fam] = p->G[fam] = p->P[fam] = p->T[fam] = p->D[fam] = p->C[fam] = nullptr;
-        p->Tf[fam] = nullptr;
-    }
-    if (c.base)
-        for (int fam = 0; fam < d; ++fam) {
-            p->part[fam] = bp ? bp + op : nullptr;
-            p->F[fam] = bf ? bf + of : nullptr;
-            p->G[fam] = bg + 2 * os;
-            p->P[fam] = bpk + 6 * os;
-            if (bt) {
-                p->T[fam] = bt + 10 * os;
-                p->Tf[fam] = reinterpret_cast<float *>(bt) + 10 * os;
-            }
-            if (bd) p->D[fam] = bd + 4 * os;
-            if (bc) p->C[fam] = bc + 8 * os;
-            op += fsz[fam] * p->nch[fam];
-            of += fsz[fam];
-            os += ssz[fam];
+        p->part[fam] = p->F[fam] = nullptr;
+        if (fam >= d) continue;
+        if (bp && !p->part_phi[fam]) {
+            p->part[fam] = bp + op;
+            op += part_size(p, fam);
         }
-    if (d == 3) {
-        c.take(&p->P1T, 6 * ssz[1] * sizeof(double));
-        c.take(&p->P2T, 6 * ssz[2] * sizeof(double));
+        if (bf) {
+            size_t slots, nodes;
+            family_sizes(p, fam, slots, nodes);
+            p->F[fam] = bf + of;
+            of += slots;
+        }
     }
     if (p->ws_adj) layout_adj(p, c);
 }
 
-// The adjoint's buffers: two interior volumes, the shell arrays (FP64) or another
-// volume and two grids (mixed modes, order 6), face weights and their spectra, and
-// one slice stack (3D).
+// The adjoint's buffers: two interior volumes, another volume and two grids (mixed
+// modes, order 6), face weights and their spectra, and one slice stack (3D). The FP64
+// shell arrays lie in the forward solve's shell layers, which hold nothing between two
+// calls (plans with ws_adj), or in the slice stack, which is written after their last
+// use; the packed spectra Tp take the place of the layers Db and Cb.
 void layout_adj(ips_plan p, Carver &c)
 {
     const int d = p->d;
@@ -762,34 +802,13 @@ void layout_adj(ips_plan p, Carver &c)
     }
     c.take(&p->AX, vol * sizeof(double));
     c.take(&p->AY, vol * sizeof(double));
-    const bool shell = p->precision == IPS_FP64;
-    if (shell) {
-        // families back to back, as the forward solve's shell layers
-        size_t ss[3] = {0, 0, 0}, ts = 0;
-        for (int fam = 0; fam < d; ++fam) ts += ss[fam] = vol / I[fam];
-        auto take = [&](double **arr, int nl) {
-            double *blk;
-            c.take(&blk, nl * ts * sizeof(double));
-            size_t os = 0;
-            for (int fam = 0; fam < d; ++fam) {
-                arr[fam] = blk ? blk + nl * os : nullptr;
-                os += ss[fam];
-            }
-        };
-        take(p->ash.Gb, 2);
-        if (p->order == 6) {
-            take(p->ash.Db, 4);
-            take(p->ash.Rb, 10);
-            take(p->ash.Cb, 8);
-            take(p->ash.Tp, 10);
-            take(p->ash.Z, 2);
-        }
-    } else if (p->order == 6) {
+    const bool shell = p->precision == IPS_FP64, own = shell && !p->ws_adj;
+    if (!shell && p->order == 6) {
         c.take(&p->AX2, vol * sizeof(double));
         c.take(&p->AF, grid * sizeof(double));
         c.take(&p->AU, grid * sizeof(double));
     }
-    size_t zmax = 0;
+    size_t zmax = 0, ts = 0;
     for (int fam = 0; fam < d; ++fam) {
         int b, cc;
         kaxes(d, fam, b, cc);
@@ -798,10 +817,34 @@ void layout_adj(ips_plan p, Carver &c)
         c.take(&p->LF[fam], lf * sizeof(double));
         c.take(&p->LH[fam], lh * sizeof(double));
         if (d == 3) zmax = std::max(zmax, (size_t)I[fam] * N[b] * I[cc]);
+        ts += vol / I[fam];
     }
     // order 6 also uses it as one grid-shaped scratch array (adjoint stencil)
     if (d == 3 && p->order == 6 && !shell) zmax = std::max(zmax, grid);
-    if (d == 3) c.take(&p->AZ, zmax * sizeof(double));
+    if (own) zmax = std::max(zmax, (p->order == 6 ? 24 : 2) * ts);
+    if (d == 3 || own) c.take(&p->AZ, zmax * sizeof(double));
+    if (!shell || !c.base) return;
+    size_t os = 0;
+    for (int fam = 0; fam < d; ++fam) {
+        AdjShell &s = p->ash;
+        if (own) {
+            // [Db 4 | Cb 8 | Rb 10 | Z 2], families back to back in each
+            s.Db[fam] = p->AZ + 4 * os;
+            s.Cb[fam] = p->AZ + 4 * ts + 8 * os;
+            s.Rb[fam] = p->AZ + (p->order == 6 ? 12 * ts : 0) + 10 * os;
+            s.Z[fam] = p->AZ + 22 * ts + 2 * os;
+            s.Gb[fam] = p->AZ + (p->order == 6 ? 12 * ts : 0) + 2 * os;
+        } else {
+            s.Db[fam] = p->D[fam];
+            s.Cb[fam] = p->C[fam];
+            s.Rb[fam] = p->T[fam];
+            s.Z[fam] = p->P[fam]; // (two of its six layers)
+            s.Gb[fam] = p->G[fam];
+        }
+        // ten layers where the twelve of Db and Cb, consecutive buffers, were
+        s.Tp[fam] = p->order == 6 ? s.Db[0] + 10 * os : nullptr;
+        os += vol / I[fam];
+    }
 }
 
 // Point the plan's buffers into `base` (size checked by the caller), or
@@ -824,6 +867,67 @@ size_t measure_ws(ips_plan p)
     Carver c;
     layout_ws(p, c);
     return p->d == 1 ? 0 : c.off;
+}
+
+// Chunks of the contraction over the face-normal axis of every family, with tiles of
+// at least wmin columns (0: not narrowed).
+void chunk_families(ips_plan p, int wmin)
+{
+    const int *I = p->I, *N = p->N, d = p->d;
+    for (int fam = 0; fam < d; ++fam) {
+        int pen, nbatch;
+        if (d == 3) {
+            pen = fam == 0 ? 1 : 0;
+            nbatch = fam == 2 ? N[1] : N[2];
+        } else {
+            pen = 1 - fam;
+            nbatch = 1;
+        }
+        // a tile holds W/2 columns of the first half of the axis and their
+        // mirrors: the chunks split the (I + 1)/2 first-half columns
+        const int W = p->ccW[fam] = wmin > 0 ? fill_width(N[pen], p->work, I[fam], nbatch, kFillConv, wmin)
+                                             : tile_width(N[pen], p->work, I[fam]);
+        const int hc = (I[fam] + 1) / 2, Wh = W / 2;
+        const int ncb = (hc + Wh - 1) / Wh;
+        // about 4096 (2M <= 512) or 6144 blocks of 256 threads, a few tiles
+        // each (more chunks give more blocks but more partials for the face
+        // pass to sum); 256 blocks of 1024 for long transforms
+        const int target = N[pen] > kLdsMaxN ? 256 : cc_block_target(N[pen]);
+        int nch = std::max(1, std::min(ncb, (target + nbatch - 1) / nbatch));
+        const int per = (ncb + nch - 1) / nch;
+        p->chunk[fam] = per * Wh;
+        p->nch[fam] = (hc + per * Wh - 1) / (per * Wh);
+    }
+}
+
+// Tile widths and chunks of the contractions. Narrowed tiles mean more chunks, whose
+// partials must not raise the workspace above what whole tiles and a shell area of their
+// own would take: they share the shell area's place, then families go to phi, which a
+// solve writes only after the last partial is read, then tiles get wider. (Mixed modes
+// keep the widths of whole tiles, and with them the order of the FP64 sums.)
+void plan_chunks(ips_plan p)
+{
+    const int d = p->d;
+    chunk_families(p, 0);
+    if (p->precision != IPS_FP64) return;
+    Carver sh;
+    layout_shell(p, sh);
+    size_t room = sh.off / sizeof(double), grid = 1;
+    for (int fam = 0; fam < d; ++fam) {
+        room += part_size(p, fam);
+        grid *= (size_t)p->n[fam];
+    }
+    for (int wmin = 4;; wmin *= 2) {
+        chunk_families(p, wmin);
+        size_t ws = 0, ph = 0;
+        for (int fam = 0; fam < d; ++fam) ws += part_size(p, fam);
+        for (int fam = 0; fam < d; ++fam) {
+            const size_t sz = part_size(p, fam);
+            p->part_phi[fam] = ws > room && ph + sz <= grid;
+            if (p->part_phi[fam]) ws -= sz, ph += sz;
+        }
+        if (ws <= room) return;
+    }
 }
 
 int plan_build(ips_plan p, hipStream_t st)
@@ -872,33 +976,7 @@ int plan_build(ips_plan p, hipStream_t st)
 
     const int *I = p->I, *M = p->M, *N = p->N;
     int rc;
-    for (int fam = 0; fam < d; ++fam) {
-        // chunking of the contraction over the face-normal axis (column-contraction kernel)
-        int pen, nbatch;
-        if (d == 3) {
-            pen = fam == 0 ? 1 : 0;
-            nbatch = fam == 2 ? N[1] : N[2];
-        } else {
-            pen = 1 - fam;
-            nbatch = 1;
-        }
-        // a tile holds W/2 columns of the first half of the axis and their
-        // mirrors: the chunks split the (I + 1)/2 first-half columns
-        // (mixed modes keep the widths, and with them the order of the FP64 sums)
-        const int W = p->ccW[fam] = p->precision == IPS_FP64
-                                        ? fill_width(N[pen], p->work, I[fam], nbatch, kFillConv, 4)
-                                        : tile_width(N[pen], p->work, I[fam]);
-        const int hc = (I[fam] + 1) / 2, Wh = W / 2;
-        const int ncb = (hc + Wh - 1) / Wh;
-        // about 4096 (2M <= 512) or 6144 blocks of 256 threads, a few tiles
-        // each (more chunks give more blocks but more partials for the face
-        // pass to sum); 256 blocks of 1024 for long transforms
-        const int target = N[pen] > kLdsMaxN ? 256 : cc_block_target(N[pen]);
-        int nch = std::max(1, std::min(ncb, (target + nbatch - 1) / nbatch));
-        const int per = (ncb + nch - 1) / nch;
-        p->chunk[fam] = per * Wh;
-        p->nch[fam] = (hc + per * Wh - 1) / (per * Wh);
-    }
+    plan_chunks(p);
     // uniform families: one launch covers the three (two in 2D) families
     p->cube = true;
     for (int fam = 1; fam < d; ++fam)
@@ -1358,6 +1436,17 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         return IPS_OK;
     }
     FaceVals face{}; // stays empty for screening plans (boundary values in phi only)
+    double *part[3] = {p->part[0], p->part[1], p->part[2]};
+    bool joined = p->cube; // the families' partials lie back to back
+    {
+        size_t at = 0;
+        for (int fam = 0; fam < d; ++fam) {
+            joined = joined && p->part_phi[fam] == p->part_phi[0];
+            if (!p->part_phi[fam]) continue;
+            part[fam] = phi + at;
+            at += part_size(p, fam);
+        }
+    }
     if (p->screen) {
         if ((rc = screen_boundary(p, rho, phi, st))) return rc;
     } else if (d == 3) {
@@ -1403,7 +1492,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.K = p->K[0];
             a.Kd = (int64_t)(M[2] + 1) * (M[1] + 1);
             a.Ko = M[1] + 1;
-            a.part = p->part[0];
+            a.part = part[0];
             a.Bout = p->B;
             a.Bf32 = f32;
             a.Bcs = I[1];
@@ -1432,7 +1521,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.K = p->K[1];
             a.Kd = (int64_t)(M[2] + 1) * (M[0] + 1);
             a.Ko = M[0] + 1;
-            a.part = p->part[1];
+            a.part = part[1];
             a.Bout = nullptr;
             a.fd = p->fd[0];
             a.tw = p->tw[0];
@@ -1479,7 +1568,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.K = p->K[2];
             a.Kd = (int64_t)(M[1] + 1) * (M[0] + 1);
             a.Ko = M[0] + 1;
-            a.part = p->part[2];
+            a.part = part[2];
             a.Bout = nullptr;
             a.fd = p->fd[0];
             a.tw = p->tw[0];
@@ -1492,14 +1581,14 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         //     contiguous slot axis c, then along r; F[fam][face][slot_r][slot_c]
         const int fr[3] = {2, 2, 1}, fc[3] = {1, 0, 0};
         PassArgs fa[3], fb[3];
-        const int nf = p->cube ? 1 : 3;
+        const int nf = joined ? 1 : 3;
         for (int fam = 0; fam < nf; ++fam) {
-            const int nfam = p->cube ? 3 : 1;
+            const int nfam = joined ? 3 : 1;
             const int r = fr[fam], c = fc[fam];
             const int64_t plane = (int64_t)N[r] * N[c];
             PassArgs &a = fa[fam];
             a = PassArgs{};
-            a.in = p->part[fam];
+            a.in = part[fam];
             a.out = p->F[fam];
             a.irs = a.ors = 1;
             a.ics = a.ocs = N[c];
@@ -1571,7 +1660,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.K = p->K[fam];
             a.Kd = M[pen] + 1;
             a.Ko = 0;
-            a.part = p->part[fam];
+            a.part = part[fam];
             if (fam == 0) {
                 a.Bout = p->B;
                 a.Bf32 = f32;
@@ -1590,12 +1679,12 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         // few columns, so a summing load inside the pass would leave most of
         // the GPU idle), then the inverse transforms in place; the families together
         ReduceArgs ra{};
-        ra.njobs = p->cube ? 1 : 2;
-        ra.nset = p->cube ? 4 : 2;
+        ra.njobs = joined ? 1 : 2;
+        ra.nset = joined ? 4 : 2;
         PassArgs fa[2];
         for (int fam = 0; fam < ra.njobs; ++fam) {
             const int pen = 1 - fam;
-            ra.job[fam] = {p->part[fam], p->F[fam], N[pen], p->nch[fam]};
+            ra.job[fam] = {part[fam], p->F[fam], N[pen], p->nch[fam]};
             PassArgs &a = fa[fam];
             a = PassArgs{};
             a.in = p->F[fam];
