@@ -246,3 +246,32 @@ def test_expand_register_tiles(shape, order):
     got = api.Plan(shape, h, order=order, adjoint=True).adjoint(to_dev(w))
     torch.cuda.synchronize()
     assert rel_err(got.cpu().numpy(), P.adjoint(w, h, order)) < 1e-12
+
+
+# the tile budget of a plan does not reach the expansion's register tiles (the budget is
+# read once per process: each runs in one of its own)
+@pytest.mark.parametrize("work", ["1024", "4096"])
+def test_adjoint_at_other_tile_budgets(work):
+    import os
+    import subprocess
+    import sys
+    from gpu_util import banner
+
+    banner("adjoint, tile budget " + work)
+    code = """
+import numpy as np, torch
+from oracle import poisson as P
+from paper_2108_11871_amd import api, inputs as I
+for shape in ((129, 20, 257), (8, 257, 129), (257, 130)):
+    h = I.grid_spacing(shape, -1.0, 1.3)
+    w = np.random.default_rng(8).standard_normal(shape)
+    got = api.Plan(shape, h, order=6, adjoint=True).adjoint(torch.from_numpy(w).cuda()).cpu().numpy()
+    ref = P.adjoint(w, h, 6)
+    err = np.abs(got - ref).max() / np.abs(ref).max()
+    assert err < 1e-12, (shape, err)
+print("adjoint budgets ok")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, env=dict(os.environ, IPS_TILE_WORK=work), text=True,
+                       capture_output=True, timeout=110)
+    assert r.returncode == 0 and "adjoint budgets ok" in r.stdout, r.stdout[-2000:] + r.stderr[-2000:]

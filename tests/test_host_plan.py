@@ -1,4 +1,4 @@
-"""What plans decide on the host -- workspace sizes -- through the library on a
+"""What plans decide on the host -- workspace sizes, kernels -- through the library on a
 stand-in runtime (tests/stub_runtime.cpp): no GPU needed."""
 import os
 import shutil
@@ -76,3 +76,14 @@ def test_static_scratch_still_holds_these_plans(stub):
     assert len(fit) > 10
     for s, now in zip(fit, stub([s[:4] + ("size",) for s in fit])):
         assert int(now) <= SCRATCH, (s, now)
+
+
+# lengths with register tiles: 3D the transformed axes are 1 and 0, with and without
+# enough slices for a tile's columns; 2D both axes
+@pytest.mark.parametrize("work", ["1024", "2048", "4096"])
+@pytest.mark.parametrize("n", [(129, 257, 20), (129, 513, 200), (257, 129, 12), (1025, 257, 40), (129, 257), (2049, 1025)])
+def test_expansion_takes_register_tiles_at_every_budget(stub, n, work):
+    out = stub([(n, 6, 0, ADJOINT, "adjoint")], IPS_TILE_WORK=work)
+    exp = [line.split()[0] for line in out if "k_expand" in line]
+    assert len(exp) == len(n)
+    assert all(e.startswith("k_expand_rt<") for e in exp), exp
