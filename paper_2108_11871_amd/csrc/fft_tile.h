@@ -21,8 +21,8 @@
 //
 // The FFT itself is a Stockham autosort transform with radix-2/3/4/5/8
 // butterflies held in registers (FP64 also 7, 11 and 13); larger prime factors
-// take a dense product on the matrix cores (FP64) or direct sums (FP32).  Twiddles come from a table w[t] = exp(-2 pi i t/N)
-// computed on the host in extended precision.
+// take a dense product on the matrix cores (FP64) or direct sums (FP32).  Twiddles
+// come from a table w[t] = exp(-2 pi i t/N) computed on the host in extended precision.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -290,19 +290,25 @@ __device__ __forceinline__ void stage_bfly(T *buf, int rs, int lgs, const FftDes
 // floor(x / d) = __umulhi(x, recip_u(d)) for 0 <= x < 2^16, 2 <= d < 2^16.
 __device__ __forceinline__ unsigned recip_u(int d) { return 0xffffffffu / (unsigned)d + 1u; }
 
+// Most items of a direct stage per thread: at most MAXE NT / (R ST) groups times
+// ceil(R / QT), most groups per frequency at R = 7 (4 of 2, 2 of 4), 13 (4 of 4) and
+// 11 (2 of 8).
+template <int MAXE, int ST, int QT>
+constexpr int direct_items()
+{
+    constexpr int R = QT == 1 ? 1 : QT == 2 ? 7 : QT == 4 ? 13 : 11, G = QT == 1 ? 1 : QT == 8 ? 2 : 4;
+    return (MAXE * G + ST * R - 1) / (ST * R);
+}
+
 // Stockham stage of any radix as direct sums. A thread forms ST * QT outputs,
 // QT neighbouring frequencies of ST sequences, so that an input read from LDS
 // serves QT outputs and a twiddle ST (one output at a time was bound by its two
 // LDS reads per input, 16 bytes for four FP32 operations).
-template <typename T, int MAXE, int NT, bool INV, int ST>
+template <typename T, int MAXE, int NT, bool INV, int ST, int QT>
 __device__ __forceinline__ void stage_direct(T *buf, int rs, int lgs, const FftDesc &fd, int st,
                                                     const cx<T> *tw, int tid)
 {
-    constexpr int QT = (sizeof(T) == 8 ? 4 : 8) / ST; // (FP64: half as many held registers)
-    // items per thread: at most MAXE NT / (R ST) groups times ceil(R / QT), most
-    // groups per frequency at R = 7 (4 of 2, 2 of 4), 13 (4 of 4) and 11 (2 of 8)
-    constexpr int RW = QT == 2 ? 7 : QT == 4 ? 13 : 11, GW = QT == 8 ? 2 : 4;
-    constexpr int IPT = (MAXE * GW + ST * RW - 1) / (ST * RW);
+    constexpr int IPT = direct_items<MAXE, ST, QT>();
     const int N = fd.N, Ns = fd.ns[st], R = fd.rad[st];
     const int NR = N / R, tstep = N / (Ns * R);
     const int ncg = (NR << lgs) / ST;  // (position, group of ST sequences)
@@ -481,6 +487,20 @@ __device__ __forceinline__ void stage_prime(double *buf, int rs, int lgs, const 
     __syncthreads();
 }
 
+// Whether the direct sums of a stage of radix R at NR positions share their reads
+// (see stage_direct): not where that leaves threads idle, i.e. where the rounds of items
+// that a thread goes through, times the LDS reads (FP32: and multiply-adds) of an input,
+// are fewer one output at a time. Mixed plans, one output at a time -> shared: 98^3 solve
+// (R = 97, full tiles) 1001 -> 572 us; adjoint of 1000^2 (R = 37) 619 -> 712, of 212^2 (211,
+// narrow tiles) 425 -> 718, solve of 14^3 (13) 139 -> 170.
+template <bool F64, int NT>
+__host__ __device__ __forceinline__ bool direct_shared(int R, int NR, int lgs)
+{
+    const int S = lgs > 0 ? 2 : 1, Q = (F64 ? 4 : 8) / S, np = NR << lgs;
+    const int si = np / S * ((R + Q - 1) / Q); // items, shared
+    return (si + NT - 1) / NT * (F64 ? S + Q : S + Q + S * Q) <= (np * R + NT - 1) / NT * (F64 ? 2 : 3);
+}
+
 // Stockham stage of any other radix. FP64 plans: 7, 11 and 13 in registers, larger
 // primes on the matrix cores while a wave holds the blocks (all lengths up to
 // 1024). Otherwise direct sums. In the mixed modes (fd.direct) every transform
@@ -501,10 +521,16 @@ __device__ __forceinline__ void stage_other(T *buf, int rs, int lgs, const FftDe
                 return stage_prime<NT, INV>(buf, rs, lgs, fd, st, tw, tid);
         }
     }
-    if (lgs > 0)
-        stage_direct<T, MAXE, NT, INV, 2>(buf, rs, lgs, fd, st, tw, tid);
-    else
-        stage_direct<T, MAXE, NT, INV, 1>(buf, rs, lgs, fd, st, tw, tid);
+    // outputs per item: half as many held registers in FP64
+    constexpr int Q2 = sizeof(T) == 8 ? 2 : 4;
+    if (direct_shared<sizeof(T) == 8, NT>(fd.rad[st], fd.N / fd.rad[st], lgs)) {
+        if (lgs > 0)
+            stage_direct<T, MAXE, NT, INV, 2, Q2>(buf, rs, lgs, fd, st, tw, tid);
+        else
+            stage_direct<T, MAXE, NT, INV, 1, 2 * Q2>(buf, rs, lgs, fd, st, tw, tid);
+    } else {
+        stage_direct<T, MAXE, NT, INV, 1, 1>(buf, rs, lgs, fd, st, tw, tid);
+    }
 }
 
 // Stockham stage with every size known at compile time: transform length
