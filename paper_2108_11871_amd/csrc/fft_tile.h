@@ -919,6 +919,16 @@ __device__ __forceinline__ void rt_fetch(TI (&x)[8], const TI *src, int64_t rsd,
     }
 }
 
+// The thread index in a loop over stages, opaque to the compiler: per-thread index
+// values of every stage would otherwise be held in registers across the loop (FP64,
+// all radices: 248 instead of 144 VGPRs).
+template <int NT>
+__device__ __forceinline__ int stage_tid(int tid)
+{
+    asm volatile("" : "+v"(tid));
+    return tid & (NT - 1);
+}
+
 // Full length-N complex FFT of 2^lgs sequences held in LDS (in place), in the
 // direction INV (false: exp(-2 pi i t/N), true: the conjugate).
 // KD: the radices that are compiled in (LenKind; a kernel for fewer of them holds
@@ -939,22 +949,18 @@ __device__ __forceinline__ void fft_tile_dir(T *buf, int rs, int lgs, const FftD
     if constexpr (KD == kPow2) {
         for (int st = 0; st < fd.nst; ++st) {
             const int R = fd.rad[st];
+            const int t = MAXE > 8 ? stage_tid<NT>(tid) : tid; // (FP32 contractions of 16 elements a thread: 134 -> 91 VGPRs)
             if (R == 8)
-                stage_bfly<T, 8, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid);
+                stage_bfly<T, 8, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t);
             else if (R == 4)
-                stage_bfly<T, 4, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid);
+                stage_bfly<T, 4, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t);
             else
-                stage_bfly<T, 2, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, tid);
+                stage_bfly<T, 2, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t);
         }
         return;
     }
     for (int st = 0; st < fd.nst; ++st) {
-        // the thread index, opaque to the compiler: per-thread index values of
-        // every stage would otherwise be held in registers across the loop (FP64,
-        // all radices: 248 instead of 144 VGPRs)
-        int t = tid;
-        asm volatile("" : "+v"(t));
-        t &= NT - 1;
+        const int t = stage_tid<NT>(tid);
         switch (fd.rad[st]) {
         case 2: stage_bfly<T, 2, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t); break;
         case 3: stage_bfly<T, 3, MAXE, NT, INV>(buf, rs, lgs, fd, st, tw, t); break;
