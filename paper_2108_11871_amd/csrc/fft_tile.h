@@ -489,16 +489,16 @@ __device__ __forceinline__ void stage_prime(double *buf, int rs, int lgs, const 
 
 // Whether the direct sums of a stage of radix R at NR positions share their reads
 // (see stage_direct): not where that leaves threads idle, i.e. where the rounds of items
-// that a thread goes through, times the LDS reads (FP32: and multiply-adds) of an input,
-// are fewer one output at a time. Mixed plans, one output at a time -> shared: 98^3 solve
-// (R = 97, full tiles) 1001 -> 572 us; adjoint of 1000^2 (R = 37) 619 -> 712, of 212^2 (211,
-// narrow tiles) 425 -> 718, solve of 14^3 (13) 139 -> 170.
+// that a thread goes through, times the LDS reads of an input, are fewer one output at a
+// time. Mixed plans, one output at a time -> shared: 98^3 solve (R = 97, full tiles) 1001
+// -> 572 us, adjoint of 603^2 (43) 446 -> 412; adjoint of 1000^2 (37) 617 -> 712, of 212^2
+// (211, narrow tiles) 424 -> 718, solve of 14^3 (13) 139 -> 170.
 template <bool F64, int NT>
 __host__ __device__ __forceinline__ bool direct_shared(int R, int NR, int lgs)
 {
     const int S = lgs > 0 ? 2 : 1, Q = (F64 ? 4 : 8) / S, np = NR << lgs;
     const int si = np / S * ((R + Q - 1) / Q); // items, shared
-    return (si + NT - 1) / NT * (F64 ? S + Q : S + Q + S * Q) <= (np * R + NT - 1) / NT * (F64 ? 2 : 3);
+    return (si + NT - 1) / NT * (S + Q) <= (np * R + NT - 1) / NT * 2;
 }
 
 // Stockham stage of any other radix. FP64 plans: 7, 11 and 13 in registers, larger

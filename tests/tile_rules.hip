@@ -41,7 +41,7 @@ static void check(int maxn)
                 // tiles without an output per thread never share, and a thread that
                 // shares reads less than one that does not
                 expect(r1 > 1 || !sh, "a tile of fewer outputs than threads shares", R, NR, lgs);
-                expect(!sh || rs * (ST + QT) <= 2 * r1 || !F64, "LDS reads of the shared form", R, NR, lgs);
+                expect(sh == (rs * (ST + QT) <= 2 * r1), "LDS reads of the shared form", R, NR, lgs);
             }
     }
 }
