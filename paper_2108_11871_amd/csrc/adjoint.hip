@@ -1157,7 +1157,7 @@ hipError_t launch_expand(const ExpandArgs &a, hipStream_t st)
 //   lambda_0 = w_0 + sum_j w_j (1 - j/M),  lambda_M = w_M + sum_j w_j j/M,
 //   rho_bar_s = phi_star(w_I)_s + h (G(s h) lambda_0 + G((M - s) h) lambda_M),
 // G(r) = r/2, rho_bar on the two end nodes = 0.
-template <int MAXE, int NTT>
+template <int MAXE, int KD, int NTT>
 __global__ __launch_bounds__(NTT) void k_adj_1d(const double *w, double *out, int M, double h,
                                                 FftDesc fd, const cx<double> *twg, AxisTabs tab)
 {
@@ -1187,13 +1187,13 @@ __global__ __launch_bounds__(NTT) void k_adj_1d(const double *w, double *out, in
         __syncthreads();
     }
     const double l0 = w[0] + red[0][0], l1 = w[M] + red[1][0];
-    fft_tile<double, MAXE, NTT>(buf, rs, 0, fd, tw, false);
+    fft_tile<double, MAXE, NTT, KD, false>(buf, rs, 0, fd, tw, false);
     post_cs<double, MAXE, NTT>(buf, rs, 0, M);
     for (int k = 1 + threadIdx.x; k < M; k += NTT)
         buf[(M + k) * rs] = -(2.0 / M) * buf[(M + k) * rs] / tab.q[k - 1];
     __syncthreads();
     pre_herm<double, MAXE, NTT>(buf, rs, 0, M, true);
-    fft_tile<double, MAXE, NTT>(buf, rs, 0, fd, tw, true);
+    fft_tile<double, MAXE, NTT, KD, false>(buf, rs, 0, fd, tw, true);
     for (int j = threadIdx.x; j <= M; j += NTT) {
         double v = 0.0;
         if (j > 0 && j < M)
@@ -1205,29 +1205,17 @@ __global__ __launch_bounds__(NTT) void k_adj_1d(const double *w, double *out, in
 hipError_t launch_adj_1d(const double *w, double *out, int M, double h, const FftDesc &fd,
                          const cx<double> *tw, const AxisTabs &tab, hipStream_t st)
 {
-    if (fd.N > 2048) {
-        const size_t lds = (size_t)fd.N * 2 * sizeof(double);
-        if (fd.N > 8 * 1024) return hipErrorInvalidValue;
-        if (fd.N <= 4 * 1024) {
-            set_lds((const void *)&k_adj_1d<4, 1024>, lds);
-            hipLaunchKernelGGL((k_adj_1d<4, 1024>), dim3(1), dim3(1024), lds, st, w, out, M, h, fd, tw, tab);
-        } else {
-            set_lds((const void *)&k_adj_1d<8, 1024>, lds);
-            hipLaunchKernelGGL((k_adj_1d<8, 1024>), dim3(1), dim3(1024), lds, st, w, out, M, h, fd, tw, tab);
-        }
+    const size_t lds = tile_lds<double>(fd.N, 2);
+    auto go = [&](auto maxe, auto ntt) {
+        constexpr int MAXE = decltype(maxe)::value, NTT = decltype(ntt)::value;
+        by_kind(fd.N, [&](auto kd) {
+            constexpr int KD = decltype(kd)::value;
+            set_lds((const void *)&k_adj_1d<MAXE, KD, NTT>, lds);
+            hipLaunchKernelGGL((k_adj_1d<MAXE, KD, NTT>), dim3(1), dim3(NTT), lds, st, w, out, M, h, fd, tw, tab);
+        });
         return hipGetLastError();
-    }
-    const size_t lds = (size_t)fd.N * sizeof(cx<double>) + (size_t)fd.N * 3 * sizeof(double);
-    if (fd.N <= 4 * NTA) {
-        set_lds((const void *)&k_adj_1d<4, NTA>, lds);
-        hipLaunchKernelGGL((k_adj_1d<4, NTA>), dim3(1), dim3(NTA), lds, st, w, out, M, h, fd, tw, tab);
-    } else if (fd.N <= 8 * NTA) {
-        set_lds((const void *)&k_adj_1d<8, NTA>, lds);
-        hipLaunchKernelGGL((k_adj_1d<8, NTA>), dim3(1), dim3(NTA), lds, st, w, out, M, h, fd, tw, tab);
-    } else {
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    };
+    return by_length(fd.N, go);
 }
 
 } // namespace ips

@@ -74,6 +74,18 @@ constexpr int kLdsTwMaxN = 2048;
 
 inline bool big_fft(int N) { return N > kLdsTwMaxN; }
 
+// f(elements per thread, threads) for the one-block 1D kernels of length N.
+template <typename F>
+inline hipError_t by_length(int N, F f)
+{
+    using std::integral_constant;
+    if (N <= 4 * NT) return f(integral_constant<int, 4>(), integral_constant<int, NT>());
+    if (!big_fft(N)) return f(integral_constant<int, 8>(), integral_constant<int, NT>());
+    if (N <= 4 * NTB) return f(integral_constant<int, 4>(), integral_constant<int, NTB>());
+    if (N <= 8 * NTB) return f(integral_constant<int, 8>(), integral_constant<int, NTB>());
+    return hipErrorInvalidValue;
+}
+
 template <typename T>
 inline size_t tile_lds(int N, int W)
 {

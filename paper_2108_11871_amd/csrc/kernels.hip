@@ -1581,7 +1581,7 @@ hipError_t launch_ksample(double *out, int d, int a, int b, int c, const int *M,
 // sigma_hi = sum (pi k/L)(-1)^k alpha_k are the outward derivatives at the two
 // ends and g(x) = sum over both ends of G(|x - end|) sigma, i.e.
 // g_0 = (L/2) sigma_hi and g_M = (L/2) sigma_lo (G = r/2 vanishes at r = 0).
-template <int MAXE, int NTT>
+template <int MAXE, int KD, int NTT>
 __global__ __launch_bounds__(NTT) void k_1d(const double *rho, double *phi, int M, double h,
                                             FftDesc fd, const cx<double> *twg, AxisTabs tab, int screen)
 {
@@ -1612,7 +1612,7 @@ __global__ __launch_bounds__(NTT) void k_1d(const double *rho, double *phi, int 
         __syncthreads();
     }
     double g0 = h * red[0][0], g1 = h * red[1][0];
-    fft_tile<double, MAXE, NTT>(buf, rs, 0, fd, tw, false);
+    fft_tile<double, MAXE, NTT, KD, false>(buf, rs, 0, fd, tw, false);
     post_cs<double, MAXE, NTT>(buf, rs, 0, M);
     __syncthreads();
     double slo = 0.0, shi = 0.0;
@@ -1640,7 +1640,7 @@ __global__ __launch_bounds__(NTT) void k_1d(const double *rho, double *phi, int 
     }
     __syncthreads();
     pre_herm<double, MAXE, NTT>(buf, rs, 0, M, true);
-    fft_tile<double, MAXE, NTT>(buf, rs, 0, fd, tw, true);
+    fft_tile<double, MAXE, NTT, KD, false>(buf, rs, 0, fd, tw, true);
     for (int j = threadIdx.x; j <= M; j += NTT) {
         double v;
         if (j == 0)
@@ -1657,25 +1657,16 @@ hipError_t launch_1d(const double *rho, double *phi, int M, double h, const FftD
                      const cx<double> *tw, const AxisTabs &tab, int screen, hipStream_t st)
 {
     const size_t lds = tile_lds<double>(fd.N, 2);
-    if (big_fft(fd.N)) {
-        if (fd.N > 8 * NTB) return hipErrorInvalidValue;
-        if (fd.N <= 4 * NTB) {
-            set_lds((const void *)&k_1d<4, NTB>, lds);
-            hipLaunchKernelGGL((k_1d<4, NTB>), dim3(1), dim3(NTB), lds, st, rho, phi, M, h, fd, tw, tab, screen);
-        } else {
-            set_lds((const void *)&k_1d<8, NTB>, lds);
-            hipLaunchKernelGGL((k_1d<8, NTB>), dim3(1), dim3(NTB), lds, st, rho, phi, M, h, fd, tw, tab, screen);
-        }
-    } else if (fd.N <= 4 * NT) {
-        set_lds((const void *)&k_1d<4, NT>, lds);
-        hipLaunchKernelGGL((k_1d<4, NT>), dim3(1), dim3(NT), lds, st, rho, phi, M, h, fd, tw, tab, screen);
-    } else if (fd.N <= 8 * NT) {
-        set_lds((const void *)&k_1d<8, NT>, lds);
-        hipLaunchKernelGGL((k_1d<8, NT>), dim3(1), dim3(NT), lds, st, rho, phi, M, h, fd, tw, tab, screen);
-    } else {
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    auto go = [&](auto maxe, auto ntt) {
+        constexpr int MAXE = decltype(maxe)::value, NTT = decltype(ntt)::value;
+        by_kind(fd.N, [&](auto kd) {
+            constexpr int KD = decltype(kd)::value;
+            set_lds((const void *)&k_1d<MAXE, KD, NTT>, lds);
+            hipLaunchKernelGGL((k_1d<MAXE, KD, NTT>), dim3(1), dim3(NTT), lds, st, rho, phi, M, h, fd, tw, tab, screen);
+        });
+        return hipGetLastError();
+    };
+    return by_length(fd.N, go);
 }
 
 } // namespace ips

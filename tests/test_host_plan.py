@@ -87,3 +87,12 @@ def test_expansion_takes_register_tiles_at_every_budget(stub, n, work):
     exp = [line.split()[0] for line in out if "k_expand" in line]
     assert len(exp) == len(n)
     assert all(e.startswith("k_expand_rt<") for e in exp), exp
+
+
+# powers of two, 5-smooth and other panel counts in one block of 256 or 1024 threads
+@pytest.mark.parametrize("n,kind", [(65, 1), (1025, 1), (4097, 1), (61, 2), (1001, 2), (3001, 2), (50, 0), (2047, 0)])
+def test_1d_kernels_hold_the_radices_of_their_length_only(stub, n, kind):
+    out = stub([((n,), 4, 0, 0, "execute"), ((n,), 4, 0, ADJOINT, "adjoint")])
+    names = [line.split()[0] for line in out if line.startswith("k_")]
+    assert [x.split("<")[0] for x in names] == ["k_1d", "k_adj_1d"]
+    assert all(x.split(",")[1] == str(kind) for x in names), names
