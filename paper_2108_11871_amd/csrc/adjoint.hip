@@ -402,12 +402,18 @@ hipError_t launch_adj_lambda(const AdjArgs &a, const double *w, const double *y1
 // The sums over k_a read X once per family (24..47 us at 257^3, near the copy rate);
 // k_adj_x (158 us) is bound by its ten cached loads per element.
 // ---------------------------------------------------------------------------
-struct ContractArgs {
-    const double *X, *s; // s[(j-1)*Ia + k-1] = sin(pi k j/M)
+struct ContractJob {
+    const double *s;      // s[(j-1)*Ia + k-1] = sin(pi k j/M)
     int Ia;
-    int64_t np, st;             // positions, stride of k_a
-    int64_t inner, outer;       // position p starts at (p / inner) * outer + p % inner
-    double *out;                // [splits][nl][np]
+    int64_t np, st;       // positions, stride of k_a
+    int64_t inner, outer; // position p starts at (p / inner) * outer + p % inner
+    double *out;          // [splits][nl][np]
+    int nblk, splits;     // blocks, of which nblk / splits per split
+};
+struct ContractArgs {
+    const double *X;
+    ContractJob job[3]; // the last one's axis is contiguous
+    int d;
 };
 
 // Layer sums from the odd and the even wavenumbers' sums of weights 1 (and 2).
@@ -424,15 +430,15 @@ __device__ __forceinline__ void layer_out(double *out, int64_t np, int64_t p, co
 
 // Strided axis: one position per thread, neighbouring positions side by side.
 template <int NW>
-__global__ __launch_bounds__(NTA) void k_adj_contract(ContractArgs a)
+__device__ __forceinline__ void contract_strided(const ContractJob &a, const double *Xv, int blk)
 {
-    const int64_t p = blockIdx.x * (int64_t)NTA + threadIdx.x;
+    const int nb = a.nblk / a.splits, sp = blk / nb, ns = a.splits;
+    const int64_t p = (int64_t)(blk % nb) * NTA + threadIdx.x;
     if (p >= a.np) return;
-    const int sp = blockIdx.y, ns = gridDim.y;
     // whole pairs of wavenumbers (odd, even) per split
     const int pairs = (a.Ia + 1) / 2;
     const int i0 = 2 * (int)((int64_t)pairs * sp / ns), i1 = min(a.Ia, 2 * (int)((int64_t)pairs * (sp + 1) / ns));
-    const double *X = a.X + p / a.inner * a.outer + p % a.inner;
+    const double *X = Xv + p / a.inner * a.outer + p % a.inner;
     double o[NW], e[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) o[w] = e[w] = 0.0;
@@ -463,12 +469,12 @@ __global__ __launch_bounds__(NTA) void k_adj_contract(ContractArgs a)
 
 // Contiguous axis: one position (row) per wave; lane parity is wavenumber parity.
 template <int NW>
-__global__ __launch_bounds__(NTA) void k_adj_contract_row(ContractArgs a)
+__device__ __forceinline__ void contract_rows(const ContractJob &a, const double *Xv, int blk)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t p = blockIdx.x * (int64_t)(NTA / 64) + (threadIdx.x >> 6);
+    const int64_t p = (int64_t)blk * (NTA / 64) + (threadIdx.x >> 6);
     if (p >= a.np) return;
-    const double *X = a.X + p * a.outer;
+    const double *X = Xv + p * a.outer;
     double t[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) t[w] = 0.0;
@@ -488,7 +494,22 @@ __global__ __launch_bounds__(NTA) void k_adj_contract_row(ContractArgs a)
     if (lane == 0) layer_out<NW>(a.out, a.np, p, o, e);
 }
 
-int adj_splits(const Geo &g, int a, int nl)
+// The families' sums in one launch: small grids are bound by the number of dependent
+// launches (with k_adj_rs_z below: adjoint of 14^2 103 -> 99 us, 33^3 207 -> 191, 257^3
+// 2024 -> 2003).
+template <int NW>
+__global__ __launch_bounds__(NTA) void k_adj_contract(ContractArgs a)
+{
+    int fam = 0, blk = blockIdx.x;
+    while (fam < a.d - 1 && blk >= a.job[fam].nblk) blk -= a.job[fam++].nblk;
+    if (fam < a.d - 1)
+        contract_strided<NW>(a.job[fam], a.X, blk);
+    else
+        contract_rows<NW>(a.job[fam], a.X, blk);
+}
+
+// Splits of the sums along axis a (1: none).
+static int adj_splits(const Geo &g, int a)
 {
     if (a == g.d - 1) return 1; // rows
     int64_t np = 1;
@@ -496,43 +517,50 @@ int adj_splits(const Geo &g, int a, int nl)
         if (b != a) np *= g.M[b] - 1;
     const int Ia = g.M[a] - 1;
     const int64_t want = ((int64_t)512 * 1024 + np - 1) / np; // threads of a full device
-    return (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min(Ia / nl, Ia / 16)));
+    // (the partials of two families, up to 4 layers per split, fit one volume)
+    return (int)std::max<int64_t>(1, std::min<int64_t>(want, Ia / 16));
 }
 
-hipError_t launch_adj_contract(const AdjArgs &a, int ax, int nl, const double *X, double *part, double *out,
+hipError_t launch_adj_contract(const AdjArgs &a, int nl, const double *X, double *part, double *const *out,
                                hipStream_t st)
 {
     const Geo &g = a.geo;
     if (nl != 2 && nl != 4) return hipErrorInvalidValue;
     ContractArgs c{};
+    ReduceArgs r{};
     c.X = X;
-    c.s = a.tab[ax].s;
-    c.Ia = g.M[ax] - 1;
-    c.np = 1;
-    c.st = 1;
-    for (int b = 0; b < g.d; ++b) {
-        if (b != ax) c.np *= g.M[b] - 1;
-        if (b > ax) c.st *= g.M[b] - 1;
+    c.d = g.d;
+    r.nset = 1;
+    int64_t tot = 0;
+    for (int ax = 0; ax < g.d; ++ax) {
+        ContractJob &j = c.job[ax];
+        j.s = a.tab[ax].s;
+        j.Ia = g.M[ax] - 1;
+        j.np = 1;
+        j.st = 1;
+        for (int b = 0; b < g.d; ++b) {
+            if (b != ax) j.np *= g.M[b] - 1;
+            if (b > ax) j.st *= g.M[b] - 1;
+        }
+        j.inner = j.st;
+        j.outer = j.st * j.Ia;
+        j.splits = adj_splits(g, ax);
+        j.out = out[ax];
+        if (j.splits > 1) {
+            j.out = part;
+            r.job[r.njobs++] = {part, out[ax], nl * j.np, j.splits};
+            part += j.splits * nl * j.np;
+        }
+        const int per = ax == g.d - 1 ? NTA / 64 : NTA; // positions per block
+        j.nblk = (int)((j.np + per - 1) / per) * j.splits;
+        tot += j.nblk;
     }
-    c.inner = c.st;
-    c.outer = c.st * c.Ia;
-    const int ks = adj_splits(g, ax, nl);
-    c.out = ks > 1 ? part : out;
-    if (ax == g.d - 1) {
-        const unsigned nb = (unsigned)((c.np + NTA / 64 - 1) / (NTA / 64));
-        if (nl == 2)
-            hipLaunchKernelGGL(k_adj_contract_row<1>, dim3(nb), dim3(NTA), 0, st, c);
-        else
-            hipLaunchKernelGGL(k_adj_contract_row<2>, dim3(nb), dim3(NTA), 0, st, c);
-        return hipGetLastError();
-    }
-    const dim3 grid((unsigned)((c.np + NTA - 1) / NTA), (unsigned)ks);
     if (nl == 2)
-        hipLaunchKernelGGL(k_adj_contract<1>, grid, dim3(NTA), 0, st, c);
+        hipLaunchKernelGGL(k_adj_contract<1>, dim3((unsigned)tot), dim3(NTA), 0, st, c);
     else
-        hipLaunchKernelGGL(k_adj_contract<2>, grid, dim3(NTA), 0, st, c);
+        hipLaunchKernelGGL(k_adj_contract<2>, dim3((unsigned)tot), dim3(NTA), 0, st, c);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && ks > 1) e = launch_reduce(ReduceArgs{{{part, out, nl * c.np, ks}}, 1, 1}, st);
+    if (e == hipSuccess && r.njobs > 0) e = launch_reduce(r, st);
     return e;
 }
 
@@ -629,10 +657,9 @@ __global__ __launch_bounds__(NTA) void k_adj_core(AdjArgs a, AdjShell s)
 
 // Rb[fam][r] = core layers' part minus the owned D layers (D = R - R_spec).
 template <int D>
-__global__ __launch_bounds__(NTA) void k_adj_rs(AdjArgs a, AdjShell s)
+__device__ __forceinline__ void adj_rs(const AdjArgs &a, const AdjShell &s, int fam, int r)
 {
     const Geo &g = a.geo;
-    const int fam = blockIdx.y / 10, r = blockIdx.y % 10;
     const int64_t ss = adj_shell_size(g, fam);
     const int e = blockIdx.x * NTA + threadIdx.x;
     if (e >= ss) return;
@@ -655,10 +682,9 @@ __global__ __launch_bounds__(NTA) void k_adj_rs(AdjArgs a, AdjShell s)
 // Z[x][side]: the transposed core values at the nodes with index 2 (M-2) along x,
 // of every family whose core layers hold the node, over h_x^4.
 template <int D>
-__global__ __launch_bounds__(NTA) void k_adj_z(AdjArgs a, AdjShell s)
+__device__ __forceinline__ void adj_z(const AdjArgs &a, const AdjShell &s, int x, int f)
 {
     const Geo &g = a.geo;
-    const int x = blockIdx.y >> 1, f = blockIdx.y & 1;
     const int64_t ss = adj_shell_size(g, x);
     const int e = blockIdx.x * NTA + threadIdx.x;
     if (e >= ss) return;
@@ -686,6 +712,17 @@ __global__ __launch_bounds__(NTA) void k_adj_z(AdjArgs a, AdjShell s)
     s.Z[x][(int64_t)f * ss + e] = v;
 }
 
+// Both from the core layers: block rows 0 .. 10 D - 1 and 10 D .. 12 D - 1.
+template <int D>
+__global__ __launch_bounds__(NTA) void k_adj_rs_z(AdjArgs a, AdjShell s)
+{
+    const int y = blockIdx.y;
+    if (y < 10 * D)
+        adj_rs<D>(a, s, y / 10, y % 10);
+    else
+        adj_z<D>(a, s, (y - 10 * D) >> 1, y & 1);
+}
+
 hipError_t launch_adj_shell(const AdjArgs &a, const AdjShell &s, hipStream_t st)
 {
     const Geo &g = a.geo;
@@ -699,12 +736,10 @@ hipError_t launch_adj_shell(const AdjArgs &a, const AdjShell &s, hipStream_t st)
     const unsigned nb = (unsigned)((mx + NTA - 1) / NTA), d = (unsigned)g.d;
     if (d == 3) {
         hipLaunchKernelGGL(k_adj_core<3>, dim3(nb, 8 * d), dim3(NTA), 0, st, a, s);
-        hipLaunchKernelGGL(k_adj_rs<3>, dim3(nb, 10 * d), dim3(NTA), 0, st, a, s);
-        hipLaunchKernelGGL(k_adj_z<3>, dim3(nb, 2 * d), dim3(NTA), 0, st, a, s);
+        hipLaunchKernelGGL(k_adj_rs_z<3>, dim3(nb, 12 * d), dim3(NTA), 0, st, a, s);
     } else {
         hipLaunchKernelGGL(k_adj_core<2>, dim3(nb, 8 * d), dim3(NTA), 0, st, a, s);
-        hipLaunchKernelGGL(k_adj_rs<2>, dim3(nb, 10 * d), dim3(NTA), 0, st, a, s);
-        hipLaunchKernelGGL(k_adj_z<2>, dim3(nb, 2 * d), dim3(NTA), 0, st, a, s);
+        hipLaunchKernelGGL(k_adj_rs_z<2>, dim3(nb, 12 * d), dim3(NTA), 0, st, a, s);
     }
     return hipGetLastError();
 }

@@ -286,12 +286,9 @@ struct ExpandArgs {
     const cx<double> *tw;
 };
 
-// splits of the contraction over axis a with nl output layers (1: none); the
-// partials of more take splits * nl * (other axes) doubles, at most the volume
-int adj_splits(const Geo &g, int a, int nl);
-// layers (1, M - 1; nl = 4: 1, 2, M - 2, M - 1) of the sine series X along axis ax,
-// as spectra over the other axes
-hipError_t launch_adj_contract(const AdjArgs &a, int ax, int nl, const double *X, double *part, double *out,
+// layers (1, M - 1; nl = 4: 1, 2, M - 2, M - 1) of the sine series X along every axis, as
+// spectra over the other axes (out[axis]); part: one volume, for the partials of splits
+hipError_t launch_adj_contract(const AdjArgs &a, int nl, const double *X, double *part, double *const *out,
                                hipStream_t st);
 // transposed extrapolation and sixth-order stencils on the shell (Db -> Cb, Rb, Z)
 hipError_t launch_adj_shell(const AdjArgs &a, const AdjShell &s, hipStream_t st);

@@ -2097,15 +2097,13 @@ int execute_adjoint(ips_plan p, const double *w, double *out, hipStream_t st)
         // the harmonic part on the shell (AY, consumed above, holds split partials)
         const AdjShell &sh = p->ash;
         if (six) {
-            for (int fam = 0; fam < d; ++fam)
-                IPS_HIP(launch_adj_contract(aa, fam, 4, p->AX, p->AY, sh.Db[fam], st));
+            IPS_HIP(launch_adj_contract(aa, 4, p->AX, p->AY, sh.Db, st));
             if ((rc = shell_dst_all(p, sh.Db, 4, true, st))) return rc;
             IPS_HIP(launch_adj_shell(aa, sh, st));
             if ((rc = shell_dst_all(p, sh.Rb, 10, false, st))) return rc;
             IPS_HIP(launch_adj_x(aa, sh, p->AX, st));
         }
-        for (int fam = 0; fam < d; ++fam)
-            IPS_HIP(launch_adj_contract(aa, fam, 2, p->AX, p->AY, sh.Gb[fam], st));
+        IPS_HIP(launch_adj_contract(aa, 2, p->AX, p->AY, sh.Gb, st));
         if ((rc = shell_dst_all(p, sh.Gb, 2, true, st))) return rc;
         IPS_HIP(launch_adj_lambda_shell(aa, sh, w, six, st));
     } else {

@@ -96,3 +96,12 @@ def test_1d_kernels_hold_the_radices_of_their_length_only(stub, n, kind):
     names = [line.split()[0] for line in out if line.startswith("k_")]
     assert [x.split("<")[0] for x in names] == ["k_1d", "k_adj_1d"]
     assert all(x.split(",")[1] == str(kind) for x in names), names
+
+
+# the launches of the volume-form adjoint (two and three axes, orders 6 and 4), which the
+# shell form must not exceed on grids that launches bound
+@pytest.mark.parametrize("n,order,most", [((14, 14), 6, 20), ((14, 14), 4, 13), ((33, 40), 6, 20), ((14, 15, 16), 6, 38),
+                                          ((14, 15, 16), 4, 24), ((33, 33, 33), 6, 38), ((257, 257, 257), 6, 38)])
+def test_fp64_adjoint_launches(stub, n, order, most):
+    out = stub([(n, order, 0, ADJOINT, "adjoint")])
+    assert 0 < len([line for line in out if line.startswith("k_")]) <= most
