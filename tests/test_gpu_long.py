@@ -157,3 +157,25 @@ def test_2d_4097_forward_backward():
         banner("  direction %d: <grad,v> %.12e FD %.12e rel %.2e" % (t, an, fd, rel))
         assert rel < 1e-10
     plan.close()
+
+
+# long axes next to short ones: a tile of two contiguous columns in a block of 4 and 16
+# waves, the last column alone
+@pytest.mark.parametrize("mode,tol", [("fp64", 1e-12), ("mixed_fp32_slices", 1e-6)])
+@pytest.mark.parametrize("shape", [(2751, 10), (10, 2751), (2401, 67), (1201, 9), (9, 1201)])
+def test_long_axis_few_columns(shape, mode, tol):
+    import torch
+    from oracle import poisson as P
+    from paper_2108_11871_amd import api
+    from paper_2108_11871_amd import inputs as I
+    from gpu_util import banner, rel_err, to_dev
+
+    banner("shape=%s %s" % (shape, mode))
+    rho, h, _ = I.workload_bumps(shape, seed=44, scale=[1.0, 1.2])
+    plan = api.Plan(shape, h, order=6, precision=mode, adjoint=True)
+    phi = plan(to_dev(rho))
+    w = np.random.default_rng(9).standard_normal(shape)
+    grad = plan.adjoint(to_dev(w))
+    torch.cuda.synchronize()
+    assert rel_err(phi.cpu().numpy(), P.solve(rho, h, 6, boundary="fft")) < tol
+    assert rel_err(grad.cpu().numpy(), P.adjoint(w, h, 6)) < tol

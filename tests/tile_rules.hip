@@ -1,7 +1,9 @@
-// Host-only checks of the rules in fft_tile.h by which a kernel picks the form of a
-// direct stage, over every radix, length and width that a tile takes. Exit status 0
-// when all hold.
+// Host-only checks of rules in fft_tile.h: the form of a direct stage, over every radix,
+// length and width that a tile takes, and the walk over rows-contiguous data. Exit status
+// 0 when all hold.
+#include <algorithm>
 #include <cstdio>
+#include <vector>
 
 #include "fft_tile.h"
 
@@ -46,8 +48,36 @@ static void check(int maxn)
     }
 }
 
+// by_columns: every element once, and no thread with more rows than an even split leaves
+template <int NT>
+static void check_columns()
+{
+    constexpr int NW = NT / 64;
+    for (int lgW = 1; lgW <= 5; ++lgW)
+        for (int ncols = 1; ncols <= 1 << lgW; ++ncols)
+            for (int nrows : {1, 63, 64, 65, 255, 256, 257, 1023, 1025, 5999}) {
+                std::vector<int> seen((size_t)ncols * nrows, 0);
+                int most = 0;
+                for (int t = 0; t < NT; ++t) {
+                    int n = 0;
+                    by_columns<NT>(lgW, ncols, nrows, t, [&](int c, int r) {
+                        ++seen[(size_t)c * nrows + r];
+                        ++n;
+                    });
+                    most = std::max(most, n);
+                }
+                const int W = 1 << lgW, waves = std::max(1, NW / W); // per column
+                expect(std::all_of(seen.begin(), seen.end(), [](int v) { return v == 1; }), "every element once", ncols,
+                       nrows, lgW);
+                expect(most <= (ncols + NW - 1) / NW * ((nrows + 64 * waves - 1) / (64 * waves)), "idle waves", ncols,
+                       nrows, lgW);
+            }
+}
+
 int main()
 {
+    check_columns<256>();
+    check_columns<1024>();
     check<true, 4, 256>(2048);
     check<true, 8, 256>(2048);
     check<true, 16, 256>(2048);
