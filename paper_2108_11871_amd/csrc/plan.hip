@@ -174,7 +174,10 @@ int fill_width(int N, int maxwork, int ncols, int64_t nbatch, int fill, int wmin
     // the tiles with compile-time stages stay whole: even 48 of them beat four
     // times as many narrower ones with run-time stages (129^3 283 against 286 us)
     if (N * W == 4096 && (N == 256 || N == 512 || N == 1024)) return W;
-    while (W > wmin && (int64_t)((ncols + W - 1) / W) * nbatch < fill) W /= 2;
+    // (the lines of a tiny 2D grid not below 64 elements, a wave's: mixed adjoint of 14^2 102.5
+    // -> 99.9 us, solve of 9^2 64.5 -> 63.4; with batch entries narrower tiles win, 9^3
+    // 114.8 -> 112.9)
+    while (W > wmin && (int64_t)((ncols + W - 1) / W) * nbatch < fill && (nbatch > 1 || W / 2 * N > 64)) W /= 2;
     return W;
 }
 

@@ -105,3 +105,12 @@ def test_1d_kernels_hold_the_radices_of_their_length_only(stub, n, kind):
 def test_fp64_adjoint_launches(stub, n, order, most):
     out = stub([(n, order, 0, ADJOINT, "adjoint")])
     assert 0 < len([line for line in out if line.startswith("k_")]) <= most
+
+
+@pytest.mark.parametrize("precision", [0, 2])
+def test_tiny_lines_are_not_split_below_a_wave(stub, precision):
+    # 2M = 26: a tile of two columns would hold 26 elements, of four 52
+    out = stub([((14, 14), 6, precision, ADJOINT, call) for call in ("execute", "adjoint")])
+    passes = [line.split() for line in out if line.startswith("k_pass<")]
+    assert len(passes) > 8
+    assert all(int(blocks) <= 5 for _, blocks, _ in passes), passes
