@@ -81,30 +81,26 @@ struct Geo {
 // Shell spectra: g~ layers (2 per axis) and the deferred-correction layers
 // (4 per axis, layers 1, 2, M-2, M-1).  Index [layer][k_b-1][k_c-1] over the
 // two other axes in increasing order (3D) or [layer][k_b-1] (2D).
+// Parity-packed form used by the spectral kernels, [par][t][k_other] with
+// par = k_a & 1 and sg = +1 (odd k_a) or -1 (even k_a):
+//   t = 0: G_lo + sg G_hi          (multiplies sin(pi k_a / M_a))
+//   t = 1: D_1 + sg D_{M-1}        (multiplies sin(pi k_a / M_a))
+//   t = 2: D_2 + sg D_{M-2}        (multiplies sin(2 pi k_a / M_a))
+// What the final pass reads: family 0 (its columns) and, 3D, family 2 transposed to
+// [par][t][k1][k0] (its lanes walk k0), in its transform type (FP32 in the mixed modes);
+// family 1 comes in the row table.
 struct ShellSpec {
-    const double *G[3];
-    const double *D[3];
-    // Parity-packed form used by the spectral kernels, [par][t][k_other] with
-    // par = k_a & 1 and sg = +1 (odd k_a) or -1 (even k_a):
-    //   t = 0: G_lo + sg G_hi          (multiplies sin(pi k_a / M_a))
-    //   t = 1: D_1 + sg D_{M-1}        (multiplies sin(pi k_a / M_a))
-    //   t = 2: D_2 + sg D_{M-2}        (multiplies sin(2 pi k_a / M_a))
-    const double *P[3];
-    // 3D: family 1 packed values transposed to [par][t][k2][k0] (k0 contiguous),
-    // for the final pass which walks k0 at fixed k2
-    const double *P1T;
-    // 3D: family 2 packed values transposed to [par][t][k1][k0] (k0 contiguous),
-    // for the final pass, whose lanes walk k0; stored in the final pass's
-    // transform type (FP32 in the mixed modes)
+    const double *P0;
     const void *P2T;
 };
 
+// The packing of all families; of 1 and 2 only t = 0 is stored, for k_r6t (order 6).
 struct PackArgs {
     Geo geo;
     const double *G[3];
     const double *D[3];
     double *P[3];
-    double *P1T; // 3D only
+    double *P1T; // 3D only: family 1 transposed to [par][t][k2][k0]
     void *P2T;   // 3D only: FP32 if p2t_f32, else FP64
     int p2t_f32;
     int withD;   // pack the deferred-correction layers (else the g~ layers)
@@ -196,8 +192,8 @@ hipError_t launch_screen_g(const ScreenArgs &a, double *phi, hipStream_t st);
 struct R6Args {
     Geo geo;
     AxisTabs tab[3];
-    const double *P[3]; // packed shell spectra (ShellSpec::P)
-    const double *P1T;  // 3D: family 1 transposed (ShellSpec::P1T)
+    const double *P[3]; // packed shell spectra, t = 0 (PackArgs)
+    const double *P1T;  // 3D: family 1 transposed (PackArgs)
     void *T[3];         // [10][other axes] per axis: layers 1..5, then M-1..M-5
     int t_f32;          // T holds FP32 (mixed modes), else FP64
     int nblk[3];        // filled by the launcher
@@ -334,7 +330,6 @@ hipError_t launch_dcorr(const DcorrArgs &a, hipStream_t st);
 // false: dst is extended) or restrict (extract = true: src is extended).
 hipError_t launch_embed(const double *src, double *dst, int d, const int64_t *n, const int64_t *ne,
                         const int64_t *off, bool extract, hipStream_t st);
-// Row table of the final pass: once per solve, before launch_final.
 hipError_t launch_final(const FinalArgs &a, hipStream_t st);
 // K[dd][ib][ic] (3D) or K[dd][ib] (2D) for faces normal to axis a; (b, c) are
 // the in-face axes in storage order (c contiguous).

@@ -267,7 +267,7 @@ __host__ __device__ __forceinline__ int64_t shell_size(const Geo &g, int a)
 }
 
 // ---------------------------------------------------------------------------
-// Parity packing of the shell spectra (see ShellSpec::P)
+// Parity packing of the shell spectra (see ShellSpec)
 // ---------------------------------------------------------------------------
 // A block takes one 16 x 16 tile of a family's (k_lo, k_hi) plane, an element per
 // thread; the transposed copies go through LDS, so that every write is a run of 16.
@@ -275,7 +275,8 @@ __host__ __device__ __forceinline__ int64_t shell_size(const Geo &g, int a)
 // one with them. 257^3: 8 + 13 -> 6 + 7 us, 513^3 13 + 41 -> 11 + 18 us (one element
 // per thread with strided copies before); bound by launch latency below. The last call
 // also writes the final pass's row table from the values in hand (257^3 7 + 7 us for
-// two launches -> 11).
+// two launches -> 11); of families 1 and 2 only the call before k_r6t stores P and P1T,
+// which nothing else reads (513^3 21 -> 18 us for the last call).
 constexpr int kPackTile = 16;
 
 // Row i of batch index kB - 1 of the final pass's row table [batch][M0 - 1][12] (see
@@ -327,6 +328,7 @@ __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
     const bool tr = g.d == 3 && fam > 0;
     const bool rows = fam == 1 && a.rowtab; // (the last call: all parts are known)
     const int nk = a.withD ? 4 : 2; // values per element, of kind (parity, t)
+    const bool keep = !a.withD && !a.rowtab; // k_r6t follows
     auto kind = [&](int q) { return a.withD ? (q >> 1) * 3 + 1 + (q & 1) : 3 * q; };
     if (r0 + ty < Il && c0 + tx < Ih) {
         const int64_t e = (int64_t)(r0 + ty) * Ih + c0 + tx;
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if (q >= nk) break;
-            a.P[fam][kind(q) * ss + e] = v[q];
+            if (fam == 0 || keep) a.P[fam][kind(q) * ss + e] = v[q];
             if (tr) tile[q][ty][tx] = v[q];
         }
         if (tr && rows) {
@@ -370,9 +372,9 @@ __global__ __launch_bounds__(kPackTile *kPackTile) void k_pack(PackArgs a)
     for (int q = 0; q < 4; ++q) {
         if (q >= nk) break;
         const double v = tile[q][tx][ty];
-        if (fam == 1)
-            a.P1T[kind(q) * ss + et] = v;
-        else if (a.p2t_f32)
+        if (fam == 1) {
+            if (keep) a.P1T[kind(q) * ss + et] = v;
+        } else if (a.p2t_f32)
             static_cast<float *>(a.P2T)[kind(q) * ss + et] = (float)v;
         else
             static_cast<double *>(a.P2T)[kind(q) * ss + et] = v;
@@ -1111,7 +1113,7 @@ __device__ __forceinline__ void final_col(const FinalArgs &a, int j, int kB, T *
     // family 0: other index (k1, k2) in 3D, (k1) in 2D
     const int64_t ss0 = shell_size(geo, 0), o = d == 3 ? (int64_t)j * I2 + (kB - 1) : j;
     for (int par = 0; par < 2; ++par)
-        for (int t = 0; t < nt; ++t) r[4 + par * 3 + t] = (T)a.sh.P[0][(par * 3 + t) * ss0 + o];
+        for (int t = 0; t < nt; ++t) r[4 + par * 3 + t] = (T)a.sh.P0[(par * 3 + t) * ss0 + o];
 }
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }

@@ -276,7 +276,8 @@ struct ips_plan_s {
     double *T[3] = {nullptr, nullptr, nullptr};
     float *Tf[3] = {nullptr, nullptr, nullptr}; // the same buffer as FP32 (mixed modes)
     double *D[3] = {nullptr, nullptr, nullptr};
-    double *P[3] = {nullptr, nullptr, nullptr}; // parity-packed shell spectra
+    double *P[3] = {nullptr, nullptr, nullptr}; // parity-packed shell spectra [par][t] (of families
+                                                // 1 and 2, and of P1T, only t = 0 is written)
     double *P1T = nullptr;                      // 3D: transposed family-1 copy
     void *P2T = nullptr;                        // 3D: transposed family-2 copy (final pass type)
     bool cube = false; // all families share sizes and chunking (batched launches)
@@ -1731,14 +1732,11 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
     PackArgs pk{};
     pk.geo = p->geo;
     for (int fam = 0; fam < d; ++fam) {
-        sh.G[fam] = p->G[fam];
-        sh.D[fam] = p->D[fam];
-        sh.P[fam] = p->P[fam];
         pk.G[fam] = p->G[fam];
         pk.D[fam] = p->D[fam];
         pk.P[fam] = p->P[fam];
     }
-    sh.P1T = p->P1T;
+    sh.P0 = p->P[0];
     sh.P2T = p->P2T;
     pk.P1T = p->P1T;
     pk.P2T = p->P2T;
