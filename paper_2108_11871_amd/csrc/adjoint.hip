@@ -1146,7 +1146,9 @@ static void launch_expand_m(const ExpandArgs &a, unsigned nblk, size_t lds, hipS
         set_lds((const void *)&k_expand<MAXE, KD, NTT>, lds);
         hipLaunchKernelGGL((k_expand<MAXE, KD, NTT>), dim3(nblk), dim3(NTT), lds, st, a);
     };
-    if constexpr (NTT == NTA && MAXE <= 8)
+    if constexpr (NTT != NTA)
+        go(std::integral_constant<int, kAnyLen>()); // (powers of two: register tiles)
+    else if constexpr (MAXE <= 8)
         by_kind(a.fd.N, go);
     else
         by_pow2(a.fd.N, go);

@@ -397,12 +397,15 @@ static void launch_cc_m(const CcArgs &a, int nchunk, hipStream_t st)
                 if (prefetch_fits<4, MAXE>(a)) return launch_cc_k<T, TI, MAXE, WB, KD, 2, NT, 4>(a, nchunk, st);
             }
             launch_cc_k<T, TI, MAXE, WB, KD, 2>(a, nchunk, st);
-        } else if (a.fd.N <= 4 * NT) {
-            if (prefetch_fits<2, MAXE>(a))
-                launch_cc_k<T, TI, MAXE, WB, KD, 4, NT, 2>(a, nchunk, st);
-            else
-                launch_cc_k<T, TI, MAXE, WB, KD, 4>(a, nchunk, st);
-        } else {
+            return;
+        }
+        // (W = 4 at 2M = 1024 and every tile at 2048 are register tiles up to 8 NT elements)
+        constexpr bool RT = P2 && MAXE == 8;
+        if (a.fd.N <= 4 * NT) {
+            if constexpr (!RT)
+                if (prefetch_fits<2, MAXE>(a)) return launch_cc_k<T, TI, MAXE, WB, KD, 4, NT, 2>(a, nchunk, st);
+            launch_cc_k<T, TI, MAXE, WB, KD, 4>(a, nchunk, st);
+        } else if constexpr (!RT) {
             launch_cc_k<T, TI, MAXE, WB, KD, 8>(a, nchunk, st);
         }
     };
@@ -433,6 +436,8 @@ hipError_t launch_cc_t(const CcArgs &a, int nchunk, hipStream_t st)
             launch_cc_k<T, TI, 8, WB, kAnyLen, 8, NTB>(a, nchunk, st);
         return hipGetLastError();
     }
+    // (no other kernel holds these rows of a power of two)
+    if (is_pow2(a.fd.N) && a.fd.N > 4 * NT && work <= 8 * NT) return hipErrorInvalidValue;
     if (work <= 8 * NT)
         launch_cc_m<T, TI, 8, WB>(a, nchunk, st);
     else

@@ -1487,11 +1487,14 @@ static void launch_final_k(const FinalArgs &a, int nblk, hipStream_t st)
     // compile-time widths also prefetch the next tile: MAXE registers per
     // thread must cover the tile's rows
     const bool rc = a.irs == 1 && a.ics != 1;
-    if (a.W == 8 && PairMap<NT, 8, MAXE>::covers(a.nrows_in, rc))
-        launch_final_w<T, MAXE, KD, 8>(a, nblk, lds, st);
-    else if (a.W == 16 && PairMap<NT, 16, MAXE>::covers(a.nrows_in, rc))
-        launch_final_w<T, MAXE, KD, 16>(a, nblk, lds, st);
-    else if (a.W == 32 && PairMap<NT, 32, MAXE>::covers(a.nrows_in, rc))
+    // (8 and 16 columns of more than 4 NT elements, powers of two: register tiles)
+    if constexpr (KD != kPow2 || MAXE != 8) {
+        if (a.W == 8 && PairMap<NT, 8, MAXE>::covers(a.nrows_in, rc))
+            return launch_final_w<T, MAXE, KD, 8>(a, nblk, lds, st);
+        if (a.W == 16 && PairMap<NT, 16, MAXE>::covers(a.nrows_in, rc))
+            return launch_final_w<T, MAXE, KD, 16>(a, nblk, lds, st);
+    }
+    if (a.W == 32 && PairMap<NT, 32, MAXE>::covers(a.nrows_in, rc))
         launch_final_w<T, MAXE, KD, 32>(a, nblk, lds, st);
     else
         launch_final_w<T, MAXE, KD, 0>(a, nblk, lds, st);

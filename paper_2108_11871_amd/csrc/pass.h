@@ -162,12 +162,6 @@ __global__ __launch_bounds__(NTT) void k_pass(PassArgs a, int ntiles)
                 tile_at(nx, c1, n1, i1, o1);
                 fetch_pair<TI, NTT, WC, EPT, false>(pf, in0 + i1, a.nrows_in, a.irs, a.ics, 0, n1, 0, 0, tid);
             }
-        } else {
-            if (mode == IN_HERM && a.nsum > 1)
-                tile_load_sum<T, TI, NTT>(buf, rs, 0, in0 + io, a.nrows_in, nc, a.irs, a.ics, lgW, a.nsum,
-                                          a.sstride, tid);
-            else
-                tile_load<T, TI, NTT>(buf, rs, row0, in0 + io, a.nrows_in, nc, a.irs, a.ics, lgW, tid);
         }
         __syncthreads();
         bool inv = false;
@@ -391,13 +385,18 @@ hipError_t launch_pass_t(const PassArgs &a, hipStream_t st)
     if (launch_pass_rt<T, TI, TO>(a, ntiles, st)) return hipGetLastError();
     if (big_fft(a.fd.N)) {
         if (a.W != 2 || work > 8 * NTB) return hipErrorInvalidValue;
-        by_pow2(a.fd.N, [&](auto kd) {
+        auto go = [&](auto kd) {
             constexpr int KD = decltype(kd)::value;
             if (work <= 4 * NTB)
                 launch_pass_k<T, TI, TO, 4, KD, NTB>(a, ntiles, lds, st);
             else
                 launch_pass_k<T, TI, TO, 8, KD, NTB>(a, ntiles, lds, st);
-        });
+        };
+        // (FP32 passes of the powers of two are register tiles)
+        if constexpr (sizeof(T) == 4)
+            go(std::integral_constant<int, kAnyLen>());
+        else
+            by_pow2(a.fd.N, go);
         return hipGetLastError();
     }
     if (work > 16 * NT) return hipErrorInvalidValue;
