@@ -399,8 +399,9 @@ hipError_t launch_adj_lambda(const AdjArgs &a, const double *w, const double *y1
 //                V(k) = sum over the layers of all families of sin(pi k_f l/M_f) T_l(k_o)
 // and lambda collects g~ and Z. Three volume transforms instead of twelve and no
 // volume stencils: 257^3 forward and backward 5.03 -> 3.93 ms, 4097^2 5.52 -> 4.29 ms.
-// The sums over k_a read X once per family (24..47 us at 257^3, near the copy rate);
-// k_adj_x (158 us) is bound by its ten cached loads per element.
+// The sums over k_a read X once per family (257^3, three families: 67 us for two layers,
+// 96 for four, 12 and 23 to add the splits); k_adj_x (150 to 159 us over the boxes measured)
+// is bound by its ten cached loads per element.
 // ---------------------------------------------------------------------------
 struct ContractJob {
     const double *s;      // s[(j-1)*Ia + k-1] = sin(pi k j/M)
@@ -759,7 +760,7 @@ __global__ __launch_bounds__(NTA) void k_adj_tpack(AdjArgs a, AdjShell s)
 // One position of the axes after the first per thread (neighbours side by side), a
 // range of k0 per block row: the family-0 values of the position stay in registers.
 // Bound by the ten loads of the other families' values per element, two elements' at
-// once in flight (257^3: 159 -> 148 us).
+// once in flight (257^3, one box: 159 -> 148 us).
 template <int D>
 __global__ __launch_bounds__(NTA) void k_adj_x(AdjArgs a, AdjShell s, double *X)
 {
@@ -1038,7 +1039,7 @@ __global__ __launch_bounds__(NTT) void k_expand(ExpandArgs a)
 // rows that its first butterfly takes, results go straight to global memory. Columns
 // that are slices (SCOL) share the rows of the face spectra. Slices s and M - s, and the
 // cosine and the sine column of one frequency, read the same rows of K, so blocks that
-// share them run next to each other. 257^3, per family: 283 -> 195 us (of it 80 for K and
+// share them run next to each other. 257^3, per family: 283 -> 187 to 198 us (of it 80 for K and
 // the result at 5.1 TB/s; the rest is the latency of the loads before each transform);
 // with the other slots as columns 320 us (36 loads per thread -> 52); 4097^2: 820 -> 230 and 270.
 // All loads issued before their first use measured 3% slower.

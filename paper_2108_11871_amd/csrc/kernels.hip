@@ -1338,15 +1338,14 @@ __device__ __forceinline__ double quad_get(double v)
     return __hiloint2double(hi, lo);
 }
 
-// The final pass in register tiles (full tiles of the power-of-two lengths): 8
-// instead of 12 passes over the tile in LDS, six barriers less. Its row records are
-// read a part per lane (whole records per lane: 117 us) and its columns in pairs.
-// Now bound by VALU issue (FP32 75% busy) and the latency of B and the shell spectra.
-// 257^3: FP32 102 -> 97 us, FP64 191 -> 178 us; 513^3 FP32 1243 -> 847 us.
-// the first forward and the last inverse stage read and write B directly, and
-// the spectral combination works on the registers between the last forward and
-// the first inverse stage (see RegTile): thread (j, s) combines rows k = j + r N/8,
-// r < 4, of its two columns; its inverse inputs are these and its mirror's.
+// The final pass in register tiles (full tiles of the power-of-two lengths): the first
+// forward and the last inverse stage read and write B directly, and the spectral
+// combination works on the registers between the last forward and the first inverse
+// stage (see RegTile): thread (j, s) combines rows k = j + r N/8, r < 4, of its two columns;
+// its inverse inputs are these and its mirror's. 8 instead of 12 passes over the tile in
+// LDS, six barriers less. Its row records are read a part per lane (whole records per lane:
+// 117 us) and its columns in pairs. Bound by VALU issue (FP32 75% busy) and the latency of
+// B and the shell spectra. 257^3: FP32 102 -> 97 us, FP64 191 -> 178; 513^3 FP32 1243 -> 847.
 template <typename T, typename R>
 __global__ __launch_bounds__(R::NTH) void k_final_rt(FinalArgs a, int ntiles)
 {

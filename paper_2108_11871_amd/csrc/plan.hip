@@ -158,12 +158,11 @@ int tile_width(int N, int maxwork, int ncols)
 // Blocks that a launch of a small grid is split into: a small grid fills only
 // part of the 256 compute units, and a launch then lasts as long as its widest
 // tile, so tiles are narrowed while a launch has fewer blocks than these. Whole
-// solves in FP64 (order 6), default widths -> narrowed: passes at 256 blocks,
-// 33^3 209 -> 189 us, 65^3 250 -> 203 us, 129^3 283 -> 286 us (512 blocks: 189,
-// 205, 285); contractions at 512, 33^3 209 -> 199 us, 65^3 250 -> 234 us (256:
-// 198, 250), not below 4 columns (2D 513 x 385: 162 us with 2, 156 with 4); the
-// final pass at 256, 65^2 77 -> 72 us, 65^3 250 -> 243 us, and 129^3, which has
-// 1016 blocks, keeps its 283 us (292 when split further).
+// solves in FP64 (order 6; default widths, 128, 256, 512 blocks): passes 33^3 156, 126,
+// 127, 127 us, 65^3 209, 159, 154, 157, 97x90x113 361, 322, 336, 342, 129^3 all 240;
+// contractions (default, 256, 512, 1024) 33^3 139, 127, 127, 127, 65^3 171, 170, 154, 159, not
+// below 4 columns (2D 513 x 385: 162 us with 2, 156 with 4); the final pass (default,
+// 128, 256, 512) 65^2 order 4 55, 49, 49, 49, 65^3 160, 156, 154, 155.
 constexpr int kFillPass = 256, kFillConv = 512, kFillFinal = 256;
 
 // tile_width, narrowed (down to wmin columns) while nbatch rows of tiles make
@@ -171,9 +170,10 @@ constexpr int kFillPass = 256, kFillConv = 512, kFillFinal = 256;
 int fill_width(int N, int maxwork, int ncols, int64_t nbatch, int fill, int wmin = 2)
 {
     int W = tile_width(N, maxwork, ncols);
-    // the tiles with compile-time stages stay whole: even 48 of them beat four
-    // times as many narrower ones with run-time stages (129^3 283 against 286 us)
-    if (N * W == 4096 && (N == 256 || N == 512 || N == 1024)) return W;
+    // register tiles stay whole: even 48 of them mostly beat four times as many narrower
+    // tiles of run-time stages (whole and narrowed: 129^3 240 and 256 us, 257^2 91 and 100,
+    // 257^3 1251 and 1268; against it 129x65x257 345 and 320)
+    if (W == rt_width(N)) return W;
     // (the lines of a tiny 2D grid not below 64 elements, a wave's: mixed adjoint of 14^2 102.5
     // -> 99.9 us, solve of 9^2 64.5 -> 63.4; with batch entries narrower tiles win, 9^3
     // 114.8 -> 112.9)
@@ -341,10 +341,9 @@ int final_work(int precision)
 }
 
 // Column blocks of the final pass taken together: they cover 256 bytes of
-// each row (two 128-byte lines), which measured fastest with the direct
-// global I/O of the compile-time stages (257^3: FP32 106 -> 102 us, FP64
-// 196 -> 191 us against one line) (IPS_FINAL_GROUP overrides it, for
-// measurements).
+// each row (two 128-byte lines). Whole solves with 1, 2, 4, 8, 16 blocks: 257^3 FP32 (8: 256
+// bytes) 876, 858, 858, 853, 852 us, FP64 (4) 1267, 1257, 1251, 1247, 1250; 513^3 FP32 (16)
+// 6968, 6683, 6545, 6425, 6302 (IPS_FINAL_GROUP overrides it, for measurements).
 int final_group(int W, int tsz)
 {
     static const int env = [] {
@@ -471,7 +470,8 @@ int run_pass(ips_plan p, PassArgs a, const FftDesc &fd, const cx<double> *tw, bo
 // 6600 -> 6320 (513^3 rho_z 791 -> 591, rho_y 586 -> 504). The adjoint's pass at 2M =
 // 512 3888 -> 3842 (at 1024 0.5 ms slower, so not there). inv_y, inv_z and the final
 // pass gain nothing. FP32 tiles of the lengths from 1024 on without register tiles
-// take twice the plan's budget.
+// take twice the plan's budget. (Not measured: FP64 5-smooth lengths, and 2M = 2048, which
+// has no wider register tile.)
 int wide_width(ips_plan p, int N, int ncols, int nbatch, bool f32)
 {
     if (N == 512 || N == 1024) {
@@ -1607,7 +1607,8 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.out_r0 = 0;
             a.out_nrows = M[c] + 1;
             a.scale = 1.0 / N[c];
-            // few faces: narrow tiles give enough blocks to fill the device
+            // few faces: narrow tiles give enough blocks to fill the device (a budget of 512
+            // against 2048: 129^3 solve 240 and 248 us, 513^3 mixed 6295 and 6334)
             a.W = fill_width(N[c], std::min(p->work, 512), a.ncols, 2 * nfam, kFillPass);
             prep_pass(p, a, p->fd[c], p->tw[c]);
             PassArgs &b = fb[fam];
@@ -1623,8 +1624,9 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             b.out_r0 = 0;
             b.out_nrows = M[r] + 1;
             b.scale = 1.0 / N[r];
-            // the second step reads no partials: the default tile budget
-            // (compile-time stages) measured faster than narrow tiles
+            // the second step reads no partials: the default tile budget (register tiles)
+            // measured faster than narrow tiles (129^3 solve 240 and 244 us, 513^3 mixed 6295
+            // and 6320)
             b.W = fill_width(N[r], std::min(p->work, 2048), b.ncols, 2 * nfam, kFillPass);
             prep_pass(p, b, p->fd[r], p->tw[r]);
         }
