@@ -1630,9 +1630,14 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             b.W = fill_width(N[r], std::min(p->work, 2048), b.ncols, 2 * nfam, kFillPass);
             prep_pass(p, b, p->fd[r], p->tw[r]);
         }
-        // the families' passes of each step together (one launch each when uniform)
+        // the families' passes of each step together (one launch each when uniform: the
+        // second step's, on F, of every cube)
         if ((rc = run_passes(fa, nf, false, false, st))) return rc;
-        if ((rc = run_passes(fb, nf, false, false, st))) return rc;
+        if (p->cube && !joined) {
+            fb[0].nbatch = 6;
+            fb[0].W = fill_width(N[fr[0]], std::min(p->work, 2048), fb[0].ncols, 6, kFillPass);
+        }
+        if ((rc = run_passes(fb, p->cube ? 1 : 3, false, false, st))) return rc;
         // (8) boundary values: F[fam][face][j_r][j_c] -> strides of the in-face axes in
         //     increasing order
         for (int fam = 0; fam < 3; ++fam) {
@@ -1688,9 +1693,10 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
         ra.njobs = joined ? 1 : 2;
         ra.nset = joined ? 4 : 2;
         PassArgs fa[2];
-        for (int fam = 0; fam < ra.njobs; ++fam) {
+        for (int fam = 0; fam < ra.njobs; ++fam) ra.job[fam] = {part[fam], p->F[fam], N[1 - fam], p->nch[fam]};
+        const int nf = p->cube ? 1 : 2; // (F: back to back)
+        for (int fam = 0; fam < nf; ++fam) {
             const int pen = 1 - fam;
-            ra.job[fam] = {part[fam], p->F[fam], N[pen], p->nch[fam]};
             PassArgs &a = fa[fam];
             a = PassArgs{};
             a.in = p->F[fam];
@@ -1700,7 +1706,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             a.ocs = N[pen];
             a.ibs = a.obs = 0;
             a.nrows_in = N[pen];
-            a.ncols = ra.nset;
+            a.ncols = p->cube ? 4 : 2;
             a.nbatch = 1;
             a.in_mode = IN_HERM;
             a.out_r0 = 0;
@@ -1709,7 +1715,7 @@ int execute(ips_plan p, const double *rho, double *phi, hipStream_t st)
             prep_pass(p, a, p->fd[pen], p->tw[pen]);
         }
         IPS_HIP(launch_reduce(ra, st));
-        if ((rc = run_passes(fa, ra.njobs, false, false, st))) return rc;
+        if ((rc = run_passes(fa, nf, false, false, st))) return rc;
         for (int fam = 0; fam < 2; ++fam) {
             face.F[fam] = p->F[fam];
             face.fs[fam][0] = N[1 - fam];
