@@ -907,8 +907,10 @@ void chunk_families(ips_plan p, int wmin)
 // Tile widths and chunks of the contractions. Narrowed tiles mean more chunks, whose
 // partials must not raise the workspace above what whole tiles and a shell area of their
 // own would take: they share the shell area's place, then families go to phi, which a
-// solve writes only after the last partial is read, then tiles get wider. (Mixed modes
-// keep the widths of whole tiles, and with them the order of the FP64 sums.)
+// solve writes only after the last partial is read, then tiles get wider (against narrowing
+// without that limit 32x34x36 order 4 108 -> 113 us and 63x60 63 -> 65, but 38x39x48 136 ->
+// 121 and, order 6, 44x59x53 206 -> 190). (Mixed modes keep the widths of whole tiles, and
+// with them the order of the FP64 sums.)
 void plan_chunks(ips_plan p)
 {
     const int d = p->d;
