@@ -39,3 +39,42 @@ def test_shared_buffers(shape, order, adjoint):
         assert rel_err(phi.cpu().numpy(), ref) < 1e-12
         assert rel_err(grad.cpu().numpy(), ref_adj) < 1e-12
     plan.close()
+
+
+def test_partials_in_phi_under_capture_and_in_static_scratch():
+    """Order-4 boxes whose chunk partials lie in phi: graph replays over outputs that hold
+    NaN, with eager work between, extended solves and the static scratch, bit for bit."""
+    import ctypes
+
+    import torch
+    from paper_2108_11871_amd import _lib, api
+    from gpu_util import banner, to_dev
+
+    banner("partials in phi: batch graph, static scratch, extended")
+    shapes = [(33, 33, 33), (25, 25, 25), (65, 70, 61), (65, 65), (9, 200)]
+    cases = [I.workload_bumps(s, seed=45 + b, scale=[1.0, 1.2, 0.9][:len(s)])[:2] for b, s in enumerate(shapes)]
+    rhos = [to_dev(r) for r, _ in cases]
+    plans = [api.Plan(s, h, order=4) for s, (_, h) in zip(shapes, cases)]
+    refs = [p(r) for p, r in zip(plans, rhos)]
+    batch = api.Batch(shapes, [h for _, h in cases], order=4)
+    outs = [torch.empty_like(r) for r in rhos]
+    for _ in range(4):  # eager and captured, then replays
+        for o in outs:
+            o.fill_(float("nan"))
+        batch(rhos, outs)
+        eager = plans[0](rhos[0])
+        torch.cuda.synchronize()
+        assert all(torch.equal(o, r) for o, r in zip(outs, refs)) and torch.equal(eager, refs[0])
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for p, r, ref in zip(plans, rhos, refs):
+        out = torch.full_like(r, float("nan"))
+        rc = _lib.lib().ips_execute_static(p._h, ctypes.c_void_p(r.data_ptr()), ctypes.c_void_p(out.data_ptr()), stream)
+        torch.cuda.synchronize()
+        assert rc == 0 and torch.equal(out, ref)
+    ext = api.Plan((27, 27, 27), cases[0][1], order=4, margin=3)  # solves on 33^3
+    inner = rhos[0][3:30, 3:30, 3:30].contiguous()
+    grown = torch.zeros_like(rhos[0])
+    grown[3:30, 3:30, 3:30] = inner
+    got = ext(inner)
+    torch.cuda.synchronize()
+    assert torch.equal(got, plans[0](grown)[3:30, 3:30, 3:30])
