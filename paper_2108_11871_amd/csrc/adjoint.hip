@@ -400,7 +400,7 @@ hipError_t launch_adj_lambda(const AdjArgs &a, const double *w, const double *y1
 // and lambda collects g~ and Z. Three volume transforms instead of twelve and no
 // volume stencils: 257^3 forward and backward 5.03 -> 3.93 ms, 4097^2 5.52 -> 4.29 ms.
 // The sums over k_a read X once per family (257^3, three families: 67 us for two layers,
-// 96 for four, 12 and 23 to add the splits); k_adj_x (150 to 159 us over the boxes measured)
+// 96 for four, 12 and 23 to add the splits); k_adj_x (150 to 159 us in the runs measured)
 // is bound by its ten cached loads per element.
 // ---------------------------------------------------------------------------
 struct ContractJob {
@@ -760,7 +760,7 @@ __global__ __launch_bounds__(NTA) void k_adj_tpack(AdjArgs a, AdjShell s)
 // One position of the axes after the first per thread (neighbours side by side), a
 // range of k0 per block row: the family-0 values of the position stay in registers.
 // Bound by the ten loads of the other families' values per element, two elements' at
-// once in flight (257^3, one box: 159 -> 148 us).
+// once in flight (257^3, one run: 159 -> 148 us).
 template <int D>
 __global__ __launch_bounds__(NTA) void k_adj_x(AdjArgs a, AdjShell s, double *X)
 {
